@@ -58,7 +58,7 @@ extern "C" {
 #define UGKS_BC_OUTFLOW 3  /* ghost cell: the interior state */
 
 /* ---- precision forms (ugks_options.precision) -------------------------- */
-/* most rows one ugks_mlp_forward_noalloc call takes (its static staging array) */
+/* most rows one ugks_mlp_forward_noalloc call takes (its static array) */
 #define UGKS_NOALLOC_MAX_ROWS 65536
 
 #define UGKS_FP64 64 /* h, b, their gradients and fluxes in FP64 */
@@ -443,11 +443,12 @@ int ugks_mlp_forward(ugks_mlp* net, const float* x, int64_t rows, float* y, int3
  * pointer, rows x 9 floats (outputs, physical units), written.  The caller
  * owns both.  The call only enqueues work on the network's stream and
  * returns: y is ready once that stream has reached this point.  It allocates
- * nothing: its staging rows live in a static device array of
- * UGKS_NOALLOC_MAX_ROWS rows (8 MiB per GPU, held until the process ends),
- * looked up once per device.  Every call on one GPU shares that array, so
- * calls that overlap on one GPU (other streams, other threads) race; calls
- * ordered on one stream do not.  Nothing in the array has to start at zero.
+ * nothing.  y may be x (in place).  Where y's rows overlap x's without being
+ * the same rows, x is first copied to a static device array of
+ * UGKS_NOALLOC_MAX_ROWS rows (2.25 MiB per GPU, held until the process ends,
+ * looked up once per device); such calls share that array, so they race if
+ * they overlap on one GPU (other streams, other threads), while calls ordered
+ * on one stream do not.
  * The network's device must be current.
  * Errors: UGKS_EINVAL for rows < 0 or rows > UGKS_NOALLOC_MAX_ROWS, null
  * pointers, or another current device (nothing is enqueued); UGKS_EHIP if a
