@@ -78,6 +78,94 @@ void check_case_args(const ugks_mesh* mesh, const ugks_velocity* vel, const ugks
           "gas constants must be positive");
 }
 
+// The velocity slots of the fused path (see FusedMesh): the caller's point of
+// every slot (-1: pad), and vidx the packed node indices of all of them.  ax:
+// the sorted symmetric nodes that every coordinate is one of.
+std::vector<int64_t> pair_slots(int D, const ugks_velocity* vel, const std::vector<double>& ax,
+                                std::vector<int32_t>& vidx) {
+  const int64_t nv = vel->nv, na = (int64_t)ax.size();
+  std::vector<int32_t> id(nv * D);
+  int64_t cube = 1;
+  for (int d = 0; d < D; ++d) cube *= na;
+  std::vector<int64_t> at(cube, -1);
+  auto cell = [&](const int32_t* i) {
+    int64_t r = 0;
+    for (int d = 0; d < D; ++d) r = r * na + i[d];
+    return r;
+  };
+  for (int64_t k = 0; k < nv; ++k) {
+    for (int d = 0; d < D; ++d)
+      id[k * D + d] = (int32_t)(std::lower_bound(ax.begin(), ax.end(), vel->u[k * D + d]) - ax.begin());
+    at[cell(&id[k * D])] = k;
+  }
+  struct Pair {
+    int64_t key, k, m;  // order, first member, its mirror (-1: pad)
+  };
+  std::vector<Pair> pairs;
+  std::vector<char> done(nv, 0);
+  const int sh = D == 3 ? 2 : 3;  // blocks of 4 x 4 x 4 or 8 x 8 nodes
+  for (int64_t k = 0; k < nv; ++k) {
+    if (done[k]) continue;
+    int32_t mi[3];
+    for (int d = 0; d < D; ++d) mi[d] = (int32_t)na - 1 - id[k * D + d];
+    int64_t first = k, m = at[cell(mi)];
+    if (m >= 0 && (m == k || done[m])) m = -1;
+    done[k] = 1;
+    if (m >= 0) {
+      done[m] = 1;
+      // the member on the far side of the first axis that tells them apart
+      if (std::lexicographical_compare(&id[k * D], &id[k * D] + D, mi, mi + D)) std::swap(first, m);
+    }
+    int64_t block = 0, in = 0;
+    for (int d = 0; d < D; ++d) {
+      // blocks are counted from the middle of the first axis
+      const int64_t i = id[first * D + d] + (d == 0 ? (1 << 10) - na / 2 : 0);
+      block = (block << 10) | (i >> sh);
+      in = (in << sh) | (i & ((1 << sh) - 1));
+    }
+    pairs.push_back({(block << 10) | in, first, m});
+  }
+  std::sort(pairs.begin(), pairs.end(),
+            [](const Pair& a, const Pair& b) { return a.key != b.key ? a.key < b.key : a.k < b.k; });
+  const int64_t half = ((int64_t)pairs.size() + WAVE - 1) / WAVE * WAVE;
+  std::vector<int64_t> slots(2 * half, -1);
+  vidx.assign(2 * half, 0);
+  for (int64_t j = 0; j < half; ++j) {
+    const bool real = j < (int64_t)pairs.size();
+    const Pair& p = pairs[real ? j : pairs.size() - 1];  // pads repeat the last pair's velocities
+    if (real) {
+      slots[j] = p.k;
+      slots[half + j] = p.m;
+    }
+    for (int d = 0; d < D; ++d) {
+      const int32_t i = id[p.k * D + d];
+      vidx[j] |= (i * 16) << (10 * d);
+      vidx[half + j] |= (((int32_t)na - 1 - i) * 16) << (10 * d);
+    }
+  }
+  return slots;
+}
+
+// Fewest cells that take the whole-cell form where a cell has more than one
+// velocity block.  Measured per step, whole cells against blocks of 4096: 6
+// cells x 28^3 130 / 128 us, 48 x 28^3 148 / 160, 384 x 28^3 193 / 226, 750 x
+// 20^3 135 / 150, 1,296 x 24^3 316 / 349, 2,058 x 28^3 736 / 737 us.
+constexpr int64_t kWholeCells = 48;
+
+// Lanes per work-group of the whole-cell form (one mirror pair each): four
+// pairs per lane where a cell has them, so that the item's fixed costs (tables,
+// sums, the new equilibrium) are spread, and more lanes than that only while
+// the cells do not fill the GPU's 4,096 resident waves.  Measured per step, by
+// lanes 64 / 128 / 256 / 512: 16,384 cells x 512 pairs FP32 0.343 / 0.317 /
+// 0.343 / 0.463 ms; 1,024 x 448 FP64 0.073 / 0.061 / 0.056 / 0.066 ms; 48,000 x
+// 6,912 FP64 - / - / 9.85 / 9.18 ms (1,024 lanes: slower by a tenth).
+int cell_lanes(int64_t nc, int64_t pairs) {
+  const int64_t waves = pairs / WAVE;
+  int64_t w = 1;
+  while (w < 8 && (8 * w <= waves || (nc * w < 4096 && 2 * w <= waves))) w *= 2;
+  return (int)(w * WAVE);
+}
+
 void build(ugks_ctx* c, const ugks_mesh* mesh, const ugks_velocity* vel, const ugks_gas* gas,
            const ugks_bc* bcs, int32_t n_bc, const double* W0, const ugks_options* opt) {
   check_case_args(mesh, vel, gas, W0);
@@ -104,23 +192,6 @@ void build(ugks_ctx* c, const ugks_mesh* mesh, const ugks_velocity* vel, const u
   c->nc = nc;
   c->nf = nf;
   c->nv = nv;
-  // rows are padded to whole waves; the velocity block of the sweep is a
-  // scheduling unit and needs no padding
-  c->nvp = (nv + WAVE - 1) / WAVE * WAVE;
-  {
-    // a point whose mirror -u_k is not in the set is paired with a pad slot
-    // on the fused sweep: keep at least one
-    std::set<std::vector<double>> pts;
-    for (int64_t k = 0; k < nv; ++k) pts.insert(std::vector<double>(vel->u + k * D, vel->u + (k + 1) * D));
-    bool all_mirrored = true;
-    for (int64_t k = 0; k < nv && all_mirrored; ++k) {
-      std::vector<double> m(D);
-      for (int d = 0; d < D; ++d) m[d] = -vel->u[k * D + d];
-      all_mirrored = pts.count(m) > 0;
-    }
-    if (!all_mirrored && c->nvp == nv) c->nvp += WAVE;
-  }
-
   // ---- mesh validation and cell -> face tables --------------------------
   for (int64_t i = 0; i < nc; ++i)
     fail_if(!(mesh->cell_volume[i] > 0.0), "non-positive cell volume");
@@ -259,19 +330,9 @@ void build(ugks_ctx* c, const ugks_mesh* mesh, const ugks_velocity* vel, const u
     std::fill(lsG.begin(), lsG.end(), 0.0);
   }
   // ---- velocity set -----------------------------------------------------
-  const int64_t nvp = c->nvp;
-  std::vector<double> u(3 * nvp, 0.0), w(nvp, 0.0), u2(nvp, 0.0);
   for (int64_t k = 0; k < nv; ++k) {
     fail_if(!(vel->w[k] > 0.0), "velocity weights must be positive");
-    double s = 0.0;
-    for (int d = 0; d < D; ++d) {
-      double x = vel->u[k * D + d];
-      fail_if(!std::isfinite(x), "non-finite velocity");
-      u[d * nvp + k] = x;
-      s += x * x;
-    }
-    w[k] = vel->w[k];
-    u2[k] = s;
+    for (int d = 0; d < D; ++d) fail_if(!std::isfinite(vel->u[k * D + d]), "non-finite velocity");
   }
   // ---- fused-path eligibility ----------------------------------------------
   // A tensor product of one symmetric 1-D node set, first axis slowest, so
@@ -322,6 +383,25 @@ void build(ugks_ctx* c, const ugks_mesh* mesh, const ugks_velocity* vel, const u
       }
     }
     c->fused = ok;
+  }
+  // ---- velocity slots -------------------------------------------------------
+  std::vector<int32_t> vidx;
+  c->vel_perm = c->fused ? pair_slots(D, vel, ax, vidx) : std::vector<int64_t>();
+  if (!c->fused) {
+    // the caller's order, rows padded to whole waves
+    c->vel_perm.assign((nv + WAVE - 1) / WAVE * WAVE, -1);
+    for (int64_t k = 0; k < nv; ++k) c->vel_perm[k] = k;
+  }
+  const int64_t nvp = c->nvp = (int64_t)c->vel_perm.size();
+  std::vector<double> u(3 * nvp, 0.0), w(nvp, 0.0), u2(nvp, 0.0);
+  for (int64_t k = 0; k < nvp; ++k) {
+    const int64_t kk = c->vel_perm[k];
+    if (kk >= 0) w[k] = vel->w[kk];
+    for (int d = 0; d < D; ++d) {
+      if (kk >= 0) u[d * nvp + k] = vel->u[kk * D + d];
+      else if (c->fused) u[d * nvp + k] = ax[((uint32_t)vidx[k] >> (10 * d + 4)) & 63];
+      u2[k] += u[d * nvp + k] * u[d * nvp + k];
+    }
   }
   // ---- initial state check ---------------------------------------------
   for (int64_t i = 0; i < nc; ++i) {
@@ -520,55 +600,9 @@ void build(ugks_ctx* c, const ugks_mesh* mesh, const ugks_velocity* vel, const u
         fd[22] = (j >= 0 || gr >= 0) ? 1.0 : 0.0;
       }
     }
-    std::vector<int32_t> vidx(nv);
-    const int64_t na = c->fmesh.na;
-    if (!c->fmesh.sparse) {
-      for (int64_t k = 0; k < nv; ++k) {
-        int64_t r = k;
-        int32_t packed = 0;
-        for (int d = D - 1; d >= 0; --d) {
-          packed |= (int32_t)(r % na) << (8 * d);
-          r /= na;
-        }
-        vidx[k] = packed;
-      }
-      c->fmesh.npairs = (nv + 1) / 2;
-    } else {
-      // node indices of every coordinate, then mirror pairs: point k with the
-      // point at the mirrored indices, itself (u = 0), or a pad slot whose
-      // weight is 0 and which is never stored (a "phantom" partner)
-      std::map<std::vector<int32_t>, int64_t> at;
-      std::vector<std::vector<int32_t>> ids(nv, std::vector<int32_t>(D));
-      for (int64_t k = 0; k < nv; ++k) {
-        int32_t packed = 0;
-        for (int d = 0; d < D; ++d) {
-          const double x = vel->u[k * D + d];
-          const int32_t n = (int32_t)(std::lower_bound(ax.begin(), ax.end(), x) - ax.begin());
-          ids[k][d] = n;
-          packed |= n << (8 * d);
-        }
-        vidx[k] = packed;
-        at[ids[k]] = k;
-      }
-      std::vector<int32_t> pairs, pvidx;
-      std::vector<char> done(nv, 0);
-      for (int64_t k = 0; k < nv; ++k) {
-        if (done[k]) continue;
-        std::vector<int32_t> m(D);
-        for (int d = 0; d < D; ++d) m[d] = (int32_t)na - 1 - ids[k][d];
-        auto it = at.find(m);
-        int64_t k1 = (int64_t)nv;  // pad slot
-        if (it != at.end() && !done[it->second]) k1 = it->second;
-        done[k] = 1;
-        if (k1 < nv) done[k1] = 1;
-        pairs.push_back((int32_t)k);
-        pairs.push_back((int32_t)k1);
-        pvidx.push_back(vidx[k]);
-      }
-      c->fmesh.npairs = (int64_t)pvidx.size();
-      c->fmesh.pairs = upload(c, pairs);
-      c->fmesh.pvidx = upload(c, pvidx);
-    }
+    c->fmesh.half = nvp / 2;
+    // the sweep reads one iteration ahead
+    vidx.resize(vidx.size() + 512, 0);
     c->fmesh.nc = nc;
     c->fmesh.nv = nv;
     c->fmesh.axis = upload(c, ax);
@@ -632,42 +666,47 @@ void build(ugks_ctx* c, const ugks_mesh* mesh, const ugks_velocity* vel, const u
   B.frec = dalloc<double>(c, nf * FREC);
   B.F = dalloc<double>(c, nf * 5);
   if (c->fused) {
-    // velocity block: B_v velocities = B_v/2 mirror pairs per work item
-    const int64_t npairs = c->fmesh.npairs;
-    // (at least 32 pairs, or all: the batched form's smallest block, whose
-    // per-block moment buffer below is sized from this)
+    const int64_t npairs = c->fmesh.half;
+    // Whole cells per work-group, unless the caller fixes a velocity block or
+    // the cells are too few for the GPU and a cell has more than one block of
+    // 4096 velocities
     int64_t cp = Bv ? Bv / 2 : 2048;
     cp = std::max<int64_t>(std::min<int64_t>(32, npairs), std::min<int64_t>(cp, npairs));
-    c->sched.nf = nf;
+    c->sched.whole = cp >= npairs || (!Bv && nc >= kWholeCells) ? 1 : 0;
+    if (c->sched.whole) cp = npairs;
+    c->sched.lanes = cell_lanes(nc, npairs);
     c->sched.chunk_pairs = cp;
     c->sched.nchunk = (npairs + cp - 1) / cp;
     c->sched.tile = tile ? tile : 32;
     c->Bv = (int)(2 * cp);
-    B.dW = dalloc<double>(c, nc * c->sched.nchunk * 5);
-    B.tabs = dalloc<double>(c, (nf + nc) * (int64_t)D * c->fmesh.na);
+    if (!c->sched.whole) {
+      B.dW = dalloc<double>(c, nc * c->sched.nchunk * 5);
+      B.csn = dalloc<double>(c, nc * CSREC);
+    }
     B.cs = dalloc<double>(c, nc * CSREC);
-    B.csn = dalloc<double>(c, nc * CSREC);
     if (prec == UGKS_FP32) {
       B.frec32 = dalloc<float>(c, nf * FREC);
       B.cs32 = dalloc<float>(c, nc * CSREC);
-      B.tabs32 = dalloc<float>(c, (nf + nc) * (int64_t)D * c->fmesh.na);
-      // defined before the first step (the batched autotuner times the sweep on them)
       HIP_TRY(hipMemset(B.frec32, 0, nf * FREC * sizeof(float)));
-      HIP_TRY(hipMemset(B.cs32, 0, nc * CSREC * sizeof(float)));
-      HIP_TRY(hipMemset(B.tabs32, 0, (nf + nc) * (int64_t)D * c->fmesh.na * sizeof(float)));
     }
   } else {
     B.dW = dalloc<double>(c, nc * 5);
   }
   // row nc of h and b stays zero: the fused sweep's wall faces read it;
-  // rows nc+1 ... are the fused sweep's far-field ghost rows
-  const int64_t rows = nc + 1 + (c->fused ? c->fmesh.nff : 0);
+  // rows nc+1 ... are the fused sweep's far-field ghost rows.  On the fused
+  // path h and ht (b and bt) trade places every step, so both have them.
+  const int64_t rows = nc + 1 + (c->fused ? c->fmesh.nff : 0), trows = c->fused ? rows : nc;
   B.h = dalloc<char>(c, (size_t)rows * nvp * esz);
-  B.ht = dalloc<char>(c, (size_t)nc * nvp * esz);
+  B.ht = dalloc<char>(c, (size_t)trows * nvp * esz);
   B.b = c->nr == 2 ? (void*)dalloc<char>(c, (size_t)rows * nvp * esz) : nullptr;
-  B.bt = c->nr == 2 ? (void*)dalloc<char>(c, (size_t)nc * nvp * esz) : nullptr;
+  B.bt = c->nr == 2 ? (void*)dalloc<char>(c, (size_t)trows * nvp * esz) : nullptr;
   HIP_TRY(hipMemset(B.h, 0, (size_t)rows * nvp * esz));
   if (B.b) HIP_TRY(hipMemset(B.b, 0, (size_t)rows * nvp * esz));
+  if (c->fused) {
+    // the zero row, and the pad slots of every row, which no step writes
+    HIP_TRY(hipMemset(B.ht, 0, (size_t)rows * nvp * esz));
+    if (B.bt) HIP_TRY(hipMemset(B.bt, 0, (size_t)rows * nvp * esz));
+  }
   if (!c->fused) {
     // the staged sweep keeps every gradient and microscopic flux in HBM
     B.gradh = dalloc<double>(c, (size_t)nc * 3 * nvp);
@@ -704,12 +743,12 @@ int set_err(ugks_ctx* c, int code, const std::string& msg) {
 // Kernel kinds timed by ugks_profile_enable.
 enum KernelKind {
   KK_PRIMS, KK_HEATFLUX, KK_GRADW, KK_FACE_EQ, KK_WALL, KK_SWEEP, KK_STAGE1, KK_GRAD_MICRO,
-  KK_FLUX, KK_MACRO, KK_STAGE2, KK_RESID, KK_COMMIT, KK_TABLES, KK_COUNT
+  KK_FLUX, KK_MACRO, KK_STAGE2, KK_RESID, KK_COMMIT, KK_COUNT
 };
 const char* const kKernelNames[KK_COUNT] = {
     "cell_prims", "heat_flux", "macro_gradient", "face_equilibrium", "wall_density",
     "sweep", "stage1", "micro_gradient", "face_flux", "macro_update", "stage2", "residual",
-    "commit", "maxwell_tables"};
+    "commit"};
 
 hipEvent_t take_event(ugks_ctx* c) {
   if (!c->event_pool.empty()) {
@@ -748,25 +787,36 @@ struct Timed {
     HIP_TRY(call);               \
   } while (0)
 
+// The buffers that a step of the fused path leaves in each other's place.
+void swap_buffers(StepBuffers& B) {
+  std::swap(B.W, B.Wn);
+  std::swap(B.q, B.qn);
+  std::swap(B.h, B.ht);
+  std::swap(B.b, B.bt);
+}
+
 // One time step of the fused path, enqueued.
-void enqueue_step_fused(ugks_ctx* c) {
+void enqueue_step_fused(ugks_ctx* c, bool residual) {
   const int D = c->D, P = c->prec;
   const DevMesh& m = c->mesh;
   const DevVel& v = c->vel;
   const GasP& g = c->gas;
   StepBuffers& B = c->buf;
   hipStream_t s = c->stream;
-  // 2 heat flux of h^n: carried over from the previous second stage once valid
+  // 2 heat flux of h^n: left by the previous step once valid
   if (!c->q_valid) {
     TIMED(KK_PRIMS, launch_prims(D, m, g, B.W, B.prim, B.flag, 1, s));
     TIMED(KK_HEATFLUX, launch_heatflux(D, P, m, v, B.h, B.b, B.prim, B.q, B.flag, s));
     c->q_valid = true;
   }
-  // 1 primitives of W^n and the cell equilibrium data of the first stage
-  TIMED(KK_PRIMS, launch_cell_prep(D, c->nc, g, B.W, B.q, B.prim, B.cs, B.flag, s));
+  // 1 primitives of W^n and the cell equilibrium data of the first stage:
+  // left by the previous step in the whole-cell form
+  if (!c->cs_valid)
+    TIMED(KK_PRIMS, launch_cell_prep(D, c->nc, g, B.W, B.q, B.prim, B.cs, B.cs32, B.flag, s));
+  c->cs_valid = c->sched.whole != 0;
   // 4 macroscopic reconstruction; 6.1-6.6 interface equilibrium
-  TIMED(KK_GRADW, launch_gradW(D, m, c->bcs, g, B.W, B.gW, B.flag, s));
-  TIMED(KK_FACE_EQ, launch_face_eq(D, m, c->bcs, g, B.W, B.gW, B.q, B.frec, B.flag, s));
+  TIMED(KK_GRADW, launch_gradW(D, m, c->bcs, g, B.W, B.gW, B.flag, 1, s));
+  TIMED(KK_FACE_EQ, launch_face_eq(D, m, c->bcs, g, B.W, B.gW, B.q, B.frec, B.frec32, B.flag, s));
   // 7 far-field ghost rows (the wall cells' stencils may read them), then
   // the wall densities
   if (c->fmesh.nff)
@@ -776,34 +826,26 @@ void enqueue_step_fused(ugks_ctx* c) {
   TIMED(KK_WALL, launch_wall_rho_inline(D, P, m, v, c->fmesh, g, B.h, B.frec, B.flag, s, track ? 1 : 0,
                                         track ? (const void*)B.b : nullptr));
   if (track) TIMED(KK_RESID, launch_bflux(D, m, B.frec, B.F, 0, B.bflux, B.flag, s));
-  // Maxwellian axis tables of every face and cell of this step
-  TIMED(KK_TABLES, launch_tables(D, m, c->fmesh, g, B.frec, B.prim, B.cs, B.tabs, B.flag, s));
-  // 5, 6.7-6.8, 9: the fused velocity sweep
-  if (P == UGKS_FP32) {
-    // the FP32 sweep reads FP32 copies of this step's records and tables
-    TIMED(KK_TABLES, launch_to_f32(B.frec, B.frec32, c->nf * FREC, B.cs, B.cs32, c->nc * CSREC,
-                                   B.tabs, B.tabs32, (c->nf + c->nc) * (int64_t)D * c->fmesh.na, s));
-    TIMED(KK_SWEEP, launch_sweep(D, P, c->fmesh, v, g, c->sched, c->fmesh.crec_d32, c->fmesh.crec_l32, B.cs32,
-                                 B.frec32, B.tabs32, B.h, B.b, B.ht, B.bt, B.dW, B.flag, s));
+  if (c->sched.whole) {
+    // 5, 6.7-6.8, 8-11: the velocity sweep and the rest of every cell's step
+    TIMED(KK_SWEEP, launch_step_cell(D, P, m, c->fmesh, v, g, c->sched, B, s));
   } else {
-    TIMED(KK_SWEEP, launch_sweep(D, P, c->fmesh, v, g, c->sched, c->fmesh.crec_d, c->fmesh.crec_l, B.cs, B.frec,
-                                 B.tabs, B.h, B.b, B.ht, B.bt, B.dW, B.flag, s));
+    // 5, 6.7-6.8, 9: the velocity sweep
+    TIMED(KK_SWEEP, launch_sweep(D, P, c->fmesh, v, g, c->sched, B, s));
+    // 8 conservative update; 10 new equilibrium (with q^n, reading R17)
+    TIMED(KK_MACRO, launch_apply_dW(D, m, c->sched.nchunk, B.W, B.dW, B.Wn, B.cellred, B.flag, s));
+    TIMED(KK_PRIMS, launch_cell_prep(D, c->nc, g, B.Wn, B.q, B.primn, B.csn, nullptr, B.flag, s));
+    // 11 second stage and the heat flux of h^{n+1}
+    TIMED(KK_STAGE2, launch_stage2_q(D, P, c->fmesh, v, B.primn, B.csn, B.ht, B.bt, B.qn, B.flag, s));
   }
-  // 8 conservative update; 10 new equilibrium (with q^n, reading R17)
-  TIMED(KK_MACRO, launch_apply_dW(D, m, c->sched.nchunk, B.W, B.dW, B.Wn, B.cellred, B.flag, s));
-  TIMED(KK_PRIMS, launch_cell_prep(D, c->nc, g, B.Wn, B.q, B.primn, B.csn, B.flag, s));
-  // 11 second stage and the heat flux of h^{n+1}
-  TIMED(KK_STAGE2, launch_stage2_q(D, P, c->fmesh, v, B.primn, B.csn, B.ht, B.bt, B.h, B.b, B.qn,
-                                    B.flag, s));
-  std::swap(B.q, B.qn);
-  if (!(c->flags & 1)) TIMED(KK_RESID, launch_residual(m, B.cellred, B.resid, B.flag, s));
-  TIMED(KK_COMMIT, launch_commit_W(D, m, B.Wn, B.W, B.flag, s));
+  if (residual) TIMED(KK_RESID, launch_residual(m, B.cellred, B.resid, B.flag, s));
+  swap_buffers(B);
 }
 
 // One time step, enqueued (the one-step algorithm).
-void enqueue_step(ugks_ctx* c) {
+void enqueue_step(ugks_ctx* c, bool residual) {
   if (c->fused) {
-    enqueue_step_fused(c);
+    enqueue_step_fused(c, residual);
     return;
   }
   const int D = c->D, P = c->prec;
@@ -816,9 +858,9 @@ void enqueue_step(ugks_ctx* c) {
   TIMED(KK_PRIMS, launch_prims(D, m, g, B.W, B.prim, B.flag, 1, s));
   TIMED(KK_HEATFLUX, launch_heatflux(D, P, m, v, B.h, B.b, B.prim, B.q, B.flag, s));
   // 3-4 ghost states and macroscopic reconstruction
-  TIMED(KK_GRADW, launch_gradW(D, m, c->bcs, g, B.W, B.gW, B.flag, s));
+  TIMED(KK_GRADW, launch_gradW(D, m, c->bcs, g, B.W, B.gW, B.flag, 1, s));
   // 6.1-6.6 interface equilibrium data
-  TIMED(KK_FACE_EQ, launch_face_eq(D, m, c->bcs, g, B.W, B.gW, B.q, B.frec, B.flag, s));
+  TIMED(KK_FACE_EQ, launch_face_eq(D, m, c->bcs, g, B.W, B.gW, B.q, B.frec, nullptr, B.flag, s));
   // 5 microscopic reconstruction
   TIMED(KK_GRAD_MICRO, launch_grad_micro(D, P, m, v, B.frec, B.h, B.b, B.gradh, B.gradb, B.flag, s));
   // 7 wall densities
@@ -836,7 +878,7 @@ void enqueue_step(ugks_ctx* c) {
   // 11 second stage
   TIMED(KK_STAGE2, launch_stage2(D, P, m, v, g, B.primn, B.q, B.ht, B.bt, B.h, B.b, B.flag, s));
   // 12 residual, commit W^{n+1}
-  if (!(c->flags & 1)) TIMED(KK_RESID, launch_residual(m, B.cellred, B.resid, B.flag, s));
+  if (residual) TIMED(KK_RESID, launch_residual(m, B.cellred, B.resid, B.flag, s));
   TIMED(KK_COMMIT, launch_commit_W(D, m, B.Wn, B.W, B.flag, s));
 }
 
@@ -849,7 +891,7 @@ struct ugks_batch_impl;
 
 namespace {
 
-// Autotuner cache: case shape -> (velocity-block pairs, tile cells, time),
+// Autotuner cache: case shape -> (pairs per work item, tile cells, time),
 // batch shape list -> lanes per work-group.
 struct TuneCase {
   int64_t chunk_pairs = 0, tile = 0;
@@ -874,12 +916,13 @@ struct ugks_batch {
   hipStream_t stream = nullptr;
   bool own_stream = false;
   std::vector<void*> allocations;
-  CaseDev* cases_dev[2] = {nullptr, nullptr};  // even / odd step: q and qn swapped
-  int64_t* offs = nullptr;                    // cell, face, wall, tab, ghost offsets, [5][n+1]
+  CaseDev* cases_dev[2] = {nullptr, nullptr};  // even / odd step: the buffers a step swaps
+  int64_t* offs = nullptr;                    // cell, face, wall, ghost offsets, [4][n+1]
   int32_t* items = nullptr;
   int64_t nitems = 0, grid = 0;
-  int64_t ncell = 0, nface = 0, nwall = 0, ntab = 0, nff = 0;
+  int64_t ncell = 0, nface = 0, nwall = 0, nff = 0;
   int32_t* flags_dev = nullptr;  // [4*n]
+  std::vector<int> odd;          // per case: its state is in the second set of buffers
   double* resid_dev = nullptr;   // [8*n]
   int parity = 0;
   hipGraph_t graph[2] = {nullptr, nullptr};
@@ -911,8 +954,7 @@ BatchDev batch_dev(const ugks_batch* b, int par) {
   bd.cell_off = b->offs;
   bd.face_off = b->offs + n1;
   bd.wall_off = b->offs + 2 * n1;
-  bd.tab_off = b->offs + 3 * n1;
-  bd.ff_off = b->offs + 4 * n1;
+  bd.ff_off = b->offs + 3 * n1;
   bd.items = b->items;
   bd.nitems = b->nitems;
   return bd;
@@ -933,17 +975,17 @@ void upload_cases(ugks_batch* b) {
       d.sc = c->sched;
       d.bcs = c->bcs;
       d.B = c->buf;
-      if (par) std::swap(d.B.q, d.B.qn);
+      if (par) swap_buffers(d.B);
     }
     if (!b->cases_dev[par]) b->cases_dev[par] = balloc<CaseDev>(b, n);
     HIP_TRY(hipMemcpy(b->cases_dev[par], h.data(), n * sizeof(CaseDev), hipMemcpyHostToDevice));
   }
 }
 
-// Work list of the batched sweep.  Tiles of each case go to the XCD queue
-// with the least work so far; queue x holds the items of its tiles, velocity
-// block by velocity block; queues are padded to one length and interleaved
-// so that item w lands on a work-group with index = w (mod 8), i.e. on XCD w mod 8.
+// Work list of the batched step.  Tiles of each case go to the XCD queue with
+// the least work so far; queue x holds the cells of its tiles; queues are
+// padded to one length and interleaved so that item w lands on a work-group
+// with index = w (mod 8), i.e. on XCD w mod 8.
 std::vector<int32_t> work_list(const ugks_batch* b, const std::vector<int64_t>& only) {
   std::vector<std::vector<int32_t>> q(8);
   std::vector<double> load(8, 0.0);
@@ -954,13 +996,10 @@ std::vector<int32_t> work_list(const ugks_batch* b, const std::vector<int64_t>& 
     for (int64_t t = 0; t < ntile; ++t) {
       const int x = (int)(std::min_element(load.begin(), load.end()) - load.begin());
       const int64_t c0 = t * sc.tile, c1 = std::min(c->nc, c0 + sc.tile);
-      for (int64_t ch = 0; ch < sc.nchunk; ++ch)
-        for (int64_t ic = c0; ic < c1; ++ic) {
-          q[x].push_back((int32_t)ci);
-          q[x].push_back((int32_t)ic);
-          q[x].push_back((int32_t)ch);
-          q[x].push_back(0);
-        }
+      for (int64_t ic = c0; ic < c1; ++ic) {
+        q[x].push_back((int32_t)ci);
+        q[x].push_back((int32_t)ic);
+      }
       load[x] += (double)(c1 - c0) * (double)((c->nv + 1) / 2);
     }
   };
@@ -969,12 +1008,12 @@ std::vector<int32_t> work_list(const ugks_batch* b, const std::vector<int64_t>& 
   else
     for (int64_t ci : only) add_case(ci);
   size_t len = 0;
-  for (auto& v : q) len = std::max(len, v.size() / 4);
-  std::vector<int32_t> out(8 * len * 4, 0);
+  for (auto& v : q) len = std::max(len, v.size() / 2);
+  std::vector<int32_t> out(8 * len * 2, 0);
   for (size_t j = 0; j < len; ++j)
     for (int x = 0; x < 8; ++x) {
-      int32_t* o = &out[(8 * j + x) * 4];
-      if (j < q[x].size() / 4) std::memcpy(o, &q[x][4 * j], 4 * sizeof(int32_t));
+      int32_t* o = &out[(8 * j + x) * 2];
+      if (j < q[x].size() / 2) std::memcpy(o, &q[x][2 * j], 2 * sizeof(int32_t));
       else o[0] = -1;
     }
   return out;
@@ -984,7 +1023,7 @@ int64_t sweep_grid(const ugks_batch* b, int64_t nitems) {
   int dev = 0, ncu = 0;
   HIP_TRY(hipGetDevice(&dev));
   HIP_TRY(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
-  const int per = std::max(1, sweep_b_blocks_per_cu(b->D, b->prec, b->threads));
+  const int per = std::max(1, step_b_blocks_per_cu(b->D, b->prec, b->threads));
   int64_t g = (int64_t)ncu * per;
   g = std::min<int64_t>(g, nitems);
   g = std::max<int64_t>(8, g / 8 * 8);
@@ -992,7 +1031,7 @@ int64_t sweep_grid(const ugks_batch* b, int64_t nitems) {
 }
 
 void set_items(ugks_batch* b, const std::vector<int32_t>& items, int32_t** dst, int64_t* cap) {
-  const int64_t n = (int64_t)items.size() / 4;
+  const int64_t n = (int64_t)items.size() / 2;
   if (n > *cap) {
     *dst = balloc<int32_t>(b, items.size());
     *cap = n;
@@ -1005,45 +1044,35 @@ void enqueue_batch_step(ugks_batch* b, int par) {
   const int D = b->D, P = b->prec;
   const BatchDev bd = batch_dev(b, par);
   hipStream_t s = b->stream;
-  // 1 primitives of W^n and the first-stage cell data
-  HIP_TRY(launch_cell_prep_b(D, bd, b->ncell, 0, s));
   // 4 macroscopic reconstruction; 6.1-6.6 interface equilibrium
   HIP_TRY(launch_gradW_b(D, bd, b->ncell, s));
   HIP_TRY(launch_face_eq_b(D, bd, b->nface, s));
   // 7 wall densities; far-field ghost rows
   HIP_TRY(launch_ghost_rows_b(D, P, bd, b->nff, s));
   HIP_TRY(launch_wall_rho_b(D, P, bd, b->nwall, s));
-  // Maxwellian axis tables
-  HIP_TRY(launch_tables_b(D, bd, b->ntab, s));
-  // the FP32 form's sweep computes from FP32 copies of the step's records
-  if (P == UGKS_FP32) HIP_TRY(launch_to_f32_b(bd, b->nface, b->ncell, b->ntab, s));
-  // 5, 6.7-6.8, 9: the fused velocity sweep, one persistent launch
-  HIP_TRY(launch_sweep_b(D, P, bd, b->grid, b->threads, s));
-  // 8 conservative update; 10 new equilibrium
-  HIP_TRY(launch_apply_dW_b(D, bd, b->ncell, s));
-  HIP_TRY(launch_cell_prep_b(D, bd, b->ncell, 1, s));
-  // 11 second stage with the heat flux of h^{n+1}
-  HIP_TRY(launch_stage2_q_b(D, P, bd, b->ncell, s));
-  // 12 residuals, commit W^{n+1}
+  // 5, 6.7-6.8, 8-11: the velocity sweep and the rest of every cell's step,
+  // one persistent launch
+  HIP_TRY(launch_step_b(D, P, bd, b->grid, b->threads, s));
+  // 12 residuals
   if (!(b->flags & 1)) HIP_TRY(launch_residual_b(bd, s));
-  HIP_TRY(launch_commit_W_b(D, bd, b->ncell, s));
 }
 
-// Average duration of `reps` launches of the batched sweep over `items`.
+// Average duration of `reps` launches of the batched step over `items`.  They
+// leave the state alone, but not the cell records and the error flags.
 double time_sweep(ugks_batch* b, const std::vector<int32_t>& items, int32_t** buf, int64_t* cap,
                   int reps) {
   upload_cases(b);  // the kernels read each case's schedule from the case table
   set_items(b, items, buf, cap);
   BatchDev bd = batch_dev(b, 0);
   bd.items = *buf;
-  bd.nitems = (int64_t)items.size() / 4;
+  bd.nitems = (int64_t)items.size() / 2;
   const int64_t g = sweep_grid(b, bd.nitems);
   hipEvent_t e0, e1;
   HIP_TRY(hipEventCreate(&e0));
   HIP_TRY(hipEventCreate(&e1));
-  HIP_TRY(launch_sweep_b(b->D, b->prec, bd, g, b->threads, b->stream));  // warm-up
+  HIP_TRY(launch_step_b(b->D, b->prec, bd, g, b->threads, b->stream));  // warm-up
   HIP_TRY(hipEventRecord(e0, b->stream));
-  for (int r = 0; r < reps; ++r) HIP_TRY(launch_sweep_b(b->D, b->prec, bd, g, b->threads, b->stream));
+  for (int r = 0; r < reps; ++r) HIP_TRY(launch_step_b(b->D, b->prec, bd, g, b->threads, b->stream));
   HIP_TRY(hipEventRecord(e1, b->stream));
   HIP_TRY(hipEventSynchronize(e1));
   float ms = 0.0f;
@@ -1054,19 +1083,17 @@ double time_sweep(ugks_batch* b, const std::vector<int32_t>& items, int32_t** bu
   return 1e3 * ms / reps;
 }
 
-void apply_sched(ugks_ctx* c, int64_t chunk_pairs, int64_t tile) {
-  const int64_t npairs = c->fmesh.npairs;
-  // at least 32 pairs (or all): the per-block moment buffer was sized for that
-  chunk_pairs = std::max(std::min<int64_t>(32, npairs), std::min(chunk_pairs, npairs));
-  c->sched.chunk_pairs = chunk_pairs;
-  c->sched.nchunk = (npairs + chunk_pairs - 1) / chunk_pairs;
+void apply_sched(ugks_ctx* c, int64_t tile) {
+  c->sched.whole = 1;
+  c->sched.chunk_pairs = c->fmesh.half;
+  c->sched.nchunk = 1;
   c->sched.tile = std::max<int64_t>(1, std::min(tile, c->nc));
-  c->Bv = (int)(2 * chunk_pairs);
+  c->Bv = (int)(2 * c->fmesh.half);
 }
 
-// Autotuner: for each lane count, each case's velocity block and tile by
-// timing that case's sweep alone, then the lane count by timing the whole
-// batch's sweep; shapes found in the cache are not timed again.
+// Autotuner: for each lane count, each case's tile by timing that case's step
+// alone, then the lane count by timing the whole batch's step; shapes found
+// in the cache are not timed again.
 void autotune(ugks_batch* b) {
   const int64_t n = (int64_t)b->cases.size();
   int32_t* buf = nullptr;
@@ -1098,26 +1125,17 @@ void autotune(ugks_batch* b) {
         }
       }
       if (!hit) {
-        const int64_t npairs = c->fmesh.npairs;
         tc.us = INFINITY;
-        int64_t last_cp = -1;
-        // velocity blocks from 64 velocities (half a wave of pairs) up to the whole set
-        for (int mult2 : {1, 2, 4, 8, 16, 1 << 21}) {
-          if (mult2 == 1 && th != 64) continue;
-          const int64_t cp = std::min<int64_t>(npairs, (int64_t)mult2 * th / 2);
-          if (cp == last_cp) continue;
-          last_cp = cp;
-          for (int64_t tile : {16, 64, 256}) {
-            if (tile > 16 && tile / 4 >= c->nc) continue;
-            apply_sched(c, cp, tile);
-            const double us = time_sweep(b, work_list(b, {i}), &buf, &cap, 3);
-            if (us < tc.us) tc = {c->sched.chunk_pairs, c->sched.tile, us};
-          }
+        for (int64_t tile : {16, 64, 256}) {
+          if (tile > 16 && tile / 4 >= c->nc) continue;
+          apply_sched(c, tile);
+          const double us = time_sweep(b, work_list(b, {i}), &buf, &cap, 3);
+          if (us < tc.us) tc = {c->sched.chunk_pairs, c->sched.tile, us};
         }
         std::lock_guard<std::mutex> lk(g_tune_mu);
         g_tune_case[key] = tc;
       }
-      apply_sched(c, tc.chunk_pairs, tc.tile);
+      apply_sched(c, tc.tile);
     }
     if (best_threads) break;  // cached lane count: schedules applied above
     const double t = time_sweep(b, work_list(b, {}), &buf, &cap, 3);
@@ -1133,7 +1151,7 @@ void autotune(ugks_batch* b) {
       ugks_ctx* c = b->cases[i];
       std::lock_guard<std::mutex> lk(g_tune_mu);
       const TuneCase& tc = g_tune_case[case_key(b->D, b->prec, best_threads, c->nc, c->nv)];
-      apply_sched(c, tc.chunk_pairs, tc.tile);
+      apply_sched(c, tc.tile);
     }
   }
   std::lock_guard<std::mutex> lk(g_tune_mu);
@@ -1187,7 +1205,7 @@ void batch_build(ugks_batch* b, const ugks_case* cases, int32_t n, const ugks_op
     const ugks_case& k = cases[i];
     ugks_options o{};
     o.precision = prec;
-    o.block_v = 64;  // smallest velocity block: sizes the per-block moment buffer
+    o.block_v = 0;
     o.tile_cells = 0;
     o.flags = b->flags & ~(2 | 8);
     o.stream = b->stream;
@@ -1224,57 +1242,62 @@ void batch_build(ugks_batch* b, const ugks_case* cases, int32_t n, const ugks_op
     HIP_TRY(launch_heatflux(cc->D, cc->prec, cc->mesh, cc->vel, cc->buf.h, cc->buf.b, cc->buf.prim,
                             cc->buf.q, cc->buf.flag, b->stream));
     cc->q_valid = true;
+    apply_sched(cc, 32);
   }
+  b->odd.assign(n, 0);
   // case-offset tables
   const int64_t n1 = n + 1;
-  std::vector<int64_t> off(5 * n1, 0);
+  std::vector<int64_t> off(4 * n1, 0);
   for (int32_t i = 0; i < n; ++i) {
     const ugks_ctx* c = b->cases[i];
     off[i + 1] = off[i] + c->nc;
     off[n1 + i + 1] = off[n1 + i] + c->nf;
     off[2 * n1 + i + 1] = off[2 * n1 + i] + c->mesh.nwall;
-    off[3 * n1 + i + 1] = off[3 * n1 + i] + (c->nf + c->nc) * (int64_t)c->D * c->fmesh.na;
-    off[4 * n1 + i + 1] = off[4 * n1 + i] + c->fmesh.nff;
+    off[3 * n1 + i + 1] = off[3 * n1 + i] + c->fmesh.nff;
   }
   b->ncell = off[n];
   b->nface = off[n1 + n];
   b->nwall = off[2 * n1 + n];
-  b->ntab = off[3 * n1 + n];
-  b->nff = off[4 * n1 + n];
+  b->nff = off[3 * n1 + n];
   b->offs = balloc<int64_t>(b, off.size());
   HIP_TRY(hipMemcpy(b->offs, off.data(), off.size() * sizeof(int64_t), hipMemcpyHostToDevice));
   upload_cases(b);
-  // the step's phases up to the sweep once, so the autotuner times the
-  // sweep on this batch's own records
+  // the step's phases up to the sweep once, so the autotuner times the step
+  // on this batch's own records
   {
     const BatchDev bd = batch_dev(b, 0);
-    HIP_TRY(launch_cell_prep_b(b->D, bd, b->ncell, 0, b->stream));
+    HIP_TRY(launch_cell_prep_b(b->D, bd, b->ncell, b->stream));
     HIP_TRY(launch_gradW_b(b->D, bd, b->ncell, b->stream));
     HIP_TRY(launch_face_eq_b(b->D, bd, b->nface, b->stream));
     HIP_TRY(launch_ghost_rows_b(b->D, b->prec, bd, b->nff, b->stream));
     HIP_TRY(launch_wall_rho_b(b->D, b->prec, bd, b->nwall, b->stream));
-    HIP_TRY(launch_tables_b(b->D, bd, b->ntab, b->stream));
+  }
+  HIP_TRY(hipStreamSynchronize(b->stream));
+  {
+    int32_t f0 = 0;
+    std::vector<int32_t> fl(4 * (size_t)n);
+    HIP_TRY(hipMemcpy(fl.data(), b->flags_dev, fl.size() * sizeof(int32_t), hipMemcpyDeviceToHost));
+    for (int32_t i = 0; i < n; ++i) f0 |= fl[4 * i];
+    fail_if(f0 != 0, "non-positive density or temperature in an initial state");
   }
   if (fixed_bv || fixed_tile) {
     b->threads = 256;
-    for (ugks_ctx* c : b->cases)
-      apply_sched(c, fixed_bv ? fixed_bv / 2 : 2048, fixed_tile ? fixed_tile : 256);
+    for (ugks_ctx* c : b->cases) apply_sched(c, fixed_tile ? fixed_tile : 256);
   } else {
     autotune(b);
     b->tuned = true;
+    HIP_TRY(hipStreamSynchronize(b->stream));
   }
+  // the timed launches' traces: flags, step counts and the first step's records
+  HIP_TRY(hipMemset(b->flags_dev, 0, 4 * (size_t)n * sizeof(int32_t)));
   upload_cases(b);
+  HIP_TRY(launch_cell_prep_b(b->D, batch_dev(b, 0), b->ncell, b->stream));
   const std::vector<int32_t> items = work_list(b, {});
   int64_t cap = 0;
   set_items(b, items, &b->items, &cap);
-  b->nitems = (int64_t)items.size() / 4;
+  b->nitems = (int64_t)items.size() / 2;
   b->grid = sweep_grid(b, b->nitems);
   HIP_TRY(hipStreamSynchronize(b->stream));
-  int32_t f0 = 0;
-  std::vector<int32_t> fl(4 * (size_t)n);
-  HIP_TRY(hipMemcpy(fl.data(), b->flags_dev, fl.size() * sizeof(int32_t), hipMemcpyDeviceToHost));
-  for (int32_t i = 0; i < n; ++i) f0 |= fl[4 * i];
-  fail_if(f0 != 0, "non-positive density or temperature in an initial state");
   if (b->use_graph) {
     for (int par = 0; par < 2; ++par) {
       HIP_TRY(hipStreamBeginCapture(b->stream, hipStreamCaptureModeThreadLocal));
@@ -1334,7 +1357,7 @@ int ugks_create(const ugks_mesh* mesh, const ugks_velocity* vel, const ugks_gas*
 
 namespace {
 
-// Capture one step per order of the q / q^{n+1} buffers as HIP graphs.  The
+// Capture one step per order of the buffers it swaps as HIP graphs.  The
 // step records kernels only (no memset or copy), and two captures swap the
 // buffers twice, so the context ends as it started.
 void capture_step_graphs(ugks_ctx* c) {
@@ -1342,7 +1365,7 @@ void capture_step_graphs(ugks_ctx* c) {
   for (int par = 0; par < 2; ++par) {
     HIP_TRY(hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
     try {
-      enqueue_step(c);
+      enqueue_step(c, !(c->flags & 1));
     } catch (...) {
       hipGraph_t g = nullptr;
       (void)hipStreamEndCapture(c->stream, &g);
@@ -1358,16 +1381,16 @@ void capture_step_graphs(ugks_ctx* c) {
 // applies (not profiling, the heat flux of the current f known, a stream
 // that can be captured), else the kernels one by one.  Both run the same
 // kernels with the same arguments.
-void run_step(ugks_ctx* c) {
+void run_step(ugks_ctx* c, bool residual) {
   const bool graphs = (c->flags & 32) && !c->profiling && c->stream != nullptr;
-  if (!graphs || !c->q_valid) {
-    enqueue_step(c);
+  if (!graphs || !c->q_valid || (c->sched.whole && !c->cs_valid)) {
+    enqueue_step(c, residual);
     return;
   }
   if (!c->graph_exec[0]) capture_step_graphs(c);
   const int par = c->buf.q == c->graph_q0 ? 0 : 1;
   HIP_TRY(hipGraphLaunch(c->graph_exec[par], c->stream));
-  if (c->fused) std::swap(c->buf.q, c->buf.qn);  // as the fused step does on the host
+  if (c->fused) swap_buffers(c->buf);  // as the fused step does on the host
 }
 
 }  // namespace
@@ -1377,18 +1400,27 @@ int ugks_step(ugks_ctx* c, int32_t n_steps, double* residual_out) {
   if (n_steps < 0) return set_err(c, UGKS_EINVAL, "n_steps < 0");
   Range range("ugks_step");
   try {
-    for (int32_t s = 0; s < n_steps; ++s) run_step(c);
-    int32_t flag = 0;
-    HIP_TRY(hipMemcpyAsync(&flag, c->buf.flag, sizeof(int32_t), hipMemcpyDeviceToHost, c->stream));
-    double res[2] = {0.0, 0.0};
-    if (residual_out)
-      HIP_TRY(hipMemcpyAsync(res, c->buf.resid, 2 * sizeof(double), hipMemcpyDeviceToHost, c->stream));
+    // the residual is the last step's, in units of the first non-zero change:
+    // the steps before the last need it only until that unit is known
+    for (int32_t s = 0; s < n_steps; ++s)
+      run_step(c, !(c->flags & 1) && (s + 1 == n_steps || !c->resid_set));
+    int32_t flag[4] = {0, 0, 0, 0};
+    HIP_TRY(hipMemcpyAsync(flag, c->buf.flag, sizeof flag, hipMemcpyDeviceToHost, c->stream));
+    double res[4] = {0.0, 0.0, 0.0, 0.0};
+    HIP_TRY(hipMemcpyAsync(res, c->buf.resid, sizeof res, hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));
-    if (flag) {
-      // leave the flag set: the state is the last completed step and further
-      // steps would repeat the failure
+    c->resid_set = res[3] != 0.0;
+    const int32_t begun = flag[1] - c->begun;
+    c->begun = flag[1];
+    if (flag[0] | flag[2]) {
+      // The state is the one before the step that failed: of the steps begun,
+      // all but the last are complete (the fused path swapped its buffers for
+      // every step enqueued).  The flag stays set: further steps would repeat
+      // the failure.
+      const int32_t done = std::max(0, begun - 1);
+      if (c->fused && ((n_steps - done) & 1)) swap_buffers(c->buf);
       return set_err(c, UGKS_ENUMERIC, "non-positive density or temperature (flag " +
-                                           std::to_string(flag) + ")");
+                                           std::to_string(flag[0] | flag[2]) + ")");
     }
     c->steps_done += n_steps;
     if (residual_out) {
@@ -1462,6 +1494,7 @@ int ugks_get_state(ugks_ctx* c, double* W, double* h, double* b) {
       int rc = ugks_moments(c, 0, W, 0);
       if (rc) return rc;
     }
+    const int64_t* slot = c->vel_perm.data();
     void* src[2] = {c->buf.h, c->buf.b};
     double* dst[2] = {h, b};
     for (int r = 0; r < 2; ++r) {
@@ -1474,12 +1507,14 @@ int ugks_get_state(ugks_ctx* c, double* W, double* h, double* b) {
         std::vector<float> tmp(nc * nvp);
         HIP_TRY(hipMemcpy(tmp.data(), src[r], tmp.size() * sizeof(float), hipMemcpyDeviceToHost));
         for (int64_t i = 0; i < nc; ++i)
-          for (int64_t k = 0; k < nv; ++k) dst[r][c->cell_perm[i] * nv + k] = tmp[i * nvp + k];
+          for (int64_t k = 0; k < nvp; ++k)
+            if (slot[k] >= 0) dst[r][c->cell_perm[i] * nv + slot[k]] = tmp[i * nvp + k];
       } else {
         std::vector<double> tmp(nc * nvp);
         HIP_TRY(hipMemcpy(tmp.data(), src[r], tmp.size() * sizeof(double), hipMemcpyDeviceToHost));
         for (int64_t i = 0; i < nc; ++i)
-          for (int64_t k = 0; k < nv; ++k) dst[r][c->cell_perm[i] * nv + k] = tmp[i * nvp + k];
+          for (int64_t k = 0; k < nvp; ++k)
+            if (slot[k] >= 0) dst[r][c->cell_perm[i] * nv + slot[k]] = tmp[i * nvp + k];
       }
     }
   } catch (const HipFail& e) {
@@ -1500,6 +1535,7 @@ int ugks_set_state(ugks_ctx* c, const double* W, const double* h, const double* 
         for (int x = 0; x < NW; ++x) lib[i * NW + x] = W[c->cell_perm[i] * NW + x];
       HIP_TRY(hipMemcpy(c->buf.W, lib.data(), lib.size() * sizeof(double), hipMemcpyHostToDevice));
     }
+    const int64_t* slot = c->vel_perm.data();
     void* dst[2] = {c->buf.h, c->buf.b};
     const double* src[2] = {h, b};
     for (int r = 0; r < c->nr; ++r) {
@@ -1507,12 +1543,14 @@ int ugks_set_state(ugks_ctx* c, const double* W, const double* h, const double* 
       if (c->prec == UGKS_FP32) {
         std::vector<float> tmp(nc * nvp, 0.0f);
         for (int64_t i = 0; i < nc; ++i)
-          for (int64_t k = 0; k < nv; ++k) tmp[i * nvp + k] = (float)src[r][c->cell_perm[i] * nv + k];
+          for (int64_t k = 0; k < nvp; ++k)
+            if (slot[k] >= 0) tmp[i * nvp + k] = (float)src[r][c->cell_perm[i] * nv + slot[k]];
         HIP_TRY(hipMemcpy(dst[r], tmp.data(), tmp.size() * sizeof(float), hipMemcpyHostToDevice));
       } else {
         std::vector<double> tmp(nc * nvp, 0.0);
         for (int64_t i = 0; i < nc; ++i)
-          for (int64_t k = 0; k < nv; ++k) tmp[i * nvp + k] = src[r][c->cell_perm[i] * nv + k];
+          for (int64_t k = 0; k < nvp; ++k)
+            if (slot[k] >= 0) tmp[i * nvp + k] = src[r][c->cell_perm[i] * nv + slot[k]];
         HIP_TRY(hipMemcpy(dst[r], tmp.data(), tmp.size() * sizeof(double), hipMemcpyHostToDevice));
       }
     }
@@ -1520,6 +1558,9 @@ int ugks_set_state(ugks_ctx* c, const double* W, const double* h, const double* 
     // sum, and clears a failure
     HIP_TRY(hipMemset(c->buf.bflux, 0, 5 * sizeof(double)));
     c->q_valid = false;
+    c->cs_valid = false;
+    c->resid_set = false;
+    c->begun = 0;
     HIP_TRY(hipMemset(c->buf.resid, 0, 8 * sizeof(double)));
     HIP_TRY(hipMemset(c->buf.flag, 0, 4 * sizeof(int32_t)));
   } catch (const HipFail& e) {
@@ -1684,8 +1725,14 @@ int ugks_batch_step(ugks_batch* b, int32_t n_steps, double* residual_out) {
     HIP_TRY(hipMemcpyAsync(fl.data(), b->flags_dev, fl.size() * sizeof(int32_t), hipMemcpyDeviceToHost, b->stream));
     HIP_TRY(hipMemcpyAsync(rs.data(), b->resid_dev, rs.size() * sizeof(double), hipMemcpyDeviceToHost, b->stream));
     HIP_TRY(hipStreamSynchronize(b->stream));
+    // where each case's state is: after the steps it has begun, or before the
+    // one that failed
+    for (size_t i = 0; i < n; ++i) {
+      const bool bad = fl[4 * i] | fl[4 * i + 2];
+      b->odd[i] = (bad ? std::max(0, fl[4 * i + 1] - 1) : fl[4 * i + 1]) & 1;
+    }
     for (size_t i = 0; i < n; ++i)
-      if (fl[4 * i]) {
+      if (fl[4 * i] | fl[4 * i + 2]) {
         return batch_err(b, UGKS_ENUMERIC, "case " + std::to_string(i) +
                                                ": non-positive density or temperature");
       }
@@ -1702,24 +1749,35 @@ int ugks_batch_step(ugks_batch* b, int32_t n_steps, double* residual_out) {
   return UGKS_OK;
 }
 
+namespace {
+// Case i as a context whose buffers hold its current state.
+struct CaseView {
+  ugks_ctx* c;
+  bool odd;
+  CaseView(ugks_batch* b, int32_t i) : c(b->cases[i]), odd(b->odd[i] != 0) {
+    if (odd) swap_buffers(c->buf);
+  }
+  ~CaseView() {
+    if (odd) swap_buffers(c->buf);
+  }
+};
+}  // namespace
+
 int ugks_batch_moments(ugks_batch* b, int32_t i, int32_t which, double* out, int32_t on_device) {
   if (!b) return batch_err(nullptr, UGKS_EINVAL, "batch is NULL");
   if (i < 0 || i >= (int32_t)b->cases.size()) return batch_err(b, UGKS_EINVAL, "case index out of range");
-  ugks_ctx* c = b->cases[i];
-  // the batch alternates q and qn by step parity; the case's own view is the
-  // even one, so after an odd number of steps its scratch qn is the current q
-  if (b->parity) std::swap(c->buf.q, c->buf.qn);
-  int rc = ugks_moments(c, which, out, on_device);
-  if (b->parity) std::swap(c->buf.q, c->buf.qn);
-  if (rc) batch_err(b, rc, c->err);
+  CaseView v(b, i);
+  int rc = ugks_moments(v.c, which, out, on_device);
+  if (rc) batch_err(b, rc, v.c->err);
   return rc;
 }
 
 int ugks_batch_get_state(ugks_batch* b, int32_t i, double* W, double* h, double* bb) {
   if (!b) return batch_err(nullptr, UGKS_EINVAL, "batch is NULL");
   if (i < 0 || i >= (int32_t)b->cases.size()) return batch_err(b, UGKS_EINVAL, "case index out of range");
-  int rc = ugks_get_state(b->cases[i], W, h, bb);
-  if (rc) batch_err(b, rc, b->cases[i]->err);
+  CaseView v(b, i);
+  int rc = ugks_get_state(v.c, W, h, bb);
+  if (rc) batch_err(b, rc, v.c->err);
   return rc;
 }
 

@@ -88,35 +88,40 @@ constexpr int CRL = 88, CRL_F0 = 8, CRL_FS = 20;
 // Per-cell, per-step record of the fused path (CSREC doubles per cell).
 constexpr int CSREC = 48, CS_CC = 0, CS_KAP = 1, CS_NORM = 2, CS_SH = 4, CS_SB = 24;
 
+// Velocity slots of the fused path: mirror pairs are kept as slot k and slot
+// half + k (k < half = half a row), the first members ordered by compact blocks
+// of the node lattice, so that 64 consecutive slots have mostly one sign of
+// u.n.  A point whose mirror is not in the set (or is the point itself) has a
+// pad slot there: the mirrored velocity with weight 0, advanced like any other.
 struct FusedMesh {
   int64_t nc, nv;
   int na;                   // nodes per velocity axis
+  int64_t half;             // mirror pairs with padding (a multiple of 64)
   const double* axis;       // [na] symmetric 1-D nodes
-  const int32_t* vidx;      // [nv] packed axis indices of point k (8 bits per axis, first axis low)
+  const int32_t* vidx;      // [2*half + padding] 16 * node index of every slot, 10 bits per axis, first axis low
   const int32_t* crec_i;    // [nc*CRI]
   const double* crec_d;     // [nc*CRD]
   const float* crec_d32;    // [nc*CRD] FP32 copy (FP32 compute form), else null
   bool sparse = false;      // points on the tensor product of `axis`, not all of it
-  int64_t npairs = 0;       // mirror pairs of the sweep
-  const int32_t* pairs = nullptr;  // sparse: [2*npairs] (k, mirror of k, or the pad slot nv)
-  const int32_t* pvidx = nullptr;  // sparse: [npairs] packed axis indices of each pair's first point
   const double* crec_l = nullptr;  // [nc*CRL] limiter record, null without the limiter
   const float* crec_l32 = nullptr; // its FP32 copy (FP32 compute form)
   const int32_t* ffaces;    // [nff] far-field / outflow faces; face m owns ghost row nc+1+m
   int64_t nff;
 };
 
-// Schedule of the fused sweep: work item = (cell, velocity block of
-// chunk_pairs mirror pairs); tiles of `tile` consecutive cells per XCD.
+// Schedule of the fused sweep: work item = a cell with all of its velocities
+// (whole), or (cell, velocity block of chunk_pairs mirror pairs); tiles of
+// `tile` consecutive cells per XCD.
 struct SweepSched {
-  int64_t nf;             // face count (cell tables follow the face tables)
+  int32_t whole = 0;      // 1: whole cells
+  int32_t lanes = 256;    // lanes per work-group of the whole-cell form
   int64_t tile;           // cells per tile
   int64_t nchunk;         // velocity blocks
   int64_t chunk_pairs;    // mirror pairs per velocity block
 };
 
 struct DevVel {
-  int64_t nv, nvp;          // true and padded counts
+  int64_t nv, nvp;          // points, and slots of a row (pads have weight 0)
   const double* u;          // [3*nvp] SoA: u[d*nvp + k]
   const double* w;          // [nvp]
   const double* u2;         // [nvp]
@@ -148,25 +153,25 @@ __host__ __device__ inline double area_for(const GasP& g, int64_t i, double S) {
 
 // Kernel launchers (ugks_kernels.hip).  Each returns hipGetLastError().
 struct StepBuffers {
+  // (on the fused path a step ends with W and Wn, q and qn, h and ht, b and
+  // bt trading places)
   double* W;       // [nc*(D+2)] state W^n
   double* Wn;      // [nc*(D+2)] W^{n+1}
   double* prim;    // [nc*NPRIM] of W^n
-  double* primn;   // [nc*NPRIM] of W^{n+1}
+  double* primn;   // [nc*NPRIM] of W^{n+1} (staged and blocked forms)
   double* q;       // [nc*3] heat flux of h^n
   double* qn;      // [nc*3] heat flux of h^{n+1} (fused path)
   double* gW;      // [nc*3*5]
   double* frec;    // [nf*FREC]
   double* F;       // [nf*5] face fluxes (staged sweep)
   double* dW;      // [nc*nchunk*5] per-(cell, velocity block) net outflow moments (fused sweep)
-  double* tabs;    // [(nf+nc)*D*na] Maxwellian axis tables of the step (fused sweep)
   double* cs;      // [nc*CSREC] per-step cell record of W^n (fused sweep)
-  double* csn;     // [nc*CSREC] per-step cell record of W^{n+1}
-  float* frec32;   // FP32 copies of frec, cs, tabs for the FP32 sweep (null in FP64)
+  double* csn;     // [nc*CSREC] per-step cell record of W^{n+1} (blocked form)
+  float* frec32;   // FP32 copies of frec, cs for the FP32 sweep (null in FP64)
   float* cs32;
-  float* tabs32;
   void* h;         // [nc*nvp] storage type
-  void* b;         // [nc*nvp] (2-D only)
-  void* ht;        // [nc*nvp] first-stage result
+  void* b;         // [nc*nvp] where b is carried
+  void* ht;        // [nc*nvp] first-stage result; on the fused path then h^{n+1}
   void* bt;
   double* gradh;   // [nc*3*nvp] microscopic gradients (staged sweep)
   double* gradb;
@@ -175,7 +180,19 @@ struct StepBuffers {
   double* resid;   // [8] residual accumulators and state
   double* bflux;   // [5] running boundary flux (with boundary-flux tracking)
   double* cellred; // [nc*3] per-cell residual contributions
-  int32_t* flag;   // numeric error flag
+  // [0] numeric error; [1] steps begun without one; [2] numeric error of the
+  // whole-cell step now running (taken over into [0] by the next step, so that
+  // every wave of that launch sees one value of [0])
+  int32_t* flag;
+};
+
+// What the rest of a cell's step reads and writes (whole-cell form).
+struct CellOut {
+  const double *vol, *W, *q;
+  double *Wn, *qn, *prim, *cs;
+  float* cs32;
+  double* cellred;
+  int32_t* flag;
 };
 
 // One case of a batch as the batched kernels see it (an array of these in
@@ -198,9 +215,8 @@ struct BatchDev {
   const int64_t* cell_off;  // [n+1] cells
   const int64_t* face_off;  // [n+1] faces
   const int64_t* wall_off;  // [n+1] wall faces
-  const int64_t* tab_off;   // [n+1] Maxwellian axis-table entries, (nf+nc)*D*na
   const int64_t* ff_off;    // [n+1] far-field / outflow faces (ghost rows)
-  const int32_t* items;     // [4*nitems] sweep work items: case (-1 = padding), cell, block, 0
+  const int32_t* items;     // [2*nitems] work items: case (-1 = padding), cell
   int64_t nitems;
 };
 
@@ -210,10 +226,10 @@ hipError_t launch_heatflux(int D, int prec, const DevMesh& m, const DevVel& v, c
                            const void* b, const double* prim, double* q, const int32_t* flag,
                            hipStream_t s);
 hipError_t launch_gradW(int D, const DevMesh& m, const DevBC* bcs, const GasP& g, const double* W,
-                        double* gW, const int32_t* flag, hipStream_t s);
+                        double* gW, int32_t* flag, int count, hipStream_t s);
 hipError_t launch_face_eq(int D, const DevMesh& m, const DevBC* bcs, const GasP& g,
                           const double* W, const double* gW, const double* q, double* frec,
-                          int32_t* flag, hipStream_t s);
+                          float* frec32, int32_t* flag, hipStream_t s);
 hipError_t launch_grad_micro(int D, int prec, const DevMesh& m, const DevVel& v,
                              const double* frec, const void* h, const void* b, double* gh,
                              double* gb, const int32_t* flag, hipStream_t s);
@@ -245,24 +261,17 @@ hipError_t launch_dt_cells(int D, const DevMesh& m, const DevVel& v, double* cel
                            hipStream_t s);
 // fused sweep (ugks_sweep.hip)
 hipError_t launch_cell_prep(int D, int64_t nc, const GasP& g, const double* W, const double* q,
-                            double* prim, double* cs, int32_t* flag, hipStream_t s);
-// crec_d, cs, frec, tabs: FP64 records, or their FP32 copies when prec is FP32
+                            double* prim, double* cs, float* cs32, int32_t* flag, hipStream_t s);
 hipError_t launch_sweep(int D, int prec, const FusedMesh& fm, const DevVel& v, const GasP& g,
-                        const SweepSched& sc, const void* crec_d, const void* crec_l,
-                        const void* cs, const void* frec,
-                        const void* tabs, const void* h, const void* b, void* ht, void* bt,
-                        double* dWp, const int32_t* flag, hipStream_t s);
-hipError_t launch_to_f32(const double* a, float* fa, int64_t na, const double* b, float* fb,
-                         int64_t nb, const double* c, float* fc, int64_t nc, hipStream_t s);
-hipError_t launch_tables(int D, const DevMesh& m, const FusedMesh& fm, const GasP& g,
-                         const double* frec, const double* prim, const double* cs, double* tabs,
-                         const int32_t* flag, hipStream_t s);
+                        const SweepSched& sc, const StepBuffers& B, hipStream_t s);
+hipError_t launch_step_cell(int D, int prec, const DevMesh& m, const FusedMesh& fm, const DevVel& v,
+                            const GasP& g, const SweepSched& sc, const StepBuffers& B, hipStream_t s);
 hipError_t launch_apply_dW(int D, const DevMesh& m, int64_t nchunk, const double* W,
                           const double* dWp, double* Wn, double* cellred, const int32_t* flag,
                           hipStream_t s);
 hipError_t launch_stage2_q(int D, int prec, const FusedMesh& fm, const DevVel& v,
-                           const double* primn, const double* csn, const void* ht, const void* bt,
-                           void* h, void* b, double* qn, const int32_t* flag, hipStream_t s);
+                           const double* primn, const double* csn, void* h, void* b, double* qn,
+                           const int32_t* flag, hipStream_t s);
 hipError_t launch_wall_rho_inline(int D, int prec, const DevMesh& m, const DevVel& v,
                                   const FusedMesh& fm, const GasP& g, const void* h, double* frec,
                                   const int32_t* flag, hipStream_t s, int track = 0,
@@ -274,22 +283,16 @@ hipError_t launch_ghost_rows(int D, int prec, const FusedMesh& fm, const DevVel&
                              hipStream_t s);
 
 // batched forms (one launch per phase over every case of a batch)
-hipError_t launch_cell_prep_b(int D, const BatchDev& bd, int64_t ncell, int next, hipStream_t s);
+hipError_t launch_cell_prep_b(int D, const BatchDev& bd, int64_t ncell, hipStream_t s);
 hipError_t launch_gradW_b(int D, const BatchDev& bd, int64_t ncell, hipStream_t s);
 hipError_t launch_face_eq_b(int D, const BatchDev& bd, int64_t nface, hipStream_t s);
 hipError_t launch_wall_rho_b(int D, int prec, const BatchDev& bd, int64_t nwall, hipStream_t s);
-hipError_t launch_to_f32_b(const BatchDev& bd, int64_t nface, int64_t ncell, int64_t ntab,
-                           hipStream_t s);
-hipError_t launch_tables_b(int D, const BatchDev& bd, int64_t ntab, hipStream_t s);
 hipError_t launch_ghost_rows_b(int D, int prec, const BatchDev& bd, int64_t nff, hipStream_t s);
-hipError_t launch_sweep_b(int D, int prec, const BatchDev& bd, int64_t grid, int threads,
-                          hipStream_t s);
-// resident work-groups of the batched sweep per CU at `threads` lanes
-int sweep_b_blocks_per_cu(int D, int prec, int threads);
-hipError_t launch_apply_dW_b(int D, const BatchDev& bd, int64_t ncell, hipStream_t s);
-hipError_t launch_stage2_q_b(int D, int prec, const BatchDev& bd, int64_t ncell, hipStream_t s);
+hipError_t launch_step_b(int D, int prec, const BatchDev& bd, int64_t grid, int threads,
+                         hipStream_t s);
+// resident work-groups of the batched step per CU at `threads` lanes
+int step_b_blocks_per_cu(int D, int prec, int threads);
 hipError_t launch_residual_b(const BatchDev& bd, hipStream_t s);
-hipError_t launch_commit_W_b(int D, const BatchDev& bd, int64_t ncell, hipStream_t s);
 
 }  // namespace ugks
 
@@ -297,6 +300,9 @@ struct ugks_ctx {
   int D = 0, kxi = 0, nr = 0, prec = 64, Bv = 64, flags = 0;
   bool fused = false;       // tensor-product symmetric velocity set, walls / interior only
   bool q_valid = false;     // buf.q holds the heat flux of the current h
+  bool cs_valid = false;    // buf.prim, buf.cs hold the records of the current W and q
+  bool resid_set = false;   // the residual's unit (its first non-zero change) is known
+  int32_t begun = 0;        // buf.flag[1] when last read
   // HIP graphs of one step, one per order of the q / q^{n+1} buffers (the
   // step swaps them); graph_q0 is buf.q when graph 0 was captured
   hipGraph_t graph[2] = {nullptr, nullptr};
@@ -309,7 +315,7 @@ struct ugks_ctx {
   ugks::GasP gas{};
   std::vector<int64_t> cell_perm;   // library cell c -> caller cell
   std::vector<int64_t> face_perm;   // library face f -> caller face
-  std::vector<int64_t> vel_perm;    // library velocity k -> caller velocity (k < nv)
+  std::vector<int64_t> vel_perm;    // velocity slot k < nvp -> caller velocity (-1: pad)
   ugks::DevMesh mesh{};
   const double* lsG_exact = nullptr;  // least-squares coefficients even under first-order reconstruction
   ugks::DevVel vel{};

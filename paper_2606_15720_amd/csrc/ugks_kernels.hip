@@ -82,8 +82,15 @@ __device__ __forceinline__ double venkat_phi(const DevMesh& m, int64_t i, int nf
 template <int D>
 __device__ __forceinline__ void gradW_at(int64_t i, const DevMesh& m, const DevBC* __restrict__ bcs,
                                          const GasP& g, const double* __restrict__ W,
-                                         double* __restrict__ gW, const int32_t* flag) {
-  if (*flag) return;
+                                         double* __restrict__ gW, int32_t* flag, int count) {
+  // the first kernel of a step: takes over the error of the step before, and
+  // counts the steps begun without one (a failed step's results are dropped)
+  const bool bad = flag[0] | flag[2];
+  if (count && i == 0) {
+    if (bad) flag[0] = 1;
+    else flag[1] += 1;
+  }
+  if (bad) return;
   const int nfc = m.nfc[i];
   const double* Wi = &W[i * (D + 2)];
   double acc[3][5], vmin[5], vmax[5];
@@ -122,9 +129,9 @@ __device__ __forceinline__ void gradW_at(int64_t i, const DevMesh& m, const DevB
 
 template <int D>
 __global__ void k_gradW(DevMesh m, const DevBC* __restrict__ bcs, GasP g, const double* __restrict__ W,
-                        double* __restrict__ gW, const int32_t* flag) {
+                        double* __restrict__ gW, int32_t* flag, int count) {
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (i < m.nc) gradW_at<D>(i, m, bcs, g, W, gW, flag);
+  if (i < m.nc) gradW_at<D>(i, m, bcs, g, W, gW, flag, count);
 }
 
 // Interface equilibrium data of every face (steps 6.1-6.6), wall Maxwellian
@@ -134,9 +141,10 @@ __device__ __forceinline__ void face_eq_at(int64_t f, const DevMesh& m, const De
                                            const GasP& g, const double* __restrict__ W,
                                            const double* __restrict__ gW,
                                            const double* __restrict__ q, double* __restrict__ frec,
-                                           int32_t* flag) {
+                                           float* __restrict__ frec32, int32_t* flag) {
   if (*flag) return;
   double* R = &frec[f * FREC];
+  float* R32 = frec32 ? &frec32[f * FREC] : nullptr;  // what the FP32 sweep reads of the record
   const int kind = m.fbc[f];
   const int L = m.fL[f];
   if (kind == UGKS_BC_WALL) {
@@ -152,6 +160,13 @@ __device__ __forceinline__ void face_eq_at(int64_t f, const DevMesh& m, const De
     for (int x = 0; x < 20; ++x) {
       R[FR_PH + x] = x == 0 ? 1.0 : 0.0;
       R[FR_PB + x] = x == 0 ? (g.K + 3.0 - D) / (2.0 * lamw) : 0.0;
+    }
+    if (R32) {
+      for (int x = 0; x < 2; ++x) R32[FR_G + x] = (float)R[FR_G + x];
+      for (int x = 0; x < 20; ++x) {
+        R32[FR_PH + x] = (float)R[FR_PH + x];
+        R32[FR_PB + x] = (float)R[FR_PB + x];
+      }
     }
     return;
   }
@@ -299,15 +314,23 @@ __device__ __forceinline__ void face_eq_at(int64_t f, const DevMesh& m, const De
       R[FR_PH + x] = x < Cb::N ? PH[x] : 0.0;
       R[FR_PB + x] = x < Cb::N ? PB[x] : 0.0;
     }
+    if (R32) {
+      for (int x = 0; x < 2; ++x) R32[FR_G + x] = (float)R[FR_G + x];
+      for (int x = 0; x < Cb::N; ++x) {
+        R32[FR_PH + x] = (float)PH[x];
+        R32[FR_PB + x] = (float)PB[x];
+      }
+    }
   }
 }
 
 template <int D>
 __global__ void k_face_eq(DevMesh m, const DevBC* __restrict__ bcs, GasP g,
                           const double* __restrict__ W, const double* __restrict__ gW,
-                          const double* __restrict__ q, double* __restrict__ frec, int32_t* flag) {
+                          const double* __restrict__ q, double* __restrict__ frec,
+                          float* __restrict__ frec32, int32_t* flag) {
   const int64_t f = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (f < m.nf) face_eq_at<D>(f, m, bcs, g, W, gW, q, frec, flag);
+  if (f < m.nf) face_eq_at<D>(f, m, bcs, g, W, gW, q, frec, frec32, flag);
 }
 
 // Microscopic gradients of h (and b) for every (cell, velocity) (step 5).
@@ -661,7 +684,7 @@ __global__ __launch_bounds__(TPB) void k_stage2(DevVel v, GasP g, const double* 
 __device__ __forceinline__ void residual_of(int64_t nc, const double* __restrict__ cellred,
                                             double* __restrict__ resid, const int32_t* flag,
                                             double* lds) {
-  if (*flag) return;
+  if (flag[0] | flag[2]) return;
   double acc[3] = {0, 0, 0};
   for (int64_t i = threadIdx.x; i < nc; i += blockDim.x)
     for (int x = 0; x < 3; ++x) acc[x] += cellred[i * 3 + x];
@@ -733,7 +756,6 @@ __global__ __launch_bounds__(TPB) void k_dt_cells(DevMesh m, DevVel v, double* _
   const int nfc = m.nfc[i];
   double mx = 0.0;
   for (int64_t k = threadIdx.x; k < v.nvp; k += TPB) {
-    if (k >= v.nv) break;
     double s = 0.0;
     for (int p = 0; p < nfc; ++p) {
       const int64_t f = m.cface[i * MAXF + p];
@@ -766,7 +788,7 @@ __global__ void k_gradW_b(BatchDev bd) {
   if (t >= bd.cell_off[bd.n]) return;
   const int c = case_of(bd.cell_off, bd.n, t);
   const CaseDev& C = bd.cases[c];
-  gradW_at<D>(t - bd.cell_off[c], C.m, C.bcs, C.g, C.B.W, C.B.gW, C.B.flag);
+  gradW_at<D>(t - bd.cell_off[c], C.m, C.bcs, C.g, C.B.W, C.B.gW, C.B.flag, 1);
 }
 
 template <int D>
@@ -775,7 +797,8 @@ __global__ void k_face_eq_b(BatchDev bd) {
   if (t >= bd.face_off[bd.n]) return;
   const int c = case_of(bd.face_off, bd.n, t);
   const CaseDev& C = bd.cases[c];
-  face_eq_at<D>(t - bd.face_off[c], C.m, C.bcs, C.g, C.B.W, C.B.gW, C.B.q, C.B.frec, C.B.flag);
+  face_eq_at<D>(t - bd.face_off[c], C.m, C.bcs, C.g, C.B.W, C.B.gW, C.B.q, C.B.frec,
+                C.B.frec32, C.B.flag);
 }
 
 // one block per case
@@ -783,17 +806,6 @@ __global__ __launch_bounds__(1024) void k_residual_b(BatchDev bd) {
   __shared__ double lds[3 * 16];
   const CaseDev& C = bd.cases[blockIdx.x];
   residual_of(C.m.nc, C.B.cellred, C.B.resid, C.B.flag, lds);
-}
-
-template <int D>
-__global__ void k_commit_W_b(BatchDev bd) {
-  const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (t >= bd.cell_off[bd.n]) return;
-  const int c = case_of(bd.cell_off, bd.n, t);
-  const CaseDev& C = bd.cases[c];
-  if (*C.B.flag) return;
-  const int64_t i = t - bd.cell_off[c];
-  for (int x = 0; x < D + 2; ++x) C.B.W[i * (D + 2) + x] = C.B.Wn[i * (D + 2) + x];
 }
 
 }  // namespace
@@ -835,15 +847,15 @@ hipError_t launch_heatflux(int D, int prec, const DevMesh& m, const DevVel& v, c
 }
 
 hipError_t launch_gradW(int D, const DevMesh& m, const DevBC* bcs, const GasP& g, const double* W,
-                        double* gW, const int32_t* flag, hipStream_t s) {
-  UGKS_DISPATCH_D(D, k_gradW<DD><<<blocks_for(m.nc, 128), 128, 0, s>>>(m, bcs, g, W, gW, flag));
+                        double* gW, int32_t* flag, int count, hipStream_t s) {
+  UGKS_DISPATCH_D(D, k_gradW<DD><<<blocks_for(m.nc, 128), 128, 0, s>>>(m, bcs, g, W, gW, flag, count));
   return hipGetLastError();
 }
 
 hipError_t launch_face_eq(int D, const DevMesh& m, const DevBC* bcs, const GasP& g,
                           const double* W, const double* gW, const double* q, double* frec,
-                          int32_t* flag, hipStream_t s) {
-  UGKS_DISPATCH_D(D, k_face_eq<DD><<<blocks_for(m.nf, 64), 64, 0, s>>>(m, bcs, g, W, gW, q, frec, flag));
+                          float* frec32, int32_t* flag, hipStream_t s) {
+  UGKS_DISPATCH_D(D, k_face_eq<DD><<<blocks_for(m.nf, 64), 64, 0, s>>>(m, bcs, g, W, gW, q, frec, frec32, flag));
   return hipGetLastError();
 }
 
@@ -949,14 +961,6 @@ hipError_t launch_face_eq_b(int D, const BatchDev& bd, int64_t nface, hipStream_
 hipError_t launch_residual_b(const BatchDev& bd, hipStream_t s) {
   if (bd.n == 0) return hipSuccess;
   k_residual_b<<<(unsigned)bd.n, 1024, 0, s>>>(bd);
-  return hipGetLastError();
-}
-
-hipError_t launch_commit_W_b(int D, const BatchDev& bd, int64_t ncell, hipStream_t s) {
-  if (ncell == 0) return hipSuccess;
-  const unsigned grid = (unsigned)((ncell + 255) / 256);
-  if (D == 2) k_commit_W_b<2><<<grid, 256, 0, s>>>(bd);
-  else k_commit_W_b<3><<<grid, 256, 0, s>>>(bd);
   return hipGetLastError();
 }
 

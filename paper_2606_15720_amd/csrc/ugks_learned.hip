@@ -107,7 +107,7 @@ __global__ __launch_bounds__(TPB) void k_targets(DevVel v, GasP g, const double*
   prim_of<D>(&W[i * (D + 2)], g, P);
   const double p = P[6], RT = 0.5 / P[4];
   double acc[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0};  // Pxx Pyy Pzz Pxy Pxz Pyz qx qy qz
-  for (int64_t k = threadIdx.x; k < v.nv; k += TPB) {
+  for (int64_t k = threadIdx.x; k < v.nvp; k += TPB) {
     double c[3] = {0, 0, 0};
     double c2 = 0.0;
     for (int d = 0; d < D; ++d) {
@@ -487,11 +487,6 @@ __global__ __launch_bounds__(TPB) void k_grad_init(DevVel v, GasP g, const doubl
   const double nrm = rho * maxw_norm<D>(lam);
   const double sq = 2.0 * sqrt(lam);
   for (int64_t k = threadIdx.x; k < v.nvp; k += TPB) {
-    if (k >= v.nv) {
-      st(h, i * v.nvp + k, 0.0);
-      if (D == 2) st(b, i * v.nvp + k, 0.0);
-      continue;
-    }
     double c[3] = {0, 0, 0};
     double c2 = 0.0;
     for (int d = 0; d < D; ++d) {
@@ -885,7 +880,7 @@ int ugks_snapshot(ugks_ctx* c, float* feat, float* targ) {
     DevMesh mg = c->mesh;
     mg.lsG = c->lsG_exact;  // features use the true gradient at any reconstruction order
     mg.limiter = 0;         // and unlimited
-    HIP_TRY(launch_gradW(D, mg, c->bcs, c->gas, B.W, B.gW, B.flag, s));
+    HIP_TRY(launch_gradW(D, mg, c->bcs, c->gas, B.W, B.gW, B.flag, 0, s));
     const unsigned g1 = (unsigned)((nc + 127) / 128);
     if (D == 2) hipLaunchKernelGGL(k_features<2>, dim3(g1), dim3(128), 0, s, nc, c->gas, B.W, B.gW, fd);
     else hipLaunchKernelGGL(k_features<3>, dim3(g1), dim3(128), 0, s, nc, c->gas, B.W, B.gW, fd);
@@ -944,7 +939,7 @@ int ugks_warm_start(ugks_ctx* c, const ugks_mlp* net, const double* W, int64_t* 
     DevMesh mg = c->mesh;
     mg.lsG = c->lsG_exact;  // features use the true gradient at any reconstruction order
     mg.limiter = 0;         // and unlimited
-    HIP_TRY(launch_gradW(D, mg, c->bcs, c->gas, B.W, B.gW, B.flag, s));
+    HIP_TRY(launch_gradW(D, mg, c->bcs, c->gas, B.W, B.gW, B.flag, 0, s));
     const unsigned g1 = (unsigned)((nc + 127) / 128);
     if (D == 2) hipLaunchKernelGGL(k_features<2>, dim3(g1), dim3(128), 0, s, nc, c->gas, B.W, B.gW, fd);
     else hipLaunchKernelGGL(k_features<3>, dim3(g1), dim3(128), 0, s, nc, c->gas, B.W, B.gW, fd);
@@ -963,6 +958,8 @@ int ugks_warm_start(ugks_ctx* c, const ugks_mlp* net, const double* W, int64_t* 
     HIP_TRY(hipStreamSynchronize(s));
     if (n_fallback) *n_fallback = nf;
     c->q_valid = false;  // the next step takes the heat flux of the new f
+    c->cs_valid = false;
+    c->resid_set = false;
     HIP_TRY(hipMemsetAsync(B.resid, 0, 8 * sizeof(double), s));  // residuals restart from here
     for (void* p : {(void*)fd, (void*)od, (void*)cnt}) {
       (void)hipFree(p);

@@ -1,7 +1,7 @@
 // Fused velocity sweep for tensor-product, mirror-symmetric velocity sets.
 //
-// A work item is one cell and one block of its velocity space.  Each lane
-// owns a mirror pair of velocities (u, -u): for every face of the cell
+// A work item is one cell with all of its velocities (or, where cells are
+// too few, with one block of them).  Each lane owns a mirror pair of velocities (u, -u): for every face of the cell
 // exactly one of the two leaves the cell, so the lane evaluates one
 // time-integrated flux from the cell's own reconstruction (outgoing) and one
 // from the neighbour's reconstruction (incoming), with no divergence between
@@ -25,9 +25,12 @@
 // u and -u, each neighbour's stencil at the incoming member) are issued
 // before any arithmetic so their latency overlaps.  In 2-D the b equation
 // (same transport and relaxation, its own equilibrium polynomials) runs as a
-// second pass over the block after h, except in the batched form, whose
-// short work items carry h and b in one pass.  Stage 2 (Eq. f_final) and
-// the heat flux of the new distribution are fused in a second kernel.
+// second pass over the cell's velocities after h, except in the batched form,
+// whose short work items carry h and b in one pass.  The work-group that has
+// swept a whole cell goes on with the rest of the cell's step (conservative
+// update, second stage of Eq. f_final, heat flux, the next step's cell
+// record); the new state goes to the second of two buffers, which the host
+// swaps, so neighbours keep reading h^n.
 #include <type_traits>
 
 #include "ugks_device.h"
@@ -39,7 +42,8 @@ using namespace dev;
 namespace {
 
 constexpr int SWF = 4;      // faces per cell on the fused path (triangles, quads, tets)
-constexpr int SWT = 256;    // threads per work-group
+constexpr int SWT = 256;    // lanes per work-group of the blocked form
+constexpr int CELLT = 512;  // most lanes per work-group of the whole-cell form
 constexpr int NAX = 64;     // nodes per velocity axis (max)
 
 // A wave-uniform row of f in the global address space, kept opaque in
@@ -65,6 +69,23 @@ using crec_t = const __attribute__((address_space(4))) X;
 template <typename T, typename C>
 __device__ __forceinline__ C ldo(grow_t* row, uint32_t off) {
   return static_cast<C>(*(const __attribute__((address_space(1))) T*)(row + off));
+}
+
+// The same for stores.
+typedef __attribute__((address_space(1))) char gout_t;
+template <typename T>
+__device__ __forceinline__ gout_t* sout(T* p) {
+  gout_t* g = (gout_t*)p;
+  __asm__("" : "+s"(g));
+  return g;
+}
+template <typename T>
+__device__ __forceinline__ void sto(gout_t* row, uint32_t off, T v) {
+  *(__attribute__((address_space(1))) T*)(row + off) = v;
+}
+template <typename T>
+__device__ __forceinline__ void sto_nt(gout_t* row, uint32_t off, T v) {
+  __builtin_nontemporal_store(v, (__attribute__((address_space(1))) T*)(row + off));
 }
 
 // Even and odd parts of a cubic P = c + l.u + u^T Q u + (kappa . u)|u|^2
@@ -112,560 +133,439 @@ __device__ __forceinline__ C venkat_phi(C vi, C vmin, C vmax, const C* g, PT off
   return Nm / Dm;
 }
 
-// Per-cell first-stage data of one step: dt/(2 tau), K_xi/(2 lambda) and the
-// Shakhov polynomials H+/H, B+/B of the cell's equilibrium (Eqs. H_plus, B_plus).
+// Shakhov polynomials H+/H and B+/B of a cell's equilibrium with heat flux qc
+// (Eqs. H_plus, B_plus).
+template <int D>
+__device__ __forceinline__ void shakhov_polys(const double* P, const GasP& g, const double* qc,
+                                              double* SH, double* SB) {
+  using Cb = Cubic<D>;
+#pragma unroll
+  for (int x = 0; x < Cb::N; ++x) SH[x] = SB[x] = 0.0;
+  const double lam = P[4];
+  const double sh = 4.0 * (1.0 - g.Pr) * lam * lam / ((g.K + 5.0) * P[0]);
+  const double U[3] = {P[1], P[2], P[3]};
+  Cb::add_shakhov(SH, sh, U, qc, lam, 2.0 + D);
+  Cb::add_shakhov(SB, sh, U, qc, lam, (double)D);
+}
+
+// Per-step record of a cell with primitives P: dt/(2 tau), K_xi/(2 lambda),
+// the Maxwellian's norm and the Shakhov polynomials (and its FP32 copy).
+template <int D>
+__device__ __forceinline__ void cell_record(const double* P, const GasP& g, double dt, const double* qc,
+                                            double* __restrict__ C, float* __restrict__ C32) {
+  constexpr int N = Cubic<D>::N;
+  double SH[N], SB[N];
+  shakhov_polys<D>(P, g, qc, SH, SB);
+  const double cc = dt / (2.0 * P[5]), kap = (g.K + 3.0 - D) / (2.0 * P[4]);
+  C[CS_CC] = cc;
+  C[CS_KAP] = kap;
+  C[CS_NORM] = P[0] * maxw_norm<D>(P[4]);
+#pragma unroll
+  for (int x = 0; x < N; ++x) {
+    C[CS_SH + x] = SH[x];
+    C[CS_SB + x] = SB[x];
+  }
+  if (C32) {
+    C32[CS_CC] = (float)cc;
+    C32[CS_KAP] = (float)kap;
+#pragma unroll
+    for (int x = 0; x < N; ++x) {
+      C32[CS_SH + x] = (float)SH[x];
+      C32[CS_SB + x] = (float)SB[x];
+    }
+  }
+}
+
 template <int D>
 __device__ __forceinline__ void cell_prep_at(int64_t i, const GasP& g, const double* __restrict__ W,
                                              const double* __restrict__ q,
                                              double* __restrict__ prim, double* __restrict__ cs,
-                                             int32_t* flag) {
+                                             float* __restrict__ cs32, int32_t* flag) {
   if (*flag) return;
   double* P = &prim[i * NPRIM];
   if (!prim_of<D>(&W[i * (D + 2)], g, P)) {
     atomicOr(flag, 1);
     return;
   }
-  using Cb = Cubic<D>;
-  double SH[Cb::N], SB[Cb::N];
-  for (int x = 0; x < Cb::N; ++x) SH[x] = SB[x] = 0.0;
-  const double lam = P[4], rho = P[0];
-  const double sh = 4.0 * (1.0 - g.Pr) * lam * lam / ((g.K + 5.0) * rho);
-  const double U[3] = {P[1], P[2], P[3]};
   const double qc[3] = {q[i * 3], q[i * 3 + 1], q[i * 3 + 2]};
-  Cb::add_shakhov(SH, sh, U, qc, lam, 2.0 + D);
-  Cb::add_shakhov(SB, sh, U, qc, lam, (double)D);
-  double* C = &cs[i * CSREC];
-  C[CS_CC] = dt_cell(g, i) / (2.0 * P[5]);
-  C[CS_KAP] = (g.K + 3.0 - D) / (2.0 * lam);
-  C[CS_NORM] = rho * maxw_norm<D>(lam);
-  for (int x = 0; x < 20; ++x) {
-    C[CS_SH + x] = x < Cb::N ? SH[x] : 0.0;
-    C[CS_SB + x] = x < Cb::N ? SB[x] : 0.0;
-  }
+  cell_record<D>(P, g, dt_cell(g, i), qc, &cs[i * CSREC], cs32 ? &cs32[i * CSREC] : nullptr);
 }
 
 template <int D>
 __global__ void k_cell_prep(int64_t nc, GasP g, const double* __restrict__ W,
                             const double* __restrict__ q, double* __restrict__ prim,
-                            double* __restrict__ cs, int32_t* flag) {
+                            double* __restrict__ cs, float* __restrict__ cs32, int32_t* flag) {
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (i < nc) cell_prep_at<D>(i, g, W, q, prim, cs, flag);
+  if (i < nc) cell_prep_at<D>(i, g, W, q, prim, cs, cs32, flag);
 }
 
-// Axis tables of every face Maxwellian and every cell Maxwellian of the
-// step, tab[e][d][n] = scale_d exp(-lambda (a_n - U_d)^2) with the density
-// and normalisation folded into d = 0, so that g(u) at a tensor point is a
-// product of D entries.  Entities 0..nf-1 are faces (interface g0, or on a
-// wall the re-emitted Maxwellian scaled by rho_w dt), nf..nf+nc-1 cells.
+// LDS of one work item.  A table holds, for node n, the entry at n and the
+// entry at its mirror na-1-n side by side: one read serves u and -u.
+// During the sweep: the Maxwellian axis tables of the cell's four faces and of
+// the cell, and the velocity nodes; afterwards: the new state's tables and
+// Shakhov polynomials (FP64 in either form).
+template <int D, typename C>
+struct SweepTabs {
+  alignas(16) C tab[5][D][NAX][2];  // faces 0..3, then the cell
+  C ax[NAX][2];
+};
 template <int D>
-__device__ __forceinline__ void tables_at(int64_t t, int64_t nf, int na,
-                                          const double* __restrict__ axis,
-                                          const int32_t* __restrict__ fbc, const GasP& g,
-                                          const double* __restrict__ frec,
-                                          const double* __restrict__ prim,
-                                          const double* __restrict__ cs, double* __restrict__ tabs,
-                                          const int32_t* __restrict__ flag) {
-  const int64_t per = (int64_t)D * na;
-  if (*flag) return;
-  const int64_t e = t / per;
-  const int r = (int)(t % per), d = r / na, n = r % na;
-  const double a = axis[n];
-  double lam, U, scale = 1.0;
-  if (e < nf) {
-    const double* R = &frec[e * FREC];
-    lam = R[FR_LAM];
-    U = R[FR_U + d];
-    if (d == 0)  // rho0 (lambda0/pi)^(D/2), or rho_w dt (lambda_w/pi)^(D/2) on a wall
-      scale = fbc[e] == UGKS_BC_WALL ? R[FR_C0] * R[FR_RHOW] * g.dt : R[FR_C0];
-  } else {
-    const int64_t i = e - nf;
-    lam = prim[i * NPRIM + 4];
-    U = prim[i * NPRIM + 1 + d];
-    if (d == 0) scale = cs[i * CSREC + CS_NORM];
-  }
-  tabs[e * per + d * na + n] = scale * exp(-lam * (a - U) * (a - U));
-}
-
-template <int D>
-__global__ void k_tables(int64_t nf, int64_t nc, int na, const double* __restrict__ axis,
-                         const int32_t* __restrict__ fbc, GasP g, const double* __restrict__ frec,
-                         const double* __restrict__ prim, const double* __restrict__ cs,
-                         double* __restrict__ tabs, const int32_t* __restrict__ flag) {
-  const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (t < (nf + nc) * (int64_t)D * na) tables_at<D>(t, nf, na, axis, fbc, g, frec, prim, cs, tabs, flag);
-}
-
-// LDS of one sweep work item: the Maxwellian axis tables of the cell's four
-// faces and of the cell, the velocity nodes and the reduction scratch.
-template <typename C>
+struct CellTabs {
+  alignas(16) double tab[D][NAX][2];
+  double ax[NAX][2];
+  double poly[40];
+};
+template <int D, typename C>
 struct SweepLds {
-  C tab[SWF][3][NAX];
-  C ctab[3][NAX];
-  C ax[NAX];
+  union {
+    SweepTabs<D, C> s;
+    CellTabs<D> c;
+  };
   double red[5 * 16];
 };
 
-// One work item of the fused sweep: cell ic, velocity block `chunk`.
-// Every read-only array is its own __restrict__ argument so that the
-// compiler can prove no store of the sweep clobbers it and serve the
-// wave-uniform reads from the scalar cache.
-template <int D, typename T, typename C, bool SPLIT, bool LIM = false, bool SPARSE = false,
-          bool NB = false>
-__device__ __forceinline__ void sweep_item(
-    const FusedMesh& fm, int64_t nvp, const SweepSched& sc, const int32_t* __restrict__ crec_i,
-    const C* __restrict__ crec_d, const C* __restrict__ crec_l, const int32_t* __restrict__ vidx,
-    const double* __restrict__ w, const C* __restrict__ cs, const C* __restrict__ frec,
-    const C* __restrict__ tabs, const T* __restrict__ h, const T* __restrict__ b,
-    T* __restrict__ ht, T* __restrict__ bt, double* __restrict__ dWp,
-    const int32_t* __restrict__ flag, int64_t ic, int64_t chunk, SweepLds<C>& L) {
-  if (*flag) return;
-  // every pointer below is wave-uniform: its loads are scalar loads
-  crec_i_t* ci0 = (crec_i_t*)(crec_i + ic * CRI);
-  crec_t<C>* cd0 = (crec_t<C>*)(crec_d + ic * CRD);
-  crec_t<C>* cc0 = (crec_t<C>*)(cs + ic * CSREC);
-  crec_t<C>* frc = (crec_t<C>*)frec;
-  crec_t<C>* cl0 = LIM ? (crec_t<C>*)(crec_l + ic * CRL) : nullptr;
-  const unsigned nthr = blockDim.x;  // lanes of the work-group, one mirror pair each
-  const int na = fm.na;
-  {
-    // Stage this cell's face and cell tables in LDS (faces 0..3, then the
-    // cell).  The five table entities are scalar loads; each wave copies
-    // whole (entity, axis) rows, one node per lane (na <= 64, and the
-    // work-group is 1, 2 or 4 waves), and with the row loop unrolled all of
-    // a wave's loads are in flight together.
-    const int64_t ent[5] = {(int64_t)ci0[CRI_F0], (int64_t)ci0[CRI_F0 + CRI_FS],
-                            (int64_t)ci0[CRI_F0 + 2 * CRI_FS], (int64_t)ci0[CRI_F0 + 3 * CRI_FS],
-                            sc.nf + ic};
-    const unsigned lane = threadIdx.x & 63u;
-    const unsigned wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const unsigned wmask = (nthr >> 6) - 1;
-    if (lane < (unsigned)na) {
-      C v[5 * D];
+// Pair entry at a byte offset into one table row.
+template <typename C>
+__device__ __forceinline__ void tab_pair(const C (*row)[2], unsigned off, C& at_u, C& at_mu) {
+  typedef C pair_t __attribute__((ext_vector_type(2)));
+  const pair_t v = *(const pair_t*)((const char*)row + off);
+  at_u = v.x;
+  at_mu = v.y;
+}
+
+// Byte offset of a point's node on axis d in a table of C pairs (packed
+// indices: 16 * node in 10 bits per axis).
+template <typename C>
+__device__ __forceinline__ unsigned node_off(int pk, int d) {
+  return sizeof(C) == 8 ? ((unsigned)pk >> (10 * d)) & 1023u : ((unsigned)pk >> (10 * d + 1)) & 511u;
+}
+__device__ __forceinline__ int node_of(int pk, int d) { return (pk >> (10 * d + 4)) & 63; }
+
+// One 64-lane sum, valid in lane 63: shifts within rows of 16, then the rows
+// joined by broadcasts (no LDS round trips).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_add(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, false);
+  return v + __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double wave_total(double v) {
+  v = dpp_add<0x111, 0xf>(v);  // row_shr:1, 2, 4, 8
+  v = dpp_add<0x112, 0xf>(v);
+  v = dpp_add<0x114, 0xf>(v);
+  v = dpp_add<0x118, 0xf>(v);
+  v = dpp_add<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
+  return dpp_add<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3
+}
+
+// Work-group totals of N values, in every lane: each wave's sum, then the
+// waves in order.
+template <int N>
+__device__ __forceinline__ void block_total(double (&v)[N], double* lds) {
 #pragma unroll
-      for (int row = 0; row < 5 * D; ++row)
-        if (((unsigned)row & wmask) == wv) v[row] = tabs[(ent[row / D] * D + row % D) * na + lane];
+  for (int n = 0; n < N; ++n) v[n] = wave_total(v[n]);
+  const int wv = threadIdx.x / WAVE, nw = blockDim.x / WAVE;
+  if (threadIdx.x % WAVE == WAVE - 1)
 #pragma unroll
-      for (int row = 0; row < 5 * D; ++row)
-        if (((unsigned)row & wmask) == wv) {
-          if (row / D < 4) L.tab[row / D][row % D][lane] = v[row];
-          else L.ctab[row % D][lane] = v[row];
-        }
-      if (wv == 0) L.ax[lane] = fm.axis[lane];
-    }
-    __syncthreads();
+    for (int n = 0; n < N; ++n) lds[n * 16 + wv] = v[n];
+  __syncthreads();
+#pragma unroll
+  for (int n = 0; n < N; ++n) {
+    double t = lds[n * 16];
+    for (int w = 1; w < nw; ++w) t += lds[n * 16 + w];
+    v[n] = t;
   }
-  constexpr int NM = D + 2;
-  const unsigned nv = (unsigned)fm.nv;
-  const unsigned npairs = (unsigned)fm.npairs;
-  const unsigned kbeg = (unsigned)(chunk * sc.chunk_pairs);
-  const unsigned kend = (unsigned)min((int64_t)npairs, (chunk + 1) * sc.chunk_pairs);
+}
+
+// A wave-uniform double in scalar registers.
+__device__ __forceinline__ double uniform(double v) {
+  return __hiloint2double(__builtin_amdgcn_readfirstlane(__double2hiint(v)),
+                          __builtin_amdgcn_readfirstlane(__double2loint(v)));
+}
+
+// What a sweep reads besides f: every pointer wave-uniform.
+template <typename C>
+struct SweepIn {
+  const int32_t* crec_i;
+  const C* crec_d;
+  const C* crec_l;
+  const int32_t* vidx;
+  const double* w;
+  const C* cs;
+  const C* frec;
+  const double* frec64;
+  const double* prim;
+  double norm, dt;
+  int64_t nvp;
+  unsigned half;  // slots of the first members; the mirror of slot k is slot half + k
+  int na;
+  const double* axis;
+};
+
+// The Maxwellian axis tables of the cell's four faces (the interface g0, or
+// on a wall the re-emitted Maxwellian scaled by rho_w dt) and of the cell,
+// scale exp(-lambda (a_n - U_d)^2) with density and norm folded into the
+// first axis, so that g(u) at a tensor point is a product of D entries.
+// A half wave (a wave where an axis has more than 32 nodes) takes one
+// (entity, axis) row at a time.  Computing them here takes about one exp per
+// lane; as arrays written once per step and read by each cell they cost a
+// launch and, with their FP32 copies, 1-3 % of the step.
+template <int D, typename C>
+__device__ __forceinline__ void sweep_tables(const SweepIn<C>& in, int64_t ic, SweepTabs<D, C>& L) {
+  const unsigned nthr = blockDim.x, na = (unsigned)in.na;
+  const bool half = na <= 32;
+  const unsigned n = half ? threadIdx.x & 31u : threadIdx.x & 63u;
+  const unsigned r0 = half ? threadIdx.x >> 5 : threadIdx.x >> 6, rs = half ? nthr >> 5 : nthr >> 6;
+  if (n < na) {
+    const double a = in.axis[n];
+    for (unsigned row = r0; row < 5u * D; row += rs) {
+      const unsigned e = row / D, d = row % D;
+      double lam, U, scale = 1.0;
+      if (e < 4) {
+        const int32_t* fi = in.crec_i + ic * CRI + CRI_F0 + CRI_FS * e;
+        const double* R = in.frec64 + (uint64_t)(uint32_t)fi[0] * FREC;
+        lam = R[FR_LAM];
+        U = R[FR_U + d];
+        if (d == 0) scale = fi[1] == UGKS_BC_WALL ? R[FR_C0] * R[FR_RHOW] * in.dt : R[FR_C0];
+      } else {
+        lam = in.prim[ic * NPRIM + 4];
+        U = in.prim[ic * NPRIM + 1 + d];
+        if (d == 0) scale = in.norm;
+      }
+      const C v = (C)(scale * exp(-lam * (a - U) * (a - U)));
+      L.tab[e][d][n][0] = v;
+      L.tab[e][d][na - 1 - n][1] = v;
+    }
+    if (r0 == 0) L.ax[n][0] = (C)a;
+  }
+}
+
+// One pass over the mirror pairs [kbeg, kend) of cell ic (multiples of 64
+// except the lanes' stride) for NR reduced distributions, X0 the first:
+// X = 0 is h (mass, momentum and its share of the energy), X = 1 is b (the
+// rest of the energy).  The b equation has the same transport and relaxation
+// as h with its own equilibrium polynomials.  Adds the lane's moments
+// sum_k w_k psi_k (net outflow of the cell at u_k) to mw.
+//
+// The sign of u.n, which says which member leaves through a face, is a branch
+// and not a select: a wave's 64 pairs are a compact block of the velocity
+// lattice (4 x 4 x 4 or 8 x 8), so at most faces all lanes agree and one side
+// is skipped.  With one table read for both members that leaves about 380 VALU
+// instructions per pair of the 480 that selects took (3-D FP64).  Of 8.9 ms on
+// 48,000 tets x 24^3, rows beyond the cell's own cost 1.7 (L2 misses), the
+// first stage's stores 0.9 and the rest of the step 1.7; the loop alone is
+// at 65 % of its VALU time.
+template <int D, typename T, typename C, int NR, int X0, bool LIM>
+__device__ __forceinline__ void sweep_pass(const SweepIn<C>& in, const T* __restrict__ h,
+                                           const T* __restrict__ b, T* __restrict__ ht,
+                                           T* __restrict__ bt, int64_t ic, unsigned kbeg, unsigned kend,
+                                           const SweepTabs<D, C>& L, double (&mw)[D + 2]) {
+  crec_i_t* ci0 = (crec_i_t*)(in.crec_i + ic * CRI);
+  crec_t<C>* cd0 = (crec_t<C>*)(in.crec_d + ic * CRD);
+  crec_t<C>* cc0 = (crec_t<C>*)(in.cs + ic * CSREC);
+  crec_t<C>* frc = (crec_t<C>*)in.frec;
+  crec_t<C>* cl0 = LIM ? (crec_t<C>*)(in.crec_l + ic * CRL) : nullptr;
+  const unsigned nthr = blockDim.x;  // lanes of the work-group, one mirror pair each
   // Row r of h (or b) starts r * rowb bytes in.  Row indices are 32-bit and
   // non-negative, and a row is under 4 GiB, so the offset is one 32x32->64
   // scalar multiply.
-  const uint32_t rowb = (uint32_t)nvp * (uint32_t)sizeof(T);
+  const uint32_t rowb = (uint32_t)in.nvp * (uint32_t)sizeof(T), halfb = in.half * (uint32_t)sizeof(T);
   auto row_of = [rowb](const T* base, int32_t r) {
     return srow((const char*)base + (uint64_t)(uint32_t)r * rowb);
   };
-  // per-lane moments sum_k w_k psi_k (net outflow of the cell at u_k): the
-  // conservative update of the cell is W - sum (Eq. macro_update regrouped
-  // by velocity: sum_j sigma S_j F_j / V = sum_k w_k psi_k sum_j sigma S_j H_jk / V)
-  double mw[NM];
+  const T* src[NR];
+  gout_t* dst[NR];
+  grow_t *own[NR], *wt = srow(in.w), *ix = srow(in.vidx);
 #pragma unroll
-  for (int x = 0; x < NM; ++x) mw[x] = 0.0;
-
-  // In 2-D, h and b run as two passes over the block (each pass's records
-  // and row addresses then fit the scalar registers, where h and b together
-  // spill them), except for the batched form: the items of its small cases
-  // run only a few iterations, whose dependent-load latency two passes would
-  // pay twice, so there one pass carries both.
-  if constexpr (D == 2 && !SPLIT) {
-    // (64-bit row arithmetic here: the 32-bit form costs this body scalar
-    // registers it does not have)
-    constexpr bool B2 = true;
-    const T* __restrict__ hi = h + ic * nvp;
-    const T* __restrict__ bi = b + ic * nvp;
-    // the packed axis indices of the next pair are loaded one iteration ahead
-    int pk_next = kbeg + threadIdx.x < kend ? vidx[kbeg + threadIdx.x] : 0;
-    for (unsigned kp = kbeg + threadIdx.x; kp < kend; kp += nthr) {
-      // The cell and face records are loop invariant but too large to keep in
-      // scalar registers for the whole loop: an opaque uniform zero added to
-      // their addresses makes them scalar re-loads (scalar cache) each
-      // iteration instead of hoisted, spilled registers.
-      int z;
-      __asm__ volatile("s_mov_b32 %0, 0" : "=s"(z));
-      crec_i_t* ci = ci0 + z;
-      crec_t<C>* cd = cd0 + z;
-      crec_t<C>* cc = cc0 + z;
-      const unsigned k0 = kp, k1 = nv - 1 - kp;
-      const int pk = pk_next;
-      pk_next = vidx[min(kp + nthr, kend - 1)];
-      int id[3], im[3];
-  #pragma unroll
-      for (int d = 0; d < 3; ++d) {
-        id[d] = (pk >> (8 * d)) & 255;
-        im[d] = na - 1 - id[d];
-      }
-      C vv[3] = {C(0), C(0), C(0)};
-  #pragma unroll
-      for (int d = 0; d < D; ++d) vv[d] = L.ax[id[d]];
-      // orientation of u against every outward normal
-      C sp[4];
-  #pragma unroll
-      for (int p = 0; p < 4; ++p) {
-        C s = C(0);
-  #pragma unroll
-        for (int d = 0; d < D; ++d) s += vv[d] * cd[CRD_F0 + CRD_FS * p + 0 + d];
-        sp[p] = s;
-      }
-      // ---- the cell's own stencil at u and -u (4 rows, padded) ----
-      const uint32_t o0 = k0 * (uint32_t)sizeof(T), o1 = k1 * (uint32_t)sizeof(T);
-      grow_t* rhi = srow(hi);
-      const C h0 = ldo<T, C>(rhi, o0), h1 = ldo<T, C>(rhi, o1);
-      C b0 = C(0), b1 = C(0);
-      if (B2) {
-        grow_t* rbi = srow(bi);
-        b0 = ldo<T, C>(rbi, o0);
-        b1 = ldo<T, C>(rbi, o1);
-      }
-      C os0[4], os1[4], ob0[4], ob1[4];
-  #pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const int64_t cell = ci[2 + s];
-        grow_t* rh = srow(h + cell * nvp);
-        os0[s] = ldo<T, C>(rh, o0);
-        os1[s] = ldo<T, C>(rh, o1);
-        ob0[s] = ob1[s] = C(0);
-        if (B2) {
-          grow_t* rb = srow(b + cell * nvp);
-          ob0[s] = ldo<T, C>(rb, o0);
-          ob1[s] = ldo<T, C>(rb, o1);
-        }
-      }
-      // ---- every neighbour's value and stencil at the incoming member ----
-      // Slot p of the own stencil is the row across face p, and slot 0 of
-      // neighbour p's stencil is this cell: both are already in registers.
-      C nh[4], nhs[4][4], nb[4], nbs[4][4];
-  #pragma unroll
-      for (int p = 0; p < 4; ++p) {
-        crec_i_t* fi = ci + CRI_F0 + CRI_FS * p;
-        const bool in1 = sp[p] > C(0);  // the incoming member is -u
-        uint32_t oin = in1 ? o1 : o0;
-        __asm__("" : "+v"(oin));  // keep the select on the offset, not on 64-bit addresses
-        nh[p] = in1 ? os1[p] : os0[p];
-        nb[p] = B2 ? (in1 ? ob1[p] : ob0[p]) : C(0);
-        nhs[p][0] = in1 ? h1 : h0;
-        nbs[p][0] = B2 ? (in1 ? b1 : b0) : C(0);
-  #pragma unroll
-        for (int r = 1; r < 4; ++r) {
-          const int64_t cell = fi[5 + r];
-          nhs[p][r] = ldo<T, C>(srow(h + cell * nvp), oin);
-          nbs[p][r] = B2 ? ldo<T, C>(srow(b + cell * nvp), oin) : C(0);
-        }
-      }
-      // ---- arithmetic ----
-      C g0[3] = {C(0), C(0), C(0)}, g1[3] = {C(0), C(0), C(0)}, gb0[3] = {C(0), C(0), C(0)}, gb1[3] = {C(0), C(0), C(0)};
-  #pragma unroll
-      for (int s = 0; s < 4; ++s) {
-        const C d0 = os0[s] - h0, d1 = os1[s] - h1;
-        const C e0 = ob0[s] - b0, e1 = ob1[s] - b1;
-  #pragma unroll
-        for (int d = 0; d < D; ++d) {
-          const C G = cd[d * 4 + s];
-          g0[d] += G * d0;
-          g1[d] += G * d1;
-          if (B2) {
-            gb0[d] += G * e0;
-            gb1[d] += G * e1;
-          }
-        }
-      }
-      C ug0 = C(0), ug1 = C(0), ub0 = C(0), ub1 = C(0);
-  #pragma unroll
-      for (int d = 0; d < D; ++d) {
-        ug0 += vv[d] * g0[d];
-        ug1 -= vv[d] * g1[d];
-        if (B2) {
-          ub0 += vv[d] * gb0[d];
-          ub1 -= vv[d] * gb1[d];
-        }
-      }
-      C v2 = C(0);
-  #pragma unroll
-      for (int d = 0; d < D; ++d) v2 += vv[d] * vv[d];
-      C acc0 = C(0), acc1 = C(0), accb0 = C(0), accb1 = C(0);
-  #pragma unroll
-      for (int p = 0; p < 4; ++p) {
-        crec_t<C>* fd = cd + CRD_F0 + CRD_FS * p;
-        crec_t<C>* R = frc + (int64_t)ci[CRI_F0 + CRI_FS * p] * FREC;
-        const bool pos = sp[p] > C(0);
-        const C as = fabs(sp[p]);
-        const C G1 = R[FR_G], G2 = R[FR_G + 1];
-        // outgoing member: the cell's own reconstruction at the face
-        const C us = pos ? ug0 : ug1;
-        C hf = pos ? h0 : h1;
-  #pragma unroll
-        for (int d = 0; d < D; ++d) hf += fd[4 + d] * (pos ? g0[d] : g1[d]);
-        // incoming member: the neighbour's reconstruction at the face (all
-        // zero rows on a wall)
-        const C sgn_in = pos ? -1.0 : 1.0;  // u_in = sgn_in * u
-        const C hj = nh[p], bj = nb[p];
-        C gj[3] = {C(0), C(0), C(0)}, gbj[3] = {C(0), C(0), C(0)};
-  #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const C dh = nhs[p][r] - hj, db = nbs[p][r] - bj;
-  #pragma unroll
-          for (int d = 0; d < D; ++d) {
-            const C G = fd[10 + d * 4 + r];
-            gj[d] += G * dh;
-            if (B2) gbj[d] += G * db;
-          }
-        }
-        C hfj = hj, ugj = C(0);
-  #pragma unroll
-        for (int d = 0; d < D; ++d) {
-          hfj += fd[7 + d] * gj[d];
-          ugj += vv[d] * gj[d];
-        }
-        ugj *= sgn_in;
-        // g0 (or the scaled wall Maxwellian) at u and -u from the axis tables,
-        // times the equilibrium polynomial (constant on a wall)
-        C e0 = L.tab[p][0][id[0]], e1 = L.tab[p][0][im[0]];
-  #pragma unroll
-        for (int d = 1; d < D; ++d) {
-          e0 *= L.tab[p][d][id[d]];
-          e1 *= L.tab[p][d][im[d]];
-        }
-        C E, O;
-        cubic_eo<D>(R + FR_PH, vv, v2, E, O);
-        const C q0 = e0 * (E + O), q1 = e1 * (E - O);
-        const C eqm = fd[22];  // 0 on a wall: no equilibrium term going out
-        const C eqo = eqm * (pos ? q0 : q1);
-        const C eqi = pos ? q1 : q0;
-        const C out = as * (G1 * hf + G2 * us + eqo);
-        const C in = -as * (G1 * hfj + G2 * ugj + eqi);
-        C outb = 0.0, inb = 0.0;
-        if (B2) {
-          C bfo = pos ? b0 : b1;
-          const C ubs = pos ? ub0 : ub1;
-  #pragma unroll
-          for (int d = 0; d < D; ++d) bfo += fd[4 + d] * (pos ? gb0[d] : gb1[d]);
-          C bfj = bj, ubj = C(0);
-  #pragma unroll
-          for (int d = 0; d < D; ++d) {
-            bfj += fd[7 + d] * gbj[d];
-            ubj += vv[d] * gbj[d];
-          }
-          ubj *= sgn_in;
-          C Eb, Ob;
-          cubic_eo<D>(R + FR_PB, vv, v2, Eb, Ob);
-          const C r0 = e0 * (Eb + Ob), r1 = e1 * (Eb - Ob);
-          outb = as * (G1 * bfo + G2 * ubs + eqm * (pos ? r0 : r1));
-          inb = -as * (G1 * bfj + G2 * ubj + (pos ? r1 : r0));
-        }
-        // fluxes at u and at -u along this cell's outward normal, times S/V
-        const C sv = fd[3];
-        acc0 += sv * (pos ? out : in);
-        acc1 += sv * (pos ? in : out);
-        if (B2) {
-          accb0 += sv * (pos ? outb : inb);
-          accb1 += sv * (pos ? inb : outb);
-        }
-      }
-      // moments of the net outflow (the zero velocity of an odd grid once)
-      {
-        const double a0 = w[k0] * (double)acc0, a1 = (k1 != k0) ? w[k1] * (double)acc1 : 0.0;
-        mw[0] += a0 + a1;
-  #pragma unroll
-        for (int d = 0; d < D; ++d) mw[1 + d] += (double)vv[d] * (a0 - a1);
-        double e = 0.5 * (double)v2 * (a0 + a1);
-        if (B2) e += 0.5 * (w[k0] * (double)accb0 + ((k1 != k0) ? w[k1] * (double)accb1 : 0.0));
-        mw[D + 1] += e;
-      }
-      // first stage with the cell's BGK-Shakhov equilibrium at u and -u
-      C c0 = L.ctab[0][id[0]], c1 = L.ctab[0][im[0]];
-  #pragma unroll
-      for (int d = 1; d < D; ++d) {
-        c0 *= L.ctab[d][id[d]];
-        c1 *= L.ctab[d][im[d]];
-      }
-      C E, O;
-      cubic_eo<D>(cc + CS_SH, vv, v2, E, O);
-      const C ccoll = cc[CS_CC];
-      T* __restrict__ hto = ht + ic * nvp;
-      st(hto, k0, h0 - acc0 + ccoll * (c0 * (C(1) + E + O) - h0));
-      if (k1 != k0) st(hto, k1, h1 - acc1 + ccoll * (c1 * (C(1) + E - O) - h1));
-      if (B2) {
-        C Eb, Ob;
-        cubic_eo<D>(cc + CS_SB, vv, v2, Eb, Ob);
-        const C kc = cc[CS_KAP];
-        T* __restrict__ bto = bt + ic * nvp;
-        st(bto, k0, b0 - accb0 + ccoll * (kc * c0 * (C(1) + Eb + Ob) - b0));
-        if (k1 != k0) st(bto, k1, b1 - accb1 + ccoll * (kc * c1 * (C(1) + Eb - Ob) - b1));
+  for (int r = 0; r < NR; ++r) {
+    src[r] = X0 + r ? b : h;
+    dst[r] = sout((X0 + r ? bt : ht) + ic * in.nvp);
+    own[r] = srow(src[r] + ic * in.nvp);
+  }
+  // the packed axis indices of the next pair are loaded one iteration ahead
+  // (the array is padded for the read past the end)
+  unsigned kp = kbeg + threadIdx.x;
+  int pk_next = ldo<int32_t, int>(ix, kp * 4u);
+  for (; kp < kend; kp += nthr) {
+    // FP32: the wave takes a higher issue priority while it issues the
+    // iteration's gathers, so that they start early (measured 2-6 % faster in
+    // FP32, slower in FP64)
+    if constexpr (sizeof(C) == 4) __builtin_amdgcn_s_setprio(1);
+    // The cell and face records are loop invariant but too large to keep in
+    // scalar registers for the whole loop: an opaque uniform zero added to
+    // their addresses makes them scalar re-loads (scalar cache) each
+    // iteration instead of hoisted, spilled registers.
+    int z;
+    __asm__ volatile("s_mov_b32 %0, 0" : "=s"(z));
+    crec_i_t* ci = ci0 + z;
+    crec_t<C>* cd = cd0 + z;
+    crec_t<C>* cc = cc0 + z;
+    const int pk = pk_next;
+    pk_next = ldo<int32_t, int>(ix, (kp + nthr) * 4u);
+    unsigned at[D];
+    C vv[3] = {C(0), C(0), C(0)};
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      at[d] = node_off<C>(pk, d);
+      vv[d] = *(const C*)((const char*)L.ax + at[d]);
+    }
+    // orientation of u against every outward normal
+    C sp[4];
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+      C s = C(0);
+#pragma unroll
+      for (int d = 0; d < D; ++d) s += vv[d] * cd[CRD_F0 + CRD_FS * p + 0 + d];
+      sp[p] = s;
+    }
+    // ---- the cell's own stencil at u and -u (4 rows, padded) ----
+    const uint32_t o0 = kp * (uint32_t)sizeof(T), o1 = o0 + halfb;
+    C f0[NR], f1[NR], os0[NR][4], os1[NR][4];
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      f0[r] = ldo<T, C>(own[r], o0);
+      f1[r] = ldo<T, C>(own[r], o1);
+    }
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+#pragma unroll
+      for (int r = 0; r < NR; ++r) {
+        grow_t* rs = row_of(src[r], ci[2 + s]);
+        os0[r][s] = ldo<T, C>(rs, o0);
+        os1[r][s] = ldo<T, C>(rs, o1);
       }
     }
-  } else {
-    // One pass over the block's mirror pairs for one reduced distribution:
-    // X = 0 is h (mass, momentum and its share of the energy), X = 1 is b
-    // (2-D only: the rest of the energy).  The b equation has the same
-    // transport and relaxation as h with its own equilibrium polynomials.
-    auto pass = [&](auto xtag) {
-      constexpr int X = decltype(xtag)::value;
-      const T* __restrict__ f = X ? b : h;
-      T* __restrict__ fto = (X ? bt : ht) + ic * nvp;
-      grow_t* rfi = srow(f + ic * nvp);
-      // the packed axis indices of the next pair are loaded one iteration ahead
-      int pk_next = kbeg + threadIdx.x < kend ? vidx[kbeg + threadIdx.x] : 0;
-      for (unsigned kp = kbeg + threadIdx.x; kp < kend; kp += nthr) {
-        // FP32: the wave takes a higher issue priority while it issues the
-        // iteration's gathers, so that they start early (measured 2-6 %
-        // faster in FP32, slower in FP64)
-        if constexpr (sizeof(C) == 4) __builtin_amdgcn_s_setprio(1);
-        // The cell and face records are loop invariant but too large to keep
-        // in scalar registers for the whole loop: an opaque uniform zero
-        // added to their addresses makes them scalar re-loads (scalar cache)
-        // each iteration instead of hoisted, spilled registers.
-        int z;
-        __asm__ volatile("s_mov_b32 %0, 0" : "=s"(z));
-        crec_i_t* ci = ci0 + z;
-        crec_t<C>* cd = cd0 + z;
-        crec_t<C>* cc = cc0 + z;
-        // a pair's two points: k and its mirror; a sparse set lists them
-        // (a point without a mirror in the set has the pad slot nv as a
-        // partner: weight 0, never stored)
-        unsigned k0 = kp, k1 = nv - 1 - kp;
-        if constexpr (SPARSE) {
-          k0 = (unsigned)fm.pairs[2 * kp];
-          k1 = (unsigned)fm.pairs[2 * kp + 1];
-        }
-        const bool has1 = k1 != k0 && (!SPARSE || k1 < nv);
-        const int pk = pk_next;
-        pk_next = vidx[min(kp + nthr, kend - 1)];
-        int id[3], im[3];
+    // ---- every neighbour's stencil at the incoming member ----
+    // Slot p of the own stencil is the row across face p, and slot 0 of
+    // neighbour p's stencil is this cell: both are already in registers.
+    C ns[NR][4][3];
 #pragma unroll
-        for (int d = 0; d < 3; ++d) {
-          id[d] = (pk >> (8 * d)) & 255;
-          im[d] = na - 1 - id[d];
-        }
-        C vv[3] = {C(0), C(0), C(0)};
+    for (int p = 0; p < 4; ++p) {
+      crec_i_t* fi = ci + CRI_F0 + CRI_FS * p;
+      uint32_t oin = sp[p] > C(0) ? o1 : o0;  // u.n > 0: the incoming member is -u
+      __asm__("" : "+v"(oin));  // keep the select on the offset, not on 64-bit addresses
 #pragma unroll
-        for (int d = 0; d < D; ++d) vv[d] = L.ax[id[d]];
-        // orientation of u against every outward normal
-        C sp[4];
+      for (int q = 0; q < 3; ++q)
 #pragma unroll
-        for (int p = 0; p < 4; ++p) {
-          C s = C(0);
+        for (int r = 0; r < NR; ++r) ns[r][p][q] = ldo<T, C>(row_of(src[r], fi[6 + q]), oin);
+    }
+    if constexpr (sizeof(C) == 4) __builtin_amdgcn_s_setprio(0);
+    // ---- arithmetic ----
+    C g0[NR][D], g1[NR][D], ug0[NR], ug1[NR], acc0[NR], acc1[NR];
+    crec_t<C>* cl = LIM ? cl0 + z : nullptr;
 #pragma unroll
-          for (int d = 0; d < D; ++d) s += vv[d] * cd[CRD_F0 + CRD_FS * p + 0 + d];
-          sp[p] = s;
-        }
-        // ---- the cell's own stencil at u and -u (4 rows, padded) ----
-        const uint32_t o0 = k0 * (uint32_t)sizeof(T), o1 = k1 * (uint32_t)sizeof(T);
-        const C f0 = ldo<T, C>(rfi, o0), f1 = ldo<T, C>(rfi, o1);
-        C os0[4], os1[4];
+    for (int r = 0; r < NR; ++r) {
 #pragma unroll
-        for (int s = 0; s < 4; ++s) {
-          grow_t* rs = row_of(f, ci[2 + s]);
-          os0[s] = ldo<T, C>(rs, o0);
-          os1[s] = ldo<T, C>(rs, o1);
-        }
-        // ---- every neighbour's value and stencil at the incoming member ----
-        // Slot p of the own stencil is the row across face p, and slot 0 of
-        // neighbour p's stencil is this cell: both are already in registers.
-        C nh[4], nhs[4][4];
+      for (int d = 0; d < D; ++d) g0[r][d] = g1[r][d] = C(0);
 #pragma unroll
-        for (int p = 0; p < 4; ++p) {
-          crec_i_t* fi = ci + CRI_F0 + CRI_FS * p;
-          const bool in1 = sp[p] > C(0);  // the incoming member is -u
-          uint32_t oin = in1 ? o1 : o0;
-          __asm__("" : "+v"(oin));  // keep the select on the offset, not on 64-bit addresses
-          nh[p] = in1 ? os1[p] : os0[p];
-          nhs[p][0] = in1 ? f1 : f0;
-#pragma unroll
-          for (int r = 1; r < 4; ++r) nhs[p][r] = ldo<T, C>(row_of(f, fi[5 + r]), oin);
-        }
-        if constexpr (sizeof(C) == 4) __builtin_amdgcn_s_setprio(0);
-        // ---- arithmetic ----
-        C g0[3] = {C(0), C(0), C(0)}, g1[3] = {C(0), C(0), C(0)};
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-          const C d0 = os0[s] - f0, d1 = os1[s] - f1;
-#pragma unroll
-          for (int d = 0; d < D; ++d) {
-            const C G = cd[d * 4 + s];
-            g0[d] += G * d0;
-            g1[d] += G * d1;
-          }
-        }
-        crec_t<C>* cl = LIM ? cl0 + z : nullptr;
-        if constexpr (LIM) {
-          // the cell's own gradients at u and -u, limited (a wall slot's
-          // zero row stands for the cell's own value in the bounds)
-          C lo0 = f0, hi0 = f0, lo1 = f1, hi1 = f1;
-#pragma unroll
-          for (int s = 0; s < 4; ++s) {
-            const C wm = cl[1 + s];
-            const C v0 = wm * f0 + os0[s], v1 = wm * f1 + os1[s];
-            lo0 = fmin(lo0, v0);
-            hi0 = fmax(hi0, v0);
-            lo1 = fmin(lo1, v1);
-            hi1 = fmax(hi1, v1);
-          }
-          const C e2 = cl[0];
-          const C p0 = venkat_phi<D>(f0, lo0, hi0, g0, cd + CRD_F0 + 4, CRD_FS, e2);
-          const C p1 = venkat_phi<D>(f1, lo1, hi1, g1, cd + CRD_F0 + 4, CRD_FS, e2);
-#pragma unroll
-          for (int d = 0; d < D; ++d) {
-            g0[d] *= p0;
-            g1[d] *= p1;
-          }
-        }
-        C ug0 = C(0), ug1 = C(0);
+      for (int s = 0; s < 4; ++s) {
+        const C d0 = os0[r][s] - f0[r], d1 = os1[r][s] - f1[r];
 #pragma unroll
         for (int d = 0; d < D; ++d) {
-          ug0 += vv[d] * g0[d];
-          ug1 -= vv[d] * g1[d];
+          const C G = cd[d * 4 + s];
+          g0[r][d] += G * d0;
+          g1[r][d] += G * d1;
         }
-        C v2 = C(0);
+      }
+      if constexpr (LIM) {
+        // the cell's own gradients at u and -u, limited (a wall slot's
+        // zero row stands for the cell's own value in the bounds)
+        C lo0 = f0[r], hi0 = f0[r], lo1 = f1[r], hi1 = f1[r];
 #pragma unroll
-        for (int d = 0; d < D; ++d) v2 += vv[d] * vv[d];
-        C acc0 = C(0), acc1 = C(0);
+        for (int s = 0; s < 4; ++s) {
+          const C wm = cl[1 + s];
+          const C v0 = wm * f0[r] + os0[r][s], v1 = wm * f1[r] + os1[r][s];
+          lo0 = fmin(lo0, v0);
+          hi0 = fmax(hi0, v0);
+          lo1 = fmin(lo1, v1);
+          hi1 = fmax(hi1, v1);
+        }
+        const C e2 = cl[0];
+        const C p0 = venkat_phi<D>(f0[r], lo0, hi0, g0[r], cd + CRD_F0 + 4, CRD_FS, e2);
+        const C p1 = venkat_phi<D>(f1[r], lo1, hi1, g1[r], cd + CRD_F0 + 4, CRD_FS, e2);
 #pragma unroll
-        for (int p = 0; p < 4; ++p) {
-          crec_t<C>* fd = cd + CRD_F0 + CRD_FS * p;
-          crec_t<C>* R = frc + (uint64_t)(uint32_t)ci[CRI_F0 + CRI_FS * p] * FREC;
-          const bool pos = sp[p] > C(0);
-          const C as = fabs(sp[p]);
-          const C G1 = R[FR_G], G2 = R[FR_G + 1];
-          // outgoing member: the cell's own reconstruction at the face
-          const C us = pos ? ug0 : ug1;
-          C ff = pos ? f0 : f1;
+        for (int d = 0; d < D; ++d) {
+          g0[r][d] *= p0;
+          g1[r][d] *= p1;
+        }
+      }
+      ug0[r] = ug1[r] = acc0[r] = acc1[r] = C(0);
 #pragma unroll
-          for (int d = 0; d < D; ++d) ff += fd[4 + d] * (pos ? g0[d] : g1[d]);
-          // incoming member: the neighbour's reconstruction at the face (all
-          // zero rows on a wall)
-          const C sgn_in = pos ? -1.0 : 1.0;  // u_in = sgn_in * u
-          const C fj = nh[p];
-          C gj[3] = {C(0), C(0), C(0)};
+      for (int d = 0; d < D; ++d) {
+        ug0[r] += vv[d] * g0[r][d];
+        ug1[r] -= vv[d] * g1[r][d];
+      }
+    }
+    C v2 = C(0);
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const C df = nhs[p][r] - fj;
+    for (int d = 0; d < D; ++d) v2 += vv[d] * vv[d];
 #pragma unroll
-            for (int d = 0; d < D; ++d) gj[d] += fd[10 + d * 4 + r] * df;
+    for (int p = 0; p < 4; ++p) {
+      crec_t<C>* fd = cd + CRD_F0 + CRD_FS * p;
+      crec_t<C>* R = frc + (uint64_t)(uint32_t)ci[CRI_F0 + CRI_FS * p] * FREC;
+      const C G1 = R[FR_G], G2 = R[FR_G + 1];
+      const C eqm = fd[22];  // 0 on a wall: no equilibrium term going out
+      const C sas = fd[3] * fabs(sp[p]);  // S/V |u.n|
+      // g0 (or the scaled wall Maxwellian) at u and -u from the axis tables
+      C e0, e1;
+      tab_pair(L.tab[p][0], at[0], e0, e1);
+#pragma unroll
+      for (int d = 1; d < D; ++d) {
+        C a0, a1;
+        tab_pair(L.tab[p][d], at[d], a0, a1);
+        e0 *= a0;
+        e1 *= a1;
+      }
+#pragma unroll
+      for (int r = 0; r < NR; ++r) {
+        // times the equilibrium polynomial (constant on a wall)
+        C E, O;
+        cubic_eo<D>(R + (X0 + r ? FR_PB : FR_PH), vv, v2, E, O);
+        const C q0 = e0 * (E + O), q1 = e1 * (E - O);
+        // the neighbour's gradient from its value fj and this cell's value fi
+        // (all zero rows on a wall)
+        auto slope = [&](C fj, C fi, C* gj) {
+#pragma unroll
+          for (int d = 0; d < D; ++d) gj[d] = fd[10 + d * 4] * (fi - fj);
+#pragma unroll
+          for (int q = 0; q < 3; ++q) {
+            const C df = ns[r][p][q] - fj;
+#pragma unroll
+            for (int d = 0; d < D; ++d) gj[d] += fd[11 + d * 4 + q] * df;
           }
+        };
+        C gl[D];
+        if constexpr (LIM) {
+          // limited with the neighbour's own stencil bounds and face offsets
+          const bool pos = sp[p] > C(0);
+          const C fj = pos ? os1[r][p] : os0[r][p], fi = pos ? f1[r] : f0[r];
+          slope(fj, fi, gl);
+          crec_t<C>* Fr = cl + CRL_F0 + CRL_FS * p;
+          C lo = fj, hi = fj;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const C vr = Fr[1 + q] * fj + (q ? ns[r][p][q - 1] : fi);
+            lo = fmin(lo, vr);
+            hi = fmax(hi, vr);
+          }
+          const C pj = venkat_phi<D>(fj, lo, hi, gl, Fr + 5, 3, Fr[0]);
+#pragma unroll
+          for (int d = 0; d < D; ++d) gl[d] *= pj;
+        }
+        // Fluxes at u and at -u along this cell's outward normal, times S/V:
+        // the outgoing member's from the cell's own reconstruction (fo, go,
+        // ugo), the incoming one's from the neighbour's (fj; fi is this cell's
+        // value in its stencil; su u the incoming velocity).
+        auto flux = [&](C fo, const C* go, C ugo, C eqo, C fj, C fi, C su, C eqi, C& acco, C& acci) {
+          C ff = fo;
+#pragma unroll
+          for (int d = 0; d < D; ++d) ff += fd[4 + d] * go[d];
+          C gj[D];
           if constexpr (LIM) {
-            // the neighbour's gradient at the incoming member, limited with
-            // its own stencil bounds and face offsets
-            crec_t<C>* Fr = cl + CRL_F0 + CRL_FS * p;
-            C lo = fj, hi = fj;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-              const C vr = Fr[1 + r] * fj + nhs[p][r];
-              lo = fmin(lo, vr);
-              hi = fmax(hi, vr);
-            }
-            const C pj = venkat_phi<D>(fj, lo, hi, gj, Fr + 5, 3, Fr[0]);
-#pragma unroll
-            for (int d = 0; d < D; ++d) gj[d] *= pj;
+            for (int d = 0; d < D; ++d) gj[d] = gl[d];
+          } else {
+            slope(fj, fi, gj);
           }
           C ffj = fj, ugj = C(0);
 #pragma unroll
@@ -673,110 +573,298 @@ __device__ __forceinline__ void sweep_item(
             ffj += fd[7 + d] * gj[d];
             ugj += vv[d] * gj[d];
           }
-          ugj *= sgn_in;
-          // g0 (or the scaled wall Maxwellian) at u and -u from the axis
-          // tables, times the equilibrium polynomial (constant on a wall)
-          C e0 = L.tab[p][0][id[0]], e1 = L.tab[p][0][im[0]];
-#pragma unroll
-          for (int d = 1; d < D; ++d) {
-            e0 *= L.tab[p][d][id[d]];
-            e1 *= L.tab[p][d][im[d]];
-          }
-          C E, O;
-          cubic_eo<D>(R + (X ? FR_PB : FR_PH), vv, v2, E, O);
-          const C q0 = e0 * (E + O), q1 = e1 * (E - O);
-          const C eqm = fd[22];  // 0 on a wall: no equilibrium term going out
-          const C eqo = eqm * (pos ? q0 : q1);
-          const C eqi = pos ? q1 : q0;
-          const C out = as * (G1 * ff + G2 * us + eqo);
-          const C in = -as * (G1 * ffj + G2 * ugj + eqi);
-          // fluxes at u and at -u along this cell's outward normal, times S/V
-          const C sv = fd[3];
-          acc0 += sv * (pos ? out : in);
-          acc1 += sv * (pos ? in : out);
-        }
-        // moments of the net outflow (the zero velocity of an odd grid once)
-        {
-          const double a0 = w[k0] * (double)acc0, a1 = has1 ? w[k1] * (double)acc1 : 0.0;
-          if constexpr (X == 0) {
-            mw[0] += a0 + a1;
-#pragma unroll
-            for (int d = 0; d < D; ++d) mw[1 + d] += (double)vv[d] * (a0 - a1);
-            mw[D + 1] += 0.5 * (double)v2 * (a0 + a1);
-          } else {
-            mw[D + 1] += 0.5 * (a0 + a1);
-          }
-        }
-        // first stage with the cell's BGK-Shakhov equilibrium at u and -u
-        C c0 = L.ctab[0][id[0]], c1 = L.ctab[0][im[0]];
-#pragma unroll
-        for (int d = 1; d < D; ++d) {
-          c0 *= L.ctab[d][id[d]];
-          c1 *= L.ctab[d][im[d]];
-        }
-        if constexpr (X == 1) {  // the b equilibrium carries the internal-energy factor
-          const C kc = cc[CS_KAP];
-          c0 = kc * c0;
-          c1 = kc * c1;
-        }
-        C E, O;
-        cubic_eo<D>(cc + (X ? CS_SB : CS_SH), vv, v2, E, O);
-        const C ccoll = cc[CS_CC];
-        st(fto, k0, f0 - acc0 + ccoll * (c0 * (C(1) + E + O) - f0));
-        if (has1) st(fto, k1, f1 - acc1 + ccoll * (c1 * (C(1) + E - O) - f1));
+          acco += sas * (G1 * ff + G2 * ugo + eqm * eqo);
+          acci -= sas * (G1 * ffj + G2 * (su * ugj) + eqi);
+        };
+        if (sp[p] > C(0))
+          flux(f0[r], g0[r], ug0[r], q0, os1[r][p], f1[r], C(-1), q1, acc0[r], acc1[r]);
+        else
+          flux(f1[r], g1[r], ug1[r], q1, os0[r][p], f0[r], C(1), q0, acc1[r], acc0[r]);
       }
-    };
-    pass(std::integral_constant<int, 0>{});
-    // b: always in 2-D; in 3-D for a gas with internal degrees of freedom
-    if constexpr (D == 2 || NB) pass(std::integral_constant<int, 1>{});
+    }
+    // moments of the net outflow
+    {
+      const double w0 = ldo<double, double>(wt, kp * 8u), w1 = ldo<double, double>(wt, (kp + in.half) * 8u);
+#pragma unroll
+      for (int r = 0; r < NR; ++r) {
+        const double a0 = w0 * (double)acc0[r], a1 = w1 * (double)acc1[r];
+        if (X0 + r == 0) {
+          mw[0] += a0 + a1;
+#pragma unroll
+          for (int d = 0; d < D; ++d) mw[1 + d] += (double)vv[d] * (a0 - a1);
+          mw[D + 1] += 0.5 * (double)v2 * (a0 + a1);
+        } else {
+          mw[D + 1] += 0.5 * (a0 + a1);
+        }
+      }
+    }
+    // first stage with the cell's BGK-Shakhov equilibrium at u and -u
+    C c0, c1;
+    tab_pair(L.tab[4][0], at[0], c0, c1);
+#pragma unroll
+    for (int d = 1; d < D; ++d) {
+      C a0, a1;
+      tab_pair(L.tab[4][d], at[d], a0, a1);
+      c0 *= a0;
+      c1 *= a1;
+    }
+    const C ccoll = cc[CS_CC];
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      C m0 = c0, m1 = c1;
+      if (X0 + r == 1) {  // the b equilibrium carries the internal-energy factor
+        const C kc = cc[CS_KAP];
+        m0 *= kc;
+        m1 *= kc;
+      }
+      C E, O;
+      cubic_eo<D>(cc + (X0 + r ? CS_SB : CS_SH), vv, v2, E, O);
+      E += C(1);
+      sto<T>(dst[r], o0, (T)(f0[r] - acc0[r] + ccoll * (m0 * (E + O) - f0[r])));
+      sto<T>(dst[r], o1, (T)(f1[r] - acc1[r] + ccoll * (m1 * (E - O) - f1[r])));
+    }
   }
-  block_sum<NM>(mw, L.red);
-  if (threadIdx.x == 0)
-    for (int x = 0; x < 5; ++x) dWp[(ic * sc.nchunk + chunk) * 5 + x] = x < NM ? mw[x] : 0.0;
 }
 
+// One work item of the fused sweep: the mirror pairs [kbeg, kend) of cell ic.
+// Leaves the first stage in ht, bt and each lane's moment sums in mw.  h and b
+// run as two passes (each pass's records and row addresses then fit the scalar
+// registers, where h and b together spill them), or with BOTH in one (the
+// batched form's small cases run only a few iterations, whose dependent-load
+// latency two passes would pay twice).  HB: b is carried.
+template <int D, typename T, typename C, bool BOTH, bool LIM, bool HB>
+__device__ __forceinline__ void sweep_item(const SweepIn<C>& in, const T* __restrict__ h,
+                                           const T* __restrict__ b, T* __restrict__ ht,
+                                           T* __restrict__ bt, int64_t ic, unsigned kbeg, unsigned kend,
+                                           SweepTabs<D, C>& L, double (&mw)[D + 2]) {
+  sweep_tables<D, C>(in, ic, L);
+  __syncthreads();
+#pragma unroll
+  for (int x = 0; x < D + 2; ++x) mw[x] = 0.0;
+  if constexpr (HB && BOTH) {
+    sweep_pass<D, T, C, 2, 0, LIM>(in, h, b, ht, bt, ic, kbeg, kend, L, mw);
+  } else {
+    sweep_pass<D, T, C, 1, 0, LIM>(in, h, b, ht, bt, ic, kbeg, kend, L, mw);
+    if constexpr (HB) sweep_pass<D, T, C, 1, 1, LIM>(in, h, b, ht, bt, ic, kbeg, kend, L, mw);
+  }
+}
+
+// The rest of a cell's step, by the work-group that swept all of its
+// velocities: the conservative update W^{n+1} = W^n - sum, the second stage
+// (Eq. f_final) with the equilibrium of W^{n+1} and q^n (reading R17) in place
+// on the first stage's row, the heat flux of the result, and the next step's
+// cell record.  Each lane takes the mirror pairs it swept, so it reads back
+// what it wrote itself.
+template <int D, typename T, bool HB>
+__device__ __forceinline__ void finish_cell(const GasP& g, const int32_t* __restrict__ vidx,
+                                            const double* __restrict__ w, const CellOut& o, T* ht, T* bt,
+                                            int64_t ic, int64_t nvp, unsigned half, int na,
+                                            const double* __restrict__ axis, double (&mw)[D + 2],
+                                            CellTabs<D>& L, double* red) {
+  constexpr int NM = D + 2, N = Cubic<D>::N;
+  block_total<NM>(mw, red);
+  double Wn[NM], P[NPRIM];
+  const double* Wi = o.W + ic * NM;
+#pragma unroll
+  for (int x = 0; x < NM; ++x) Wn[x] = Wi[x] - mw[x];
+  if (!prim_of<D>(Wn, g, P)) {  // the same in every lane
+    // (flag[2]: the other work-groups of this launch go on, on flag[0])
+    if (threadIdx.x == 0) atomicOr(&o.flag[2], 1);
+    return;
+  }
+  const double dt = dt_cell(g, ic), lam = P[4];
+  const double A = dt / (2.0 * P[5]), inv = 1.0 / (1.0 + A), kc = (g.K + 3.0 - D) / (2.0 * lam);
+  const double U[3] = {P[1], P[2], P[3]};
+  // f^{n+1} = (f~ + A g (1 + P)) / (1 + A): the factor A / (1 + A) goes into
+  // the first axis's table, the 1 into the polynomial's constant
+  const double scale = P[0] * maxw_norm<D>(lam) * A * inv;
+  for (int t = threadIdx.x; t < D * NAX; t += blockDim.x) {
+    const int d = t / NAX, n = t % NAX;
+    if (n < na) {
+      const double a = axis[n], Ud = d == 0 ? U[0] : d == 1 ? U[1] : U[2];
+      const double v = (d == 0 ? scale : 1.0) * exp(-lam * (a - Ud) * (a - Ud));
+      L.tab[d][n][0] = v;
+      L.tab[d][na - 1 - n][1] = v;
+      if (d == 0) L.ax[n][0] = a;
+    }
+  }
+  if (threadIdx.x == 0) {
+    const double V = o.vol[ic], dr = Wn[0] - Wi[0];
+    o.cellred[ic * 3 + 0] = V * dr * dr;
+    o.cellred[ic * 3 + 1] = V;
+    o.cellred[ic * 3 + 2] = V * Wi[0] * Wi[0];
+#pragma unroll
+    for (int x = 0; x < NM; ++x) o.Wn[ic * NM + x] = Wn[x];
+    const double qc[3] = {o.q[ic * 3], o.q[ic * 3 + 1], o.q[ic * 3 + 2]};
+    double SH[N], SB[N];
+    shakhov_polys<D>(P, g, qc, SH, SB);
+#pragma unroll
+    for (int x = 0; x < N; ++x) {
+      L.poly[x] = SH[x] + (x == 0 ? 1.0 : 0.0);
+      if (HB) L.poly[20 + x] = kc * (SB[x] + (x == 0 ? 1.0 : 0.0));
+    }
+  }
+  __syncthreads();
+  double sh[N], sb[N];
+#pragma unroll
+  for (int x = 0; x < N; ++x) {
+    sh[x] = uniform(L.poly[x]);
+    sb[x] = HB ? uniform(L.poly[20 + x]) : 0.0;
+  }
+  double acc[3] = {0.0, 0.0, 0.0};
+  grow_t *hr = srow(ht + ic * nvp), *br = HB ? srow(bt + ic * nvp) : nullptr;
+  grow_t *wt = srow(w), *ix = srow(vidx);
+  gout_t *ho = sout(ht + ic * nvp), *bo = HB ? sout(bt + ic * nvp) : nullptr;
+  const unsigned nthr = blockDim.x;
+  // a few pairs per lane per pass, their loads issued together: as many as
+  // the sweep's registers hold
+  constexpr unsigned UN = sizeof(T) == 8 ? (HB ? 2 : 4) : (HB ? 1 : 2);
+  for (unsigned kp = threadIdx.x; kp < half; kp += UN * nthr) {
+    int pk[UN];
+    T h0[UN], h1[UN], b0[UN], b1[UN];
+    double w0[UN], w1[UN];
+#pragma unroll
+    for (unsigned u = 0; u < UN; ++u) {
+      const unsigned k = kp + u * nthr;
+      if (k < half) {  // whole waves: half is a multiple of 64
+        const uint32_t o0 = k * (uint32_t)sizeof(T), o1 = o0 + half * (uint32_t)sizeof(T);
+        h0[u] = ldo<T, T>(hr, o0);
+        h1[u] = ldo<T, T>(hr, o1);
+        b0[u] = HB ? ldo<T, T>(br, o0) : T(0);
+        b1[u] = HB ? ldo<T, T>(br, o1) : T(0);
+        pk[u] = ldo<int32_t, int>(ix, k * 4u);
+        w0[u] = ldo<double, double>(wt, k * 8u);
+        w1[u] = ldo<double, double>(wt, (k + half) * 8u);
+      }
+    }
+#pragma unroll
+    for (unsigned u = 0; u < UN; ++u) {
+      const unsigned k = kp + u * nthr;
+      if (k < half) {
+        const uint32_t o0 = k * (uint32_t)sizeof(T), o1 = o0 + half * (uint32_t)sizeof(T);
+        double vv[3] = {0, 0, 0}, c0 = 1.0, c1 = 1.0;
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+          const unsigned at = node_off<double>(pk[u], d);
+          double a0, a1;
+          vv[d] = *(const double*)((const char*)L.ax + at);
+          tab_pair(L.tab[d], at, a0, a1);
+          c0 *= a0;
+          c1 *= a1;
+        }
+        const double v2 = vv[0] * vv[0] + vv[1] * vv[1] + vv[2] * vv[2];
+        double E, O;
+        cubic_eo<D>(sh, vv, v2, E, O);
+        const double n0 = (double)h0[u] * inv + c0 * (E + O);
+        const double n1 = (double)h1[u] * inv + c1 * (E - O);
+        sto_nt<T>(ho, o0, (T)n0);
+        sto_nt<T>(ho, o1, (T)n1);
+        // heat flux of the new distribution about U^{n+1} (Eq. reduced_heat_flux)
+        double x0[3], x1[3], e0 = 0.0, e1 = 0.0;
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+          x0[d] = vv[d] - U[d];
+          x1[d] = -vv[d] - U[d];
+          e0 += x0[d] * x0[d];
+          e1 += x1[d] * x1[d];
+        }
+        double s0 = e0 * n0, s1 = e1 * n1;
+        if constexpr (HB) {
+          cubic_eo<D>(sb, vv, v2, E, O);
+          const double m0 = (double)b0[u] * inv + c0 * (E + O);
+          const double m1 = (double)b1[u] * inv + c1 * (E - O);
+          sto_nt<T>(bo, o0, (T)m0);
+          sto_nt<T>(bo, o1, (T)m1);
+          s0 += m0;
+          s1 += m1;
+        }
+        s0 *= w0[u];
+        s1 *= w1[u];
+#pragma unroll
+        for (int d = 0; d < D; ++d) acc[d] += s0 * x0[d] + s1 * x1[d];
+      }
+    }
+  }
+  block_total<3>(acc, red);
+  if (threadIdx.x == 0) {
+    double qc[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) o.qn[ic * 3 + d] = qc[d] = d < D ? 0.5 * acc[d] : 0.0;
+#pragma unroll
+    for (int x = 0; x < NPRIM; ++x) o.prim[ic * NPRIM + x] = P[x];
+    cell_record<D>(P, g, dt, qc, &o.cs[ic * CSREC], o.cs32 ? &o.cs32[ic * CSREC] : nullptr);
+  }
+}
 
 // Single case: the sweep computes in the storage type T (FP32 storage uses
-// FP32 copies of the records and tables; moment sums stay FP64).  The FP32
+// FP32 copies of the records; moment sums stay FP64).  The FP32
 // body fits in half the registers; its bound asks for the occupancy that
 // hides the gathers' latency (measured: 7 waves per SIMD, no spills).  NB:
 // a 3-D gas with internal degrees of freedom, whose b runs a second pass.
-template <int D, typename T, bool LIM, bool SPARSE, bool NB>
+//
+// Whole-cell form: one work-group takes a cell through all of its velocities
+// and then through the rest of the step, so the first stage's rows are read
+// back by the compute unit that wrote them, and four launches and their passes
+// over the cells go.  One step of 48,000 tets x 24^3, FP64: 10.27 ms as sweep
+// (7.55) and second stage (2.11) of their own, 9.54 ms so, 9.18 ms with the
+// slot order and the sign branches of the loop; FP32, 28^3: 9.60, 8.96, 8.07;
+// cavity of 32^2 cells x 28^2: 0.088, 0.059, 0.056.
+template <int D, typename T, bool LIM, bool HB>
+__global__ __launch_bounds__(CELLT, (sizeof(T) == 4 ? 6 : 4)) void k_step_cell(
+    SweepIn<T> in, SweepSched sc, int64_t nc, GasP g, const T* __restrict__ h, const T* __restrict__ b,
+    T* ht, T* bt, CellOut o) {
+  __shared__ SweepLds<D, T> L;
+  // blocks are dealt round-robin to the 8 XCDs; XCD x takes tiles x, x+8, ...
+  // of sc.tile consecutive (Z-order) cells, whose stencil rows its L2 shares
+  const int64_t xcd = blockIdx.x % 8, local = blockIdx.x / 8;
+  const int64_t ic = ((local / sc.tile) * 8 + xcd) * sc.tile + local % sc.tile;
+  if (ic >= nc || *o.flag) return;
+  in.norm = o.cs[ic * CSREC + CS_NORM];
+  double mw[D + 2];
+  sweep_item<D, T, T, false, LIM, HB>(in, h, b, ht, bt, ic, 0u, in.half, L.s, mw);
+  finish_cell<D, T, HB>(g, in.vidx, in.w, o, ht, bt, ic, in.nvp, in.half, in.na, in.axis, mw, L.c, L.red);
+}
+
+// Blocked form, for a mesh too small to fill the GPU with whole cells (or a
+// caller's block_v): work item = (cell, velocity block); the rest of the step
+// runs in kernels of its own.
+template <int D, typename T, bool LIM, bool HB>
 __global__ __launch_bounds__(SWT, (sizeof(T) == 4 ? 6 : 4)) void k_sweep(
-    FusedMesh fm, int64_t nvp, SweepSched sc, const int32_t* __restrict__ crec_i,
-    const T* __restrict__ crec_d, const T* __restrict__ crec_l, const int32_t* __restrict__ vidx,
-    const double* __restrict__ w, const T* __restrict__ cs, const T* __restrict__ frec,
-    const T* __restrict__ tabs, const T* __restrict__ h, const T* __restrict__ b,
-    T* __restrict__ ht, T* __restrict__ bt, double* __restrict__ dWp,
+    SweepIn<T> in, SweepSched sc, int64_t nc, const double* __restrict__ cs64, const T* __restrict__ h,
+    const T* __restrict__ b, T* __restrict__ ht, T* __restrict__ bt, double* __restrict__ dWp,
     const int32_t* __restrict__ flag) {
-  __shared__ SweepLds<T> L;
-  // Work item = (cell, velocity block).  Blocks are dealt round-robin to the
-  // 8 XCDs; XCD x takes tiles x, x+8, ... of sc.tile consecutive (Z-order)
-  // cells and runs all of a tile's cells through velocity block 0, then 1,
-  // ..., so the stencil rows of one tile and one velocity block are what
-  // its L2 must hold.
+  __shared__ SweepLds<D, T> L;
+  // Blocks are dealt round-robin to the 8 XCDs; XCD x takes tiles x, x+8, ...
+  // of sc.tile consecutive (Z-order) cells and runs all of a tile's cells
+  // through velocity block 0, then 1, ..., so the stencil rows of one tile and
+  // one velocity block are what its L2 must hold.
   const int64_t xcd = blockIdx.x % 8, local = blockIdx.x / 8;
   const int64_t per_tile = sc.nchunk * sc.tile;
   const int64_t tile = (local / per_tile) * 8 + xcd;
   const int64_t rem = local % per_tile;
   const int64_t chunk = rem / sc.tile;
   const int64_t ic = tile * sc.tile + rem % sc.tile;
-  if (ic >= fm.nc) return;
-  sweep_item<D, T, T, true, LIM, SPARSE, NB>(fm, nvp, sc, crec_i, crec_d, crec_l, vidx, w, cs, frec,
-                                             tabs, h, b, ht, bt, dWp, flag, ic, chunk, L);
+  if (ic >= nc || *flag) return;
+  in.norm = cs64[ic * CSREC + CS_NORM];
+  double mw[D + 2];
+  sweep_item<D, T, T, false, LIM, HB>(in, h, b, ht, bt, ic, (unsigned)(chunk * sc.chunk_pairs),
+                                      (unsigned)min((int64_t)in.half, (chunk + 1) * sc.chunk_pairs), L.s,
+                                      mw);
+  block_total<D + 2>(mw, L.red);
+  if (threadIdx.x == 0)
+    for (int x = 0; x < 5; ++x) dWp[(ic * sc.nchunk + chunk) * 5 + x] = x < D + 2 ? mw[x] : 0.0;
 }
 
-// The fused sweep over a batch of cases: a persistent grid walks a list of
-// (case, cell, velocity block) work items; item w runs on block w mod the
-// grid size, and the host orders the list so that the blocks of one XCD
-// (block index mod 8) take whole tiles of one case.  In 2-D, where one pass
-// carries h and b, the bound trades a few spilled scalar registers for a
-// third wave per SIMD.
+// The whole-cell step over a batch of cases: a persistent grid walks a list of
+// (case, cell) work items; item w runs on block w mod the grid size, and the
+// host orders the list so that the blocks of one XCD (block index mod 8) take
+// whole tiles of one case.  Measured on the 64-case batch, one pass for h and b
+// against two: 9.6 against 12.4 ms FP64, 5.5 against 6.2 FP32.
 template <int D, typename T>
-__global__ __launch_bounds__(SWT, (D == 3 ? 4 : 3)) void k_sweep_b(BatchDev bd) {
+__global__ __launch_bounds__(SWT, (D == 3 ? 4 : 3)) void k_step_b(BatchDev bd) {
   // computes in the storage type, as the single case does: an FP32 batch
-  // reads the FP32 copies of its records and tables
-  __shared__ SweepLds<T> L;
+  // reads the FP32 copies of its records
+  __shared__ SweepLds<D, T> L;
   // The work list and the case table are read-only for the whole launch:
   // read through the constant address space they are scalar loads, so the
   // case's pointers and sizes land in scalar registers as kernel arguments do.
@@ -785,50 +873,63 @@ __global__ __launch_bounds__(SWT, (D == 3 ? 4 : 3)) void k_sweep_b(BatchDev bd) 
   citem_t* items = (citem_t*)bd.items;
   ccase_t* cases = (ccase_t*)bd.cases;
   for (int64_t it = blockIdx.x; it < bd.nitems; it += gridDim.x) {
-    const int c = items[4 * it];
+    const int c = items[2 * it];
     if (c < 0) continue;  // padding
-    const int64_t ic = items[4 * it + 1], chunk = items[4 * it + 2];
-    FusedMesh fm;
-    fm.nc = cases[c].fm.nc;
-    fm.nv = cases[c].fm.nv;
-    fm.na = cases[c].fm.na;
-    fm.axis = cases[c].fm.axis;
-    fm.vidx = cases[c].fm.vidx;
-    fm.npairs = cases[c].fm.npairs;
-    fm.crec_i = cases[c].fm.crec_i;
-    fm.crec_d = cases[c].fm.crec_d;
-    SweepSched sc;
-    sc.nf = cases[c].sc.nf;
-    sc.tile = cases[c].sc.tile;
-    sc.nchunk = cases[c].sc.nchunk;
-    sc.chunk_pairs = cases[c].sc.chunk_pairs;
-    const int64_t nvp = cases[c].v.nvp;
-    const double* w = cases[c].v.w;
-    const T *crec_d, *cs, *frec, *tabs;
+    const int64_t ic = items[2 * it + 1];
+    GasP g;
+    g.Pr = cases[c].g.Pr;
+    g.R = cases[c].g.R;
+    g.Tref = cases[c].g.Tref;
+    g.muref = cases[c].g.muref;
+    g.omega = cases[c].g.omega;
+    g.dt = cases[c].g.dt;
+    CellOut o;
+    o.vol = cases[c].m.vol;
+    o.W = cases[c].B.W;
+    o.q = cases[c].B.q;
+    o.Wn = cases[c].B.Wn;
+    o.qn = cases[c].B.qn;
+    o.prim = cases[c].B.prim;
+    o.cs = cases[c].B.cs;
+    o.cs32 = cases[c].B.cs32;
+    o.cellred = cases[c].B.cellred;
+    o.flag = cases[c].B.flag;
+    SweepIn<T> in;
+    in.crec_i = cases[c].fm.crec_i;
+    in.crec_l = nullptr;
+    in.vidx = cases[c].fm.vidx;
+    in.w = cases[c].v.w;
+    in.frec64 = cases[c].B.frec;
+    in.prim = o.prim;
+    in.dt = g.dt;
+    in.nvp = cases[c].v.nvp;
+    in.half = (unsigned)cases[c].fm.half;
+    in.na = cases[c].fm.na;
+    in.axis = cases[c].fm.axis;
     if constexpr (sizeof(T) == 4) {
-      crec_d = cases[c].fm.crec_d32;
-      cs = cases[c].B.cs32;
-      frec = cases[c].B.frec32;
-      tabs = cases[c].B.tabs32;
+      in.crec_d = cases[c].fm.crec_d32;
+      in.cs = cases[c].B.cs32;
+      in.frec = cases[c].B.frec32;
     } else {
-      crec_d = cases[c].fm.crec_d;
-      cs = cases[c].B.cs;
-      frec = cases[c].B.frec;
-      tabs = cases[c].B.tabs;
+      in.crec_d = cases[c].fm.crec_d;
+      in.cs = cases[c].B.cs;
+      in.frec = cases[c].B.frec;
     }
     const T* h = (const T*)cases[c].B.h;
     const T* b = (const T*)cases[c].B.b;
     T* ht = (T*)cases[c].B.ht;
     T* bt = (T*)cases[c].B.bt;
-    double* dW = cases[c].B.dW;
-    const int32_t* flag = cases[c].B.flag;
-    __syncthreads();  // the previous item's readers of L are done
-    sweep_item<D, T, T, false>(fm, nvp, sc, fm.crec_i, crec_d, nullptr, fm.vidx, w, cs, frec, tabs, h, b,
-                               ht, bt, dW, flag, ic, chunk, L);
+    if (*o.flag) continue;
+    in.norm = o.cs[ic * CSREC + CS_NORM];
+    __syncthreads();  // the previous item's readers of LDS are done
+    double mw[D + 2];
+    sweep_item<D, T, T, true, false, D == 2>(in, h, b, ht, bt, ic, 0u, in.half, L.s, mw);
+    finish_cell<D, T, D == 2>(g, in.vidx, in.w, o, ht, bt, ic, in.nvp, in.half, in.na, in.axis, mw, L.c,
+                              L.red);
   }
 }
 
-// Conservative update of the fused path: W^{n+1} = W^n - dW.
+// Conservative update of the blocked form: W^{n+1} = W^n - dW.
 // The partial sums of the velocity blocks are added in block order.
 template <int D>
 __device__ __forceinline__ void apply_dW_at(int64_t i, int64_t nchunk, const double* __restrict__ vol,
@@ -856,8 +957,9 @@ __global__ void k_apply_dW(int64_t nc, int64_t nchunk, const double* __restrict_
   if (i < nc) apply_dW_at<D>(i, nchunk, vol, W, dWp, Wn, cellred, flag);
 }
 
-// Second stage (Eq. f_final) fused with the heat flux of the result.
-// csn holds dt/(2 tau^{n+1}) and the Shakhov polynomials of W^{n+1} with q^n.
+// Second stage of the blocked form (Eq. f_final) fused with the heat flux of
+// the result, in place on the first stage's row.  csn holds
+// dt/(2 tau^{n+1}) and the Shakhov polynomials of W^{n+1} with q^n.
 struct Stage2Lds {
   double ctab[3][NAX];
   double ax[NAX];
@@ -869,10 +971,8 @@ __device__ __forceinline__ void stage2_q_cell(int64_t ic, const FusedMesh& fm, i
                                               const double* __restrict__ w,
                                               const double* __restrict__ primn,
                                               const double* __restrict__ csn,
-                                              const T* __restrict__ ht, const T* __restrict__ bt,
-                                              T* __restrict__ h, T* __restrict__ b,
-                                              double* __restrict__ qn, const int32_t* flag,
-                                              Stage2Lds& L) {
+                                              T* h, T* b, double* __restrict__ qn,
+                                              const int32_t* flag, Stage2Lds& L) {
   if (*flag) return;
   double(&ctab)[3][NAX] = L.ctab;
   double(&ax)[NAX] = L.ax;
@@ -890,21 +990,20 @@ __device__ __forceinline__ void stage2_q_cell(int64_t ic, const FusedMesh& fm, i
   const double inv = 1.0 / (1.0 + A);
   const double kc = cc[CS_KAP];
   const double U0 = P[1], U1 = P[2], U2 = P[3];
-  const T* __restrict__ hti = ht + ic * nvp;
-  T* __restrict__ hi = h + ic * nvp;
+  T* hi = h + ic * nvp;
   double acc[3] = {0.0, 0.0, 0.0};
-  const unsigned nv = (unsigned)fm.nv;
+  const unsigned nv = (unsigned)nvp;  // every slot (the pads' weights are 0)
   crec_t<double>* csh = (crec_t<double>*)(cc + CS_SH);  // scalar loads of the uniform polynomials
   crec_t<double>* csb = (crec_t<double>*)(cc + CS_SB);
   // b: always in 2-D; in 3-D when the gas has internal degrees of freedom
-  const bool hb = bt != nullptr;
-  const T* __restrict__ bti = hb ? bt + ic * nvp : nullptr;
+  const bool hb = b != nullptr;
+  const T* bi = hb ? b + ic * nvp : nullptr;
   auto body = [&](unsigned k, int pk, double htk, double btk, double wk) {
     double vv[3] = {0, 0, 0};
     double c0 = 1.0;
 #pragma unroll
     for (int d = 0; d < D; ++d) {
-      const int i = (pk >> (8 * d)) & 255;
+      const int i = node_of(pk, d);
       vv[d] = ax[i];
       c0 *= ctab[d][i];
     }
@@ -939,8 +1038,8 @@ __device__ __forceinline__ void stage2_q_cell(int64_t ic, const FusedMesh& fm, i
     double wv[UN];
 #pragma unroll
     for (unsigned u = 0; u < UN; ++u) {
-      hv[u] = __builtin_nontemporal_load(&hti[k + u * SWT]);
-      bv[u] = hb ? bti[k + u * SWT] : T(0);
+      hv[u] = __builtin_nontemporal_load(&hi[k + u * SWT]);
+      bv[u] = hb ? bi[k + u * SWT] : T(0);
     }
     // the HBM reads go out first, the small cached arrays next, and no
     // arithmetic is moved between them
@@ -954,7 +1053,7 @@ __device__ __forceinline__ void stage2_q_cell(int64_t ic, const FusedMesh& fm, i
 #pragma unroll
     for (unsigned u = 0; u < UN; ++u) body(k + u * SWT, pk[u], (double)hv[u], (double)bv[u], wv[u]);
   }
-  for (; k < nv; k += SWT) body(k, fm.vidx[k], ld(hti, k), hb ? ld(bti, k) : 0.0, w[k]);
+  for (; k < nv; k += SWT) body(k, fm.vidx[k], ld(hi, k), hb ? ld(bi, k) : 0.0, w[k]);
   block_sum<3>(acc, L.red);
   if (threadIdx.x == 0)
     for (int d = 0; d < 3; ++d) qn[ic * 3 + d] = d < D ? 0.5 * acc[d] : 0.0;
@@ -964,15 +1063,13 @@ template <int D, typename T>
 __global__ __launch_bounds__(SWT) void k_stage2_q(FusedMesh fm, int64_t nvp,
                                                   const double* __restrict__ w,
                                                   const double* __restrict__ primn,
-                                                  const double* __restrict__ csn,
-                                                  const T* __restrict__ ht, const T* __restrict__ bt,
-                                                  T* __restrict__ h, T* __restrict__ b,
+                                                  const double* __restrict__ csn, T* h, T* b,
                                                   double* __restrict__ qn, const int32_t* flag) {
   __shared__ Stage2Lds L;
   const int64_t per = (fm.nc + 7) / 8;
   const int64_t ic = (int64_t)(blockIdx.x % 8) * per + blockIdx.x / 8;
   if (ic >= fm.nc) return;
-  stage2_q_cell<D, T>(ic, fm, nvp, w, primn, csn, ht, bt, h, b, qn, flag, L);
+  stage2_q_cell<D, T>(ic, fm, nvp, w, primn, csn, h, b, qn, flag, L);
 }
 
 // Wall density with the wall cell's gradient evaluated in place.
@@ -1032,7 +1129,7 @@ __device__ __forceinline__ void wall_rho_at(int64_t wi, const DevMesh& m, const 
   // pass ahead, and the rows of the incident ones (u.n > 0, the only ones
   // that read f) are loaded together before any arithmetic.
   constexpr unsigned UN = 4;
-  const unsigned nb = blockDim.x, nv = (unsigned)v.nv;
+  const unsigned nb = blockDim.x, nv = (unsigned)v.nvp;  // every slot (the pads' weights are 0)
   int pkn[UN];
 #pragma unroll
   for (unsigned u = 0; u < UN; ++u) {
@@ -1056,7 +1153,7 @@ __device__ __forceinline__ void wall_rho_at(int64_t wi, const DevMesh& m, const 
       un[u] = 0.0;
 #pragma unroll
       for (int d = 0; d < 3; ++d) {
-        id[u][d] = (pk[u] >> (8 * d)) & 255;
+        id[u][d] = node_of(pk[u], d);
         uu[u][d] = d < D ? S.ax[id[u][d]] : 0.0;
         if (d < D) un[u] += uu[u][d] * nrm[d];
       }
@@ -1225,15 +1322,12 @@ __device__ __forceinline__ void ghost_row_at(int64_t m, int64_t nc, const int32_
   const double U[3] = {R[FR_GU], R[FR_GU + 1], R[FR_GU + 2]};
   const int64_t row = (nc + 1 + m) * v.nvp;
   for (int64_t k = threadIdx.x; k < v.nvp; k += blockDim.x) {
-    double hv = 0.0;
-    if (k < v.nv) {
-      double c2 = 0.0;
-      for (int d = 0; d < D; ++d) {
-        const double c = v.u[d * v.nvp + k] - U[d];
-        c2 += c * c;
-      }
-      hv = C * exp(-lam * c2);
+    double c2 = 0.0;
+    for (int d = 0; d < D; ++d) {
+      const double c = v.u[d * v.nvp + k] - U[d];
+      c2 += c * c;
     }
+    const double hv = C * exp(-lam * c2);
     st(h, row + k, hv);
     if (v.has_b) st(b, row + k, v.kxi / (2.0 * lam) * hv);
   }
@@ -1259,107 +1353,14 @@ __device__ __forceinline__ int case_of(const int64_t* __restrict__ off, int n, i
   return lo;
 }
 
-// elements per lane of the batch's flattened element-wise kernels (k_tables_b,
-// k_to_f32_b)
-constexpr int PER_LANE = 16;
-
-// next = 0: W^n, q -> prim, cs;  next = 1: W^{n+1}, q -> primn, csn
+// W^n, q -> prim, cs before the first step (the step itself leaves the next one's)
 template <int D>
-__global__ void k_cell_prep_b(BatchDev bd, int next) {
+__global__ void k_cell_prep_b(BatchDev bd) {
   const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (t >= bd.cell_off[bd.n]) return;
   const int c = case_of(bd.cell_off, bd.n, t);
   const CaseDev& C = bd.cases[c];
-  const int64_t i = t - bd.cell_off[c];
-  if (next) cell_prep_at<D>(i, C.g, C.B.Wn, C.B.q, C.B.primn, C.B.csn, C.B.flag);
-  else cell_prep_at<D>(i, C.g, C.B.W, C.B.q, C.B.prim, C.B.cs, C.B.flag);
-}
-
-template <int D>
-__global__ void k_tables_b(BatchDev bd) {
-  // each wave takes PER_LANE consecutive runs of 64 entries; a lane searches
-  // for an entry's case only when it leaves the previous entry's case
-  const int64_t lane = threadIdx.x & 63;
-  const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
-  const int64_t n = bd.tab_off[bd.n];
-  int c = 0;
-  int64_t lo = 0, hi = 0;
-  for (int j = 0; j < PER_LANE; ++j) {
-    const int64_t t = (wave * PER_LANE + j) * 64 + lane;
-    if (t >= n) break;
-    if (t < lo || t >= hi) {
-      c = case_of(bd.tab_off, bd.n, t);
-      lo = bd.tab_off[c];
-      hi = bd.tab_off[c + 1];
-    }
-    const CaseDev& C = bd.cases[c];
-    tables_at<D>(t - lo, C.m.nf, C.fm.na, C.fm.axis, C.m.fbc, C.g, C.B.frec, C.B.prim, C.B.cs,
-                 C.B.tabs, C.B.flag);
-  }
-}
-
-// FP32 copies of every case's per-step face records, cell records and axis
-// tables (an FP32 batch's sweep computes from them): three flattened ranges.
-// Each wave converts PER_LANE consecutive runs of 64 elements, so that the
-// search for an element's case (a chain of dependent loads) is made once per
-// case a lane meets, not once per element.
-__global__ void k_to_f32_b(BatchDev bd, int64_t nfr, int64_t ncs, int64_t ntab) {
-  const int64_t lane = threadIdx.x & 63;
-  const int64_t wave = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) >> 6;
-  // the case of the lane's previous element: its range kind, the range's
-  // first unit (face, cell or table entry) and end, and the arrays
-  int kind_c = -1;
-  int64_t lo = 0, hi = 0;
-  const double* src = nullptr;
-  float* dst = nullptr;
-  for (int j = 0; j < PER_LANE; ++j) {
-    const int64_t t = (wave * PER_LANE + j) * 64 + lane;
-    int kind;
-    int64_t e, unit;  // element within its range, and the unit holding it
-    const int64_t* off;
-    if (t < nfr) {
-      kind = 0, e = t, unit = t / FREC, off = bd.face_off;
-    } else if (t - nfr < ncs) {
-      kind = 1, e = t - nfr, unit = e / CSREC, off = bd.cell_off;
-    } else if (t - nfr - ncs < ntab) {
-      kind = 2, e = t - nfr - ncs, unit = e, off = bd.tab_off;
-    } else {
-      break;
-    }
-    if (kind != kind_c || unit < lo || unit >= hi) {
-      const int c = case_of(off, bd.n, unit);
-      const CaseDev& C = bd.cases[c];
-      kind_c = kind;
-      lo = off[c];
-      hi = off[c + 1];
-      src = kind == 0 ? C.B.frec : kind == 1 ? C.B.cs : C.B.tabs;
-      dst = kind == 0 ? C.B.frec32 : kind == 1 ? C.B.cs32 : C.B.tabs32;
-    }
-    const int64_t i = e - lo * (kind == 0 ? FREC : kind == 1 ? CSREC : 1);
-    dst[i] = (float)src[i];
-  }
-}
-
-template <int D>
-__global__ void k_apply_dW_b(BatchDev bd) {
-  const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (t >= bd.cell_off[bd.n]) return;
-  const int c = case_of(bd.cell_off, bd.n, t);
-  const CaseDev& C = bd.cases[c];
-  apply_dW_at<D>(t - bd.cell_off[c], C.sc.nchunk, C.m.vol, C.B.W, C.B.dW, C.B.Wn, C.B.cellred,
-                 C.B.flag);
-}
-
-// one block per cell of the batch
-template <int D, typename T>
-__global__ __launch_bounds__(SWT) void k_stage2_q_b(BatchDev bd) {
-  __shared__ Stage2Lds L;
-  const int64_t t = blockIdx.x;
-  const int c = case_of(bd.cell_off, bd.n, t);
-  const CaseDev& C = bd.cases[c];
-  stage2_q_cell<D, T>(t - bd.cell_off[c], C.fm, C.v.nvp, C.v.w, C.B.primn, C.B.csn,
-                      (const T*)C.B.ht, (const T*)C.B.bt, (T*)C.B.h, (T*)C.B.b, C.B.qn, C.B.flag,
-                      L);
+  cell_prep_at<D>(t - bd.cell_off[c], C.g, C.B.W, C.B.q, C.B.prim, C.B.cs, C.B.cs32, C.B.flag);
 }
 
 // one block per far-field / outflow face of the batch
@@ -1427,78 +1428,113 @@ hipError_t launch_apply_dW(int D, const DevMesh& m, int64_t nchunk, const double
   return hipGetLastError();
 }
 
-hipError_t launch_tables(int D, const DevMesh& m, const FusedMesh& fm, const GasP& g,
-                         const double* frec, const double* prim, const double* cs, double* tabs,
-                         const int32_t* flag, hipStream_t s) {
-  const int64_t n = (m.nf + m.nc) * (int64_t)D * fm.na;
-  const unsigned grid = (unsigned)((n + 255) / 256);
-  UGKS_DISPATCH_D(D, k_tables<DD><<<grid, 256, 0, s>>>(m.nf, m.nc, fm.na, fm.axis, m.fbc, g, frec,
-                                                        prim, cs, tabs, flag));
-  return hipGetLastError();
-}
-
 hipError_t launch_cell_prep(int D, int64_t nc, const GasP& g, const double* W, const double* q,
-                            double* prim, double* cs, int32_t* flag, hipStream_t s) {
+                            double* prim, double* cs, float* cs32, int32_t* flag, hipStream_t s) {
   const unsigned grid = (unsigned)((nc + 127) / 128);
-  UGKS_DISPATCH_D(D, k_cell_prep<DD><<<grid, 128, 0, s>>>(nc, g, W, q, prim, cs, flag));
+  UGKS_DISPATCH_D(D, k_cell_prep<DD><<<grid, 128, 0, s>>>(nc, g, W, q, prim, cs, cs32, flag));
   return hipGetLastError();
 }
 
-hipError_t launch_sweep(int D, int prec, const FusedMesh& fm, const DevVel& v, const GasP& g,
-                        const SweepSched& sc, const void* crec_d, const void* crec_l,
-                        const void* cs, const void* frec,
-                        const void* tabs, const void* h, const void* b, void* ht, void* bt,
-                        double* dWp, const int32_t* flag, hipStream_t s) {
+namespace {
+
+template <typename T>
+SweepIn<T> sweep_in(const FusedMesh& fm, const DevVel& v, const GasP& g, const StepBuffers& B) {
+  SweepIn<T> in{};
+  in.crec_i = fm.crec_i;
+  in.vidx = fm.vidx;
+  in.w = v.w;
+  in.frec64 = B.frec;
+  in.prim = B.prim;
+  in.dt = g.dt;
+  in.nvp = v.nvp;
+  in.half = (unsigned)fm.half;
+  in.na = fm.na;
+  in.axis = fm.axis;
+  if constexpr (sizeof(T) == 4) {
+    in.crec_d = fm.crec_d32;
+    in.crec_l = fm.crec_l32;
+    in.cs = B.cs32;
+    in.frec = B.frec32;
+  } else {
+    in.crec_d = fm.crec_d;
+    in.crec_l = fm.crec_l;
+    in.cs = B.cs;
+    in.frec = B.frec;
+  }
+  return in;
+}
+
+CellOut cell_out(const DevMesh& m, const StepBuffers& B) {
+  CellOut o{};
+  o.vol = m.vol;
+  o.W = B.W;
+  o.q = B.q;
+  o.Wn = B.Wn;
+  o.qn = B.qn;
+  o.prim = B.prim;
+  o.cs = B.cs;
+  o.cs32 = B.cs32;
+  o.cellred = B.cellred;
+  o.flag = B.flag;
+  return o;
+}
+
+template <int D, typename T, bool LIM, bool HB>
+void launch_sweep_as(const FusedMesh& fm, const DevVel& v, const GasP& g, const SweepSched& sc,
+                     const StepBuffers& B, hipStream_t s) {
   const int64_t ntile = (fm.nc + sc.tile - 1) / sc.tile;
   const unsigned grid = (unsigned)(((ntile + 7) / 8) * 8 * sc.nchunk * sc.tile);
-  // a sparse set's pairs carry their own packed axis indices
-  const int32_t* pv = fm.sparse ? fm.pvidx : fm.vidx;
-#define UGKS_SWEEP_ARGS                                                                       \
-  fm, v.nvp, sc, fm.crec_i, (const TT*)crec_d, (const TT*)crec_l, pv, v.w, (const TT*)cs,      \
-      (const TT*)frec, (const TT*)tabs, (const TT*)h, (const TT*)b, (TT*)ht, (TT*)bt, dWp, flag
-#define UGKS_SWEEP_NB(LIMV, SPV)                                                             \
-  do {                                                                                        \
-    if (D == 3 && b)                                                                          \
-      UGKS_DISPATCH_T(prec, (k_sweep<3, TT, LIMV, SPV, true><<<grid, SWT, 0, s>>>(UGKS_SWEEP_ARGS))); \
-    else                                                                                      \
-      UGKS_DISPATCH_DT(D, prec, (k_sweep<DD, TT, LIMV, SPV, false><<<grid, SWT, 0, s>>>(UGKS_SWEEP_ARGS))); \
+  k_sweep<D, T, LIM, HB><<<grid, SWT, 0, s>>>(sweep_in<T>(fm, v, g, B), sc, fm.nc, B.cs, (const T*)B.h,
+                                              (const T*)B.b, (T*)B.ht, (T*)B.bt, B.dW, B.flag);
+}
+
+template <int D, typename T, bool LIM, bool HB>
+void launch_step_as(const DevMesh& m, const FusedMesh& fm, const DevVel& v, const GasP& g,
+                    const SweepSched& sc, const StepBuffers& B, hipStream_t s) {
+  const int64_t ntile = (fm.nc + sc.tile - 1) / sc.tile;
+  const unsigned grid = (unsigned)(((ntile + 7) / 8) * 8 * sc.tile);
+  k_step_cell<D, T, LIM, HB><<<grid, sc.lanes, 0, s>>>(sweep_in<T>(fm, v, g, B), sc, fm.nc, g,
+                                                       (const T*)B.h, (const T*)B.b, (T*)B.ht, (T*)B.bt,
+                                                       cell_out(m, B));
+}
+
+}  // namespace
+
+// dimension, limiter and whether b is carried (always in 2-D)
+#define UGKS_SWEEP_AS(FN, ...)                                                       \
+  do {                                                                              \
+    if (D == 2) {                                                                   \
+      if (fm.crec_l) UGKS_DISPATCH_T(prec, (FN<2, TT, true, true>(__VA_ARGS__)));   \
+      else UGKS_DISPATCH_T(prec, (FN<2, TT, false, true>(__VA_ARGS__)));            \
+    } else if (B.b) {                                                               \
+      if (fm.crec_l) UGKS_DISPATCH_T(prec, (FN<3, TT, true, true>(__VA_ARGS__)));   \
+      else UGKS_DISPATCH_T(prec, (FN<3, TT, false, true>(__VA_ARGS__)));            \
+    } else {                                                                        \
+      if (fm.crec_l) UGKS_DISPATCH_T(prec, (FN<3, TT, true, false>(__VA_ARGS__)));  \
+      else UGKS_DISPATCH_T(prec, (FN<3, TT, false, false>(__VA_ARGS__)));           \
+    }                                                                               \
   } while (0)
-  if (fm.sparse) {
-    if (crec_l) UGKS_SWEEP_NB(true, true);
-    else UGKS_SWEEP_NB(false, true);
-  } else {
-    if (crec_l) UGKS_SWEEP_NB(true, false);
-    else UGKS_SWEEP_NB(false, false);
-  }
-#undef UGKS_SWEEP_NB
-#undef UGKS_SWEEP_ARGS
+
+hipError_t launch_sweep(int D, int prec, const FusedMesh& fm, const DevVel& v, const GasP& g,
+                        const SweepSched& sc, const StepBuffers& B, hipStream_t s) {
+  UGKS_SWEEP_AS(launch_sweep_as, fm, v, g, sc, B, s);
   return hipGetLastError();
 }
 
-// FP64 -> FP32 copies of the sweep's per-step records (FP32 compute form)
-__global__ void k_to_f32(const double* __restrict__ a, float* __restrict__ fa, int64_t na,
-                         const double* __restrict__ b, float* __restrict__ fb, int64_t nb,
-                         const double* __restrict__ c, float* __restrict__ fc, int64_t nc) {
-  const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (t < na) fa[t] = (float)a[t];
-  else if (t < na + nb) fb[t - na] = (float)b[t - na];
-  else if (t < na + nb + nc) fc[t - na - nb] = (float)c[t - na - nb];
-}
-
-hipError_t launch_to_f32(const double* a, float* fa, int64_t na, const double* b, float* fb,
-                         int64_t nb, const double* c, float* fc, int64_t nc, hipStream_t s) {
-  const int64_t n = na + nb + nc;
-  if (n == 0) return hipSuccess;
-  k_to_f32<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(a, fa, na, b, fb, nb, c, fc, nc);
+hipError_t launch_step_cell(int D, int prec, const DevMesh& m, const FusedMesh& fm, const DevVel& v,
+                            const GasP& g, const SweepSched& sc, const StepBuffers& B, hipStream_t s) {
+  if (sc.lanes % 64 != 0 || sc.lanes < 64 || sc.lanes > CELLT) return hipErrorInvalidValue;
+  UGKS_SWEEP_AS(launch_step_as, m, fm, v, g, sc, B, s);
   return hipGetLastError();
 }
+#undef UGKS_SWEEP_AS
 
 hipError_t launch_stage2_q(int D, int prec, const FusedMesh& fm, const DevVel& v,
-                           const double* primn, const double* csn, const void* ht, const void* bt,
-                           void* h, void* b, double* qn, const int32_t* flag, hipStream_t s) {
+                           const double* primn, const double* csn, void* h, void* b, double* qn,
+                           const int32_t* flag, hipStream_t s) {
   const unsigned grid = (unsigned)(((fm.nc + 7) / 8) * 8);
   UGKS_DISPATCH_DT(D, prec, k_stage2_q<DD, TT><<<grid, SWT, 0, s>>>(
-      fm, v.nvp, v.w, primn, csn, (const TT*)ht, (const TT*)bt, (TT*)h, (TT*)b, qn, flag));
+      fm, v.nvp, v.w, primn, csn, (TT*)h, (TT*)b, qn, flag));
   return hipGetLastError();
 }
 
@@ -1545,40 +1581,10 @@ hipError_t launch_bflux(int D, const DevMesh& m, const double* frec, const doubl
 }
 
 // ---- batched launchers ------------------------------------------------------
-hipError_t launch_cell_prep_b(int D, const BatchDev& bd, int64_t ncell, int next, hipStream_t s) {
+hipError_t launch_cell_prep_b(int D, const BatchDev& bd, int64_t ncell, hipStream_t s) {
   if (ncell == 0) return hipSuccess;
   const unsigned grid = (unsigned)((ncell + 127) / 128);
-  UGKS_DISPATCH_D(D, k_cell_prep_b<DD><<<grid, 128, 0, s>>>(bd, next));
-  return hipGetLastError();
-}
-
-hipError_t launch_to_f32_b(const BatchDev& bd, int64_t nface, int64_t ncell, int64_t ntab,
-                           hipStream_t s) {
-  const int64_t n = nface * FREC + ncell * CSREC + ntab;
-  if (n == 0) return hipSuccess;
-  const int64_t waves = (n + 64 * PER_LANE - 1) / (64 * PER_LANE);
-  k_to_f32_b<<<(unsigned)((waves + 3) / 4), 256, 0, s>>>(bd, nface * FREC, ncell * CSREC, ntab);
-  return hipGetLastError();
-}
-
-hipError_t launch_tables_b(int D, const BatchDev& bd, int64_t ntab, hipStream_t s) {
-  if (ntab == 0) return hipSuccess;
-  const int64_t waves = (ntab + 64 * PER_LANE - 1) / (64 * PER_LANE);
-  const unsigned grid = (unsigned)((waves + 3) / 4);
-  UGKS_DISPATCH_D(D, k_tables_b<DD><<<grid, 256, 0, s>>>(bd));
-  return hipGetLastError();
-}
-
-hipError_t launch_apply_dW_b(int D, const BatchDev& bd, int64_t ncell, hipStream_t s) {
-  if (ncell == 0) return hipSuccess;
-  const unsigned grid = (unsigned)((ncell + 255) / 256);
-  UGKS_DISPATCH_D(D, k_apply_dW_b<DD><<<grid, 256, 0, s>>>(bd));
-  return hipGetLastError();
-}
-
-hipError_t launch_stage2_q_b(int D, int prec, const BatchDev& bd, int64_t ncell, hipStream_t s) {
-  if (ncell == 0) return hipSuccess;
-  UGKS_DISPATCH_DT(D, prec, k_stage2_q_b<DD, TT><<<(unsigned)ncell, SWT, 0, s>>>(bd));
+  UGKS_DISPATCH_D(D, k_cell_prep_b<DD><<<grid, 128, 0, s>>>(bd));
   return hipGetLastError();
 }
 
@@ -1603,19 +1609,19 @@ hipError_t launch_ghost_rows_b(int D, int prec, const BatchDev& bd, int64_t nff,
   return hipGetLastError();
 }
 
-hipError_t launch_sweep_b(int D, int prec, const BatchDev& bd, int64_t grid, int threads,
-                          hipStream_t s) {
+hipError_t launch_step_b(int D, int prec, const BatchDev& bd, int64_t grid, int threads,
+                         hipStream_t s) {
   if (bd.nitems == 0) return hipSuccess;
   if (threads % 64 != 0 || threads < 64 || threads > SWT) return hipErrorInvalidValue;
-  UGKS_DISPATCH_DT(D, prec, k_sweep_b<DD, TT><<<(unsigned)grid, threads, 0, s>>>(bd));
+  UGKS_DISPATCH_DT(D, prec, k_step_b<DD, TT><<<(unsigned)grid, threads, 0, s>>>(bd));
   return hipGetLastError();
 }
 
-int sweep_b_blocks_per_cu(int D, int prec, int threads) {
+int step_b_blocks_per_cu(int D, int prec, int threads) {
   int n = 0;
   hipError_t e = hipSuccess;
   UGKS_DISPATCH_DT(D, prec, e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                                &n, reinterpret_cast<const void*>(&k_sweep_b<DD, TT>), threads, 0));
+                                &n, reinterpret_cast<const void*>(&k_step_b<DD, TT>), threads, 0));
   return e == hipSuccess ? n : 0;
 }
 
