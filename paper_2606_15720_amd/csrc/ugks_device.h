@@ -364,5 +364,18 @@ struct Cubic {
   }
 };
 
+// A record of the fused sweep (SREC): two scalars and a polynomial P, whose
+// cubic part has the form (kappa . u)|u|^2.
+template <int D, typename C>
+__device__ __forceinline__ void write_srec(C* __restrict__ r, double a, double b, const double* P) {
+  using Cb = Cubic<D>;
+  r[0] = (C)a;
+  r[1] = (C)b;
+#pragma unroll
+  for (int x = 0; x < Cb::C0; ++x) r[SR_P + x] = (C)P[x];
+#pragma unroll
+  for (int d = 0; d < D; ++d) r[SR_P + Cb::C0 + d] = (C)P[Cb::ci(d, d, d)];
+}
+
 }  // namespace dev
 }  // namespace ugks

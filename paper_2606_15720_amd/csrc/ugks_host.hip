@@ -554,53 +554,48 @@ void build(ugks_ctx* c, const ugks_mesh* mesh, const ugks_velocity* vel, const u
     for (int64_t i = 0; i < nc; ++i) {
       int32_t* I = &ci[i * CRI];
       double* Dd = &cdr[i * CRD];
-      I[0] = nfc[i];
-      I[1] = 4;
-      stencil(i, &I[2], Dd);
+      stencil(i, &I[CI_OWN], &Dd[CD_G]);
       for (int p = 0; p < 4; ++p) {
         const int pp = p < nfc[i] ? p : 0;
-        int32_t* fi = &I[CRI_F0 + CRI_FS * p];
-        double* fd = &Dd[CRD_F0 + CRD_FS * p];
+        double* fd = &Dd[CD_F0 + CD_FS * p];
         const int f = cface[i * MAXF + pp];
         const double sg = csign[i * MAXF + pp];
         const int j = cnbr[i * MAXF + pp];
-        fi[0] = f;
-        fi[1] = fbc[f];
-        fi[2] = (p < nfc[i] && sg > 0.0) ? 1 : 0;
+        I[CI_FACE + p] = f;
+        I[CI_KIND + p] = fbc[f];
         const int32_t gr = ghost_row[f];
-        fi[3] = j >= 0 ? j : (gr >= 0 ? gr : zero_row);
-        fi[4] = 4;
         if (j >= 0) {
           // the neighbour's stencil with this cell's row (through the shared
           // face) moved to slot 0: the sweep reads that value from registers
-          stencil(j, &fi[5], &fd[10]);
+          int32_t rows[4];
+          stencil(j, rows, &fd[6]);
           int q = 0;
           for (int t = 0; t < nfc[j]; ++t)
             if (cface[j * MAXF + t] == f) q = t;
           if (q != 0) {
-            std::swap(fi[5], fi[5 + q]);
-            for (int d = 0; d < 3; ++d) std::swap(fd[10 + d * 4], fd[10 + d * 4 + q]);
+            std::swap(rows[0], rows[q]);
+            for (int d = 0; d < 3; ++d) std::swap(fd[6 + d * 4], fd[6 + d * 4 + q]);
           }
+          for (int r = 1; r < 4; ++r) I[CI_RING + 3 * p + r - 1] = rows[r];
         } else {
           // zero or ghost row: its own value with zero gradient
-          for (int r = 0; r < 4; ++r) {
-            fi[5 + r] = fi[3];
-            for (int d = 0; d < 3; ++d) fd[10 + d * 4 + r] = 0.0;
-          }
+          for (int r = 0; r < 3; ++r) I[CI_RING + 3 * p + r] = gr >= 0 ? gr : zero_row;
         }
         for (int d = 0; d < 3; ++d) {
-          fd[0 + d] = sg * fnorm[f * 3 + d];
-          fd[4 + d] = sg > 0.0 ? fdxL[f * 3 + d] : fdxR[f * 3 + d];
-          fd[7 + d] = j >= 0 ? (sg > 0.0 ? fdxR[f * 3 + d] : fdxL[f * 3 + d]) : 0.0;
+          Dd[CD_N + 3 * p + d] = sg * fnorm[f * 3 + d];
+          fd[0 + d] = sg > 0.0 ? fdxL[f * 3 + d] : fdxR[f * 3 + d];
+          fd[3 + d] = j >= 0 ? (sg > 0.0 ? fdxR[f * 3 + d] : fdxL[f * 3 + d]) : 0.0;
         }
-        fd[3] = p < nfc[i] ? farea[f] / vol[i] : 0.0;
+        double& sv = fd[19];
+        sv = p < nfc[i] ? farea[f] / vol[i] : 0.0;
         // local steps: the face's integral over dt, applied for dt_i
-        if (lts && p < nfc[i]) fd[3] *= dtc[i] / c->gas.dt;
+        if (lts && p < nfc[i]) sv *= dtc[i] / c->gas.dt;
         // equilibrium term of the outgoing member: none at a wall
-        fd[22] = (j >= 0 || gr >= 0) ? 1.0 : 0.0;
+        fd[18] = (j >= 0 || gr >= 0) ? 1.0 : 0.0;
       }
     }
     c->fmesh.half = nvp / 2;
+    c->fmesh.nr = c->nr;
     // the sweep reads one iteration ahead
     vidx.resize(vidx.size() + 512, 0);
     c->fmesh.nc = nc;
@@ -679,16 +674,9 @@ void build(ugks_ctx* c, const ugks_mesh* mesh, const ugks_velocity* vel, const u
     c->sched.nchunk = (npairs + cp - 1) / cp;
     c->sched.tile = tile ? tile : 32;
     c->Bv = (int)(2 * cp);
-    if (!c->sched.whole) {
-      B.dW = dalloc<double>(c, nc * c->sched.nchunk * 5);
-      B.csn = dalloc<double>(c, nc * CSREC);
-    }
-    B.cs = dalloc<double>(c, nc * CSREC);
-    if (prec == UGKS_FP32) {
-      B.frec32 = dalloc<float>(c, nf * FREC);
-      B.cs32 = dalloc<float>(c, nc * CSREC);
-      HIP_TRY(hipMemset(B.frec32, 0, nf * FREC * sizeof(float)));
-    }
+    if (!c->sched.whole) B.dW = dalloc<double>(c, nc * c->sched.nchunk * 5);
+    B.srec = dalloc<char>(c, (size_t)nf * c->nr * SREC * esz);
+    B.cs = dalloc<char>(c, (size_t)nc * c->nr * SREC * esz);
   } else {
     B.dW = dalloc<double>(c, nc * 5);
   }
@@ -810,13 +798,13 @@ void enqueue_step_fused(ugks_ctx* c, bool residual) {
     c->q_valid = true;
   }
   // 1 primitives of W^n and the cell equilibrium data of the first stage:
-  // left by the previous step in the whole-cell form
+  // left by the previous step once valid
   if (!c->cs_valid)
-    TIMED(KK_PRIMS, launch_cell_prep(D, c->nc, g, B.W, B.q, B.prim, B.cs, B.cs32, B.flag, s));
-  c->cs_valid = c->sched.whole != 0;
+    TIMED(KK_PRIMS, launch_cell_prep(D, P, c->nr, c->nc, g, B.W, B.q, B.prim, B.cs, B.flag, s));
+  c->cs_valid = true;
   // 4 macroscopic reconstruction; 6.1-6.6 interface equilibrium
   TIMED(KK_GRADW, launch_gradW(D, m, c->bcs, g, B.W, B.gW, B.flag, 1, s));
-  TIMED(KK_FACE_EQ, launch_face_eq(D, m, c->bcs, g, B.W, B.gW, B.q, B.frec, B.frec32, B.flag, s));
+  TIMED(KK_FACE_EQ, launch_face_eq(D, m, c->bcs, g, B.W, B.gW, B.q, B.frec, P, c->nr, B.srec, B.flag, s));
   // 7 far-field ghost rows (the wall cells' stencils may read them), then
   // the wall densities
   if (c->fmesh.nff)
@@ -832,11 +820,9 @@ void enqueue_step_fused(ugks_ctx* c, bool residual) {
   } else {
     // 5, 6.7-6.8, 9: the velocity sweep
     TIMED(KK_SWEEP, launch_sweep(D, P, c->fmesh, v, g, c->sched, B, s));
-    // 8 conservative update; 10 new equilibrium (with q^n, reading R17)
-    TIMED(KK_MACRO, launch_apply_dW(D, m, c->sched.nchunk, B.W, B.dW, B.Wn, B.cellred, B.flag, s));
-    TIMED(KK_PRIMS, launch_cell_prep(D, c->nc, g, B.Wn, B.q, B.primn, B.csn, nullptr, B.flag, s));
-    // 11 second stage and the heat flux of h^{n+1}
-    TIMED(KK_STAGE2, launch_stage2_q(D, P, c->fmesh, v, B.primn, B.csn, B.ht, B.bt, B.qn, B.flag, s));
+    // 8 conservative update; 10 new equilibrium (with q^n, reading R17); 11
+    // second stage and the heat flux of h^{n+1}
+    TIMED(KK_STAGE2, launch_finish(D, P, m, c->fmesh, v, g, c->sched, B, s));
   }
   if (residual) TIMED(KK_RESID, launch_residual(m, B.cellred, B.resid, B.flag, s));
   swap_buffers(B);
@@ -860,7 +846,7 @@ void enqueue_step(ugks_ctx* c, bool residual) {
   // 3-4 ghost states and macroscopic reconstruction
   TIMED(KK_GRADW, launch_gradW(D, m, c->bcs, g, B.W, B.gW, B.flag, 1, s));
   // 6.1-6.6 interface equilibrium data
-  TIMED(KK_FACE_EQ, launch_face_eq(D, m, c->bcs, g, B.W, B.gW, B.q, B.frec, nullptr, B.flag, s));
+  TIMED(KK_FACE_EQ, launch_face_eq(D, m, c->bcs, g, B.W, B.gW, B.q, B.frec, P, c->nr, nullptr, B.flag, s));
   // 5 microscopic reconstruction
   TIMED(KK_GRAD_MICRO, launch_grad_micro(D, P, m, v, B.frec, B.h, B.b, B.gradh, B.gradb, B.flag, s));
   // 7 wall densities
@@ -1046,7 +1032,7 @@ void enqueue_batch_step(ugks_batch* b, int par) {
   hipStream_t s = b->stream;
   // 4 macroscopic reconstruction; 6.1-6.6 interface equilibrium
   HIP_TRY(launch_gradW_b(D, bd, b->ncell, s));
-  HIP_TRY(launch_face_eq_b(D, bd, b->nface, s));
+  HIP_TRY(launch_face_eq_b(D, P, bd, b->nface, s));
   // 7 wall densities; far-field ghost rows
   HIP_TRY(launch_ghost_rows_b(D, P, bd, b->nff, s));
   HIP_TRY(launch_wall_rho_b(D, P, bd, b->nwall, s));
@@ -1266,9 +1252,9 @@ void batch_build(ugks_batch* b, const ugks_case* cases, int32_t n, const ugks_op
   // on this batch's own records
   {
     const BatchDev bd = batch_dev(b, 0);
-    HIP_TRY(launch_cell_prep_b(b->D, bd, b->ncell, b->stream));
+    HIP_TRY(launch_cell_prep_b(b->D, b->prec, bd, b->ncell, b->stream));
     HIP_TRY(launch_gradW_b(b->D, bd, b->ncell, b->stream));
-    HIP_TRY(launch_face_eq_b(b->D, bd, b->nface, b->stream));
+    HIP_TRY(launch_face_eq_b(b->D, b->prec, bd, b->nface, b->stream));
     HIP_TRY(launch_ghost_rows_b(b->D, b->prec, bd, b->nff, b->stream));
     HIP_TRY(launch_wall_rho_b(b->D, b->prec, bd, b->nwall, b->stream));
   }
@@ -1291,7 +1277,7 @@ void batch_build(ugks_batch* b, const ugks_case* cases, int32_t n, const ugks_op
   // the timed launches' traces: flags, step counts and the first step's records
   HIP_TRY(hipMemset(b->flags_dev, 0, 4 * (size_t)n * sizeof(int32_t)));
   upload_cases(b);
-  HIP_TRY(launch_cell_prep_b(b->D, batch_dev(b, 0), b->ncell, b->stream));
+  HIP_TRY(launch_cell_prep_b(b->D, b->prec, batch_dev(b, 0), b->ncell, b->stream));
   const std::vector<int32_t> items = work_list(b, {});
   int64_t cap = 0;
   set_items(b, items, &b->items, &cap);
@@ -1383,7 +1369,7 @@ void capture_step_graphs(ugks_ctx* c) {
 // kernels with the same arguments.
 void run_step(ugks_ctx* c, bool residual) {
   const bool graphs = (c->flags & 32) && !c->profiling && c->stream != nullptr;
-  if (!graphs || !c->q_valid || (c->sched.whole && !c->cs_valid)) {
+  if (!graphs || !c->q_valid || (c->fused && !c->cs_valid)) {
     enqueue_step(c, residual);
     return;
   }

@@ -14,7 +14,7 @@ namespace ugks {
 
 constexpr int MAXF = 8;    // faces per cell
 constexpr int NPRIM = 8;   // rho, U[3], lambda, tau, p, spare
-constexpr int FREC = 96;   // doubles per face record
+constexpr int FREC = 48;   // doubles per face record
 constexpr int WAVE = 64;
 
 // Face record layout (doubles).  Interior / far-field faces hold the
@@ -33,9 +33,7 @@ enum FaceRec : int {
   FR_GU = 36,
   FR_GLAM = 39,
   FR_GC = 40,    // ghost: rho_g (lambda_g/pi)^(D/2)
-  FR_PH = 48,    // cubic polynomial PH(u) of the h-equation equilibrium terms (20)
-  FR_PB = 68,    // cubic polynomial PB(u) of the b-equation equilibrium terms (20, 2-D)
-  FR_BF = 88,    // wall: the step's flux of mass, momentum, energy (boundary-flux tracking)
+  FR_BF = 41,    // wall: the step's flux of mass, momentum, energy (boundary-flux tracking)
 };
 
 struct DevMesh {
@@ -64,20 +62,21 @@ struct DevMesh {
   const double* veps2 = nullptr;  // [nc] its eps^2 = (K V^(1/D))^3
 };
 
-// Static per-cell records of the fused sweep (built once at create).
+// Static per-cell records of the fused sweep (built once at create), laid out
+// in the order of their use, so that each step of the sweep's loop reads its
+// wave-uniform values in one or two wide scalar loads.
 // Integer record (CRI ints per cell):
-//   [0] faces, [1] own stencil size, [2..5] own stencil cells,
-//   face p at CRI_F0 + CRI_FS p: [0] face id, [1] kind, [2] 1 if the cell is L,
-//   [3] neighbour cell (-1 on a wall), [4] neighbour stencil size,
-//   [5..8] neighbour stencil cells.
+//   [CI_OWN + s] rows of the own stencil, slot s across face s; [CI_RING + 3p + q]
+//   rows 1..3 of the stencil of the neighbour across face p (its row 0 is this
+//   cell); [CI_FACE + p] face ids; [CI_KIND + p] face kinds.
 // Double record (CRD doubles per cell):
-//   [d*4 + s] own least-squares coefficients G[d][s],
-//   face p at CRD_F0 + CRD_FS p: [0..2] outward unit normal, [3] S/V,
-//   [4..6] x_f - x_cell, [7..9] x_f - x_neighbour, [10 + d*4 + r] the
-//   neighbour's coefficients G[d][r], [22] 1 (0 on a wall: the outgoing
-//   member has no equilibrium term).
-constexpr int CRI = 48, CRI_F0 = 6, CRI_FS = 10;
-constexpr int CRD = 112, CRD_F0 = 12, CRD_FS = 24;
+//   [CD_N + 3p + d] outward unit normal of face p;
+//   [CD_G + 4d + s] own least-squares coefficients G[d][s];
+//   face p at CD_F0 + CD_FS p: [0..2] x_f - x_cell, [3..5] x_f - x_neighbour,
+//   [6 + 4d + r] the neighbour's coefficients G[d][r], [18] 1 (0 on a wall: the
+//   outgoing member has no equilibrium term), [19] S/V.
+constexpr int CRI = 32, CI_OWN = 0, CI_RING = 4, CI_FACE = 16, CI_KIND = 20;
+constexpr int CRD = 112, CD_N = 0, CD_G = 16, CD_F0 = 32, CD_FS = 20;
 // Limiter record of the fused path (CRL doubles per cell, only with the
 // limiter): [0] eps^2 of the cell, [1..4] 1 where own stencil slot s is a
 // wall (its row is the zero row; its value for the bounds is the cell's own),
@@ -85,9 +84,12 @@ constexpr int CRD = 112, CRD_F0 = 12, CRD_FS = 24;
 // the neighbour's wall slots, [5 + 3 r + d] the offset of the neighbour's
 // face in its stencil slot r from its centroid (slot order of the record).
 constexpr int CRL = 88, CRL_F0 = 8, CRL_FS = 20;
-// Per-cell, per-step record of the fused path (CSREC doubles per cell).
-constexpr int CSREC = 48, CS_CC = 0, CS_KAP = 1, CS_NORM = 2, CS_SH = 4, CS_SB = 24;
-
+// Per-step records of the fused path in its compute type, SREC values per
+// face or cell and distribution (h, then b where it is carried):
+//   face: [0..1] Gamma_1, Gamma_2; cell: [0] dt/(2 tau), [1] K_xi/(2 lambda);
+//   [SR_P ...] the equilibrium polynomial c + l.u + u^T Q u + (kappa . u)|u|^2 as
+//   c | l (D) | quadratics (xx yy zz xy xz yz, or xx yy xy) | kappa (D).
+constexpr int SREC = 16, SR_P = 2;
 // Velocity slots of the fused path: mirror pairs are kept as slot k and slot
 // half + k (k < half = half a row), the first members ordered by compact blocks
 // of the node lattice, so that 64 consecutive slots have mostly one sign of
@@ -102,6 +104,7 @@ struct FusedMesh {
   const int32_t* crec_i;    // [nc*CRI]
   const double* crec_d;     // [nc*CRD]
   const float* crec_d32;    // [nc*CRD] FP32 copy (FP32 compute form), else null
+  int nr = 1;               // distributions carried (records per face and cell)
   bool sparse = false;      // points on the tensor product of `axis`, not all of it
   const double* crec_l = nullptr;  // [nc*CRL] limiter record, null without the limiter
   const float* crec_l32 = nullptr; // its FP32 copy (FP32 compute form)
@@ -158,17 +161,16 @@ struct StepBuffers {
   double* W;       // [nc*(D+2)] state W^n
   double* Wn;      // [nc*(D+2)] W^{n+1}
   double* prim;    // [nc*NPRIM] of W^n
-  double* primn;   // [nc*NPRIM] of W^{n+1} (staged and blocked forms)
+  double* primn;   // [nc*NPRIM] of W^{n+1} (staged form)
   double* q;       // [nc*3] heat flux of h^n
   double* qn;      // [nc*3] heat flux of h^{n+1} (fused path)
   double* gW;      // [nc*3*5]
   double* frec;    // [nf*FREC]
   double* F;       // [nf*5] face fluxes (staged sweep)
   double* dW;      // [nc*nchunk*5] per-(cell, velocity block) net outflow moments (fused sweep)
-  double* cs;      // [nc*CSREC] per-step cell record of W^n (fused sweep)
-  double* csn;     // [nc*CSREC] per-step cell record of W^{n+1} (blocked form)
-  float* frec32;   // FP32 copies of frec, cs for the FP32 sweep (null in FP64)
-  float* cs32;
+  // per-step records of the fused path, in its compute type (SREC)
+  void* srec;      // [nf*nr*SREC] faces
+  void* cs;        // [nc*nr*SREC] cells
   void* h;         // [nc*nvp] storage type
   void* b;         // [nc*nvp] where b is carried
   void* ht;        // [nc*nvp] first-stage result; on the fused path then h^{n+1}
@@ -189,8 +191,8 @@ struct StepBuffers {
 // What the rest of a cell's step reads and writes (whole-cell form).
 struct CellOut {
   const double *vol, *W, *q;
-  double *Wn, *qn, *prim, *cs;
-  float* cs32;
+  double *Wn, *qn, *prim;
+  void* cs;
   double* cellred;
   int32_t* flag;
 };
@@ -229,7 +231,7 @@ hipError_t launch_gradW(int D, const DevMesh& m, const DevBC* bcs, const GasP& g
                         double* gW, int32_t* flag, int count, hipStream_t s);
 hipError_t launch_face_eq(int D, const DevMesh& m, const DevBC* bcs, const GasP& g,
                           const double* W, const double* gW, const double* q, double* frec,
-                          float* frec32, int32_t* flag, hipStream_t s);
+                          int prec, int nr, void* srec, int32_t* flag, hipStream_t s);
 hipError_t launch_grad_micro(int D, int prec, const DevMesh& m, const DevVel& v,
                              const double* frec, const void* h, const void* b, double* gh,
                              double* gb, const int32_t* flag, hipStream_t s);
@@ -260,18 +262,14 @@ hipError_t launch_moments(int D, int prec, const DevMesh& m, const DevVel& v, co
 hipError_t launch_dt_cells(int D, const DevMesh& m, const DevVel& v, double* cellval,
                            hipStream_t s);
 // fused sweep (ugks_sweep.hip)
-hipError_t launch_cell_prep(int D, int64_t nc, const GasP& g, const double* W, const double* q,
-                            double* prim, double* cs, float* cs32, int32_t* flag, hipStream_t s);
+hipError_t launch_cell_prep(int D, int prec, int nr, int64_t nc, const GasP& g, const double* W,
+                            const double* q, double* prim, void* cs, int32_t* flag, hipStream_t s);
 hipError_t launch_sweep(int D, int prec, const FusedMesh& fm, const DevVel& v, const GasP& g,
                         const SweepSched& sc, const StepBuffers& B, hipStream_t s);
 hipError_t launch_step_cell(int D, int prec, const DevMesh& m, const FusedMesh& fm, const DevVel& v,
                             const GasP& g, const SweepSched& sc, const StepBuffers& B, hipStream_t s);
-hipError_t launch_apply_dW(int D, const DevMesh& m, int64_t nchunk, const double* W,
-                          const double* dWp, double* Wn, double* cellred, const int32_t* flag,
-                          hipStream_t s);
-hipError_t launch_stage2_q(int D, int prec, const FusedMesh& fm, const DevVel& v,
-                           const double* primn, const double* csn, void* h, void* b, double* qn,
-                           const int32_t* flag, hipStream_t s);
+hipError_t launch_finish(int D, int prec, const DevMesh& m, const FusedMesh& fm, const DevVel& v,
+                         const GasP& g, const SweepSched& sc, const StepBuffers& B, hipStream_t s);
 hipError_t launch_wall_rho_inline(int D, int prec, const DevMesh& m, const DevVel& v,
                                   const FusedMesh& fm, const GasP& g, const void* h, double* frec,
                                   const int32_t* flag, hipStream_t s, int track = 0,
@@ -283,9 +281,9 @@ hipError_t launch_ghost_rows(int D, int prec, const FusedMesh& fm, const DevVel&
                              hipStream_t s);
 
 // batched forms (one launch per phase over every case of a batch)
-hipError_t launch_cell_prep_b(int D, const BatchDev& bd, int64_t ncell, hipStream_t s);
+hipError_t launch_cell_prep_b(int D, int prec, const BatchDev& bd, int64_t ncell, hipStream_t s);
 hipError_t launch_gradW_b(int D, const BatchDev& bd, int64_t ncell, hipStream_t s);
-hipError_t launch_face_eq_b(int D, const BatchDev& bd, int64_t nface, hipStream_t s);
+hipError_t launch_face_eq_b(int D, int prec, const BatchDev& bd, int64_t nface, hipStream_t s);
 hipError_t launch_wall_rho_b(int D, int prec, const BatchDev& bd, int64_t nwall, hipStream_t s);
 hipError_t launch_ghost_rows_b(int D, int prec, const BatchDev& bd, int64_t nff, hipStream_t s);
 hipError_t launch_step_b(int D, int prec, const BatchDev& bd, int64_t grid, int threads,

@@ -136,15 +136,17 @@ __global__ void k_gradW(DevMesh m, const DevBC* __restrict__ bcs, GasP g, const 
 
 // Interface equilibrium data of every face (steps 6.1-6.6), wall Maxwellian
 // data of wall faces.
-template <int D>
+// T: the fused path's compute type, whose record srec takes (null on the
+// staged path).
+template <int D, typename T>
 __device__ __forceinline__ void face_eq_at(int64_t f, const DevMesh& m, const DevBC* __restrict__ bcs,
                                            const GasP& g, const double* __restrict__ W,
                                            const double* __restrict__ gW,
                                            const double* __restrict__ q, double* __restrict__ frec,
-                                           float* __restrict__ frec32, int32_t* flag) {
+                                           int nr, T* __restrict__ srec, int32_t* flag) {
   if (*flag) return;
   double* R = &frec[f * FREC];
-  float* R32 = frec32 ? &frec32[f * FREC] : nullptr;  // what the FP32 sweep reads of the record
+  T* S = srec ? &srec[f * nr * SREC] : nullptr;
   const int kind = m.fbc[f];
   const int L = m.fL[f];
   if (kind == UGKS_BC_WALL) {
@@ -155,18 +157,13 @@ __device__ __forceinline__ void face_eq_at(int64_t f, const DevMesh& m, const De
     for (int d = 0; d < 3; ++d) R[FR_U + d] = d < D ? bc.U[d] : 0.0;
     // free transport of the incident member over the step (h_f - t u.grad h),
     // and the re-emitted Maxwellian as g(u) times a constant polynomial
-    R[FR_G] = g.dt;
-    R[FR_G + 1] = -0.5 * g.dt * g.dt;
-    for (int x = 0; x < 20; ++x) {
-      R[FR_PH + x] = x == 0 ? 1.0 : 0.0;
-      R[FR_PB + x] = x == 0 ? (g.K + 3.0 - D) / (2.0 * lamw) : 0.0;
-    }
-    if (R32) {
-      for (int x = 0; x < 2; ++x) R32[FR_G + x] = (float)R[FR_G + x];
-      for (int x = 0; x < 20; ++x) {
-        R32[FR_PH + x] = (float)R[FR_PH + x];
-        R32[FR_PB + x] = (float)R[FR_PB + x];
-      }
+    if (S) {
+      double P[Cubic<D>::N];
+      for (int x = 0; x < Cubic<D>::N; ++x) P[x] = 0.0;
+      P[0] = 1.0;
+      write_srec<D>(S, g.dt, -0.5 * g.dt * g.dt, P);
+      P[0] = (g.K + 3.0 - D) / (2.0 * lamw);
+      if (nr == 2) write_srec<D>(S + SREC, g.dt, -0.5 * g.dt * g.dt, P);
     }
     return;
   }
@@ -236,9 +233,10 @@ __device__ __forceinline__ void face_eq_at(int64_t f, const DevMesh& m, const De
   R[FR_C0] = rho0 * maxw_norm<D>(lam0);
   R[FR_LAM] = lam0;
   for (int d = 0; d < 3; ++d) R[FR_U + d] = U0[d];
-  R[FR_SH] = 4.0 * (1.0 - g.Pr) * lam0 * lam0 / ((g.K + 5.0) * rho0);
+  const double sh = 4.0 * (1.0 - g.Pr) * lam0 * lam0 / ((g.K + 5.0) * rho0);
   const double kxi = g.K + 3.0 - D;
-  time_coeffs(g.dt, P0[5], &R[FR_G]);
+  double G[5];
+  time_coeffs(g.dt, P0[5], G);
   // 6.4 spatial slopes from the averaged gradient
   double a[3][5];
   for (int d = 0; d < 3; ++d)
@@ -258,16 +256,21 @@ __device__ __forceinline__ void face_eq_at(int64_t f, const DevMesh& m, const De
   double r[5], At[5];
   time_slope_rhs<D>(M, a, r);
   slope_solve<D>(r, U0, lam0, g.K + 3.0, At);
-  for (int d = 0; d < 3; ++d)
-    for (int v = 0; v < 5; ++v) R[FR_A + d * 5 + v] = (d < D && v < D + 2) ? a[d][v] : 0.0;
-  for (int v = 0; v < 5; ++v) R[FR_AT + v] = v < D + 2 ? At[v] : 0.0;
   // 6.6 interface heat flux
   double q0[3] = {0.0, 0.0, 0.0};
   for (int d = 0; d < 3; ++d) {
     double ql = q[(int64_t)L * 3 + d];
     double qr = ghost ? 0.0 : q[(int64_t)Rc * 3 + d];
     q0[d] = d < D ? 0.5 * (ql + qr) : 0.0;
-    R[FR_Q + d] = q0[d];
+  }
+  if (!S) {  // the staged path evaluates the terms one by one
+    R[FR_SH] = sh;
+    for (int x = 0; x < 5; ++x) R[FR_G + x] = G[x];
+    for (int d = 0; d < 3; ++d) R[FR_Q + d] = q0[d];
+    for (int d = 0; d < 3; ++d)
+      for (int v = 0; v < 5; ++v) R[FR_A + d * 5 + v] = (d < D && v < D + 2) ? a[d][v] : 0.0;
+    for (int v = 0; v < 5; ++v) R[FR_AT + v] = v < D + 2 ? At[v] : 0.0;
+    return;
   }
   // All equilibrium terms of the time-integrated interface distribution,
   //   Gamma3 (g0 + g0+) + Gamma4 u.grad g0 + Gamma5 d_t g0,
@@ -278,8 +281,7 @@ __device__ __forceinline__ void face_eq_at(int64_t f, const DevMesh& m, const De
     for (int x = 0; x < Cb::N; ++x) PH[x] = PB[x] = 0.0;
     const double kap = kxi / (2.0 * lam0);                             // B0 / H0
     const double xi4 = kxi * (kxi + 2.0) / (4.0 * lam0 * lam0);       // int xi^4 g / H0
-    const double G3 = R[FR_G + 2], G4 = R[FR_G + 3], G5 = R[FR_G + 4];
-    const double sh = R[FR_SH];
+    const double G3 = G[2], G4 = G[3], G5 = G[4];
     double a0v[3], a4v[3], Am[9], Atl[3];
     for (int d = 0; d < D; ++d) {
       a0v[d] = a[d][0];
@@ -310,27 +312,18 @@ __device__ __forceinline__ void face_eq_at(int64_t f, const DevMesh& m, const De
       Cb::add_lin(PB, G5 * kap, Atl);
       Cb::add_u2(PB, 0.5 * G5 * kap * At[D + 1]);
     }
-    for (int x = 0; x < 20; ++x) {
-      R[FR_PH + x] = x < Cb::N ? PH[x] : 0.0;
-      R[FR_PB + x] = x < Cb::N ? PB[x] : 0.0;
-    }
-    if (R32) {
-      for (int x = 0; x < 2; ++x) R32[FR_G + x] = (float)R[FR_G + x];
-      for (int x = 0; x < Cb::N; ++x) {
-        R32[FR_PH + x] = (float)PH[x];
-        R32[FR_PB + x] = (float)PB[x];
-      }
-    }
+    write_srec<D>(S, G[0], G[1], PH);
+    if (nr == 2) write_srec<D>(S + SREC, G[0], G[1], PB);
   }
 }
 
-template <int D>
+template <int D, typename T>
 __global__ void k_face_eq(DevMesh m, const DevBC* __restrict__ bcs, GasP g,
                           const double* __restrict__ W, const double* __restrict__ gW,
                           const double* __restrict__ q, double* __restrict__ frec,
-                          float* __restrict__ frec32, int32_t* flag) {
+                          int nr, T* __restrict__ srec, int32_t* flag) {
   const int64_t f = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (f < m.nf) face_eq_at<D>(f, m, bcs, g, W, gW, q, frec, frec32, flag);
+  if (f < m.nf) face_eq_at<D, T>(f, m, bcs, g, W, gW, q, frec, nr, srec, flag);
 }
 
 // Microscopic gradients of h (and b) for every (cell, velocity) (step 5).
@@ -791,14 +784,14 @@ __global__ void k_gradW_b(BatchDev bd) {
   gradW_at<D>(t - bd.cell_off[c], C.m, C.bcs, C.g, C.B.W, C.B.gW, C.B.flag, 1);
 }
 
-template <int D>
+template <int D, typename T>
 __global__ void k_face_eq_b(BatchDev bd) {
   const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (t >= bd.face_off[bd.n]) return;
   const int c = case_of(bd.face_off, bd.n, t);
   const CaseDev& C = bd.cases[c];
-  face_eq_at<D>(t - bd.face_off[c], C.m, C.bcs, C.g, C.B.W, C.B.gW, C.B.q, C.B.frec,
-                C.B.frec32, C.B.flag);
+  face_eq_at<D, T>(t - bd.face_off[c], C.m, C.bcs, C.g, C.B.W, C.B.gW, C.B.q, C.B.frec, C.fm.nr,
+                   (T*)C.B.srec, C.B.flag);
 }
 
 // one block per case
@@ -854,8 +847,9 @@ hipError_t launch_gradW(int D, const DevMesh& m, const DevBC* bcs, const GasP& g
 
 hipError_t launch_face_eq(int D, const DevMesh& m, const DevBC* bcs, const GasP& g,
                           const double* W, const double* gW, const double* q, double* frec,
-                          float* frec32, int32_t* flag, hipStream_t s) {
-  UGKS_DISPATCH_D(D, k_face_eq<DD><<<blocks_for(m.nf, 64), 64, 0, s>>>(m, bcs, g, W, gW, q, frec, frec32, flag));
+                          int prec, int nr, void* srec, int32_t* flag, hipStream_t s) {
+  UGKS_DISPATCH_DT(D, prec, k_face_eq<DD, TT><<<blocks_for(m.nf, 64), 64, 0, s>>>(
+      m, bcs, g, W, gW, q, frec, nr, (TT*)srec, flag));
   return hipGetLastError();
 }
 
@@ -950,11 +944,10 @@ hipError_t launch_gradW_b(int D, const BatchDev& bd, int64_t ncell, hipStream_t 
   return hipGetLastError();
 }
 
-hipError_t launch_face_eq_b(int D, const BatchDev& bd, int64_t nface, hipStream_t s) {
+hipError_t launch_face_eq_b(int D, int prec, const BatchDev& bd, int64_t nface, hipStream_t s) {
   if (nface == 0) return hipSuccess;
   const unsigned grid = (unsigned)((nface + 63) / 64);
-  if (D == 2) k_face_eq_b<2><<<grid, 64, 0, s>>>(bd);
-  else k_face_eq_b<3><<<grid, 64, 0, s>>>(bd);
+  UGKS_DISPATCH_DT(D, prec, k_face_eq_b<DD, TT><<<grid, 64, 0, s>>>(bd));
   return hipGetLastError();
 }
 

@@ -68,6 +68,32 @@ typedef const __attribute__((address_space(4))) int32_t crec_i_t;
 template <typename X>
 using crec_t = const __attribute__((address_space(4))) X;
 
+// N wave-uniform record values in scalar loads of 64 bytes (and one of what
+// remains).
+template <typename C, int N>
+struct wide_t {
+  typedef C vec __attribute__((ext_vector_type(N)));
+  typedef vec type __attribute__((aligned(sizeof(C))));
+};
+template <typename C, int N>
+__device__ __forceinline__ void load_rec(crec_t<C>* p, C (&v)[N]) {
+  constexpr int W = 64 / sizeof(C);
+  typedef typename wide_t<C, W>::type whole_t;
+#pragma unroll
+  for (int i = 0; i + W <= N; i += W) {
+    const typename wide_t<C, W>::vec x = *(crec_t<whole_t>*)(p + i);
+#pragma unroll
+    for (int j = 0; j < W; ++j) v[i + j] = x[j];
+  }
+  constexpr int R = N % W;
+  if constexpr (R > 0) {
+    typedef typename wide_t<C, R>::type rest_t;
+    const typename wide_t<C, R>::vec x = *(crec_t<rest_t>*)(p + N - R);
+#pragma unroll
+    for (int j = 0; j < R; ++j) v[N - R + j] = x[j];
+  }
+}
+
 template <typename T, typename C>
 __device__ __forceinline__ C ldo(grow_t* row, uint32_t off) {
   return static_cast<C>(*(const __attribute__((address_space(1))) T*)(row + off));
@@ -90,22 +116,19 @@ __device__ __forceinline__ void sto_nt(gout_t* row, uint32_t off, T v) {
   __builtin_nontemporal_store(v, (__attribute__((address_space(1))) T*)(row + off));
 }
 
-// Even and odd parts of a cubic P = c + l.u + u^T Q u + (kappa . u)|u|^2
-// (monomial order of Cubic<D>; kappa_a is the coefficient of u_a^3, the only
-// cubic form the scheme builds) at u, with v2 = |u|^2:
+// Even and odd parts of a polynomial P = c + l.u + u^T Q u + (kappa . u)|u|^2 (a
+// sweep record's values from SR_P on) at u, with v2 = |u|^2:
 //   E = c + u^T Q u,  O = l.u + (kappa . u) v2,  P(u) = E + O,  P(-u) = E - O.
 template <int D, typename C, typename PT>
 __device__ __forceinline__ void cubic_eo(PT P, const C* v, C v2, C& E, C& O) {
   if constexpr (D == 3) {
     const C x = v[0], y = v[1], z = v[2];
-    // quadratics xx yy zz xy xz yz = P[4..9]; u_a^3 at P[10], P[16], P[19]
     E = P[0] + x * (P[4] * x + P[7] * y + P[8] * z) + y * (P[5] * y + P[9] * z) + P[6] * z * z;
-    O = (P[1] * x + P[2] * y + P[3] * z) + (P[10] * x + P[16] * y + P[19] * z) * v2;
+    O = (P[1] * x + P[2] * y + P[3] * z) + (P[10] * x + P[11] * y + P[12] * z) * v2;
   } else {
     const C x = v[0], y = v[1];
-    // quadratics xx yy xy = P[3..5]; u_a^3 at P[6], P[9]
     E = P[0] + x * (P[3] * x + P[5] * y) + P[4] * y * y;
-    O = (P[1] * x + P[2] * y) + (P[6] * x + P[9] * y) * v2;
+    O = (P[1] * x + P[2] * y) + (P[6] * x + P[7] * y) * v2;
   }
 }
 
@@ -150,39 +173,24 @@ __device__ __forceinline__ void shakhov_polys(const double* P, const GasP& g, co
   Cb::add_shakhov(SB, sh, U, qc, lam, (double)D);
 }
 
-// Per-step record of a cell with primitives P: dt/(2 tau), K_xi/(2 lambda),
-// the Maxwellian's norm and the Shakhov polynomials (and its FP32 copy).
-template <int D>
+// Per-step record of a cell with primitives P and heat flux qc.
+template <int D, typename T>
 __device__ __forceinline__ void cell_record(const double* P, const GasP& g, double dt, const double* qc,
-                                            double* __restrict__ C, float* __restrict__ C32) {
+                                            int nr, T* __restrict__ C) {
   constexpr int N = Cubic<D>::N;
   double SH[N], SB[N];
   shakhov_polys<D>(P, g, qc, SH, SB);
   const double cc = dt / (2.0 * P[5]), kap = (g.K + 3.0 - D) / (2.0 * P[4]);
-  C[CS_CC] = cc;
-  C[CS_KAP] = kap;
-  C[CS_NORM] = P[0] * maxw_norm<D>(P[4]);
-#pragma unroll
-  for (int x = 0; x < N; ++x) {
-    C[CS_SH + x] = SH[x];
-    C[CS_SB + x] = SB[x];
-  }
-  if (C32) {
-    C32[CS_CC] = (float)cc;
-    C32[CS_KAP] = (float)kap;
-#pragma unroll
-    for (int x = 0; x < N; ++x) {
-      C32[CS_SH + x] = (float)SH[x];
-      C32[CS_SB + x] = (float)SB[x];
-    }
-  }
+  write_srec<D>(C, cc, kap, SH);
+  if (nr == 2) write_srec<D>(C + SREC, cc, kap, SB);
 }
 
-template <int D>
+// prim and the cell record of W^n, q before a first step (a step leaves the
+// next one's).
+template <int D, typename T>
 __device__ __forceinline__ void cell_prep_at(int64_t i, const GasP& g, const double* __restrict__ W,
-                                             const double* __restrict__ q,
-                                             double* __restrict__ prim, double* __restrict__ cs,
-                                             float* __restrict__ cs32, int32_t* flag) {
+                                             const double* __restrict__ q, double* __restrict__ prim,
+                                             int nr, T* __restrict__ cs, int32_t* flag) {
   if (*flag) return;
   double* P = &prim[i * NPRIM];
   if (!prim_of<D>(&W[i * (D + 2)], g, P)) {
@@ -190,15 +198,15 @@ __device__ __forceinline__ void cell_prep_at(int64_t i, const GasP& g, const dou
     return;
   }
   const double qc[3] = {q[i * 3], q[i * 3 + 1], q[i * 3 + 2]};
-  cell_record<D>(P, g, dt_cell(g, i), qc, &cs[i * CSREC], cs32 ? &cs32[i * CSREC] : nullptr);
+  cell_record<D>(P, g, dt_cell(g, i), qc, nr, &cs[i * nr * SREC]);
 }
 
-template <int D>
+template <int D, typename T>
 __global__ void k_cell_prep(int64_t nc, GasP g, const double* __restrict__ W,
-                            const double* __restrict__ q, double* __restrict__ prim,
-                            double* __restrict__ cs, float* __restrict__ cs32, int32_t* flag) {
+                            const double* __restrict__ q, double* __restrict__ prim, int nr,
+                            T* __restrict__ cs, int32_t* flag) {
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (i < nc) cell_prep_at<D>(i, g, W, q, prim, cs, cs32, flag);
+  if (i < nc) cell_prep_at<D>(i, g, W, q, prim, nr, cs, flag);
 }
 
 // LDS of one work item.  A table holds, for node n, the entry at n and the
@@ -215,7 +223,8 @@ template <int D>
 struct CellTabs {
   alignas(16) double tab[D][NAX][2];
   double ax[NAX][2];
-  double poly[40];
+  double poly[2][SREC];
+  double par[8];  // lambda, U (3), the table's factor, 1/(1 + A), valid
 };
 template <int D, typename C>
 struct SweepLds {
@@ -260,8 +269,8 @@ __device__ __forceinline__ double wave_total(double v) {
   return dpp_add<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3
 }
 
-// Work-group totals of N values, in every lane: each wave's sum, then the
-// waves in order.
+// Work-group totals of N values, in every lane of the first wave: each wave's
+// sum, then the waves in order.  A barrier for the whole work-group.
 template <int N>
 __device__ __forceinline__ void block_total(double (&v)[N], double* lds) {
 #pragma unroll
@@ -271,11 +280,13 @@ __device__ __forceinline__ void block_total(double (&v)[N], double* lds) {
 #pragma unroll
     for (int n = 0; n < N; ++n) lds[n * 16 + wv] = v[n];
   __syncthreads();
+  if (threadIdx.x < WAVE) {
 #pragma unroll
-  for (int n = 0; n < N; ++n) {
-    double t = lds[n * 16];
-    for (int w = 1; w < nw; ++w) t += lds[n * 16 + w];
-    v[n] = t;
+    for (int n = 0; n < N; ++n) {
+      double t = lds[n * 16];
+      for (int w = 1; w < nw; ++w) t += lds[n * 16 + w];
+      v[n] = t;
+    }
   }
 }
 
@@ -293,11 +304,11 @@ struct SweepIn {
   const C* crec_l;
   const int32_t* vidx;
   const double* w;
-  const C* cs;
-  const C* frec;
-  const double* frec64;
+  const C* cs;            // [nc*nr*SREC]
+  const C* srec;          // [nf*nr*SREC]
+  const double* frec;
   const double* prim;
-  double norm, dt;
+  double dt;
   int64_t nvp;
   unsigned half;  // slots of the first members; the mirror of slot k is slot half + k
   unsigned keep;  // whole-cell form: pairs (a multiple of 64) whose first stage stays in LDS
@@ -325,15 +336,15 @@ __device__ __forceinline__ void sweep_tables(const SweepIn<C>& in, int64_t ic, S
       const unsigned e = row / D, d = row % D;
       double lam, U, scale = 1.0;
       if (e < 4) {
-        const int32_t* fi = in.crec_i + ic * CRI + CRI_F0 + CRI_FS * e;
-        const double* R = in.frec64 + (uint64_t)(uint32_t)fi[0] * FREC;
+        const int32_t* ci = in.crec_i + ic * CRI;
+        const double* R = in.frec + (uint64_t)(uint32_t)ci[CI_FACE + e] * FREC;
         lam = R[FR_LAM];
         U = R[FR_U + d];
-        if (d == 0) scale = fi[1] == UGKS_BC_WALL ? R[FR_C0] * R[FR_RHOW] * in.dt : R[FR_C0];
+        if (d == 0) scale = ci[CI_KIND + e] == UGKS_BC_WALL ? R[FR_C0] * R[FR_RHOW] * in.dt : R[FR_C0];
       } else {
         lam = in.prim[ic * NPRIM + 4];
         U = in.prim[ic * NPRIM + 1 + d];
-        if (d == 0) scale = in.norm;
+        if (d == 0) scale = in.prim[ic * NPRIM] * maxw_norm<D>(lam);
       }
       const C v = (C)(scale * exp(-lam * (a - U) * (a - U)));
       L.tab[e][d][n][0] = v;
@@ -358,15 +369,16 @@ __device__ __forceinline__ void sweep_tables(const SweepIn<C>& in, int64_t ic, S
 // 48,000 tets x 24^3, rows beyond the cell's own cost 1.7 (L2 misses), the
 // first stage's stores 0.9 and the rest of the step 1.7; the loop alone is
 // at 65 % of its VALU time.
-template <int D, typename T, typename C, int NR, int X0, bool LIM>
+template <int D, typename T, typename C, int NR, int X0, bool LIM, bool HB>
 __device__ __forceinline__ void sweep_pass(const SweepIn<C>& in, const T* __restrict__ h,
                                            const T* __restrict__ b, T* __restrict__ ht,
                                            T* __restrict__ bt, int64_t ic, unsigned kbeg, unsigned kend,
                                            const SweepTabs<D, C>& L, T* stage, double (&mw)[D + 2]) {
   crec_i_t* ci0 = (crec_i_t*)(in.crec_i + ic * CRI);
   crec_t<C>* cd0 = (crec_t<C>*)(in.crec_d + ic * CRD);
-  crec_t<C>* cc0 = (crec_t<C>*)(in.cs + ic * CSREC);
-  crec_t<C>* frc = (crec_t<C>*)in.frec;
+  constexpr int RS = (HB ? 2 : 1) * SREC;  // a face's or cell's records
+  crec_t<C>* cc0 = (crec_t<C>*)(in.cs + ic * RS);
+  crec_t<C>* frc = (crec_t<C>*)in.srec;
   crec_t<C>* cl0 = LIM ? (crec_t<C>*)(in.crec_l + ic * CRL) : nullptr;
   const unsigned nthr = blockDim.x;  // lanes of the work-group, one mirror pair each
   // Row r of h (or b) starts r * rowb bytes in.  Row indices are 32-bit and
@@ -412,13 +424,17 @@ __device__ __forceinline__ void sweep_pass(const SweepIn<C>& in, const T* __rest
       at[d] = node_off<C>(pk, d);
       vv[d] = *(const C*)((const char*)L.ax + at[d]);
     }
+    int32_t rows[16];
+    C nrm[12];
+    load_rec<int32_t, 16>(ci + CI_OWN, rows);
+    load_rec<C, 12>(cd + CD_N, nrm);
     // orientation of u against every outward normal
     C sp[4];
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
       C s = C(0);
 #pragma unroll
-      for (int d = 0; d < D; ++d) s += vv[d] * cd[CRD_F0 + CRD_FS * p + 0 + d];
+      for (int d = 0; d < D; ++d) s += vv[d] * nrm[3 * p + d];
       sp[p] = s;
     }
     // ---- the cell's own stencil at u and -u (4 rows, padded) ----
@@ -433,7 +449,7 @@ __device__ __forceinline__ void sweep_pass(const SweepIn<C>& in, const T* __rest
     for (int s = 0; s < 4; ++s) {
 #pragma unroll
       for (int r = 0; r < NR; ++r) {
-        grow_t* rs = row_of(src[r], ci[2 + s]);
+        grow_t* rs = row_of(src[r], rows[CI_OWN + s]);
         os0[r][s] = ldo<T, C>(rs, o0);
         os1[r][s] = ldo<T, C>(rs, o1);
       }
@@ -444,13 +460,12 @@ __device__ __forceinline__ void sweep_pass(const SweepIn<C>& in, const T* __rest
     C ns[NR][4][3];
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
-      crec_i_t* fi = ci + CRI_F0 + CRI_FS * p;
       uint32_t oin = sp[p] > C(0) ? o1 : o0;  // u.n > 0: the incoming member is -u
       __asm__("" : "+v"(oin));  // keep the select on the offset, not on 64-bit addresses
 #pragma unroll
       for (int q = 0; q < 3; ++q)
 #pragma unroll
-        for (int r = 0; r < NR; ++r) ns[r][p][q] = ldo<T, C>(row_of(src[r], fi[6 + q]), oin);
+        for (int r = 0; r < NR; ++r) ns[r][p][q] = ldo<T, C>(row_of(src[r], rows[CI_RING + 3 * p + q]), oin);
     }
     if constexpr (sizeof(C) == 4) __builtin_amdgcn_s_setprio(0);
     // ---- arithmetic ----
@@ -465,7 +480,7 @@ __device__ __forceinline__ void sweep_pass(const SweepIn<C>& in, const T* __rest
         const C d0 = os0[r][s] - f0[r], d1 = os1[r][s] - f1[r];
 #pragma unroll
         for (int d = 0; d < D; ++d) {
-          const C G = cd[d * 4 + s];
+          const C G = cd[CD_G + d * 4 + s];
           g0[r][d] += G * d0;
           g1[r][d] += G * d1;
         }
@@ -484,8 +499,8 @@ __device__ __forceinline__ void sweep_pass(const SweepIn<C>& in, const T* __rest
           hi1 = fmax(hi1, v1);
         }
         const C e2 = cl[0];
-        const C p0 = venkat_phi<D>(f0[r], lo0, hi0, g0[r], cd + CRD_F0 + 4, CRD_FS, e2);
-        const C p1 = venkat_phi<D>(f1[r], lo1, hi1, g1[r], cd + CRD_F0 + 4, CRD_FS, e2);
+        const C p0 = venkat_phi<D>(f0[r], lo0, hi0, g0[r], cd + CD_F0, CD_FS, e2);
+        const C p1 = venkat_phi<D>(f1[r], lo1, hi1, g1[r], cd + CD_F0, CD_FS, e2);
 #pragma unroll
         for (int d = 0; d < D; ++d) {
           g0[r][d] *= p0;
@@ -504,11 +519,23 @@ __device__ __forceinline__ void sweep_pass(const SweepIn<C>& in, const T* __rest
     for (int d = 0; d < D; ++d) v2 += vv[d] * vv[d];
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
-      crec_t<C>* fd = cd + CRD_F0 + CRD_FS * p;
-      crec_t<C>* R = frc + (uint64_t)(uint32_t)ci[CRI_F0 + CRI_FS * p] * FREC;
-      const C G1 = R[FR_G], G2 = R[FR_G + 1];
-      const C eqm = fd[22];  // 0 on a wall: no equilibrium term going out
-      const C sas = fd[3] * fabs(sp[p]);  // S/V |u.n|
+      // the face's geometry: in wide loads (FP32, and the pass of h and b), or,
+      // where their 40 registers would spill others, value by value (FP64:
+      // 7.75 against 7.89 ms on 48,000 x 24^3; FP32 x 28^3: 7.25 against 7.11)
+      constexpr bool WIDE = sizeof(C) == 4 || NR == 2;
+      crec_t<C>* fdp = cd + CD_F0 + CD_FS * p;
+      C R[NR][SREC], fdw[CD_FS];
+#pragma unroll
+      for (int r = 0; r < NR; ++r)
+        load_rec<C, SREC>(frc + (uint64_t)(uint32_t)ci[CI_FACE + p] * RS + (X0 + r) * SREC, R[r]);
+      if constexpr (WIDE) load_rec<C, CD_FS>(fdp, fdw);
+      auto fd = [&](int i) -> C {
+        if constexpr (WIDE) return fdw[i];
+        else return fdp[i];
+      };
+      const C G1 = R[0][0], G2 = R[0][1];
+      const C eqm = fd(18);  // 0 on a wall: no equilibrium term going out
+      const C sas = fd(19) * fabs(sp[p]);  // S/V |u.n|
       // g0 (or the scaled wall Maxwellian) at u and -u from the axis tables
       C e0, e1;
       tab_pair(L.tab[p][0], at[0], e0, e1);
@@ -523,18 +550,18 @@ __device__ __forceinline__ void sweep_pass(const SweepIn<C>& in, const T* __rest
       for (int r = 0; r < NR; ++r) {
         // times the equilibrium polynomial (constant on a wall)
         C E, O;
-        cubic_eo<D>(R + (X0 + r ? FR_PB : FR_PH), vv, v2, E, O);
+        cubic_eo<D>(R[r] + SR_P, vv, v2, E, O);
         const C q0 = e0 * (E + O), q1 = e1 * (E - O);
         // the neighbour's gradient from its value fj and this cell's value fi
         // (all zero rows on a wall)
         auto slope = [&](C fj, C fi, C* gj) {
 #pragma unroll
-          for (int d = 0; d < D; ++d) gj[d] = fd[10 + d * 4] * (fi - fj);
+          for (int d = 0; d < D; ++d) gj[d] = fd(6 + d * 4) * (fi - fj);
 #pragma unroll
           for (int q = 0; q < 3; ++q) {
             const C df = ns[r][p][q] - fj;
 #pragma unroll
-            for (int d = 0; d < D; ++d) gj[d] += fd[11 + d * 4 + q] * df;
+            for (int d = 0; d < D; ++d) gj[d] += fd(7 + d * 4 + q) * df;
           }
         };
         C gl[D];
@@ -562,7 +589,7 @@ __device__ __forceinline__ void sweep_pass(const SweepIn<C>& in, const T* __rest
         auto flux = [&](C fo, const C* go, C ugo, C eqo, C fj, C fi, C su, C eqi, C& acco, C& acci) {
           C ff = fo;
 #pragma unroll
-          for (int d = 0; d < D; ++d) ff += fd[4 + d] * go[d];
+          for (int d = 0; d < D; ++d) ff += fd(d) * go[d];
           C gj[D];
           if constexpr (LIM) {
 #pragma unroll
@@ -573,7 +600,7 @@ __device__ __forceinline__ void sweep_pass(const SweepIn<C>& in, const T* __rest
           C ffj = fj, ugj = C(0);
 #pragma unroll
           for (int d = 0; d < D; ++d) {
-            ffj += fd[7 + d] * gj[d];
+            ffj += fd(3 + d) * gj[d];
             ugj += vv[d] * gj[d];
           }
           acco += sas * (G1 * ff + G2 * ugo + eqm * eqo);
@@ -611,17 +638,17 @@ __device__ __forceinline__ void sweep_pass(const SweepIn<C>& in, const T* __rest
       c0 *= a0;
       c1 *= a1;
     }
-    const C ccoll = cc[CS_CC];
+    const C ccoll = cc[0];
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
       C m0 = c0, m1 = c1;
       if (X0 + r == 1) {  // the b equilibrium carries the internal-energy factor
-        const C kc = cc[CS_KAP];
+        const C kc = cc[1];
         m0 *= kc;
         m1 *= kc;
       }
       C E, O;
-      cubic_eo<D>(cc + (X0 + r ? CS_SB : CS_SH), vv, v2, E, O);
+      cubic_eo<D>(cc + (X0 + r) * SREC + SR_P, vv, v2, E, O);
       E += C(1);
       const T t0 = (T)(f0[r] - acc0[r] + ccoll * (m0 * (E + O) - f0[r]));
       const T t1 = (T)(f1[r] - acc1[r] + ccoll * (m1 * (E - O) - f1[r]));
@@ -652,75 +679,89 @@ __device__ __forceinline__ void sweep_item(const SweepIn<C>& in, const T* __rest
 #pragma unroll
   for (int x = 0; x < D + 2; ++x) mw[x] = 0.0;
   if constexpr (HB && BOTH) {
-    sweep_pass<D, T, C, 2, 0, LIM>(in, h, b, ht, bt, ic, kbeg, kend, L, stage, mw);
+    sweep_pass<D, T, C, 2, 0, LIM, HB>(in, h, b, ht, bt, ic, kbeg, kend, L, stage, mw);
   } else {
-    sweep_pass<D, T, C, 1, 0, LIM>(in, h, b, ht, bt, ic, kbeg, kend, L, stage, mw);
-    if constexpr (HB) sweep_pass<D, T, C, 1, 1, LIM>(in, h, b, ht, bt, ic, kbeg, kend, L, stage, mw);
+    sweep_pass<D, T, C, 1, 0, LIM, HB>(in, h, b, ht, bt, ic, kbeg, kend, L, stage, mw);
+    if constexpr (HB) sweep_pass<D, T, C, 1, 1, LIM, HB>(in, h, b, ht, bt, ic, kbeg, kend, L, stage, mw);
   }
 }
 
-// The rest of a cell's step, by the work-group that swept all of its
-// velocities: the conservative update W^{n+1} = W^n - sum, the second stage
-// (Eq. f_final) with the equilibrium of W^{n+1} and q^n (reading R17) in place
-// on the first stage's row, the heat flux of the result, and the next step's
-// cell record.  Each lane takes the mirror pairs it swept, so it reads back
-// what it wrote itself.
+// The rest of a cell's step: the conservative update W^{n+1} = W^n - sum (tot,
+// in the first wave), the second stage (Eq. f_final) with the equilibrium of
+// W^{n+1} and q^n (reading R17) in place on the first stage's row, the heat
+// flux of the result, and the next step's cell record.  Where the work-group
+// has swept the cell, each lane takes the pairs it swept and reads back what
+// it wrote itself.  What is done once per cell is done by the first wave: by
+// all eight it was a tenth of the kernel's VALU instructions.
 template <int D, typename T, bool HB>
 __device__ __forceinline__ void finish_cell(const GasP& g, const int32_t* __restrict__ vidx,
                                             const double* __restrict__ w, const CellOut& o, T* ht, T* bt,
                                             int64_t ic, int64_t nvp, unsigned half, int na,
                                             const double* __restrict__ axis, const T* stage, unsigned keep,
-                                            double (&mw)[D + 2], CellTabs<D>& L, double* red) {
-  constexpr int NM = D + 2, N = Cubic<D>::N;
-  block_total<NM>(mw, red);
-  double Wn[NM], P[NPRIM];
-  const double* Wi = o.W + ic * NM;
+                                            double (&tot)[D + 2], CellTabs<D>& L, double* red) {
+  constexpr int NM = D + 2, N = Cubic<D>::N, NP = Cubic<D>::C0 + D;
+  double P[NPRIM], dt = 0.0;
+  if (threadIdx.x < WAVE) {
+    double Wn[NM];
+    const double* Wi = o.W + ic * NM;
 #pragma unroll
-  for (int x = 0; x < NM; ++x) Wn[x] = Wi[x] - mw[x];
-  if (!prim_of<D>(Wn, g, P)) {  // the same in every lane
-    // (flag[2]: the other work-groups of this launch go on, on flag[0])
-    if (threadIdx.x == 0) atomicOr(&o.flag[2], 1);
-    return;
+    for (int x = 0; x < NM; ++x) Wn[x] = Wi[x] - tot[x];
+    const bool ok = prim_of<D>(Wn, g, P);
+    dt = dt_cell(g, ic);
+    if (threadIdx.x == 0) {
+      const double lam = P[4], A = dt / (2.0 * P[5]), inv = 1.0 / (1.0 + A);
+      const double kc = (g.K + 3.0 - D) / (2.0 * lam);
+      const double qc[3] = {o.q[ic * 3], o.q[ic * 3 + 1], o.q[ic * 3 + 2]};
+      // f^{n+1} = (f~ + A g (1 + P)) / (1 + A): the factor A / (1 + A) goes into
+      // the first axis's table, the 1 into the polynomial's constant
+      double SH[N], SB[N];
+      shakhov_polys<D>(P, g, qc, SH, SB);
+      SH[0] += 1.0;
+      SB[0] += 1.0;
+      write_srec<D>(L.poly[0], 0.0, 0.0, SH);
+      if (HB) {
+#pragma unroll
+        for (int x = 0; x < N; ++x) SB[x] *= kc;
+        write_srec<D>(L.poly[1], 0.0, 0.0, SB);
+      }
+      L.par[0] = lam;
+      L.par[1] = P[1];
+      L.par[2] = P[2];
+      L.par[3] = P[3];
+      L.par[4] = P[0] * maxw_norm<D>(lam) * A * inv;
+      L.par[5] = inv;
+      L.par[6] = ok ? 1.0 : 0.0;
+      // (flag[2]: the other work-groups of this launch go on, on flag[0])
+      if (!ok) atomicOr(&o.flag[2], 1);
+      const double V = o.vol[ic], dr = Wn[0] - Wi[0];
+      o.cellred[ic * 3 + 0] = V * dr * dr;
+      o.cellred[ic * 3 + 1] = V;
+      o.cellred[ic * 3 + 2] = V * Wi[0] * Wi[0];
+#pragma unroll
+      for (int x = 0; x < NM; ++x) o.Wn[ic * NM + x] = Wn[x];
+    }
   }
-  const double dt = dt_cell(g, ic), lam = P[4];
-  const double A = dt / (2.0 * P[5]), inv = 1.0 / (1.0 + A), kc = (g.K + 3.0 - D) / (2.0 * lam);
-  const double U[3] = {P[1], P[2], P[3]};
-  // f^{n+1} = (f~ + A g (1 + P)) / (1 + A): the factor A / (1 + A) goes into
-  // the first axis's table, the 1 into the polynomial's constant
-  const double scale = P[0] * maxw_norm<D>(lam) * A * inv;
+  __syncthreads();
+  if (L.par[6] == 0.0) return;  // the same in every lane
+  const double lam = uniform(L.par[0]), inv = uniform(L.par[5]);
+  const double U[3] = {uniform(L.par[1]), uniform(L.par[2]), uniform(L.par[3])};
   for (int t = threadIdx.x; t < D * NAX; t += blockDim.x) {
     const int d = t / NAX, n = t % NAX;
     if (n < na) {
       const double a = axis[n], Ud = d == 0 ? U[0] : d == 1 ? U[1] : U[2];
-      const double v = (d == 0 ? scale : 1.0) * exp(-lam * (a - Ud) * (a - Ud));
+      const double v = (d == 0 ? L.par[4] : 1.0) * exp(-lam * (a - Ud) * (a - Ud));
       L.tab[d][n][0] = v;
       L.tab[d][na - 1 - n][1] = v;
       if (d == 0) L.ax[n][0] = a;
     }
   }
-  if (threadIdx.x == 0) {
-    const double V = o.vol[ic], dr = Wn[0] - Wi[0];
-    o.cellred[ic * 3 + 0] = V * dr * dr;
-    o.cellred[ic * 3 + 1] = V;
-    o.cellred[ic * 3 + 2] = V * Wi[0] * Wi[0];
+  double sh[NP], sb[NP];
 #pragma unroll
-    for (int x = 0; x < NM; ++x) o.Wn[ic * NM + x] = Wn[x];
-    const double qc[3] = {o.q[ic * 3], o.q[ic * 3 + 1], o.q[ic * 3 + 2]};
-    double SH[N], SB[N];
-    shakhov_polys<D>(P, g, qc, SH, SB);
-#pragma unroll
-    for (int x = 0; x < N; ++x) {
-      L.poly[x] = SH[x] + (x == 0 ? 1.0 : 0.0);
-      if (HB) L.poly[20 + x] = kc * (SB[x] + (x == 0 ? 1.0 : 0.0));
-    }
+  for (int x = 0; x < NP; ++x) {
+    sh[x] = uniform(L.poly[0][SR_P + x]);
+    sb[x] = HB ? uniform(L.poly[1][SR_P + x]) : 0.0;
   }
   __syncthreads();
-  double sh[N], sb[N];
-#pragma unroll
-  for (int x = 0; x < N; ++x) {
-    sh[x] = uniform(L.poly[x]);
-    sb[x] = HB ? uniform(L.poly[20 + x]) : 0.0;
-  }
   double acc[3] = {0.0, 0.0, 0.0};
   grow_t *hr = srow(ht + ic * nvp), *br = HB ? srow(bt + ic * nvp) : nullptr;
   grow_t *wt = srow(w), *ix = srow(vidx);
@@ -809,7 +850,8 @@ __device__ __forceinline__ void finish_cell(const GasP& g, const int32_t* __rest
     for (int d = 0; d < 3; ++d) o.qn[ic * 3 + d] = qc[d] = d < D ? 0.5 * acc[d] : 0.0;
 #pragma unroll
     for (int x = 0; x < NPRIM; ++x) o.prim[ic * NPRIM + x] = P[x];
-    cell_record<D>(P, g, dt, qc, &o.cs[ic * CSREC], o.cs32 ? &o.cs32[ic * CSREC] : nullptr);
+    constexpr int nr = HB ? 2 : 1;
+    cell_record<D>(P, g, dt, qc, nr, (T*)o.cs + ic * nr * SREC);
   }
 }
 
@@ -838,9 +880,9 @@ __global__ __launch_bounds__(CELLT, (sizeof(T) == 4 ? 6 : 4)) void k_step_cell(
   const int64_t xcd = blockIdx.x % 8, local = blockIdx.x / 8;
   const int64_t ic = ((local / sc.tile) * 8 + xcd) * sc.tile + local % sc.tile;
   if (ic >= nc || *o.flag) return;
-  in.norm = o.cs[ic * CSREC + CS_NORM];
   double mw[D + 2];
   sweep_item<D, T, T, false, LIM, HB>(in, h, b, ht, bt, ic, 0u, in.half, L.s, stage, mw);
+  block_total<D + 2>(mw, L.red);
   finish_cell<D, T, HB>(g, in.vidx, in.w, o, ht, bt, ic, in.nvp, in.half, in.na, in.axis, stage, in.keep,
                         mw, L.c, L.red);
 }
@@ -850,8 +892,8 @@ __global__ __launch_bounds__(CELLT, (sizeof(T) == 4 ? 6 : 4)) void k_step_cell(
 // runs in kernels of its own.
 template <int D, typename T, bool LIM, bool HB>
 __global__ __launch_bounds__(SWT, (sizeof(T) == 4 ? 6 : 4)) void k_sweep(
-    SweepIn<T> in, SweepSched sc, int64_t nc, const double* __restrict__ cs64, const T* __restrict__ h,
-    const T* __restrict__ b, T* __restrict__ ht, T* __restrict__ bt, double* __restrict__ dWp,
+    SweepIn<T> in, SweepSched sc, int64_t nc, const T* __restrict__ h, const T* __restrict__ b,
+    T* __restrict__ ht, T* __restrict__ bt, double* __restrict__ dWp,
     const int32_t* __restrict__ flag) {
   __shared__ SweepLds<D, T> L;
   // Blocks are dealt round-robin to the 8 XCDs; XCD x takes tiles x, x+8, ...
@@ -865,7 +907,6 @@ __global__ __launch_bounds__(SWT, (sizeof(T) == 4 ? 6 : 4)) void k_sweep(
   const int64_t chunk = rem / sc.tile;
   const int64_t ic = tile * sc.tile + rem % sc.tile;
   if (ic >= nc || *flag) return;
-  in.norm = cs64[ic * CSREC + CS_NORM];
   double mw[D + 2];
   sweep_item<D, T, T, false, LIM, HB>(in, h, b, ht, bt, ic, (unsigned)(chunk * sc.chunk_pairs),
                                       (unsigned)min((int64_t)in.half, (chunk + 1) * sc.chunk_pairs), L.s,
@@ -911,7 +952,6 @@ __global__ __launch_bounds__(SWT, (D == 3 ? 4 : 3)) void k_step_b(BatchDev bd) {
     o.qn = cases[c].B.qn;
     o.prim = cases[c].B.prim;
     o.cs = cases[c].B.cs;
-    o.cs32 = cases[c].B.cs32;
     o.cellred = cases[c].B.cellred;
     o.flag = cases[c].B.flag;
     SweepIn<T> in;
@@ -919,7 +959,9 @@ __global__ __launch_bounds__(SWT, (D == 3 ? 4 : 3)) void k_step_b(BatchDev bd) {
     in.crec_l = nullptr;
     in.vidx = cases[c].fm.vidx;
     in.w = cases[c].v.w;
-    in.frec64 = cases[c].B.frec;
+    in.frec = cases[c].B.frec;
+    in.cs = (const T*)cases[c].B.cs;
+    in.srec = (const T*)cases[c].B.srec;
     in.prim = o.prim;
     in.dt = g.dt;
     in.nvp = cases[c].v.nvp;
@@ -929,168 +971,39 @@ __global__ __launch_bounds__(SWT, (D == 3 ? 4 : 3)) void k_step_b(BatchDev bd) {
     in.axis = cases[c].fm.axis;
     if constexpr (sizeof(T) == 4) {
       in.crec_d = cases[c].fm.crec_d32;
-      in.cs = cases[c].B.cs32;
-      in.frec = cases[c].B.frec32;
     } else {
       in.crec_d = cases[c].fm.crec_d;
-      in.cs = cases[c].B.cs;
-      in.frec = cases[c].B.frec;
     }
     const T* h = (const T*)cases[c].B.h;
     const T* b = (const T*)cases[c].B.b;
     T* ht = (T*)cases[c].B.ht;
     T* bt = (T*)cases[c].B.bt;
     if (*o.flag) continue;
-    in.norm = o.cs[ic * CSREC + CS_NORM];
     __syncthreads();  // the previous item's readers of LDS are done
     double mw[D + 2];
     sweep_item<D, T, T, true, false, D == 2>(in, h, b, ht, bt, ic, 0u, in.half, L.s, nullptr, mw);
+    block_total<D + 2>(mw, L.red);
     finish_cell<D, T, D == 2>(g, in.vidx, in.w, o, ht, bt, ic, in.nvp, in.half, in.na, in.axis, nullptr, 0u,
                               mw, L.c, L.red);
   }
 }
 
-// Conservative update of the blocked form: W^{n+1} = W^n - dW.
-// The partial sums of the velocity blocks are added in block order.
-template <int D>
-__device__ __forceinline__ void apply_dW_at(int64_t i, int64_t nchunk, const double* __restrict__ vol,
-                                            const double* __restrict__ W,
-                                            const double* __restrict__ dWp, double* __restrict__ Wn,
-                                            double* __restrict__ cellred, const int32_t* flag) {
-  if (*flag) return;
+// The rest of the step of the blocked form, one work-group per cell.  The
+// partial sums of the velocity blocks are added in block order.
+template <int D, typename T, bool HB>
+__global__ __launch_bounds__(SWT) void k_finish(SweepIn<T> in, GasP g, int64_t nchunk,
+                                                const double* __restrict__ dWp, T* ht, T* bt, CellOut o) {
+  __shared__ SweepLds<D, T> L;
+  const int64_t ic = blockIdx.x;
+  if (*o.flag) return;
+  double tot[D + 2];
+#pragma unroll
   for (int x = 0; x < D + 2; ++x) {
-    double s = 0.0;
-    for (int64_t c = 0; c < nchunk; ++c) s += dWp[(i * nchunk + c) * 5 + x];
-    Wn[i * (D + 2) + x] = W[i * (D + 2) + x] - s;
+    tot[x] = 0.0;
+    for (int64_t c = 0; c < nchunk; ++c) tot[x] += dWp[(ic * nchunk + c) * 5 + x];
   }
-  const double V = vol[i];
-  const double dr = Wn[i * (D + 2)] - W[i * (D + 2)];
-  cellred[i * 3 + 0] = V * dr * dr;
-  cellred[i * 3 + 1] = V;
-  cellred[i * 3 + 2] = V * W[i * (D + 2)] * W[i * (D + 2)];
-}
-
-template <int D>
-__global__ void k_apply_dW(int64_t nc, int64_t nchunk, const double* __restrict__ vol,
-                           const double* __restrict__ W, const double* __restrict__ dWp,
-                           double* __restrict__ Wn, double* __restrict__ cellred, const int32_t* flag) {
-  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (i < nc) apply_dW_at<D>(i, nchunk, vol, W, dWp, Wn, cellred, flag);
-}
-
-// Second stage of the blocked form (Eq. f_final) fused with the heat flux of
-// the result, in place on the first stage's row.  csn holds
-// dt/(2 tau^{n+1}) and the Shakhov polynomials of W^{n+1} with q^n.
-struct Stage2Lds {
-  double ctab[3][NAX];
-  double ax[NAX];
-  double red[3 * 16];
-};
-
-template <int D, typename T>
-__device__ __forceinline__ void stage2_q_cell(int64_t ic, const FusedMesh& fm, int64_t nvp,
-                                              const double* __restrict__ w,
-                                              const double* __restrict__ primn,
-                                              const double* __restrict__ csn,
-                                              T* h, T* b, double* __restrict__ qn,
-                                              const int32_t* flag, Stage2Lds& L) {
-  if (*flag) return;
-  double(&ctab)[3][NAX] = L.ctab;
-  double(&ax)[NAX] = L.ax;
-  const int na = fm.na;
-  const double* __restrict__ P = primn + ic * NPRIM;
-  const double* __restrict__ cc = csn + ic * CSREC;
-  for (int t = threadIdx.x; t < D * na; t += SWT) {
-    const int d = t / na, n = t % na;
-    const double a = fm.axis[n], U = P[1 + d], lam = P[4];
-    ctab[d][n] = (d == 0 ? cc[CS_NORM] : 1.0) * exp(-lam * (a - U) * (a - U));
-  }
-  for (int t = threadIdx.x; t < na; t += SWT) ax[t] = fm.axis[t];
-  __syncthreads();
-  const double A = cc[CS_CC];
-  const double inv = 1.0 / (1.0 + A);
-  const double kc = cc[CS_KAP];
-  const double U0 = P[1], U1 = P[2], U2 = P[3];
-  T* hi = h + ic * nvp;
-  double acc[3] = {0.0, 0.0, 0.0};
-  const unsigned nv = (unsigned)nvp;  // every slot (the pads' weights are 0)
-  crec_t<double>* csh = (crec_t<double>*)(cc + CS_SH);  // scalar loads of the uniform polynomials
-  crec_t<double>* csb = (crec_t<double>*)(cc + CS_SB);
-  // b: always in 2-D; in 3-D when the gas has internal degrees of freedom
-  const bool hb = b != nullptr;
-  const T* bi = hb ? b + ic * nvp : nullptr;
-  auto body = [&](unsigned k, int pk, double htk, double btk, double wk) {
-    double vv[3] = {0, 0, 0};
-    double c0 = 1.0;
-#pragma unroll
-    for (int d = 0; d < D; ++d) {
-      const int i = node_of(pk, d);
-      vv[d] = ax[i];
-      c0 *= ctab[d][i];
-    }
-    const double v2 = vv[0] * vv[0] + vv[1] * vv[1] + vv[2] * vv[2];
-    double E, O;
-    cubic_eo<D>(csh, vv, v2, E, O);
-    const double hn = (htk + A * c0 * (1.0 + E + O)) * inv;
-    __builtin_nontemporal_store((T)hn, &hi[k]);
-    double bn = 0.0;
-    if (hb) {
-      double Eb, Ob;
-      cubic_eo<D>(csb, vv, v2, Eb, Ob);
-      bn = (btk + A * kc * c0 * (1.0 + Eb + Ob)) * inv;
-      st(b + ic * nvp, k, bn);
-    }
-    // heat flux of h^{n+1} about U^{n+1} (Eq. reduced_heat_flux)
-    const double c[3] = {vv[0] - U0, vv[1] - U1, D == 3 ? vv[2] - U2 : 0.0};
-    double c2 = 0.0;
-#pragma unroll
-    for (int d = 0; d < D; ++d) c2 += c[d] * c[d];
-    const double s = wk * (c2 * hn + bn);
-#pragma unroll
-    for (int d = 0; d < D; ++d) acc[d] += s * c[d];
-  };
-  // four velocities per lane per pass, all their loads issued together, so
-  // each lane keeps several HBM reads in flight
-  constexpr unsigned UN = 4;
-  unsigned k = threadIdx.x;
-  for (; k + (UN - 1) * SWT < nv; k += UN * SWT) {
-    int pk[UN];
-    T hv[UN], bv[UN];
-    double wv[UN];
-#pragma unroll
-    for (unsigned u = 0; u < UN; ++u) {
-      hv[u] = __builtin_nontemporal_load(&hi[k + u * SWT]);
-      bv[u] = hb ? bi[k + u * SWT] : T(0);
-    }
-    // the HBM reads go out first, the small cached arrays next, and no
-    // arithmetic is moved between them
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (unsigned u = 0; u < UN; ++u) {
-      pk[u] = fm.vidx[k + u * SWT];
-      wv[u] = w[k + u * SWT];
-    }
-    __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-    for (unsigned u = 0; u < UN; ++u) body(k + u * SWT, pk[u], (double)hv[u], (double)bv[u], wv[u]);
-  }
-  for (; k < nv; k += SWT) body(k, fm.vidx[k], ld(hi, k), hb ? ld(bi, k) : 0.0, w[k]);
-  block_sum<3>(acc, L.red);
-  if (threadIdx.x == 0)
-    for (int d = 0; d < 3; ++d) qn[ic * 3 + d] = d < D ? 0.5 * acc[d] : 0.0;
-}
-
-template <int D, typename T>
-__global__ __launch_bounds__(SWT) void k_stage2_q(FusedMesh fm, int64_t nvp,
-                                                  const double* __restrict__ w,
-                                                  const double* __restrict__ primn,
-                                                  const double* __restrict__ csn, T* h, T* b,
-                                                  double* __restrict__ qn, const int32_t* flag) {
-  __shared__ Stage2Lds L;
-  const int64_t per = (fm.nc + 7) / 8;
-  const int64_t ic = (int64_t)(blockIdx.x % 8) * per + blockIdx.x / 8;
-  if (ic >= fm.nc) return;
-  stage2_q_cell<D, T>(ic, fm, nvp, w, primn, csn, h, b, qn, flag, L);
+  finish_cell<D, T, HB>(g, in.vidx, in.w, o, ht, bt, ic, in.nvp, in.half, in.na, in.axis, nullptr, 0u, tot,
+                        L.c, L.red);
 }
 
 // Wall density with the wall cell's gradient evaluated in place.
@@ -1139,7 +1052,7 @@ __device__ __forceinline__ void wall_rho_at(int64_t wi, const DevMesh& m, const 
   const T* __restrict__ hl_row = h + L * nvp;
   const T* hs_row[4];
 #pragma unroll
-  for (int s = 0; s < 4; ++s) hs_row[s] = h + (int64_t)ci[2 + s] * nvp;
+  for (int s = 0; s < 4; ++s) hs_row[s] = h + (int64_t)ci[CI_OWN + s] * nvp;
   double acc[2] = {0.0, 0.0};
   // with BF: the wall flux's moments, incident (time-integrated free transport
   // of the wall cell's h, and b in 2-D) and reflected (per unit rho_w dt)
@@ -1204,7 +1117,7 @@ __device__ __forceinline__ void wall_rho_at(int64_t wi, const DevMesh& m, const 
         for (int s = 0; s < 4; ++s) {
           const double dh = hs[u][s] - hl[u];
 #pragma unroll
-          for (int d = 0; d < D; ++d) gr[d] += cd[d * 4 + s] * dh;
+          for (int d = 0; d < D; ++d) gr[d] += cd[CD_G + d * 4 + s] * dh;
         }
         if constexpr (LIM) {
           // the wall cell's gradient limited as the sweep limits it
@@ -1216,7 +1129,7 @@ __device__ __forceinline__ void wall_rho_at(int64_t wi, const DevMesh& m, const 
             lo = fmin(lo, vs);
             hi = fmax(hi, vs);
           }
-          const double ph = venkat_phi<D>(hl[u], lo, hi, gr, cd + CRD_F0 + 4, CRD_FS, cl[0]);
+          const double ph = venkat_phi<D>(hl[u], lo, hi, gr, cd + CD_F0, CD_FS, cl[0]);
 #pragma unroll
           for (int d = 0; d < D; ++d) gr[d] *= ph;
         }
@@ -1245,20 +1158,20 @@ __device__ __forceinline__ void wall_rho_at(int64_t wi, const DevMesh& m, const 
             double gb[3] = {0, 0, 0};
 #pragma unroll
             for (int s = 0; s < 4; ++s) {
-              const double db = ld(b + (int64_t)ci[2 + s] * nvp, kk) - bl;
+              const double db = ld(b + (int64_t)ci[CI_OWN + s] * nvp, kk) - bl;
 #pragma unroll
-              for (int d = 0; d < D; ++d) gb[d] += cd[d * 4 + s] * db;
+              for (int d = 0; d < D; ++d) gb[d] += cd[CD_G + d * 4 + s] * db;
             }
             if constexpr (LIM) {
               crec_t<double>* cl = (crec_t<double>*)(fm.crec_l + L * CRL);
               double lo = bl, hi = bl;
 #pragma unroll
               for (int s = 0; s < 4; ++s) {
-                const double vs = cl[1 + s] * bl + ld(b + (int64_t)ci[2 + s] * nvp, kk);
+                const double vs = cl[1 + s] * bl + ld(b + (int64_t)ci[CI_OWN + s] * nvp, kk);
                 lo = fmin(lo, vs);
                 hi = fmax(hi, vs);
               }
-              const double pb = venkat_phi<D>(bl, lo, hi, gb, cd + CRD_F0 + 4, CRD_FS, cl[0]);
+              const double pb = venkat_phi<D>(bl, lo, hi, gb, cd + CD_F0, CD_FS, cl[0]);
 #pragma unroll
               for (int d = 0; d < D; ++d) gb[d] *= pb;
             }
@@ -1375,13 +1288,13 @@ __device__ __forceinline__ int case_of(const int64_t* __restrict__ off, int n, i
 }
 
 // W^n, q -> prim, cs before the first step (the step itself leaves the next one's)
-template <int D>
+template <int D, typename T>
 __global__ void k_cell_prep_b(BatchDev bd) {
   const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (t >= bd.cell_off[bd.n]) return;
   const int c = case_of(bd.cell_off, bd.n, t);
   const CaseDev& C = bd.cases[c];
-  cell_prep_at<D>(t - bd.cell_off[c], C.g, C.B.W, C.B.q, C.B.prim, C.B.cs, C.B.cs32, C.B.flag);
+  cell_prep_at<D>(t - bd.cell_off[c], C.g, C.B.W, C.B.q, C.B.prim, C.fm.nr, (T*)C.B.cs, C.B.flag);
 }
 
 // one block per far-field / outflow face of the batch
@@ -1441,18 +1354,10 @@ __global__ __launch_bounds__(WALLT) void k_wall_rho_b(BatchDev bd) {
     }                                 \
   } while (0)
 
-hipError_t launch_apply_dW(int D, const DevMesh& m, int64_t nchunk, const double* W,
-                          const double* dWp, double* Wn, double* cellred, const int32_t* flag,
-                          hipStream_t s) {
-  const unsigned grid = (unsigned)((m.nc + 255) / 256);
-  UGKS_DISPATCH_D(D, k_apply_dW<DD><<<grid, 256, 0, s>>>(m.nc, nchunk, m.vol, W, dWp, Wn, cellred, flag));
-  return hipGetLastError();
-}
-
-hipError_t launch_cell_prep(int D, int64_t nc, const GasP& g, const double* W, const double* q,
-                            double* prim, double* cs, float* cs32, int32_t* flag, hipStream_t s) {
+hipError_t launch_cell_prep(int D, int prec, int nr, int64_t nc, const GasP& g, const double* W,
+                            const double* q, double* prim, void* cs, int32_t* flag, hipStream_t s) {
   const unsigned grid = (unsigned)((nc + 127) / 128);
-  UGKS_DISPATCH_D(D, k_cell_prep<DD><<<grid, 128, 0, s>>>(nc, g, W, q, prim, cs, cs32, flag));
+  UGKS_DISPATCH_DT(D, prec, k_cell_prep<DD, TT><<<grid, 128, 0, s>>>(nc, g, W, q, prim, nr, (TT*)cs, flag));
   return hipGetLastError();
 }
 
@@ -1464,7 +1369,9 @@ SweepIn<T> sweep_in(const FusedMesh& fm, const DevVel& v, const GasP& g, const S
   in.crec_i = fm.crec_i;
   in.vidx = fm.vidx;
   in.w = v.w;
-  in.frec64 = B.frec;
+  in.frec = B.frec;
+  in.cs = (const T*)B.cs;
+  in.srec = (const T*)B.srec;
   in.prim = B.prim;
   in.dt = g.dt;
   in.nvp = v.nvp;
@@ -1474,13 +1381,9 @@ SweepIn<T> sweep_in(const FusedMesh& fm, const DevVel& v, const GasP& g, const S
   if constexpr (sizeof(T) == 4) {
     in.crec_d = fm.crec_d32;
     in.crec_l = fm.crec_l32;
-    in.cs = B.cs32;
-    in.frec = B.frec32;
   } else {
     in.crec_d = fm.crec_d;
     in.crec_l = fm.crec_l;
-    in.cs = B.cs;
-    in.frec = B.frec;
   }
   return in;
 }
@@ -1494,7 +1397,6 @@ CellOut cell_out(const DevMesh& m, const StepBuffers& B) {
   o.qn = B.qn;
   o.prim = B.prim;
   o.cs = B.cs;
-  o.cs32 = B.cs32;
   o.cellred = B.cellred;
   o.flag = B.flag;
   return o;
@@ -1505,7 +1407,7 @@ void launch_sweep_as(const FusedMesh& fm, const DevVel& v, const GasP& g, const 
                      const StepBuffers& B, hipStream_t s) {
   const int64_t ntile = (fm.nc + sc.tile - 1) / sc.tile;
   const unsigned grid = (unsigned)(((ntile + 7) / 8) * 8 * sc.nchunk * sc.tile);
-  k_sweep<D, T, LIM, HB><<<grid, SWT, 0, s>>>(sweep_in<T>(fm, v, g, B), sc, fm.nc, B.cs, (const T*)B.h,
+  k_sweep<D, T, LIM, HB><<<grid, SWT, 0, s>>>(sweep_in<T>(fm, v, g, B), sc, fm.nc, (const T*)B.h,
                                               (const T*)B.b, (T*)B.ht, (T*)B.bt, B.dW, B.flag);
 }
 
@@ -1560,12 +1462,18 @@ hipError_t launch_step_cell(int D, int prec, const DevMesh& m, const FusedMesh& 
 }
 #undef UGKS_SWEEP_AS
 
-hipError_t launch_stage2_q(int D, int prec, const FusedMesh& fm, const DevVel& v,
-                           const double* primn, const double* csn, void* h, void* b, double* qn,
-                           const int32_t* flag, hipStream_t s) {
-  const unsigned grid = (unsigned)(((fm.nc + 7) / 8) * 8);
-  UGKS_DISPATCH_DT(D, prec, k_stage2_q<DD, TT><<<grid, SWT, 0, s>>>(
-      fm, v.nvp, v.w, primn, csn, (TT*)h, (TT*)b, qn, flag));
+hipError_t launch_finish(int D, int prec, const DevMesh& m, const FusedMesh& fm, const DevVel& v,
+                         const GasP& g, const SweepSched& sc, const StepBuffers& B, hipStream_t s) {
+  const unsigned grid = (unsigned)fm.nc;
+  if (D == 2)
+    UGKS_DISPATCH_T(prec, (k_finish<2, TT, true><<<grid, SWT, 0, s>>>(
+        sweep_in<TT>(fm, v, g, B), g, sc.nchunk, B.dW, (TT*)B.ht, (TT*)B.bt, cell_out(m, B))));
+  else if (B.b)
+    UGKS_DISPATCH_T(prec, (k_finish<3, TT, true><<<grid, SWT, 0, s>>>(
+        sweep_in<TT>(fm, v, g, B), g, sc.nchunk, B.dW, (TT*)B.ht, (TT*)B.bt, cell_out(m, B))));
+  else
+    UGKS_DISPATCH_T(prec, (k_finish<3, TT, false><<<grid, SWT, 0, s>>>(
+        sweep_in<TT>(fm, v, g, B), g, sc.nchunk, B.dW, (TT*)B.ht, (TT*)B.bt, cell_out(m, B))));
   return hipGetLastError();
 }
 
@@ -1612,10 +1520,10 @@ hipError_t launch_bflux(int D, const DevMesh& m, const double* frec, const doubl
 }
 
 // ---- batched launchers ------------------------------------------------------
-hipError_t launch_cell_prep_b(int D, const BatchDev& bd, int64_t ncell, hipStream_t s) {
+hipError_t launch_cell_prep_b(int D, int prec, const BatchDev& bd, int64_t ncell, hipStream_t s) {
   if (ncell == 0) return hipSuccess;
   const unsigned grid = (unsigned)((ncell + 127) / 128);
-  UGKS_DISPATCH_D(D, k_cell_prep_b<DD><<<grid, 128, 0, s>>>(bd));
+  UGKS_DISPATCH_DT(D, prec, k_cell_prep_b<DD, TT><<<grid, 128, 0, s>>>(bd));
   return hipGetLastError();
 }
 
