@@ -211,7 +211,7 @@ typedef struct {
   double dt;
   int64_t steps_done;
   int64_t device_bytes;      /* device memory held by the context */
-  int32_t fused;             /* 1: the fused sweep runs; 0: the staged sweep */
+  int32_t fused;             /* 1: the fused sweep runs; 0: the staged sweep, or cells of 5 to 8 faces */
   int32_t tile_cells;        /* fused sweep: cells per tile */
 } ugks_info_t;
 

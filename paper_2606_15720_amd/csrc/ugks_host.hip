@@ -359,7 +359,12 @@ void build(ugks_ctx* c, const ugks_mesh* mesh, const ugks_velocity* vel, const u
     bool mesh_ok = !(c->flags & 2);
     for (int64_t f = 0; mesh_ok && f < nf; ++f)
       mesh_ok = mesh->face_bc[f] >= UGKS_BC_INTERIOR && mesh->face_bc[f] <= UGKS_BC_OUTFLOW;
-    for (int64_t i = 0; mesh_ok && i < nc; ++i) mesh_ok = nfc[i] <= 4;
+    const bool wide = *std::max_element(nfc.begin(), nfc.end()) > 4;
+    // Cells of more faces are taken whole, one work-group each, unless they are
+    // few and have many velocities (hexahedra, ms per step whole and staged: 27
+    // cells x 16^3 0.070 and 0.097; 64 x 24^3 0.158 and 0.223, by then bound by
+    // the number of work-groups).
+    mesh_ok = mesh_ok && (!wide || nc >= kWholeCells || nv <= 4096);
     ok = ok && mesh_ok;
     if (ok) {
       ax = a0;
@@ -382,12 +387,13 @@ void build(ugks_ctx* c, const ugks_mesh* mesh, const ugks_velocity* vel, const u
         ok = true;
       }
     }
-    c->fused = ok;
+    c->fused = ok && !wide;
+    c->wide = ok && wide;
   }
   // ---- velocity slots -------------------------------------------------------
   std::vector<int32_t> vidx;
-  c->vel_perm = c->fused ? pair_slots(D, vel, ax, vidx) : std::vector<int64_t>();
-  if (!c->fused) {
+  c->vel_perm = c->slots() ? pair_slots(D, vel, ax, vidx) : std::vector<int64_t>();
+  if (!c->slots()) {
     // the caller's order, rows padded to whole waves
     c->vel_perm.assign((nv + WAVE - 1) / WAVE * WAVE, -1);
     for (int64_t k = 0; k < nv; ++k) c->vel_perm[k] = k;
@@ -399,7 +405,7 @@ void build(ugks_ctx* c, const ugks_mesh* mesh, const ugks_velocity* vel, const u
     if (kk >= 0) w[k] = vel->w[kk];
     for (int d = 0; d < D; ++d) {
       if (kk >= 0) u[d * nvp + k] = vel->u[kk * D + d];
-      else if (c->fused) u[d * nvp + k] = ax[((uint32_t)vidx[k] >> (10 * d + 4)) & 63];
+      else if (c->slots()) u[d * nvp + k] = ax[((uint32_t)vidx[k] >> (10 * d + 4)) & 63];
       u2[k] += u[d * nvp + k] * u[d * nvp + k];
     }
   }
@@ -498,6 +504,59 @@ void build(ugks_ctx* c, const ugks_mesh* mesh, const ugks_velocity* vel, const u
       c->gas.dtc = upload(c, dtc);
     }
   }
+  // Rows of h and b beyond the cells': row nc is all zero (a wall face's
+  // "neighbour"), then one ghost row per far-field or outflow face.
+  std::vector<int32_t> ghost_row(nf, -1), ffaces;
+  if (c->slots()) {
+    for (int64_t f = 0; f < nf; ++f)
+      if (fbc[f] == UGKS_BC_FARFIELD || fbc[f] == UGKS_BC_OUTFLOW) {
+        ghost_row[f] = (int32_t)(nc + 1 + (int64_t)ffaces.size());
+        ffaces.push_back((int32_t)f);
+      }
+    c->fmesh.nff = (int64_t)ffaces.size();
+    c->fmesh.ffaces = upload(c, ffaces);
+    c->fmesh.half = nvp / 2;
+    c->fmesh.nr = c->nr;
+    // the sweep reads one iteration ahead
+    vidx.resize(vidx.size() + 512, 0);
+    c->fmesh.nc = nc;
+    c->fmesh.nv = nv;
+    c->fmesh.axis = upload(c, ax);
+    c->fmesh.vidx = upload(c, vidx);
+  }
+  if (c->wide) {
+    std::vector<int32_t> ci(nc * CRI, 0), frow(nf);
+    std::vector<double> cdr(nc * CRD, 0.0);
+    for (int64_t f = 0; f < nf; ++f) frow[f] = fR[f] >= 0 ? fR[f] : ghost_row[f] >= 0 ? ghost_row[f] : (int32_t)nc;
+    for (int64_t i = 0; i < nc; ++i) {
+      int32_t* I = &ci[i * CRI];
+      I[WI_NF] = nfc[i];
+      for (int p = 0; p < MAXF; ++p) {
+        // (slots past the cell's faces: face 0, for the tables only)
+        const int pp = p < nfc[i] ? p : 0;
+        double* fd = &cdr[i * CRD + WD_FS * p];
+        const int f = cface[i * MAXF + pp];
+        const int j = cnbr[i * MAXF + pp];
+        const double sg = csign[i * MAXF + pp];
+        I[WI_ROW + p] = j >= 0 ? j : ghost_row[f] >= 0 ? ghost_row[f] : (int32_t)nc;
+        I[WI_FACE + p] = f;
+        I[WI_KIND + p] = fbc[f];
+        for (int d = 0; d < 3; ++d) {
+          fd[d] = sg * fnorm[f * 3 + d];
+          fd[3 + d] = sg > 0.0 ? fdxL[f * 3 + d] : fdxR[f * 3 + d];
+          fd[6 + d] = j >= 0 ? (sg > 0.0 ? fdxR[f * 3 + d] : fdxL[f * 3 + d]) : 0.0;
+        }
+        fd[9] = fbc[f] == UGKS_BC_WALL ? 0.0 : 1.0;
+        fd[10] = p < nfc[i] ? farea[f] / vol[i] : 0.0;
+        if (lts) fd[10] *= dtc[i] / c->gas.dt;
+      }
+    }
+    c->fmesh.crec_i = upload(c, ci);
+    c->fmesh.crec_d = upload(c, cdr);
+    c->fmesh.frow = upload(c, frow);
+    c->sched.lanes = cell_lanes(nc, c->fmesh.half);
+    c->sched.tile = 32;
+  }
   if (c->fused) {
     // Static records of the fused sweep: the cell's faces, its least-squares
     // stencil and, per face, the neighbour's stencil, all wave-uniform.
@@ -516,12 +575,6 @@ void build(ugks_ctx* c, const ugks_mesh* mesh, const ugks_velocity* vel, const u
     //     stencil of the cell that owns the face, as its mirror-ghost row;
     //   * a missing face (cells with 3 faces) repeats face 0 with S/V = 0.
     const int32_t zero_row = (int32_t)nc;
-    std::vector<int32_t> ghost_row(nf, -1), ffaces;
-    for (int64_t f = 0; f < nf; ++f)
-      if (fbc[f] == UGKS_BC_FARFIELD || fbc[f] == UGKS_BC_OUTFLOW) {
-        ghost_row[f] = (int32_t)(nc + 1 + (int64_t)ffaces.size());
-        ffaces.push_back((int32_t)f);
-      }
     std::vector<int32_t> ci(nc * CRI, 0);
     std::vector<double> cdr(nc * CRD, 0.0);
     // Stencil slot p of a cell is its face p: the neighbour's row with the
@@ -594,14 +647,6 @@ void build(ugks_ctx* c, const ugks_mesh* mesh, const ugks_velocity* vel, const u
         fd[18] = (j >= 0 || gr >= 0) ? 1.0 : 0.0;
       }
     }
-    c->fmesh.half = nvp / 2;
-    c->fmesh.nr = c->nr;
-    // the sweep reads one iteration ahead
-    vidx.resize(vidx.size() + 512, 0);
-    c->fmesh.nc = nc;
-    c->fmesh.nv = nv;
-    c->fmesh.axis = upload(c, ax);
-    c->fmesh.vidx = upload(c, vidx);
     c->fmesh.crec_i = upload(c, ci);
     c->fmesh.crec_d = upload(c, cdr);
     if (prec == UGKS_FP32) c->fmesh.crec_d32 = upload(c, std::vector<float>(cdr.begin(), cdr.end()));
@@ -641,8 +686,6 @@ void build(ugks_ctx* c, const ugks_mesh* mesh, const ugks_velocity* vel, const u
       c->fmesh.crec_l = upload(c, lr);
       if (prec == UGKS_FP32) c->fmesh.crec_l32 = upload(c, std::vector<float>(lr.begin(), lr.end()));
     }
-    c->fmesh.nff = (int64_t)ffaces.size();
-    c->fmesh.ffaces = upload(c, ffaces);
   }
   c->cell_perm = perm;
   c->face_perm.resize(nf);
@@ -677,28 +720,34 @@ void build(ugks_ctx* c, const ugks_mesh* mesh, const ugks_velocity* vel, const u
     if (!c->sched.whole) B.dW = dalloc<double>(c, nc * c->sched.nchunk * 5);
     B.srec = dalloc<char>(c, (size_t)nf * c->nr * SREC * esz);
     B.cs = dalloc<char>(c, (size_t)nc * c->nr * SREC * esz);
+  } else if (c->wide) {
+    B.srec = dalloc<double>(c, (size_t)nf * c->nr * SREC);
+    B.cs = dalloc<double>(c, (size_t)nc * c->nr * SREC);
   } else {
     B.dW = dalloc<double>(c, nc * 5);
   }
   // row nc of h and b stays zero: the fused sweep's wall faces read it;
   // rows nc+1 ... are the fused sweep's far-field ghost rows.  On the fused
   // path h and ht (b and bt) trade places every step, so both have them.
-  const int64_t rows = nc + 1 + (c->fused ? c->fmesh.nff : 0), trows = c->fused ? rows : nc;
+  const int64_t rows = nc + 1 + (c->slots() ? c->fmesh.nff : 0), trows = c->slots() ? rows : nc;
   B.h = dalloc<char>(c, (size_t)rows * nvp * esz);
   B.ht = dalloc<char>(c, (size_t)trows * nvp * esz);
   B.b = c->nr == 2 ? (void*)dalloc<char>(c, (size_t)rows * nvp * esz) : nullptr;
   B.bt = c->nr == 2 ? (void*)dalloc<char>(c, (size_t)trows * nvp * esz) : nullptr;
   HIP_TRY(hipMemset(B.h, 0, (size_t)rows * nvp * esz));
   if (B.b) HIP_TRY(hipMemset(B.b, 0, (size_t)rows * nvp * esz));
-  if (c->fused) {
+  if (c->slots()) {
     // the zero row, and the pad slots of every row, which no step writes
     HIP_TRY(hipMemset(B.ht, 0, (size_t)rows * nvp * esz));
     if (B.bt) HIP_TRY(hipMemset(B.bt, 0, (size_t)rows * nvp * esz));
   }
   if (!c->fused) {
-    // the staged sweep keeps every gradient and microscopic flux in HBM
+    // the staged sweep keeps every gradient and microscopic flux in HBM, the
+    // wide cells' step the gradients
     B.gradh = dalloc<double>(c, (size_t)nc * 3 * nvp);
     B.gradb = c->nr == 2 ? dalloc<double>(c, (size_t)nc * 3 * nvp) : nullptr;
+  }
+  if (!c->slots()) {
     B.fluxh = dalloc<double>(c, (size_t)nf * nvp);
     B.fluxb = c->nr == 2 ? dalloc<double>(c, (size_t)nf * nvp) : nullptr;
   }
@@ -783,9 +832,10 @@ void swap_buffers(StepBuffers& B) {
   std::swap(B.b, B.bt);
 }
 
-// One time step of the fused path, enqueued.
-void enqueue_step_fused(ugks_ctx* c, bool residual) {
-  const int D = c->D, P = c->prec;
+// One time step of the fused path, enqueued.  (wide cells: from stored
+// gradients, and the face fluxes only where they are asked for)
+void enqueue_step_fused(ugks_ctx* c, bool residual, bool face_flux) {
+  const int D = c->D, P = c->prec, R = c->wide ? UGKS_FP64 : P;  // R: the records' type
   const DevMesh& m = c->mesh;
   const DevVel& v = c->vel;
   const GasP& g = c->gas;
@@ -800,17 +850,27 @@ void enqueue_step_fused(ugks_ctx* c, bool residual) {
   // 1 primitives of W^n and the cell equilibrium data of the first stage:
   // left by the previous step once valid
   if (!c->cs_valid)
-    TIMED(KK_PRIMS, launch_cell_prep(D, P, c->nr, c->nc, g, B.W, B.q, B.prim, B.cs, B.flag, s));
+    TIMED(KK_PRIMS, launch_cell_prep(D, R, c->nr, c->nc, g, B.W, B.q, B.prim, B.cs, B.flag, s));
   c->cs_valid = true;
   // 4 macroscopic reconstruction; 6.1-6.6 interface equilibrium
   TIMED(KK_GRADW, launch_gradW(D, m, c->bcs, g, B.W, B.gW, B.flag, 1, s));
-  TIMED(KK_FACE_EQ, launch_face_eq(D, m, c->bcs, g, B.W, B.gW, B.q, B.frec, P, c->nr, B.srec, B.flag, s));
+  TIMED(KK_FACE_EQ, launch_face_eq(D, m, c->bcs, g, B.W, B.gW, B.q, B.frec, R, c->nr, B.srec, B.flag, s));
   // 7 far-field ghost rows (the wall cells' stencils may read them), then
   // the wall densities
   if (c->fmesh.nff)
     TIMED(KK_WALL, launch_ghost_rows(D, P, c->fmesh, v, B.frec, B.h, B.b, B.flag, s));
   // (with boundary-flux tracking the wall pass also keeps each wall face's flux)
   const bool track = (c->flags & 64) != 0;
+  if (c->wide) {
+    TIMED(KK_GRAD_MICRO, launch_grad_micro(D, P, m, v, B.frec, B.h, B.b, B.gradh, B.gradb, B.flag, s));
+    TIMED(KK_WALL, launch_wall_rho(D, P, m, v, g, B.h, B.gradh, B.frec, B.flag, s));
+    if (face_flux || track) TIMED(KK_FLUX, launch_face_flux(D, P, m, c->fmesh, v, g, B, s));
+    if (track) TIMED(KK_RESID, launch_bflux(D, m, B.frec, B.F, 1, B.bflux, B.flag, s));
+    TIMED(KK_SWEEP, launch_step_wide(D, P, m, c->fmesh, v, g, c->sched, B, s));
+    if (residual) TIMED(KK_RESID, launch_residual(m, B.cellred, B.resid, B.flag, s));
+    swap_buffers(B);
+    return;
+  }
   TIMED(KK_WALL, launch_wall_rho_inline(D, P, m, v, c->fmesh, g, B.h, B.frec, B.flag, s, track ? 1 : 0,
                                         track ? (const void*)B.b : nullptr));
   if (track) TIMED(KK_RESID, launch_bflux(D, m, B.frec, B.F, 0, B.bflux, B.flag, s));
@@ -829,9 +889,9 @@ void enqueue_step_fused(ugks_ctx* c, bool residual) {
 }
 
 // One time step, enqueued (the one-step algorithm).
-void enqueue_step(ugks_ctx* c, bool residual) {
-  if (c->fused) {
-    enqueue_step_fused(c, residual);
+void enqueue_step(ugks_ctx* c, bool residual, bool face_flux) {
+  if (c->slots()) {
+    enqueue_step_fused(c, residual, face_flux);
     return;
   }
   const int D = c->D, P = c->prec;
@@ -1351,7 +1411,7 @@ void capture_step_graphs(ugks_ctx* c) {
   for (int par = 0; par < 2; ++par) {
     HIP_TRY(hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
     try {
-      enqueue_step(c, !(c->flags & 1));
+      enqueue_step(c, !(c->flags & 1), true);
     } catch (...) {
       hipGraph_t g = nullptr;
       (void)hipStreamEndCapture(c->stream, &g);
@@ -1367,16 +1427,16 @@ void capture_step_graphs(ugks_ctx* c) {
 // applies (not profiling, the heat flux of the current f known, a stream
 // that can be captured), else the kernels one by one.  Both run the same
 // kernels with the same arguments.
-void run_step(ugks_ctx* c, bool residual) {
+void run_step(ugks_ctx* c, bool residual, bool face_flux) {
   const bool graphs = (c->flags & 32) && !c->profiling && c->stream != nullptr;
-  if (!graphs || !c->q_valid || (c->fused && !c->cs_valid)) {
-    enqueue_step(c, residual);
+  if (!graphs || !c->q_valid || (c->slots() && !c->cs_valid)) {
+    enqueue_step(c, residual, face_flux);
     return;
   }
   if (!c->graph_exec[0]) capture_step_graphs(c);
   const int par = c->buf.q == c->graph_q0 ? 0 : 1;
   HIP_TRY(hipGraphLaunch(c->graph_exec[par], c->stream));
-  if (c->fused) swap_buffers(c->buf);  // as the fused step does on the host
+  if (c->slots()) swap_buffers(c->buf);  // as the fused step does on the host
 }
 
 }  // namespace
@@ -1389,7 +1449,7 @@ int ugks_step(ugks_ctx* c, int32_t n_steps, double* residual_out) {
     // the residual is the last step's, in units of the first non-zero change:
     // the steps before the last need it only until that unit is known
     for (int32_t s = 0; s < n_steps; ++s)
-      run_step(c, !(c->flags & 1) && (s + 1 == n_steps || !c->resid_set));
+      run_step(c, !(c->flags & 1) && (s + 1 == n_steps || !c->resid_set), s + 1 == n_steps);
     int32_t flag[4] = {0, 0, 0, 0};
     HIP_TRY(hipMemcpyAsync(flag, c->buf.flag, sizeof flag, hipMemcpyDeviceToHost, c->stream));
     double res[4] = {0.0, 0.0, 0.0, 0.0};
@@ -1404,7 +1464,7 @@ int ugks_step(ugks_ctx* c, int32_t n_steps, double* residual_out) {
       // every step enqueued).  The flag stays set: further steps would repeat
       // the failure.
       const int32_t done = std::max(0, begun - 1);
-      if (c->fused && ((n_steps - done) & 1)) swap_buffers(c->buf);
+      if (c->slots() && ((n_steps - done) & 1)) swap_buffers(c->buf);
       return set_err(c, UGKS_ENUMERIC, "non-positive density or temperature (flag " +
                                            std::to_string(flag[0] | flag[2]) + ")");
     }

@@ -84,6 +84,15 @@ constexpr int CRD = 112, CD_N = 0, CD_G = 16, CD_F0 = 32, CD_FS = 20;
 // the neighbour's wall slots, [5 + 3 r + d] the offset of the neighbour's
 // face in its stencil slot r from its centroid (slot order of the record).
 constexpr int CRL = 88, CRL_F0 = 8, CRL_FS = 20;
+// Records of cells with more than four faces (the wide form of the fused
+// step, up to MAXF faces, FP64), in the same arrays with strides CRI and CRD:
+//   [WI_ROW + p] the row across face p (a neighbour, its ghost row, or the zero
+//   row at a wall); [WI_FACE + p]; [WI_KIND + p]; [WI_NF] the cell's faces;
+//   face p at WD_FS p: [0..2] outward unit normal, [3..5] x_f - x_cell,
+//   [6..8] x_f - x_neighbour, [9] as [18] above, [10] S/V.
+constexpr int WI_ROW = 0, WI_FACE = 8, WI_KIND = 16, WI_NF = 24;
+constexpr int WD_FS = 12;
+static_assert(WD_FS * MAXF <= CRD && WI_NF < CRI, "records of wide cells");
 // Per-step records of the fused path in its compute type, SREC values per
 // face or cell and distribution (h, then b where it is carried):
 //   face: [0..1] Gamma_1, Gamma_2; cell: [0] dt/(2 tau), [1] K_xi/(2 lambda);
@@ -110,6 +119,7 @@ struct FusedMesh {
   const float* crec_l32 = nullptr; // its FP32 copy (FP32 compute form)
   const int32_t* ffaces;    // [nff] far-field / outflow faces; face m owns ghost row nc+1+m
   int64_t nff;
+  const int32_t* frow = nullptr;   // wide cells: [nf] the row right of a face (cell, ghost row or zero row)
 };
 
 // Schedule of the fused sweep: work item = a cell with all of its velocities
@@ -268,6 +278,11 @@ hipError_t launch_sweep(int D, int prec, const FusedMesh& fm, const DevVel& v, c
                         const SweepSched& sc, const StepBuffers& B, hipStream_t s);
 hipError_t launch_step_cell(int D, int prec, const DevMesh& m, const FusedMesh& fm, const DevVel& v,
                             const GasP& g, const SweepSched& sc, const StepBuffers& B, hipStream_t s);
+// wide cells (more than four faces), from the stored gradients
+hipError_t launch_step_wide(int D, int prec, const DevMesh& m, const FusedMesh& fm, const DevVel& v,
+                            const GasP& g, const SweepSched& sc, const StepBuffers& B, hipStream_t s);
+hipError_t launch_face_flux(int D, int prec, const DevMesh& m, const FusedMesh& fm, const DevVel& v,
+                            const GasP& g, const StepBuffers& B, hipStream_t s);
 hipError_t launch_finish(int D, int prec, const DevMesh& m, const FusedMesh& fm, const DevVel& v,
                          const GasP& g, const SweepSched& sc, const StepBuffers& B, hipStream_t s);
 hipError_t launch_wall_rho_inline(int D, int prec, const DevMesh& m, const DevVel& v,
@@ -296,7 +311,9 @@ hipError_t launch_residual_b(const BatchDev& bd, hipStream_t s);
 
 struct ugks_ctx {
   int D = 0, kxi = 0, nr = 0, prec = 64, Bv = 64, flags = 0;
-  bool fused = false;       // tensor-product symmetric velocity set, walls / interior only
+  bool fused = false;       // tensor-product symmetric velocity set, cells of up to four faces
+  bool wide = false;        // the same with cells of more faces: gradients stored, one pass per cell
+  bool slots() const { return fused || wide; }  // mirror-pair velocity slots, two sets of state buffers
   bool q_valid = false;     // buf.q holds the heat flux of the current h
   bool cs_valid = false;    // buf.prim, buf.cs hold the records of the current W and q
   bool resid_set = false;   // the residual's unit (its first non-zero change) is known

@@ -327,66 +327,81 @@ __global__ void k_face_eq(DevMesh m, const DevBC* __restrict__ bcs, GasP g,
 }
 
 // Microscopic gradients of h (and b) for every (cell, velocity) (step 5).
+// Bound by the three gradients it writes and by the neighbour rows it reads.
+// A lane takes two adjacent velocities (16-byte accesses) and issues all of its
+// neighbour rows before any arithmetic; the work-groups of one XCD take
+// GRAD_TILE cells through one block of velocities, then the next, so that the
+// rows the cells share are read from HBM once.  The gradients bypass the caches,
+// which are left to the rows.  4,096 hexahedra x 20^3, FP64: 0.50 ms with one
+// velocity per lane in cell order, 0.35 (3.0 TB/s) so; plain stores 0.355 and the
+// wall pass that follows 0.084 instead of 0.065.
+constexpr int64_t GRAD_TILE = 32;
+
 template <int D, typename T>
 __global__ __launch_bounds__(TPB) void k_grad_micro(DevMesh m, DevVel v,
                                                     const double* __restrict__ frec,
                                                     const T* __restrict__ h, const T* __restrict__ b,
                                                     double* __restrict__ gh, double* __restrict__ gb,
                                                     const int32_t* flag) {
-  const int64_t nch = (v.nvp + TPB - 1) / TPB;
-  const int64_t i = blockIdx.x / nch;
-  const int64_t k = (blockIdx.x % nch) * TPB + threadIdx.x;
-  if (k >= v.nvp || *flag) return;
-  const int64_t nvp = v.nvp;
-  const double hi = ld(h, i * nvp + k);
-  const bool hb = v.has_b;
-  const double bi = hb ? ld(b, i * nvp + k) : 0.0;
-  double ah[3] = {0, 0, 0}, ab[3] = {0, 0, 0};
-  double hmin = hi, hmax = hi, bmin = bi, bmax = bi;
+  typedef T pair_t __attribute__((ext_vector_type(2)));
+  typedef double dpair_t __attribute__((ext_vector_type(2)));
+  const int64_t nvp = v.nvp, nch = (nvp + 2 * TPB - 1) / (2 * TPB);
+  const int64_t xcd = blockIdx.x % 8, local = blockIdx.x / 8, per_tile = nch * GRAD_TILE;
+  const int64_t rem = local % per_tile;
+  const int64_t i = ((local / per_tile) * 8 + xcd) * GRAD_TILE + rem % GRAD_TILE;
+  const int64_t k = 2 * ((rem / GRAD_TILE) * TPB + threadIdx.x);  // nvp is even
+  if (i >= m.nc || k >= nvp || *flag) return;
   const int nfc = m.nfc[i];
-  for (int p = 0; p < nfc; ++p) {
-    const int j = m.cnbr[i * MAXF + p];
-    double hn, bn;
-    if (j >= 0) {
-      hn = ld(h, (int64_t)j * nvp + k);
-      bn = hb ? ld(b, (int64_t)j * nvp + k) : 0.0;
-    } else {
-      const int f = m.cface[i * MAXF + p];
-      if (m.fbc[f] == UGKS_BC_WALL) {
-        hn = hi;
-        bn = bi;
-      } else {
-        const double* R = &frec[(int64_t)f * FREC];
-        double c2 = 0.0;
-        for (int d = 0; d < D; ++d) {
-          double c = v.u[d * nvp + k] - R[FR_GU + d];
-          c2 += c * c;
-        }
-        hn = R[FR_GC] * exp(-R[FR_GLAM] * c2);
-        bn = v.kxi / (2.0 * R[FR_GLAM]) * hn;
+  for (int r = 0; r < (v.has_b ? 2 : 1); ++r) {
+    const T* __restrict__ f = r ? b : h;
+    const pair_t fi = *(const pair_t*)&f[i * nvp + k];
+    pair_t fn[MAXF];
+#pragma unroll
+    for (int p = 0; p < MAXF; ++p) {
+      fn[p] = fi;
+      if (p < nfc) {
+        const int j = m.cnbr[i * MAXF + p];
+        if (j >= 0) fn[p] = *(const pair_t*)&f[(int64_t)j * nvp + k];
       }
     }
-    hmin = fmin(hmin, hn);
-    hmax = fmax(hmax, hn);
-    bmin = fmin(bmin, bn);
-    bmax = fmax(bmax, bn);
+    double a[2][3] = {{0, 0, 0}, {0, 0, 0}}, lo[2], hi[2], vi[2];
+    for (int e = 0; e < 2; ++e) lo[e] = hi[e] = vi[e] = (double)fi[e];
+#pragma unroll
+    for (int p = 0; p < MAXF; ++p)
+      if (p < nfc) {
+        double x[2] = {(double)fn[p][0], (double)fn[p][1]};
+        if (m.cnbr[i * MAXF + p] < 0) {
+          const int fc = m.cface[i * MAXF + p];
+          if (m.fbc[fc] != UGKS_BC_WALL) {  // (a wall's ghost value is the cell's own)
+            const double* R = &frec[(int64_t)fc * FREC];
+            for (int e = 0; e < 2; ++e) {
+              double c2 = 0.0;
+              for (int d = 0; d < D; ++d) {
+                const double c = v.u[d * nvp + k + e] - R[FR_GU + d];
+                c2 += c * c;
+              }
+              x[e] = R[FR_GC] * exp(-R[FR_GLAM] * c2);
+              if (r) x[e] *= v.kxi / (2.0 * R[FR_GLAM]);
+            }
+          }
+        }
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          lo[e] = fmin(lo[e], x[e]);
+          hi[e] = fmax(hi[e], x[e]);
+          for (int d = 0; d < D; ++d) a[e][d] += m.lsG[(i * 3 + d) * MAXF + p] * (x[e] - vi[e]);
+        }
+      }
+    if (m.limiter)
+      for (int e = 0; e < 2; ++e) {
+        const double ph = venkat_phi<D>(m, i, nfc, vi[e], lo[e], hi[e], a[e]);
+        for (int d = 0; d < D; ++d) a[e][d] *= ph;
+      }
+    double* __restrict__ g = r ? gb : gh;
     for (int d = 0; d < D; ++d) {
-      const double G = m.lsG[(i * 3 + d) * MAXF + p];
-      ah[d] += G * (hn - hi);
-      if (hb) ab[d] += G * (bn - bi);
+      const dpair_t o = {a[0][d], a[1][d]};
+      __builtin_nontemporal_store(o, (dpair_t*)&g[(i * 3 + d) * nvp + k]);
     }
-  }
-  if (m.limiter) {
-    const double ph = venkat_phi<D>(m, i, nfc, hi, hmin, hmax, ah);
-    const double pb = hb ? venkat_phi<D>(m, i, nfc, bi, bmin, bmax, ab) : 1.0;
-    for (int d = 0; d < D; ++d) {
-      ah[d] *= ph;
-      ab[d] *= pb;
-    }
-  }
-  for (int d = 0; d < D; ++d) {
-    gh[(i * 3 + d) * nvp + k] = ah[d];
-    if (hb) gb[(i * 3 + d) * nvp + k] = ab[d];
   }
 }
 
@@ -856,7 +871,8 @@ hipError_t launch_face_eq(int D, const DevMesh& m, const DevBC* bcs, const GasP&
 hipError_t launch_grad_micro(int D, int prec, const DevMesh& m, const DevVel& v,
                              const double* frec, const void* h, const void* b, double* gh,
                              double* gb, const int32_t* flag, hipStream_t s) {
-  const unsigned grid = blocks_for(v.nvp, TPB) * (unsigned)m.nc;
+  const int64_t ntile = (m.nc + GRAD_TILE - 1) / GRAD_TILE;
+  const unsigned grid = (unsigned)((ntile + 7) / 8 * 8 * GRAD_TILE) * blocks_for(v.nvp, 2 * TPB);
   UGKS_DISPATCH_DT(D, prec, k_grad_micro<DD, TT><<<grid, TPB, 0, s>>>(
       m, v, frec, (const TT*)h, (const TT*)b, gh, gb, flag));
   return hipGetLastError();
