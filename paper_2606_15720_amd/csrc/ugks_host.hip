@@ -150,6 +150,7 @@ std::vector<int64_t> pair_slots(int D, const ugks_velocity* vel, const std::vect
 // velocity block.  Measured per step, whole cells against blocks of 4096: 6
 // cells x 28^3 130 / 128 us, 48 x 28^3 148 / 160, 384 x 28^3 193 / 226, 750 x
 // 20^3 135 / 150, 1,296 x 24^3 316 / 349, 2,058 x 28^3 736 / 737 us.
+constexpr int64_t kPinnedCells = 4 << 20;  // bytes of cell data read back through pinned memory, at most
 constexpr int64_t kWholeCells = 48;
 
 // Lanes per work-group of the whole-cell form (one mirror pair each): four
@@ -751,14 +752,19 @@ void build(ugks_ctx* c, const ugks_mesh* mesh, const ugks_velocity* vel, const u
     B.fluxh = dalloc<double>(c, (size_t)nf * nvp);
     B.fluxb = c->nr == 2 ? dalloc<double>(c, (size_t)nf * nvp) : nullptr;
   }
-  B.resid = dalloc<double>(c, 8);
+  B.resid = dalloc<double>(c, kStatus);
   B.cellred = dalloc<double>(c, nc * 3);
-  B.flag = dalloc<int32_t>(c, 4);
+  B.flag = (int32_t*)(B.resid + 8);
   B.bflux = dalloc<double>(c, 5);
   HIP_TRY(hipMemsetAsync(B.frec, 0, nf * FREC * sizeof(double), c->stream));
-  HIP_TRY(hipMemsetAsync(B.resid, 0, 8 * sizeof(double), c->stream));
+  HIP_TRY(hipMemsetAsync(B.resid, 0, kStatus * sizeof(double), c->stream));
   HIP_TRY(hipMemsetAsync(B.bflux, 0, 5 * sizeof(double), c->stream));
-  HIP_TRY(hipMemsetAsync(B.flag, 0, 4 * sizeof(int32_t), c->stream));
+  // Results go to the caller through pinned memory: to pageable memory each copy
+  // is a wait of its own (a one-step call of 1,024 cells x 28^2 and its W: 108 us
+  // with three such copies, 86 with two pinned ones).  Larger states are copied
+  // at full rate either way.
+  c->host_room = nc * NW * 8 <= kPinnedCells ? nc * std::max(NW, 3) : 0;
+  HIP_TRY(hipHostMalloc((void**)&c->host, (kStatus + c->host_room) * sizeof(double), hipHostMallocDefault));
   HIP_TRY(hipMemsetAsync(B.q, 0, nc * 3 * sizeof(double), c->stream));
   std::vector<double> W0p(nc * NW);
   for (int64_t i = 0; i < nc; ++i)
@@ -967,9 +973,10 @@ struct ugks_batch {
   int32_t* items = nullptr;
   int64_t nitems = 0, grid = 0;
   int64_t ncell = 0, nface = 0, nwall = 0, nff = 0;
-  int32_t* flags_dev = nullptr;  // [4*n]
+  int32_t* flags_dev = nullptr;  // [4*n], after resid_dev in one block
   std::vector<int> odd;          // per case: its state is in the second set of buffers
   double* resid_dev = nullptr;   // [8*n]
+  double* host = nullptr;        // pinned, [kStatus*n]: a copy of both
   int parity = 0;
   hipGraph_t graph[2] = {nullptr, nullptr};
   hipGraphExec_t exec[2] = {nullptr, nullptr};
@@ -1243,8 +1250,9 @@ void batch_build(ugks_batch* b, const ugks_case* cases, int32_t n, const ugks_op
     HIP_TRY(hipStreamCreateWithFlags(&b->stream, hipStreamNonBlocking));
     b->own_stream = true;
   }
-  b->flags_dev = balloc<int32_t>(b, 4 * (size_t)n);
-  b->resid_dev = balloc<double>(b, 8 * (size_t)n);
+  b->resid_dev = balloc<double>(b, kStatus * (size_t)n);
+  b->flags_dev = (int32_t*)(b->resid_dev + 8 * (size_t)n);
+  HIP_TRY(hipHostMalloc((void**)&b->host, kStatus * (size_t)n * sizeof(double), hipHostMallocDefault));
   HIP_TRY(hipMemset(b->flags_dev, 0, 4 * (size_t)n * sizeof(int32_t)));
   HIP_TRY(hipMemset(b->resid_dev, 0, 8 * (size_t)n * sizeof(double)));
   for (int32_t i = 0; i < n; ++i) {
@@ -1450,11 +1458,11 @@ int ugks_step(ugks_ctx* c, int32_t n_steps, double* residual_out) {
     // the steps before the last need it only until that unit is known
     for (int32_t s = 0; s < n_steps; ++s)
       run_step(c, !(c->flags & 1) && (s + 1 == n_steps || !c->resid_set), s + 1 == n_steps);
-    int32_t flag[4] = {0, 0, 0, 0};
-    HIP_TRY(hipMemcpyAsync(flag, c->buf.flag, sizeof flag, hipMemcpyDeviceToHost, c->stream));
-    double res[4] = {0.0, 0.0, 0.0, 0.0};
-    HIP_TRY(hipMemcpyAsync(res, c->buf.resid, sizeof res, hipMemcpyDeviceToHost, c->stream));
+    HIP_TRY(hipMemcpyAsync(c->host, c->buf.resid, kStatus * sizeof(double), hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));
+    const double* res = c->host;
+    int32_t flag[4];
+    std::memcpy(flag, c->host + 8, sizeof flag);
     c->resid_set = res[3] != 0.0;
     const int32_t begun = flag[1] - c->begun;
     c->begun = flag[1];
@@ -1484,31 +1492,31 @@ int ugks_moments(ugks_ctx* c, int32_t which, double* out, int32_t on_device) {
   const int D = c->D;
   try {
     int64_t ncol = which == 2 ? D : D + 2;
-    std::vector<double> lib(c->nc * (which == 2 ? 3 : ncol));
+    const int64_t n = c->nc * (which == 2 ? 3 : ncol);
+    std::vector<double> pageable(n <= c->host_room ? 0 : n);
+    double* lib = pageable.empty() ? c->host + kStatus : pageable.data();
     if (which == 0) {
-      HIP_TRY(hipMemcpyAsync(lib.data(), c->buf.W, c->nc * ncol * sizeof(double), hipMemcpyDeviceToHost, c->stream));
+      HIP_TRY(hipMemcpyAsync(lib, c->buf.W, c->nc * ncol * sizeof(double), hipMemcpyDeviceToHost, c->stream));
     } else if (which == 1) {
       double* tmp = c->buf.cellred;  // reuse: needs nc*(D+2) <= nc*3? no: use Wn scratch
       tmp = c->buf.Wn;
       HIP_TRY(launch_moments(D, c->prec, c->mesh, c->vel, c->buf.h, c->buf.b, tmp, c->stream));
-      HIP_TRY(hipMemcpyAsync(lib.data(), tmp, c->nc * ncol * sizeof(double), hipMemcpyDeviceToHost, c->stream));
+      HIP_TRY(hipMemcpyAsync(lib, tmp, c->nc * ncol * sizeof(double), hipMemcpyDeviceToHost, c->stream));
     } else if (which == 2) {
       HIP_TRY(launch_prims(D, c->mesh, c->gas, c->buf.W, c->buf.prim, c->buf.flag, 0, c->stream));
       HIP_TRY(launch_heatflux(D, c->prec, c->mesh, c->vel, c->buf.h, c->buf.b, c->buf.prim, c->buf.qn,
                               c->buf.flag, c->stream));
-      HIP_TRY(hipMemcpyAsync(lib.data(), c->buf.qn, c->nc * 3 * sizeof(double), hipMemcpyDeviceToHost, c->stream));
+      HIP_TRY(hipMemcpyAsync(lib, c->buf.qn, c->nc * 3 * sizeof(double), hipMemcpyDeviceToHost, c->stream));
     } else {
       return set_err(c, UGKS_EINVAL, "which must be 0, 1 or 2");
     }
     HIP_TRY(hipStreamSynchronize(c->stream));
-    std::vector<double> user(c->nc * ncol);
+    std::vector<double> ordered(on_device ? c->nc * ncol : 0);
+    double* user = on_device ? ordered.data() : out;
     int64_t stride = which == 2 ? 3 : ncol;
     for (int64_t i = 0; i < c->nc; ++i)
       for (int64_t x = 0; x < ncol; ++x) user[c->cell_perm[i] * ncol + x] = lib[i * stride + x];
-    if (on_device)
-      HIP_TRY(hipMemcpy(out, user.data(), user.size() * sizeof(double), hipMemcpyHostToDevice));
-    else
-      std::memcpy(out, user.data(), user.size() * sizeof(double));
+    if (on_device) HIP_TRY(hipMemcpy(out, user, ordered.size() * sizeof(double), hipMemcpyHostToDevice));
   } catch (const HipFail& e) {
     return set_err(c, UGKS_EHIP, std::string(e.what) + ": " + hipGetErrorString(e.e));
   } UGKS_CATCH_REST(set_err, c)
@@ -1718,6 +1726,7 @@ void ugks_destroy(ugks_ctx* c) {
   }
   for (hipEvent_t e : c->event_pool) (void)hipEventDestroy(e);
   for (void* p : c->allocations) (void)hipFree(p);
+  if (c->host) (void)hipHostFree(c->host);
   if (c->own_stream && c->stream) (void)hipStreamDestroy(c->stream);
   delete c;
 }
@@ -1766,11 +1775,11 @@ int ugks_batch_step(ugks_batch* b, int32_t n_steps, double* residual_out) {
       else enqueue_batch_step(b, b->parity);
       b->parity ^= 1;
     }
-    std::vector<int32_t> fl(4 * n);
-    std::vector<double> rs(8 * n);
-    HIP_TRY(hipMemcpyAsync(fl.data(), b->flags_dev, fl.size() * sizeof(int32_t), hipMemcpyDeviceToHost, b->stream));
-    HIP_TRY(hipMemcpyAsync(rs.data(), b->resid_dev, rs.size() * sizeof(double), hipMemcpyDeviceToHost, b->stream));
+    HIP_TRY(hipMemcpyAsync(b->host, b->resid_dev, kStatus * n * sizeof(double), hipMemcpyDeviceToHost, b->stream));
     HIP_TRY(hipStreamSynchronize(b->stream));
+    const double* rs = b->host;
+    std::vector<int32_t> fl(4 * n);
+    std::memcpy(fl.data(), b->host + 8 * n, fl.size() * sizeof(int32_t));
     // where each case's state is: after the steps it has begun, or before the
     // one that failed
     for (size_t i = 0; i < n; ++i) {
@@ -1857,6 +1866,7 @@ void ugks_batch_destroy(ugks_batch* b) {
   }
   for (ugks_ctx* c : b->cases) ugks_destroy(c);
   for (void* p : b->allocations) (void)hipFree(p);
+  if (b->host) (void)hipHostFree(b->host);
   if (b->own_stream && b->stream) (void)hipStreamDestroy(b->stream);
   delete b;
 }

@@ -164,6 +164,8 @@ __host__ __device__ inline double area_for(const GasP& g, int64_t i, double S) {
   return g.dtc ? S * (g.dtc[i] / g.dt) : S;
 }
 
+constexpr int kStatus = 10;  // doubles of a context's resid and flag
+
 // Kernel launchers (ugks_kernels.hip).  Each returns hipGetLastError().
 struct StepBuffers {
   // (on the fused path a step ends with W and Wn, q and qn, h and ht, b and
@@ -189,7 +191,7 @@ struct StepBuffers {
   double* gradb;
   double* fluxh;   // [nf*nvp] time-integrated microscopic fluxes (staged sweep)
   double* fluxb;
-  double* resid;   // [8] residual accumulators and state
+  double* resid;   // [8] residual accumulators and state, then flag: one block, read back in one copy
   double* bflux;   // [5] running boundary flux (with boundary-flux tracking)
   double* cellred; // [nc*3] per-cell residual contributions
   // [0] numeric error; [1] steps begun without one; [2] numeric error of the
@@ -338,6 +340,10 @@ struct ugks_ctx {
   ugks::StepBuffers buf{};
   std::vector<void*> allocations;
   int64_t bytes = 0;
+  // Pinned host memory that results are copied through: the status block
+  // (kStatus doubles), then room for host_room doubles of cell data.
+  double* host = nullptr;
+  int64_t host_room = 0;
   hipStream_t stream = nullptr;
   bool own_stream = false;
   // kernel timing (ugks_profile_enable): event pairs per launch, in order
