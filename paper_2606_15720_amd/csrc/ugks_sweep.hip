@@ -1277,8 +1277,12 @@ struct WallLds {
 
 // Wall density of one wall face: the incident free transport of the wall
 // cell (its gradient evaluated in place) against the re-emitted wall
-// Maxwellian, whose value at a tensor point is a product of three LDS
-// axis factors (no per-velocity exp).
+// Maxwellian, whose value at a tensor point is a product of D LDS axis
+// factors.  A lane takes mirror pairs: exactly one member is incident, the
+// other leaves, so the lanes do not diverge and each pair reads f once.  Bound
+// by the five rows read of every wall cell: 4,800 walls x 28^3 FP32 0.42 ms
+// with one slot per lane and turn, 0.19 so;
+// 24^3 FP64 0.246 and 0.178.
 template <int D, typename T, bool LIM = false, bool BF = false>
 __device__ __forceinline__ void wall_rho_at(int64_t wi, const DevMesh& m, const DevVel& v,
                                             const FusedMesh& fm, const GasP& g,
@@ -1310,157 +1314,122 @@ __device__ __forceinline__ void wall_rho_at(int64_t wi, const DevMesh& m, const 
   // coefficients, wave-uniform for the whole loop.
   crec_i_t* ci = (crec_i_t*)(fm.crec_i + L * CRI);
   crec_t<double>* cd = (crec_t<double>*)(fm.crec_d + L * CRD);
-  const T* __restrict__ hl_row = h + L * nvp;
-  const T* hs_row[4];
+  crec_t<double>* cl = LIM ? (crec_t<double>*)(fm.crec_l + L * CRL) : nullptr;
+  auto row_of = [nvp](const T* base, int64_t r) { return srow(base + r * nvp); };
+  // value and u.gradient of the wall cell's reconstruction at the wall
+  auto at_wall = [&](double fi, const double (&fs)[4], const double* u, double& ff, double& ug) {
+    double gr[3] = {0, 0, 0};
 #pragma unroll
-  for (int s = 0; s < 4; ++s) hs_row[s] = h + (int64_t)ci[CI_OWN + s] * nvp;
+    for (int s = 0; s < 4; ++s) {
+      const double df = fs[s] - fi;
+#pragma unroll
+      for (int d = 0; d < D; ++d) gr[d] += cd[CD_G + d * 4 + s] * df;
+    }
+    if constexpr (LIM) {
+      // limited as the sweep limits it
+      double lo = fi, hi = fi;
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const double vs = cl[1 + s] * fi + fs[s];
+        lo = fmin(lo, vs);
+        hi = fmax(hi, vs);
+      }
+      const double ph = venkat_phi<D>(fi, lo, hi, gr, cd + CD_F0, CD_FS, cl[0]);
+#pragma unroll
+      for (int d = 0; d < D; ++d) gr[d] *= ph;
+    }
+    ff = fi;
+    ug = 0.0;
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+      ff += dxl[d] * gr[d];
+      ug += u[d] * gr[d];
+    }
+  };
+  grow_t *own = row_of(h, L), *rs[4];
+#pragma unroll
+  for (int s = 0; s < 4; ++s) rs[s] = row_of(h, ci[CI_OWN + s]);
+  grow_t *wt = srow(v.w), *ix = srow(fm.vidx);
   double acc[2] = {0.0, 0.0};
   // with BF: the wall flux's moments, incident (time-integrated free transport
   // of the wall cell's h, and b in 2-D) and reflected (per unit rho_w dt)
   double bfi[D + 2], bfr[D + 2];
 #pragma unroll
   for (int x = 0; x < D + 2; ++x) bfi[x] = bfr[x] = 0.0;
-  // Four velocities per lane per pass: their axis indices are loaded one
-  // pass ahead, and the rows of the incident ones (u.n > 0, the only ones
-  // that read f) are loaded together before any arithmetic.
-  constexpr unsigned UN = 4;
-  const unsigned nb = blockDim.x, nv = (unsigned)v.nvp;  // every slot (the pads' weights are 0)
-  int pkn[UN];
-#pragma unroll
-  for (unsigned u = 0; u < UN; ++u) {
-    const unsigned kk = threadIdx.x + u * nb;
-    pkn[u] = kk < nv ? fm.vidx[kk] : 0;
-  }
-  for (unsigned k0 = threadIdx.x; k0 < nv; k0 += UN * nb) {
+  // a few pairs per lane per pass, their rows loaded together (FP32 with 4: 0.207)
+  constexpr unsigned UN = sizeof(T) == 8 ? 4 : 2;
+  const unsigned nb = blockDim.x, half = (unsigned)fm.half;
+  for (unsigned k0 = threadIdx.x; k0 < half; k0 += UN * nb) {
     int pk[UN];
 #pragma unroll
     for (unsigned u = 0; u < UN; ++u) {
-      pk[u] = pkn[u];
-      const unsigned kk = k0 + (UN + u) * nb;
-      pkn[u] = kk < nv ? fm.vidx[kk] : 0;
+      const unsigned kp = k0 + u * nb;
+      if (kp < half) pk[u] = ldo<int32_t, int>(ix, kp * 4u);
     }
-    double uu[UN][3], un[UN];
-    int id[UN][3];
-    bool inc[UN], out[UN];
+    double uu[UN][3], un[UN], hl[UN], hs[UN][4], wi_[UN], wo[UN], M[UN];
+    unsigned kin[UN];
 #pragma unroll
     for (unsigned u = 0; u < UN; ++u) {
-      const bool valid = k0 + u * nb < nv;
-      un[u] = 0.0;
-#pragma unroll
-      for (int d = 0; d < 3; ++d) {
-        id[u][d] = node_of(pk[u], d);
-        uu[u][d] = d < D ? S.ax[id[u][d]] : 0.0;
-        if (d < D) un[u] += uu[u][d] * nrm[d];
-      }
-      inc[u] = valid && un[u] > 0.0;
-      out[u] = valid && un[u] < 0.0;
-    }
-    double hl[UN], hs[UN][4], wk[UN];
-#pragma unroll
-    for (unsigned u = 0; u < UN; ++u) {
-      const unsigned kk = k0 + u * nb;
-      hl[u] = 0.0;
-#pragma unroll
-      for (int s = 0; s < 4; ++s) hs[u][s] = 0.0;
-      if (inc[u]) {
-        hl[u] = ld(hl_row, kk);
-#pragma unroll
-        for (int s = 0; s < 4; ++s) hs[u][s] = ld(hs_row[s], kk);
-      }
-      wk[u] = (inc[u] || out[u]) ? v.w[kk] : 0.0;
-    }
-#pragma unroll
-    for (unsigned u = 0; u < UN; ++u) {
-      if (inc[u]) {
-        // incident: free transport of the wall cell's reconstruction
-        double gr[3] = {0, 0, 0};
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-          const double dh = hs[u][s] - hl[u];
-#pragma unroll
-          for (int d = 0; d < D; ++d) gr[d] += cd[CD_G + d * 4 + s] * dh;
-        }
-        if constexpr (LIM) {
-          // the wall cell's gradient limited as the sweep limits it
-          crec_t<double>* cl = (crec_t<double>*)(fm.crec_l + L * CRL);
-          double lo = hl[u], hi = hl[u];
-#pragma unroll
-          for (int s = 0; s < 4; ++s) {
-            const double vs = cl[1 + s] * hl[u] + hs[u][s];
-            lo = fmin(lo, vs);
-            hi = fmax(hi, vs);
-          }
-          const double ph = venkat_phi<D>(hl[u], lo, hi, gr, cd + CD_F0, CD_FS, cl[0]);
-#pragma unroll
-          for (int d = 0; d < D; ++d) gr[d] *= ph;
-        }
-        double hf = hl[u], ugh = 0.0;
+      const unsigned kp = k0 + u * nb;
+      if (kp < half) {  // whole waves: half is a multiple of 64
+        int id[3];
+        un[u] = 0.0;
 #pragma unroll
         for (int d = 0; d < D; ++d) {
-          hf += dxl[d] * gr[d];
-          ugh += uu[u][d] * gr[d];
+          id[d] = node_of(pk[u], d);
+          uu[u][d] = S.ax[id[d]];
+          un[u] += uu[u][d] * nrm[d];
         }
-        acc[0] += wk[u] * un[u] * (dt * hf - 0.5 * dt * dt * ugh);
+        const bool pos = un[u] > 0.0;  // u is incident, else -u
+        M[u] = 1.0;
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+          M[u] *= S.wx[d][pos ? na - 1 - id[d] : id[d]];
+          uu[u][d] = pos ? uu[u][d] : -uu[u][d];
+        }
+        un[u] = fabs(un[u]);
+        const unsigned kout = pos ? kp + half : kp;
+        kin[u] = pos ? kp : kp + half;
+        const uint32_t off = kin[u] * (uint32_t)sizeof(T);
+        hl[u] = ldo<T, double>(own, off);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) hs[u][s] = ldo<T, double>(rs[s], off);
+        wi_[u] = ldo<double, double>(wt, kin[u] * 8u);
+        wo[u] = ldo<double, double>(wt, kout * 8u);
+      }
+    }
+#pragma unroll
+    for (unsigned u = 0; u < UN; ++u) {
+      const unsigned kp = k0 + u * nb;
+      if (kp < half) {
+        double hf, ugh;
+        at_wall(hl[u], hs[u], uu[u], hf, ugh);
+        const double fi = wi_[u] * un[u] * (dt * hf - 0.5 * dt * dt * ugh);  // incident
+        const double fo = -wo[u] * un[u] * M[u];                             // re-emitted, per rho_w dt
+        acc[0] += fi;
+        acc[1] += fo;
         if constexpr (BF) {
-          const double fh = wk[u] * un[u] * (dt * hf - 0.5 * dt * dt * ugh);
           double u2 = 0.0;
 #pragma unroll
           for (int d = 0; d < D; ++d) {
-            bfi[1 + d] += uu[u][d] * fh;
+            bfi[1 + d] += uu[u][d] * fi;
+            bfr[1 + d] -= uu[u][d] * fo;
             u2 += uu[u][d] * uu[u][d];
           }
-          bfi[0] += fh;
-          bfi[D + 1] += 0.5 * u2 * fh;
+          bfi[0] += fi;
+          bfi[D + 1] += 0.5 * u2 * fi;
+          bfr[0] += fo;
+          // the re-emitted b = K_xi/(2 lambda_w) H_w adds to the energy
+          bfr[D + 1] += 0.5 * (u2 + v.kxi / (2.0 * lamw)) * fo;
           if (b != nullptr) {
             // the b part of the energy: the same free transport of the wall cell's b
-            const unsigned kk = k0 + u * nb;
-            const T* __restrict__ bl_row = b + L * nvp;
-            const double bl = ld(bl_row, kk);
-            double gb[3] = {0, 0, 0};
+            const uint32_t off = kin[u] * (uint32_t)sizeof(T);
+            double bs[4], bf, ugb;
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
-              const double db = ld(b + (int64_t)ci[CI_OWN + s] * nvp, kk) - bl;
-#pragma unroll
-              for (int d = 0; d < D; ++d) gb[d] += cd[CD_G + d * 4 + s] * db;
-            }
-            if constexpr (LIM) {
-              crec_t<double>* cl = (crec_t<double>*)(fm.crec_l + L * CRL);
-              double lo = bl, hi = bl;
-#pragma unroll
-              for (int s = 0; s < 4; ++s) {
-                const double vs = cl[1 + s] * bl + ld(b + (int64_t)ci[CI_OWN + s] * nvp, kk);
-                lo = fmin(lo, vs);
-                hi = fmax(hi, vs);
-              }
-              const double pb = venkat_phi<D>(bl, lo, hi, gb, cd + CD_F0, CD_FS, cl[0]);
-#pragma unroll
-              for (int d = 0; d < D; ++d) gb[d] *= pb;
-            }
-            double bf = bl, ugb = 0.0;
-#pragma unroll
-            for (int d = 0; d < D; ++d) {
-              bf += dxl[d] * gb[d];
-              ugb += uu[u][d] * gb[d];
-            }
-            bfi[D + 1] += 0.5 * wk[u] * un[u] * (dt * bf - 0.5 * dt * dt * ugb);
+            for (int s = 0; s < 4; ++s) bs[s] = ldo<T, double>(row_of(b, ci[CI_OWN + s]), off);
+            at_wall(ldo<T, double>(row_of(b, L), off), bs, uu[u], bf, ugb);
+            bfi[D + 1] += 0.5 * wi_[u] * un[u] * (dt * bf - 0.5 * dt * dt * ugb);
           }
-        }
-      } else if (out[u]) {
-        double M = S.wx[0][id[u][0]];
-#pragma unroll
-        for (int d = 1; d < D; ++d) M *= S.wx[d][id[u][d]];
-        acc[1] += wk[u] * un[u] * M;
-        if constexpr (BF) {
-          const double fm_ = wk[u] * un[u] * M;
-          double u2 = 0.0;
-#pragma unroll
-          for (int d = 0; d < D; ++d) {
-            bfr[1 + d] += uu[u][d] * fm_;
-            u2 += uu[u][d] * uu[u][d];
-          }
-          bfr[0] += fm_;
-          // the re-emitted b = K_xi/(2 lambda_w) H_w adds to the energy
-          bfr[D + 1] += 0.5 * (u2 + v.kxi / (2.0 * lamw)) * fm_;
         }
       }
     }
@@ -1485,22 +1454,15 @@ __device__ __forceinline__ void wall_rho_at(int64_t wi, const DevMesh& m, const 
 // One work-group per wall face (256 lanes measured faster than 1024).
 constexpr int WALLT = 256;
 
-template <int D, typename T>
+// with BF (boundary-flux tracking) the pass also keeps each wall face's flux; b
+// is the b array where b is stored (its part of the energy flux), else null
+template <int D, typename T, bool LIM, bool BF>
 __global__ __launch_bounds__(WALLT) void k_wall_rho_inline(DevMesh m, DevVel v, FusedMesh fm, GasP g,
                                                          const T* __restrict__ h,
                                                          double* __restrict__ frec,
-                                                         const int32_t* flag, const T* b_bf,
-                                                         int track) {
+                                                         const int32_t* flag, const T* __restrict__ b) {
   __shared__ WallLds S;
-  // with tracking the pass also keeps each wall face's flux; b_bf is the b
-  // array where b is stored (its part of the energy flux), else null
-  if (track) {
-    if (fm.crec_l) wall_rho_at<D, T, true, true>(blockIdx.x, m, v, fm, g, h, frec, flag, S, b_bf);
-    else wall_rho_at<D, T, false, true>(blockIdx.x, m, v, fm, g, h, frec, flag, S, b_bf);
-  } else {
-    if (fm.crec_l) wall_rho_at<D, T, true>(blockIdx.x, m, v, fm, g, h, frec, flag, S);
-    else wall_rho_at<D, T, false>(blockIdx.x, m, v, fm, g, h, frec, flag, S);
-  }
+  wall_rho_at<D, T, LIM, BF>(blockIdx.x, m, v, fm, g, h, frec, flag, S, b);
 }
 
 // Ghost rows of the far-field / outflow faces: the Maxwellian of the face's
@@ -1785,8 +1747,14 @@ hipError_t launch_wall_rho_inline(int D, int prec, const DevMesh& m, const DevVe
                                   const FusedMesh& fm, const GasP& g, const void* h, double* frec,
                                   const int32_t* flag, hipStream_t s, int track, const void* b_bf) {
   if (m.nwall == 0) return hipSuccess;
-  UGKS_DISPATCH_DT(D, prec, k_wall_rho_inline<DD, TT><<<(unsigned)m.nwall, WALLT, 0, s>>>(
-      m, v, fm, g, (const TT*)h, frec, flag, (const TT*)b_bf, track));
+#define UGKS_WALL(LIM, BF)                                                                          \
+  UGKS_DISPATCH_DT(D, prec, (k_wall_rho_inline<DD, TT, LIM, BF><<<(unsigned)m.nwall, WALLT, 0, s>>>( \
+                                m, v, fm, g, (const TT*)h, frec, flag, (const TT*)b_bf)))
+  if (track && fm.crec_l) UGKS_WALL(true, true);
+  else if (track) UGKS_WALL(false, true);
+  else if (fm.crec_l) UGKS_WALL(true, false);
+  else UGKS_WALL(false, false);
+#undef UGKS_WALL
   return hipGetLastError();
 }
 
