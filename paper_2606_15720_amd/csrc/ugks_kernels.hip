@@ -59,23 +59,26 @@ __global__ __launch_bounds__(TPB) void k_heatflux(DevVel v, const T* __restrict_
 // of the cell and its stencil values, g its least-squares gradient.  At each
 // face d- = g.(x_f - x_i) and d+ the room left toward the bound on its side;
 // psi = (d+^2 + eps^2 + 2 d- d+) / (d+^2 + 2 d-^2 + d- d+ + eps^2); the
-// factor is min(1, min_faces psi).
+// factor is min(1, min_faces psi).  d+ is one value per side and min(1, psi)
+// falls as |d-| grows, so the largest and the smallest d- decide.
 template <int D>
 __device__ __forceinline__ double venkat_phi(const DevMesh& m, int64_t i, int nfc, double vi,
                                              double vmin, double vmax, const double* g) {
   const double eps2 = m.veps2[i];
-  double phi = 1.0;
+  double dmax = 0.0, dmin = 0.0;
   for (int p = 0; p < nfc; ++p) {
     const int f = m.cface[i * MAXF + p];
     const double* dx = m.csign[i * MAXF + p] > 0.0 ? &m.fdxL[f * 3] : &m.fdxR[f * 3];
     double dm = 0.0;
     for (int d = 0; d < D; ++d) dm += g[d] * dx[d];
-    if (dm == 0.0) continue;
-    const double dp = dm > 0.0 ? vmax - vi : vmin - vi;
-    const double psi = (dp * dp + eps2 + 2.0 * dm * dp) / (dp * dp + 2.0 * dm * dm + dm * dp + eps2);
-    phi = fmin(phi, psi);
+    dmax = fmax(dmax, dm);
+    dmin = fmin(dmin, dm);
   }
-  return phi;
+  // (fmin drops the 0 / 0 of a side without slope or room)
+  auto psi = [eps2](double dp, double dm) {
+    return (dp * dp + eps2 + 2.0 * dm * dp) / (dp * dp + 2.0 * dm * dm + dm * dp + eps2);
+  };
+  return fmin(fmin(1.0, psi(vmax - vi, dmax)), psi(vmin - vi, dmin));
 }
 
 // Macroscopic least-squares gradients of W (step 4).
