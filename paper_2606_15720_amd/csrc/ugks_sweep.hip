@@ -263,19 +263,21 @@ __device__ __forceinline__ int node_of(int pk, int d) { return (pk >> (10 * d + 
 
 // One 64-lane sum, valid in lane 63: shifts within rows of 16, then the rows
 // joined by broadcasts (no LDS round trips).
-template <int CTRL, int ROWS>
+// (lanes without a source add 0; what the broadcasts add to other rows than the
+// last does not reach lane 63)
+template <int CTRL>
 __device__ __forceinline__ double dpp_add(double v) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, false);
+  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true);
   return v + __hiloint2double(hi, lo);
 }
 __device__ __forceinline__ double wave_total(double v) {
-  v = dpp_add<0x111, 0xf>(v);  // row_shr:1, 2, 4, 8
-  v = dpp_add<0x112, 0xf>(v);
-  v = dpp_add<0x114, 0xf>(v);
-  v = dpp_add<0x118, 0xf>(v);
-  v = dpp_add<0x142, 0xa>(v);  // row_bcast:15 into rows 1 and 3
-  return dpp_add<0x143, 0xc>(v);  // row_bcast:31 into rows 2 and 3
+  v = dpp_add<0x111>(v);  // row_shr:1, 2, 4, 8
+  v = dpp_add<0x112>(v);
+  v = dpp_add<0x114>(v);
+  v = dpp_add<0x118>(v);
+  v = dpp_add<0x142>(v);  // row_bcast:15: each row's total to the next
+  return dpp_add<0x143>(v);  // row_bcast:31: the first two rows' to the last two
 }
 
 // Work-group totals of N values, in every lane of the first wave: each wave's
@@ -892,8 +894,16 @@ __device__ __forceinline__ void finish_cell(const GasP& g, const int32_t* __rest
 // (7.55) and second stage (2.11) of their own, 9.54 ms so, 9.18 ms with the
 // slot order and the sign branches of the loop; FP32, 28^3: 9.60, 8.96, 8.07;
 // cavity of 32^2 cells x 28^2: 0.088, 0.059, 0.056.
+// In 2-D, FP32 without the limiter takes h and b in one pass (the registers of 5
+// waves per SIMD hold it): 16,384 cells x 32^2 0.220 -> 0.208 ms, 4,096 x 28^2
+// 0.067 -> 0.062.  FP64 would lose a resident wave: 1,024 x 28^2 0.031 -> 0.043.
+template <typename T, int D, bool LIM>
+constexpr bool kBothPasses = D == 2 && sizeof(T) == 4 && !LIM;
+template <typename T, int D, bool LIM>
+constexpr int kCellWaves = sizeof(T) == 8 ? 4 : kBothPasses<T, D, LIM> ? 5 : 6;  // per SIMD
+
 template <int D, typename T, bool LIM, bool HB>
-__global__ __launch_bounds__(CELLT, (sizeof(T) == 4 ? 6 : 4)) void k_step_cell(
+__global__ __launch_bounds__(CELLT, (kCellWaves<T, D, LIM>)) void k_step_cell(
     SweepIn<T> in, SweepSched sc, int64_t nc, GasP g, const T* __restrict__ h, const T* __restrict__ b,
     T* ht, T* bt, CellOut o) {
   __shared__ SweepLds<D, T> L;
@@ -905,7 +915,7 @@ __global__ __launch_bounds__(CELLT, (sizeof(T) == 4 ? 6 : 4)) void k_step_cell(
   const int64_t ic = ((local / sc.tile) * 8 + xcd) * sc.tile + local % sc.tile;
   if (ic >= nc || *o.flag) return;
   double mw[D + 2];
-  sweep_item<D, T, T, false, LIM, HB>(in, h, b, ht, bt, ic, 0u, in.half, L.s, stage, mw);
+  sweep_item<D, T, T, kBothPasses<T, D, LIM>, LIM, HB>(in, h, b, ht, bt, ic, 0u, in.half, L.s, stage, mw);
   block_total<D + 2>(mw, L.red);
   finish_cell<D, T, T, HB>(g, in.vidx, in.w, o, ht, bt, ic, in.nvp, in.half, in.na, in.axis, stage, in.keep,
                         mw, L.c, L.red);
@@ -1664,7 +1674,7 @@ void launch_step_as(const DevMesh& m, const FusedMesh& fm, const DevVel& v, cons
   // 16,384 cells x 32^2 FP32 0.317 -> 0.283 (all).  One grain too many costs a
   // resident work-group: 8.48 on the second.
   const int64_t pair = (HB ? 4 : 2) * (int64_t)sizeof(T);
-  in.keep = kept_pairs(sizeof(T) == 4 ? 24 : 16, sc, sizeof(SweepLds<D, T>), pair, in.half);
+  in.keep = kept_pairs(4 * kCellWaves<T, D, LIM>, sc, sizeof(SweepLds<D, T>), pair, in.half);
   k_step_cell<D, T, LIM, HB><<<grid, sc.lanes, (size_t)in.keep * pair, s>>>(
       in, sc, fm.nc, g, (const T*)B.h, (const T*)B.b, (T*)B.ht, (T*)B.bt, cell_out(m, B));
 }
