@@ -82,7 +82,7 @@ void check_case_args(const ugks_mesh* mesh, const ugks_velocity* vel, const ugks
 // every slot (-1: pad), and vidx the packed node indices of all of them.  ax:
 // the sorted symmetric nodes that every coordinate is one of.
 std::vector<int64_t> pair_slots(int D, const ugks_velocity* vel, const std::vector<double>& ax,
-                                std::vector<int32_t>& vidx) {
+                                std::vector<int32_t>& vidx, int64_t* full) {
   const int64_t nv = vel->nv, na = (int64_t)ax.size();
   std::vector<int32_t> id(nv * D);
   int64_t cube = 1;
@@ -125,8 +125,13 @@ std::vector<int64_t> pair_slots(int D, const ugks_velocity* vel, const std::vect
     }
     pairs.push_back({(block << 10) | in, first, m});
   }
-  std::sort(pairs.begin(), pairs.end(),
-            [](const Pair& a, const Pair& b) { return a.key != b.key ? a.key < b.key : a.k < b.k; });
+  // points without a mirror last: their waves need not do the second member
+  std::sort(pairs.begin(), pairs.end(), [](const Pair& a, const Pair& b) {
+    if ((a.m < 0) != (b.m < 0)) return b.m < 0;
+    return a.key != b.key ? a.key < b.key : a.k < b.k;
+  });
+  const int64_t with = std::count_if(pairs.begin(), pairs.end(), [](const Pair& a) { return a.m >= 0; });
+  *full = (with + WAVE - 1) / WAVE * WAVE;
   const int64_t half = ((int64_t)pairs.size() + WAVE - 1) / WAVE * WAVE;
   std::vector<int64_t> slots(2 * half, -1);
   vidx.assign(2 * half, 0);
@@ -393,7 +398,7 @@ void build(ugks_ctx* c, const ugks_mesh* mesh, const ugks_velocity* vel, const u
   }
   // ---- velocity slots -------------------------------------------------------
   std::vector<int32_t> vidx;
-  c->vel_perm = c->slots() ? pair_slots(D, vel, ax, vidx) : std::vector<int64_t>();
+  c->vel_perm = c->slots() ? pair_slots(D, vel, ax, vidx, &c->fmesh.full) : std::vector<int64_t>();
   if (!c->slots()) {
     // the caller's order, rows padded to whole waves
     c->vel_perm.assign((nv + WAVE - 1) / WAVE * WAVE, -1);

@@ -103,11 +103,13 @@ constexpr int SREC = 16, SR_P = 2;
 // half + k (k < half = half a row), the first members ordered by compact blocks
 // of the node lattice, so that 64 consecutive slots have mostly one sign of
 // u.n.  A point whose mirror is not in the set (or is the point itself) has a
-// pad slot there: the mirrored velocity with weight 0, advanced like any other.
+// pad slot there: the mirrored velocity with weight 0; such slots come last, and
+// the whole-cell form leaves out the second members of their waves.
 struct FusedMesh {
   int64_t nc, nv;
   int na;                   // nodes per velocity axis
   int64_t half;             // mirror pairs with padding (a multiple of 64)
+  int64_t full;             // the first of them with a point for either member (up to a multiple of 64)
   const double* axis;       // [na] symmetric 1-D nodes
   const int32_t* vidx;      // [2*half + padding] 16 * node index of every slot, 10 bits per axis, first axis low
   const int32_t* crec_i;    // [nc*CRI]

@@ -322,6 +322,7 @@ struct SweepIn {
   double dt;
   int64_t nvp;
   unsigned half;  // slots of the first members; the mirror of slot k is slot half + k
+  unsigned full;  // sparse sets: slots (a multiple of 64) whose mirror may be a point; pads follow
   unsigned keep;  // whole-cell form: pairs (a multiple of 64) whose first stage stays in LDS
   int na;
   const double* axis;
@@ -416,7 +417,12 @@ __device__ __forceinline__ void first_stage(PT cc, const C* vv, C v2, C c0, C c1
 // 48,000 tets x 24^3, rows beyond the cell's own cost 1.7 (L2 misses), the
 // first stage's stores 0.9 and the rest of the step 1.7; the loop alone is
 // at 65 % of its VALU time.
-template <int D, typename T, typename C, int NR, int X0, bool LIM, bool HB>
+//
+// ONE: only the first members, for pairs whose second is a pad (points of a
+// sparse set without a mirror): each face then has either its outgoing or its
+// incoming side to do.  10,368 tets x 17,408 velocities, 3,456 of them without
+// a mirror: 2.59 ms with whole pairs throughout, 2.30 so.
+template <int D, typename T, typename C, int NR, int X0, bool LIM, bool HB, bool ONE = false>
 __device__ __forceinline__ void sweep_pass(const SweepIn<C>& in, const T* __restrict__ h,
                                            const T* __restrict__ b, T* __restrict__ ht,
                                            T* __restrict__ bt, int64_t ic, unsigned kbeg, unsigned kend,
@@ -490,7 +496,7 @@ __device__ __forceinline__ void sweep_pass(const SweepIn<C>& in, const T* __rest
 #pragma unroll
     for (int r = 0; r < NR; ++r) {
       f0[r] = ldo<T, C>(own[r], o0);
-      f1[r] = ldo<T, C>(own[r], o1);
+      f1[r] = ONE ? C(0) : ldo<T, C>(own[r], o1);
     }
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
@@ -498,17 +504,18 @@ __device__ __forceinline__ void sweep_pass(const SweepIn<C>& in, const T* __rest
       for (int r = 0; r < NR; ++r) {
         grow_t* rs = row_of(src[r], rows[CI_OWN + s]);
         os0[r][s] = ldo<T, C>(rs, o0);
-        os1[r][s] = ldo<T, C>(rs, o1);
+        os1[r][s] = ONE ? C(0) : ldo<T, C>(rs, o1);
       }
     }
     // ---- every neighbour's stencil at the incoming member ----
     // Slot p of the own stencil is the row across face p, and slot 0 of
     // neighbour p's stencil is this cell: both are already in registers.
-    C ns[NR][4][3];
+    C ns[NR][4][3] = {};
 #pragma unroll
     for (int p = 0; p < 4; ++p) {
       uint32_t oin = sp[p] > C(0) ? o1 : o0;  // u.n > 0: the incoming member is -u
       __asm__("" : "+v"(oin));  // keep the select on the offset, not on 64-bit addresses
+      if (ONE && sp[p] > C(0)) continue;
 #pragma unroll
       for (int q = 0; q < 3; ++q)
 #pragma unroll
@@ -633,10 +640,13 @@ __device__ __forceinline__ void sweep_pass(const SweepIn<C>& in, const T* __rest
         // the outgoing member's from the cell's own reconstruction (fo, go,
         // ugo), the incoming one's from the neighbour's (fj; fi is this cell's
         // value in its stencil; su u the incoming velocity).
-        auto flux = [&](C fo, const C* go, C ugo, C eqo, C fj, C fi, C su, C eqi, C& acco, C& acci) {
+        auto out = [&](C fo, const C* go, C ugo, C eqo, C& acco) {
           C ff = fo;
 #pragma unroll
           for (int d = 0; d < D; ++d) ff += fd(d) * go[d];
+          acco += sas * (G1 * ff + G2 * ugo + eqm * eqo);
+        };
+        auto into = [&](C fj, C fi, C su, C eqi, C& acci) {
           C gj[D];
           if constexpr (LIM) {
 #pragma unroll
@@ -650,17 +660,20 @@ __device__ __forceinline__ void sweep_pass(const SweepIn<C>& in, const T* __rest
             ffj += fd(3 + d) * gj[d];
             ugj += vv[d] * gj[d];
           }
-          acco += sas * (G1 * ff + G2 * ugo + eqm * eqo);
           acci -= sas * (G1 * ffj + G2 * (su * ugj) + eqi);
         };
-        if (sp[p] > C(0))
-          flux(f0[r], g0[r], ug0[r], q0, os1[r][p], f1[r], C(-1), q1, acc0[r], acc1[r]);
-        else
-          flux(f1[r], g1[r], ug1[r], q1, os0[r][p], f0[r], C(1), q0, acc1[r], acc0[r]);
+        if (sp[p] > C(0)) {
+          out(f0[r], g0[r], ug0[r], q0, acc0[r]);
+          if constexpr (!ONE) into(os1[r][p], f1[r], C(-1), q1, acc1[r]);
+        } else {
+          if constexpr (!ONE) out(f1[r], g1[r], ug1[r], q1, acc1[r]);
+          into(os0[r][p], f0[r], C(1), q0, acc0[r]);
+        }
       }
     }
     // moments of the net outflow
-    const double w0 = ldo<double, double>(wt, kp * 8u), w1 = ldo<double, double>(wt, (kp + in.half) * 8u);
+    const double w0 = ldo<double, double>(wt, kp * 8u);
+    const double w1 = ONE ? 0.0 : ldo<double, double>(wt, (kp + in.half) * 8u);
     add_moments<D, C, X0>(w0, w1, acc0[0], acc1[0], vv, v2, mw);
     if constexpr (NR == 2) add_moments<D, C, 1>(w0, w1, acc0[1], acc1[1], vv, v2, mw);
     // first stage with the cell's BGK-Shakhov equilibrium at u and -u
@@ -680,10 +693,10 @@ __device__ __forceinline__ void sweep_pass(const SweepIn<C>& in, const T* __rest
       else first_stage<D, C, 1>(cc, vv, v2, c0, c1, f0[r], f1[r], acc0[r], acc1[r], t0, t1);
       if (kp < in.keep) {
         stage[2 * (X0 + r) * in.keep + kp] = (T)t0;
-        stage[(2 * (X0 + r) + 1) * in.keep + kp] = (T)t1;
+        if constexpr (!ONE) stage[(2 * (X0 + r) + 1) * in.keep + kp] = (T)t1;
       } else {
         sto<T>(dst[r], o0, (T)t0);
-        sto<T>(dst[r], o1, (T)t1);
+        if constexpr (!ONE) sto<T>(dst[r], o1, (T)t1);
       }
     }
   }
@@ -695,7 +708,8 @@ __device__ __forceinline__ void sweep_pass(const SweepIn<C>& in, const T* __rest
 // registers, where h and b together spill them), or with BOTH in one (the
 // batched form's small cases run only a few iterations, whose dependent-load
 // latency two passes would pay twice).  HB: b is carried.
-template <int D, typename T, typename C, bool BOTH, bool LIM, bool HB>
+// SPARSE: the pairs from in.full on have a pad for their second member.
+template <int D, typename T, typename C, bool BOTH, bool LIM, bool HB, bool SPARSE = false>
 __device__ __forceinline__ void sweep_item(const SweepIn<C>& in, const T* __restrict__ h,
                                            const T* __restrict__ b, T* __restrict__ ht,
                                            T* __restrict__ bt, int64_t ic, unsigned kbeg, unsigned kend,
@@ -704,7 +718,14 @@ __device__ __forceinline__ void sweep_item(const SweepIn<C>& in, const T* __rest
   __syncthreads();
 #pragma unroll
   for (int x = 0; x < D + 2; ++x) mw[x] = 0.0;
-  if constexpr (HB && BOTH) {
+  if constexpr (SPARSE) {
+    sweep_pass<D, T, C, 1, 0, LIM, HB>(in, h, b, ht, bt, ic, kbeg, in.full, L, stage, mw);
+    sweep_pass<D, T, C, 1, 0, LIM, HB, true>(in, h, b, ht, bt, ic, in.full, kend, L, stage, mw);
+    if constexpr (HB) {
+      sweep_pass<D, T, C, 1, 1, LIM, HB>(in, h, b, ht, bt, ic, kbeg, in.full, L, stage, mw);
+      sweep_pass<D, T, C, 1, 1, LIM, HB, true>(in, h, b, ht, bt, ic, in.full, kend, L, stage, mw);
+    }
+  } else if constexpr (HB && BOTH) {
     sweep_pass<D, T, C, 2, 0, LIM, HB>(in, h, b, ht, bt, ic, kbeg, kend, L, stage, mw);
   } else {
     sweep_pass<D, T, C, 1, 0, LIM, HB>(in, h, b, ht, bt, ic, kbeg, kend, L, stage, mw);
@@ -719,12 +740,13 @@ __device__ __forceinline__ void sweep_item(const SweepIn<C>& in, const T* __rest
 // has swept the cell, each lane takes the pairs it swept and reads back what
 // it wrote itself.  What is done once per cell is done by the first wave: by
 // all eight it was a tenth of the kernel's VALU instructions.
-template <int D, typename T, typename C, bool HB>
+template <int D, typename T, typename C, bool HB, bool SPARSE = false>
 __device__ __forceinline__ void finish_cell(const GasP& g, const int32_t* __restrict__ vidx,
                                             const double* __restrict__ w, const CellOut& o, T* ht, T* bt,
                                             int64_t ic, int64_t nvp, unsigned half, int na,
                                             const double* __restrict__ axis, const T* stage, unsigned keep,
-                                            double (&tot)[D + 2], CellTabs<D>& L, double* red) {
+                                            double (&tot)[D + 2], CellTabs<D>& L, double* red,
+                                            unsigned full = 0u) {
   constexpr int NM = D + 2, N = Cubic<D>::N, NP = Cubic<D>::C0 + D;
   double P[NPRIM], dt = 0.0;
   if (threadIdx.x < WAVE) {
@@ -805,20 +827,23 @@ __device__ __forceinline__ void finish_cell(const GasP& g, const int32_t* __rest
       const unsigned k = kp + u * nthr;
       if (k < half) {  // whole waves: half is a multiple of 64
         const uint32_t o0 = k * (uint32_t)sizeof(T), o1 = o0 + half * (uint32_t)sizeof(T);
+        const bool two = !SPARSE || k < full;  // not a pad
+        h1[u] = b1[u] = T(0);
+        w1[u] = 0.0;
         if (k < keep) {
           h0[u] = stage[k];
-          h1[u] = stage[keep + k];
+          if (two) h1[u] = stage[keep + k];
           b0[u] = HB ? stage[2 * keep + k] : T(0);
-          b1[u] = HB ? stage[3 * keep + k] : T(0);
+          if (two) b1[u] = HB ? stage[3 * keep + k] : T(0);
         } else {
           h0[u] = ldo<T, T>(hr, o0);
-          h1[u] = ldo<T, T>(hr, o1);
+          if (two) h1[u] = ldo<T, T>(hr, o1);
           b0[u] = HB ? ldo<T, T>(br, o0) : T(0);
-          b1[u] = HB ? ldo<T, T>(br, o1) : T(0);
+          if (two) b1[u] = HB ? ldo<T, T>(br, o1) : T(0);
         }
         pk[u] = ldo<int32_t, int>(ix, k * 4u);
         w0[u] = ldo<double, double>(wt, k * 8u);
-        w1[u] = ldo<double, double>(wt, (k + half) * 8u);
+        if (two) w1[u] = ldo<double, double>(wt, (k + half) * 8u);
       }
     }
 #pragma unroll
@@ -842,7 +867,8 @@ __device__ __forceinline__ void finish_cell(const GasP& g, const int32_t* __rest
         const double n0 = (double)h0[u] * inv + c0 * (E + O);
         const double n1 = (double)h1[u] * inv + c1 * (E - O);
         sto_nt<T>(ho, o0, (T)n0);
-        sto_nt<T>(ho, o1, (T)n1);
+        const bool two = !SPARSE || k < full;
+        if (two) sto_nt<T>(ho, o1, (T)n1);
         // heat flux of the new distribution about U^{n+1} (Eq. reduced_heat_flux)
         double x0[3], x1[3], e0 = 0.0, e1 = 0.0;
 #pragma unroll
@@ -858,7 +884,7 @@ __device__ __forceinline__ void finish_cell(const GasP& g, const int32_t* __rest
           const double m0 = (double)b0[u] * inv + c0 * (E + O);
           const double m1 = (double)b1[u] * inv + c1 * (E - O);
           sto_nt<T>(bo, o0, (T)m0);
-          sto_nt<T>(bo, o1, (T)m1);
+          if (two) sto_nt<T>(bo, o1, (T)m1);
           s0 += m0;
           s1 += m1;
         }
@@ -902,7 +928,7 @@ constexpr bool kBothPasses = D == 2 && sizeof(T) == 4 && !LIM;
 template <typename T, int D, bool LIM>
 constexpr int kCellWaves = sizeof(T) == 8 ? 4 : kBothPasses<T, D, LIM> ? 5 : 6;  // per SIMD
 
-template <int D, typename T, bool LIM, bool HB>
+template <int D, typename T, bool LIM, bool HB, bool SPARSE>
 __global__ __launch_bounds__(CELLT, (kCellWaves<T, D, LIM>)) void k_step_cell(
     SweepIn<T> in, SweepSched sc, int64_t nc, GasP g, const T* __restrict__ h, const T* __restrict__ b,
     T* ht, T* bt, CellOut o) {
@@ -915,10 +941,11 @@ __global__ __launch_bounds__(CELLT, (kCellWaves<T, D, LIM>)) void k_step_cell(
   const int64_t ic = ((local / sc.tile) * 8 + xcd) * sc.tile + local % sc.tile;
   if (ic >= nc || *o.flag) return;
   double mw[D + 2];
-  sweep_item<D, T, T, kBothPasses<T, D, LIM>, LIM, HB>(in, h, b, ht, bt, ic, 0u, in.half, L.s, stage, mw);
+  sweep_item<D, T, T, kBothPasses<T, D, LIM>, LIM, HB, SPARSE>(in, h, b, ht, bt, ic, 0u, in.half, L.s, stage,
+                                                               mw);
   block_total<D + 2>(mw, L.red);
-  finish_cell<D, T, T, HB>(g, in.vidx, in.w, o, ht, bt, ic, in.nvp, in.half, in.na, in.axis, stage, in.keep,
-                        mw, L.c, L.red);
+  finish_cell<D, T, T, HB, SPARSE>(g, in.vidx, in.w, o, ht, bt, ic, in.nvp, in.half, in.na, in.axis, stage,
+                                   in.keep, mw, L.c, L.red, in.full);
 }
 
 // Blocked form, for a mesh too small to fill the GPU with whole cells (or a
@@ -1618,6 +1645,7 @@ SweepIn<T> sweep_in(const FusedMesh& fm, const DevVel& v, const GasP& g, const S
   in.dt = g.dt;
   in.nvp = v.nvp;
   in.half = (unsigned)fm.half;
+  in.full = (unsigned)fm.full;
   in.na = fm.na;
   in.axis = fm.axis;
   if constexpr (sizeof(T) == 4) {
@@ -1675,8 +1703,12 @@ void launch_step_as(const DevMesh& m, const FusedMesh& fm, const DevVel& v, cons
   // resident work-group: 8.48 on the second.
   const int64_t pair = (HB ? 4 : 2) * (int64_t)sizeof(T);
   in.keep = kept_pairs(4 * kCellWaves<T, D, LIM>, sc, sizeof(SweepLds<D, T>), pair, in.half);
-  k_step_cell<D, T, LIM, HB><<<grid, sc.lanes, (size_t)in.keep * pair, s>>>(
-      in, sc, fm.nc, g, (const T*)B.h, (const T*)B.b, (T*)B.ht, (T*)B.bt, cell_out(m, B));
+  if (fm.sparse)
+    k_step_cell<D, T, LIM, HB, true><<<grid, sc.lanes, (size_t)in.keep * pair, s>>>(
+        in, sc, fm.nc, g, (const T*)B.h, (const T*)B.b, (T*)B.ht, (T*)B.bt, cell_out(m, B));
+  else
+    k_step_cell<D, T, LIM, HB, false><<<grid, sc.lanes, (size_t)in.keep * pair, s>>>(
+        in, sc, fm.nc, g, (const T*)B.h, (const T*)B.b, (T*)B.ht, (T*)B.bt, cell_out(m, B));
 }
 
 }  // namespace
