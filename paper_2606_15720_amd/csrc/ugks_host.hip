@@ -438,6 +438,7 @@ void build(ugks_ctx* c, const ugks_mesh* mesh, const ugks_velocity* vel, const u
   m.vol = upload(c, vol);
   m.cen = upload(c, cen);
   m.nfc = upload(c, nfc);
+  m.most = *std::max_element(nfc.begin(), nfc.end());
   m.cface = upload(c, cface);
   m.cnbr = upload(c, cnbr);
   m.csign = upload(c, csign);
@@ -521,6 +522,10 @@ void build(ugks_ctx* c, const ugks_mesh* mesh, const ugks_velocity* vel, const u
       }
     c->fmesh.nff = (int64_t)ffaces.size();
     c->fmesh.ffaces = upload(c, ffaces);
+    c->fmesh.apart = true;
+    for (int32_t f : walls)
+      for (int p = 0; p < nfc[fL[f]]; ++p)
+        if (ghost_row[cface[(int64_t)fL[f] * MAXF + p]] >= 0) c->fmesh.apart = false;
     c->fmesh.half = nvp / 2;
     c->fmesh.nr = c->nr;
     // the sweep reads one iteration ahead
@@ -868,7 +873,9 @@ void enqueue_step_fused(ugks_ctx* c, bool residual, bool face_flux) {
   TIMED(KK_FACE_EQ, launch_face_eq(D, m, c->bcs, g, B.W, B.gW, B.q, B.frec, R, c->nr, B.srec, B.flag, s));
   // 7 far-field ghost rows (the wall cells' stencils may read them), then
   // the wall densities
-  if (c->fmesh.nff)
+  // (in one launch where neither reads what the other writes)
+  const bool joint = c->fmesh.nff && c->fmesh.apart && m.nwall && !c->wide;
+  if (c->fmesh.nff && !joint)
     TIMED(KK_WALL, launch_ghost_rows(D, P, c->fmesh, v, B.frec, B.h, B.b, B.flag, s));
   // (with boundary-flux tracking the wall pass also keeps each wall face's flux)
   const bool track = (c->flags & 64) != 0;
@@ -882,8 +889,7 @@ void enqueue_step_fused(ugks_ctx* c, bool residual, bool face_flux) {
     swap_buffers(B);
     return;
   }
-  TIMED(KK_WALL, launch_wall_rho_inline(D, P, m, v, c->fmesh, g, B.h, B.frec, B.flag, s, track ? 1 : 0,
-                                        track ? (const void*)B.b : nullptr));
+  TIMED(KK_WALL, launch_wall_rho_inline(D, P, m, v, c->fmesh, g, B.h, B.b, B.frec, B.flag, s, track, joint));
   if (track) TIMED(KK_RESID, launch_bflux(D, m, B.frec, B.F, 0, B.bflux, B.flag, s));
   if (c->sched.whole) {
     // 5, 6.7-6.8, 8-11: the velocity sweep and the rest of every cell's step

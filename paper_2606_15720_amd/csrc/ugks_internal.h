@@ -42,6 +42,7 @@ struct DevMesh {
   const double* vol;        // [nc]
   const double* cen;        // [nc*3]
   const int32_t* nfc;       // [nc] faces per cell
+  int32_t most;             // faces of the cell with most
   const int32_t* cface;     // [nc*MAXF] face ids
   const int32_t* cnbr;      // [nc*MAXF] neighbour cell, -1 for a boundary face
   const double* csign;      // [nc*MAXF] +1 if the cell is L of the face, -1 if R
@@ -121,6 +122,7 @@ struct FusedMesh {
   const float* crec_l32 = nullptr; // its FP32 copy (FP32 compute form)
   const int32_t* ffaces;    // [nff] far-field / outflow faces; face m owns ghost row nc+1+m
   int64_t nff;
+  bool apart = false;              // no wall cell's stencil reads a ghost row
   const int32_t* frow = nullptr;   // wide cells: [nf] the row right of a face (cell, ghost row or zero row)
 };
 
@@ -290,9 +292,8 @@ hipError_t launch_face_flux(int D, int prec, const DevMesh& m, const FusedMesh& 
 hipError_t launch_finish(int D, int prec, const DevMesh& m, const FusedMesh& fm, const DevVel& v,
                          const GasP& g, const SweepSched& sc, const StepBuffers& B, hipStream_t s);
 hipError_t launch_wall_rho_inline(int D, int prec, const DevMesh& m, const DevVel& v,
-                                  const FusedMesh& fm, const GasP& g, const void* h, double* frec,
-                                  const int32_t* flag, hipStream_t s, int track = 0,
-                                  const void* b_bf = nullptr);
+                                  const FusedMesh& fm, const GasP& g, void* h, void* b, double* frec,
+                                  const int32_t* flag, hipStream_t s, bool track, bool ghosts);
 hipError_t launch_bflux(int D, const DevMesh& m, const double* frec, const double* F, int staged,
                         double* acc, const int32_t* flag, hipStream_t s);
 hipError_t launch_ghost_rows(int D, int prec, const FusedMesh& fm, const DevVel& v,
