@@ -211,7 +211,7 @@ __device__ __forceinline__ void cell_prep_at(int64_t i, const GasP& g, const dou
 }
 
 template <int D, typename T>
-__global__ void k_cell_prep(int64_t nc, GasP g, const double* __restrict__ W,
+__global__ __launch_bounds__(128) void k_cell_prep(int64_t nc, GasP g, const double* __restrict__ W,
                             const double* __restrict__ q, double* __restrict__ prim, int nr,
                             T* __restrict__ cs, int32_t* flag) {
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
@@ -1561,7 +1561,7 @@ __device__ __forceinline__ int case_of(const int64_t* __restrict__ off, int n, i
 
 // W^n, q -> prim, cs before the first step (the step itself leaves the next one's)
 template <int D, typename T>
-__global__ void k_cell_prep_b(BatchDev bd) {
+__global__ __launch_bounds__(128) void k_cell_prep_b(BatchDev bd) {
   const int64_t t = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (t >= bd.cell_off[bd.n]) return;
   const int c = case_of(bd.cell_off, bd.n, t);
