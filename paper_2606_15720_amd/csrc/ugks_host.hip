@@ -446,6 +446,10 @@ void build(ugks_ctx* c, const ugks_mesh* mesh, const ugks_velocity* vel, const u
   c->lsG_exact = lsG_true.empty() ? m.lsG : upload(c, lsG_true);
   m.fL = upload(c, fL);
   m.fR = upload(c, fR);
+  std::vector<int32_t> ford(nf);
+  for (int64_t f = 0; f < nf; ++f) ford[f] = (int32_t)f;
+  std::stable_sort(ford.begin(), ford.end(), [&](int32_t a, int32_t b) { return fL[a] < fL[b]; });
+  m.ford = upload(c, ford);
   m.fbc = upload(c, fbc);
   m.fbcid = upload(c, fbcid);
   m.farea = upload(c, farea);

@@ -48,6 +48,7 @@ struct DevMesh {
   const double* csign;      // [nc*MAXF] +1 if the cell is L of the face, -1 if R
   const double* lsG;        // [nc*3*MAXF] least-squares coefficients G[d][p]
   // faces
+  const int32_t* ford;      // [nf] the faces in the order of their left cells
   const int32_t* fL;        // [nf]
   const int32_t* fR;        // [nf] (-1 boundary)
   const int32_t* fbc;       // [nf]

@@ -605,7 +605,8 @@ __global__ __launch_bounds__(TPB) void k_flux(DevMesh m, DevVel v, GasP g,
                                               double* __restrict__ F, const int32_t* flag) {
   __shared__ double lds[5 * 16];
   if (*flag) return;
-  const int64_t f = blockIdx.x;
+  const int64_t f = face_of_block(m);
+  if (f < 0) return;
   const double* R = &frec[f * FREC];
   const int64_t nvp = v.nvp;
   double acc[5] = {0, 0, 0, 0, 0};
@@ -924,7 +925,7 @@ hipError_t launch_flux(int D, int prec, const DevMesh& m, const DevVel& v, const
                        const double* frec, const void* h, const void* b, const double* gh,
                        const double* gb, double* fh, double* fb, double* F, const int32_t* flag,
                        hipStream_t s) {
-  UGKS_DISPATCH_DT(D, prec, k_flux<DD, TT><<<(unsigned)m.nf, TPB, 0, s>>>(
+  UGKS_DISPATCH_DT(D, prec, k_flux<DD, TT><<<face_grid(m), TPB, 0, s>>>(
       m, v, g, frec, (const TT*)h, (const TT*)b, gh, gb, fh, fb, F, flag));
   return hipGetLastError();
 }

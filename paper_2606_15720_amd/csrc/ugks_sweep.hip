@@ -1223,7 +1223,8 @@ __global__ __launch_bounds__(SWT) void k_face_flux(DevMesh m, SweepIn<double> in
                                                    const int32_t* flag) {
   __shared__ double tab[D][NAX], red[5 * 16];
   if (*flag) return;
-  const int64_t f = blockIdx.x;
+  const int64_t f = face_of_block(m);
+  if (f < 0) return;
   const int na = in.na;
   const double* R = in.frec + f * FREC;
   const bool wall = m.fbc[f] == UGKS_BC_WALL;
@@ -1786,7 +1787,7 @@ hipError_t launch_step_wide(int D, int prec, const DevMesh& m, const FusedMesh& 
 hipError_t launch_face_flux(int D, int prec, const DevMesh& m, const FusedMesh& fm, const DevVel& v,
                             const GasP& g, const StepBuffers& B, hipStream_t s) {
   const SweepIn<double> in = sweep_in<double>(fm, v, g, B);
-  const unsigned nf = (unsigned)m.nf;
+  const unsigned nf = face_grid(m);
 #define UGKS_FACE_FLUX(DD, HB)                                                                       \
   UGKS_DISPATCH_T(prec, (k_face_flux<DD, TT, HB><<<nf, SWT, 0, s>>>(                                 \
                             m, in, fm.frow, (const TT*)B.h, (const TT*)B.b, B.gradh, B.gradb, B.F, B.flag)))
