@@ -52,7 +52,8 @@ FP32_VECTOR_TFLOPS = 78.6
 # Algorithmic FP64 flops of the sweep per cell-velocity update, 3-D tets,
 # N_r = 1 (an FMA counts 2): least-squares gradient 28, two face-velocity
 # fluxes (each face's flux serves its two cells) 2 x 69, moment sum 16,
-# first stage with the Shakhov equilibrium 51.
+# first stage with the Shakhov equilibrium 51.  (The kernel timed as the sweep
+# also does the rest of the cell's step, which these flops leave out.)
 SWEEP_FLOPS_PER_UPDATE_3D = 233
 METRIC = "cell-velocity updates/s on 1 GPU, % HBM peak; time to 1e-6 residual"
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "sweep_sod3d_48k_24cube_traffic.json")
@@ -99,9 +100,9 @@ def _step_traffic(precision: int):
 
 
 def _step_hbm(r, precision: int, updates: int, copy: dict):
-    """The whole step against HBM: algorithmic bytes (f read and written by
-    the sweep, read and written again by stage 2: 4 N_r P per update) and the
-    counters' bytes, over the measured step time; each also as a fraction of
+    """The whole step against HBM: algorithmic bytes (f read and written, and
+    the first stage's result written and read between, which the whole-cell
+    step keeps on chip in part: 4 N_r P per update) and the counters' bytes, over the measured step time; each also as a fraction of
     the measured copy bandwidth."""
     alg = 4 * (precision // 8) * updates
     sec = r["ms_per_step"] * 1e-3
@@ -187,8 +188,8 @@ def run_batched(steps: int, warmup: int):
     wall = time.perf_counter() - t
     info = b.info
     b.close()
-    # whole step against HBM: f read and written by the sweep and again by
-    # stage 2, 4 N_r P = 64 bytes per update in 2-D FP64 (h and b)
+    # whole step against HBM: f and the first stage's result, each read and
+    # written, 4 N_r P = 64 bytes per update in 2-D FP64 (h and b)
     alg_bytes = 64.0 * ups
     gbs = alg_bytes / (wall / steps) / 1e9
     return {"value": ups * steps / wall, "unit": "cell-velocity updates/s",

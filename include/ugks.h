@@ -138,10 +138,13 @@ typedef struct {
  * Options.
  *   precision  UGKS_FP64 (default when 0) or UGKS_FP32.
  *   block_v    velocity-block size B_v of the fused sweep: velocities per
- *              work item (a multiple of 64; 0 = 4096), the
- *              paper's B_v (Eq. velocity_block_partition) as a scheduling unit.
+ *              work item (a multiple of 64), the paper's B_v (Eq.
+ *              velocity_block_partition) as a scheduling unit.  0: a work
+ *              item is a cell with all of its velocities, which goes on with
+ *              the rest of the cell's step; on a mesh of fewer than 48 cells
+ *              blocks of 4096.
  *   tile_cells cells per tile of the fused sweep's schedule (0 = 32); each
- *              XCD runs one tile through one velocity block at a time.
+ *              XCD runs one tile (through one velocity block) at a time.
  *   flags      bit 0: skip the density residual (saves one small reduction).
  *              bit 1: use the staged sweep even where the fused one applies.
  *              bit 2: keep the caller's cell order internally (by default
@@ -176,9 +179,11 @@ typedef struct {
  *   subset of it, such as a locally refined set whose levels are lattices;
  *   a point whose mirror is absent is paired with a weight-0 pad slot), and
  *   every cell has at most 4 faces (far-field and outflow faces read
- *   per-step ghost rows holding the ghost Maxwellian).  Otherwise
- *   the staged sweep keeps the microscopic gradients and fluxes of the whole
- *   velocity space in device memory.
+ *   per-step ghost rows holding the ghost Maxwellian).  Cells of 5 to 8 faces
+ *   on such a set (48 cells or more, or up to 4096 velocities) keep the
+ *   microscopic gradients in device memory and do the rest in one pass;
+ *   otherwise the staged sweep keeps the gradients and fluxes of the whole
+ *   velocity space there.
  *   stream     hipStream_t to enqueue on, or NULL for a library-owned stream.
  *              A caller stream is borrowed, never destroyed.
  *   limiter    1 limits every least-squares gradient the step reconstructs
@@ -320,19 +325,20 @@ void ugks_destroy(ugks_ctx* ctx);
  * and boundary table, one dimension and one precision for all) advanced
  * together, one launch per phase of the step for the whole batch.  Scheduling
  * follows the paper's velocity-block work decomposition (Eq.
- * velocity_block_partition, Sec. 3): the velocity sweep is one persistent
- * launch walking a list of (case, cell, velocity block) work items, the
+ * velocity_block_partition, Sec. 3) with a cell's whole velocity set as the
+ * block: sweep and rest of the step are one persistent launch walking a list
+ * of (case, cell) work items, the
  * other phases flatten the cells, faces or wall faces of every case behind
  * case-offset tables, and the whole step is captured once into a HIP graph
  * and replayed.  Every case must qualify for the fused sweep (a tensor
  * product of one symmetric 1-D node set; any face kinds;
  * at most four faces per cell).
  *
- * The velocity-block size and the cell-tile size of each case, and the
- * lanes per work-group of the sweep, are chosen by an autotuner that times
- * the sweep on the device at create (options.block_v = 0 and tile_cells = 0)
- * unless the process-wide tuning cache already holds the case's shape; a
- * nonzero block_v / tile_cells fixes them for every case instead.
+ * The cell-tile size of each case and the lanes per work-group of the sweep
+ * are chosen by an autotuner that times the sweep on the device at create
+ * (options.block_v = 0 and tile_cells = 0) unless the process-wide tuning
+ * cache already holds the case's shape; a nonzero tile_cells fixes the tile
+ * for every case instead, a nonzero block_v only leaves the tuning out.
  * options.flags bit 3 runs the step eagerly (no graph); the other bits act
  * as for ugks_create.  options.stream as for ugks_create.
  */
@@ -352,7 +358,7 @@ typedef struct {
   int32_t dim;
   int32_t precision;
   int32_t threads;           /* lanes per work-group of the batched sweep */
-  int64_t work_items;        /* (case, cell, velocity block) items of one sweep */
+  int64_t work_items;        /* (case, cell) items of one sweep, with padding */
   int64_t grid;              /* persistent work-groups of the sweep */
   int32_t graph;             /* 1: steps replay a captured HIP graph */
   int32_t tuned;             /* 1: schedule from the autotuner (timed or cached) */

@@ -3,9 +3,10 @@
 // ugks_create validates the mesh and velocity set, renumbers nothing the
 // caller can see (all outputs come back in the caller's order), precomputes
 // the least-squares coefficients of every cell (unweighted, one row per face
-// neighbour or mirror ghost), pads the velocity set with zero-weight points
-// to a multiple of the velocity block, fixes the time step from the CFL bound
-// and allocates every device buffer once.  ugks_step only enqueues kernels.
+// neighbour or mirror ghost), lays the velocity set out in slots (mirror pairs
+// where it is symmetric; zero-weight pads to whole waves), fixes the time step
+// from the CFL bound and allocates every device buffer once.  ugks_step only
+// enqueues kernels and reads their status back.
 #include "ugks_host_util.h"
 
 #include <algorithm>
@@ -155,8 +156,9 @@ std::vector<int64_t> pair_slots(int D, const ugks_velocity* vel, const std::vect
 // velocity block.  Measured per step, whole cells against blocks of 4096: 6
 // cells x 28^3 130 / 128 us, 48 x 28^3 148 / 160, 384 x 28^3 193 / 226, 750 x
 // 20^3 135 / 150, 1,296 x 24^3 316 / 349, 2,058 x 28^3 736 / 737 us.
-constexpr int64_t kPinnedCells = 4 << 20;  // bytes of cell data read back through pinned memory, at most
 constexpr int64_t kWholeCells = 48;
+
+constexpr int64_t kPinnedCells = 4 << 20;  // bytes of cell data read back through pinned memory, at most
 
 // Lanes per work-group of the whole-cell form (one mirror pair each): four
 // pairs per lane where a cell has them, so that the item's fixed costs (tables,
@@ -749,12 +751,17 @@ void build(ugks_ctx* c, const ugks_mesh* mesh, const ugks_velocity* vel, const u
   B.ht = dalloc<char>(c, (size_t)trows * nvp * esz);
   B.b = c->nr == 2 ? (void*)dalloc<char>(c, (size_t)rows * nvp * esz) : nullptr;
   B.bt = c->nr == 2 ? (void*)dalloc<char>(c, (size_t)trows * nvp * esz) : nullptr;
-  HIP_TRY(hipMemset(B.h, 0, (size_t)rows * nvp * esz));
-  if (B.b) HIP_TRY(hipMemset(B.b, 0, (size_t)rows * nvp * esz));
+  // The initial state and each step write every slot of the cells' rows, but for
+  // the pads that a step of a sparse set leaves out.
+  auto clear = [&](void* f, int64_t from, int64_t to) {
+    if (f && to > from)
+      HIP_TRY(hipMemsetAsync((char*)f + (size_t)from * nvp * esz, 0, (size_t)(to - from) * nvp * esz, c->stream));
+  };
+  clear(B.h, nc, rows);
+  clear(B.b, nc, rows);
   if (c->slots()) {
-    // the zero row, and the pad slots of every row, which no step writes
-    HIP_TRY(hipMemset(B.ht, 0, (size_t)rows * nvp * esz));
-    if (B.bt) HIP_TRY(hipMemset(B.bt, 0, (size_t)rows * nvp * esz));
+    clear(B.ht, c->fmesh.sparse ? 0 : nc, rows);
+    clear(B.bt, c->fmesh.sparse ? 0 : nc, rows);
   }
   if (!c->fused) {
     // the staged sweep keeps every gradient and microscopic flux in HBM, the

@@ -60,6 +60,14 @@ __device__ __forceinline__ grow_t* srow(const T* p) {
   return g;
 }
 
+// The same of a pointer that need not be in scalar registers yet.
+template <typename T>
+__device__ __forceinline__ grow_t* srow_any(const T* p) {
+  const uint64_t a = (uint64_t)p;
+  return srow((const char*)((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(a >> 32)) << 32 |
+                            (uint32_t)__builtin_amdgcn_readfirstlane((int)a)));
+}
+
 // Per-cell and per-face records are read-only during the sweep; read
 // through the constant address space their wave-uniform loads are always
 // scalar loads, also where the record pointers themselves come from memory
@@ -1362,7 +1370,7 @@ __device__ __forceinline__ void wall_rho_at(int64_t wi, const DevMesh& m, const 
   crec_i_t* ci = (crec_i_t*)(fm.crec_i + L * CRI);
   crec_t<double>* cd = (crec_t<double>*)(fm.crec_d + L * CRD);
   crec_t<double>* cl = LIM ? (crec_t<double>*)(fm.crec_l + L * CRL) : nullptr;
-  auto row_of = [nvp](const T* base, int64_t r) { return srow(base + r * nvp); };
+  auto row_of = [nvp](const T* base, int64_t r) { return srow_any(base + r * nvp); };
   // value and u.gradient of the wall cell's reconstruction at the wall
   auto at_wall = [&](double fi, const double (&fs)[4], const double* u, double& ff, double& ug) {
     double gr[3] = {0, 0, 0};
@@ -1396,7 +1404,7 @@ __device__ __forceinline__ void wall_rho_at(int64_t wi, const DevMesh& m, const 
   grow_t *own = row_of(h, L), *rs[4];
 #pragma unroll
   for (int s = 0; s < 4; ++s) rs[s] = row_of(h, ci[CI_OWN + s]);
-  grow_t *wt = srow(v.w), *ix = srow(fm.vidx);
+  grow_t *wt = srow_any(v.w), *ix = srow_any(fm.vidx);
   double acc[2] = {0.0, 0.0};
   // with BF: the wall flux's moments, incident (time-integrated free transport
   // of the wall cell's h, and b in 2-D) and reflected (per unit rho_w dt)
