@@ -160,17 +160,24 @@ constexpr int64_t kWholeCells = 48;
 
 constexpr int64_t kPinnedCells = 4 << 20;  // bytes of cell data read back through pinned memory, at most
 
-// Lanes per work-group of the whole-cell form (one mirror pair each): four
-// pairs per lane where a cell has them, so that the item's fixed costs (tables,
-// sums, the new equilibrium) are spread, and more lanes than that only while
-// the cells do not fill the GPU's 4,096 resident waves.  Measured per step, by
-// lanes 64 / 128 / 256 / 512: 16,384 cells x 512 pairs FP32 0.343 / 0.317 /
-// 0.343 / 0.463 ms; 1,024 x 448 FP64 0.073 / 0.061 / 0.056 / 0.066 ms; 48,000 x
-// 6,912 FP64 - / - / 9.85 / 9.18 ms (1,024 lanes: slower by a tenth).
-int cell_lanes(int64_t nc, int64_t pairs) {
-  const int64_t waves = pairs / WAVE;
+// Lanes per work-group of the whole-cell form (one mirror pair each): enough
+// pairs per lane that the cell's fixed costs (tables, sums, the new
+// equilibrium) are spread, yet as much of the row as can be in the
+// work-groups' LDS and in flight; more lanes than that only while the cells do
+// not fill the GPU's 4,096 resident waves.  The lines lie where the next size
+// becomes faster, ms per step by lanes 64 / 128 / 256 / 512 (24,576 tets, and
+// 9,216 quads at 13 and 7 waves of pairs):
+//   FP64   4 waves 0.368 0.298 0.384 0.669;  7: 0.273 0.233 0.242 0.323;
+//         13: 0.494 0.423 0.390 0.466;  22: 1.377 1.041 0.978 1.228;
+//         54: - - 2.144 2.165;  63: - - 2.435 2.395
+//   FP32   7: 0.141 0.147 0.163 0.260;  8: 0.326 0.306 0.349 0.505;
+//         13: 0.236 0.218 0.237 0.331;  32 (48,000 tets): 1.834 1.572 1.524 1.768;
+//         83: - - 1.839 1.846;  172: - - 3.647 3.592
+int cell_lanes(int64_t nc, int64_t pairs, int prec) {
+  static const int64_t from[2][3] = {{3, 13, 58}, {8, 20, 128}};  // waves of pairs for 2, 4, 8 waves
+  const int64_t waves = pairs / WAVE, *line = from[prec == UGKS_FP32 ? 1 : 0];
   int64_t w = 1;
-  while (w < 8 && (8 * w <= waves || (nc * w < 4096 && 2 * w <= waves))) w *= 2;
+  for (int i = 0; i < 3 && (waves >= line[i] || (nc * w < 4096 && 2 * w <= waves)); ++i) w *= 2;
   return (int)(w * WAVE);
 }
 
@@ -571,7 +578,7 @@ void build(ugks_ctx* c, const ugks_mesh* mesh, const ugks_velocity* vel, const u
     c->fmesh.crec_i = upload(c, ci);
     c->fmesh.crec_d = upload(c, cdr);
     c->fmesh.frow = upload(c, frow);
-    c->sched.lanes = cell_lanes(nc, c->fmesh.half);
+    c->sched.lanes = cell_lanes(nc, c->fmesh.half, UGKS_FP64);
     c->sched.tile = 32;
   }
   if (c->fused) {
@@ -729,7 +736,7 @@ void build(ugks_ctx* c, const ugks_mesh* mesh, const ugks_velocity* vel, const u
     cp = std::max<int64_t>(std::min<int64_t>(32, npairs), std::min<int64_t>(cp, npairs));
     c->sched.whole = cp >= npairs || (!Bv && nc >= kWholeCells) ? 1 : 0;
     if (c->sched.whole) cp = npairs;
-    c->sched.lanes = cell_lanes(nc, npairs);
+    c->sched.lanes = cell_lanes(nc, npairs, prec);
     c->sched.chunk_pairs = cp;
     c->sched.nchunk = (npairs + cp - 1) / cp;
     c->sched.tile = tile ? tile : 32;
