@@ -259,6 +259,7 @@ int ugks_step(ugks_ctx* ctx, int32_t n_steps, double* residual_out);
  *   which = 2: the heat flux q of the current distributions (Eq.
  *              reduced_heat_flux), n_cells*dim
  *   out           caller buffer in the caller's cell order
+ * After a call that failed: those of the state that is kept.
  *   out_on_device 0: host pointer; 1: device pointer
  */
 int ugks_moments(ugks_ctx* ctx, int32_t which, double* out, int32_t out_on_device);

@@ -1527,14 +1527,14 @@ int ugks_moments(ugks_ctx* c, int32_t which, double* out, int32_t on_device) {
     if (which == 0) {
       HIP_TRY(hipMemcpyAsync(lib, c->buf.W, c->nc * ncol * sizeof(double), hipMemcpyDeviceToHost, c->stream));
     } else if (which == 1) {
-      double* tmp = c->buf.cellred;  // reuse: needs nc*(D+2) <= nc*3? no: use Wn scratch
-      tmp = c->buf.Wn;
+      double* tmp = c->buf.Wn;
       HIP_TRY(launch_moments(D, c->prec, c->mesh, c->vel, c->buf.h, c->buf.b, tmp, c->stream));
       HIP_TRY(hipMemcpyAsync(lib, tmp, c->nc * ncol * sizeof(double), hipMemcpyDeviceToHost, c->stream));
     } else if (which == 2) {
-      HIP_TRY(launch_prims(D, c->mesh, c->gas, c->buf.W, c->buf.prim, c->buf.flag, 0, c->stream));
-      HIP_TRY(launch_heatflux(D, c->prec, c->mesh, c->vel, c->buf.h, c->buf.b, c->buf.prim, c->buf.qn,
-                              c->buf.flag, c->stream));
+      // (of the state that is kept, after a failed call too)
+      HIP_TRY(launch_prims(D, c->mesh, c->gas, c->buf.W, c->buf.primn, nullptr, 0, c->stream));
+      HIP_TRY(launch_heatflux(D, c->prec, c->mesh, c->vel, c->buf.h, c->buf.b, c->buf.primn, c->buf.qn,
+                              nullptr, c->stream));
       HIP_TRY(hipMemcpyAsync(lib, c->buf.qn, c->nc * 3 * sizeof(double), hipMemcpyDeviceToHost, c->stream));
     } else {
       return set_err(c, UGKS_EINVAL, "which must be 0, 1 or 2");

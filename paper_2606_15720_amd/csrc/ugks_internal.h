@@ -178,7 +178,7 @@ struct StepBuffers {
   double* W;       // [nc*(D+2)] state W^n
   double* Wn;      // [nc*(D+2)] W^{n+1}
   double* prim;    // [nc*NPRIM] of W^n
-  double* primn;   // [nc*NPRIM] of W^{n+1} (staged form)
+  double* primn;   // [nc*NPRIM] of W^{n+1} (staged form); readouts' own
   double* q;       // [nc*3] heat flux of h^n
   double* qn;      // [nc*3] heat flux of h^{n+1} (fused path)
   double* gW;      // [nc*3*5]

@@ -23,17 +23,18 @@ __global__ void k_prims(int64_t nc, GasP g, const double* __restrict__ W, double
   if (i >= nc) return;
   if (check && *flag) return;
   bool ok = prim_of<D>(&W[i * (D + 2)], g, &prim[i * NPRIM]);
-  if (!ok) atomicOr(flag, 1);
+  if (!ok && flag) atomicOr(flag, 1);
 }
 
-// Heat flux q_i = 1/2 sum_k w_k c_k (|c_k|^2 h_ik + b_ik), c = u - U_i.
+// Heat flux q_i = 1/2 sum_k w_k c_k (|c_k|^2 h_ik + b_ik), c = u - U_i.  (A null
+// flag, here and above: a readout, which neither heeds nor raises an error.)
 template <int D, typename T>
 __global__ __launch_bounds__(TPB) void k_heatflux(DevVel v, const T* __restrict__ h,
                                                   const T* __restrict__ b,
                                                   const double* __restrict__ prim,
                                                   double* __restrict__ q, const int32_t* flag) {
   __shared__ double lds[3 * 16];
-  if (*flag) return;
+  if (flag && *flag) return;
   const int64_t i = blockIdx.x;
   const double* P = &prim[i * NPRIM];
   double acc[3] = {0.0, 0.0, 0.0};
@@ -96,14 +97,16 @@ __device__ __forceinline__ void gradW_at(int64_t t, const DevMesh& m, const DevB
                                          const GasP& g, const double* __restrict__ W,
                                          double* __restrict__ gW, int32_t* flag, int count) {
   constexpr int NV = D + 2;
-  // the first kernel of a step: takes over the error of the step before, and
-  // counts the steps begun without one (a failed step's results are dropped)
-  const bool bad = flag[0] | flag[2];
-  if (count && t == 0) {
-    if (bad) flag[0] = 1;
-    else flag[1] += 1;
+  // the first kernel of a step (count): takes over the error of the step before,
+  // and counts the steps begun without one (a failed step's results are dropped)
+  if (count) {
+    const bool bad = flag[0] | flag[2];
+    if (t == 0) {
+      if (bad) flag[0] = 1;
+      else flag[1] += 1;
+    }
+    if (bad) return;
   }
-  if (bad) return;
   const int64_t i = t / NV;
   const int v = (int)(t % NV);
   const int nfc = m.nfc[i];

@@ -876,7 +876,6 @@ int ugks_snapshot(ugks_ctx* c, float* feat, float* targ) {
     const int64_t nc = c->nc;
     float* fd = dalloc<float>(c, (size_t)nc * FS);
     float* td = dalloc<float>(c, (size_t)nc * FS);
-    HIP_TRY(launch_prims(D, c->mesh, c->gas, B.W, B.prim, B.flag, 0, s));
     DevMesh mg = c->mesh;
     mg.lsG = c->lsG_exact;  // features use the true gradient at any reconstruction order
     mg.limiter = 0;         // and unlimited

@@ -1,0 +1,79 @@
+"""What a context holds after a call that failed in the middle: the readouts are
+those of the state that is kept, bit for bit what single steps up to it give,
+however many steps were enqueued after the one that failed.  And a readout
+between two steps leaves them as they are."""
+
+import numpy as np
+import pytest
+
+import ugks_cases as uc
+from paper_2606_15720_amd.ugks import UGKS_ENUMERIC, Solver, UGKSError, ugks_snapshot
+
+pytestmark = pytest.mark.gpu
+
+STAGED = 2
+
+
+def _quads(cfl):
+    case = uc.cavity2d(n=8, nv=8, kn=0.05, lid=0.4)
+    case.gas.cfl = cfl
+    return case
+
+
+def _hexes(cfl):
+    mesh = uc.hex_box(5, 4, 4, grading=0.5, seed=5)
+    bcs = [uc.BC(uc.BC_WALL, 1.0, (0.0, 0.0 if s in (2, 3) else 0.3, 0.0), 1.0) for s in range(6)]
+    case = uc.Case("hexes", mesh, uc.midpoint_grid(8, 4.0, 3),
+                   uc.Gas(mu_ref=uc.hard_sphere_mu_ref(0.05), cfl=cfl), bcs, None, 0)
+    case.W0 = uc.uniform_W(mesh.n_cells, 3, 1.0, (0.1, 0.0, 0.0), 1.0)
+    case.W0 *= 1.0 + 0.2 * np.random.default_rng(3).uniform(-1, 1, (mesh.n_cells, 1))
+    return case
+
+
+def _until_it_fails(s, read):
+    """Single steps: what `read` gives after each, the last one of them having failed."""
+    seen = [read(s)]
+    for _ in range(200):
+        try:
+            s.step(1)
+        except UGKSError as e:
+            assert e.code == UGKS_ENUMERIC
+            return seen, read(s)
+        seen.append(read(s))
+    pytest.fail("the case did not fail")
+
+
+def _moments(s):
+    return [s.W(), s.moments(1), s.moments(2), *ugks_snapshot(s.h, s.nc)]
+
+
+@pytest.mark.parametrize("make,flags", [(_quads, 0), (_quads, STAGED), (_hexes, 0)])
+@pytest.mark.parametrize("cfl", [3.5, 5.0])
+def test_readouts_after_a_failure_are_those_of_the_kept_state(make, flags, cfl):
+    a = Solver(make(cfl), flags=flags)
+    seen, after = _until_it_fails(a, _moments)
+    good = len(seen) - 1
+    print("steps before the failure:", good, flush=True)
+    for x, y in zip(after, seen[-1]):
+        np.testing.assert_array_equal(x, y)
+    for more in (1, 2, 3):
+        b = Solver(make(cfl), flags=flags)
+        with pytest.raises(UGKSError):
+            b.step(good + more)
+        for x, y in zip(_moments(b), seen[-1]):
+            np.testing.assert_array_equal(x, y)
+        b.close()
+    a.close()
+
+
+@pytest.mark.parametrize("make", [_quads, _hexes])
+def test_a_readout_leaves_the_next_step_as_it_is(make):
+    a, b = Solver(make(0.5)), Solver(make(0.5))
+    for n in (1, 2):
+        a.step(n)
+        b.step(n)
+        _moments(a)
+    for x, y in zip(a.state(), b.state()):
+        np.testing.assert_array_equal(x, y)
+    a.close()
+    b.close()
