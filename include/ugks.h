@@ -269,7 +269,8 @@ int ugks_moments(ugks_ctx* ctx, int32_t which, double* out, int32_t out_on_devic
  * create (or the last ugks_set_state), for balance checks (Eq. macro_update
  * summed over the cells: sum_i V_i W_i^n - sum_i V_i W_i^0 + A = 0 up to
  * rounding, A = sum over steps and boundary faces of S_f F_f, F_f the face's
- * time-integrated flux of mass, momentum and energy, Eq. macro_flux).
+ * time-integrated flux of mass, momentum and energy, Eq. macro_flux; a step
+ * that failed is left out).
  * Needs options.flags bit 6 (boundary-flux tracking) at create: the wall
  * pass then also keeps each wall face's flux (fused sweep) or the staged
  * sweep's face fluxes are summed, one small reduction per step.

@@ -901,14 +901,13 @@ void enqueue_step_fused(ugks_ctx* c, bool residual, bool face_flux) {
     TIMED(KK_GRAD_MICRO, launch_grad_micro(D, P, m, v, B.frec, B.h, B.b, B.gradh, B.gradb, B.flag, s));
     TIMED(KK_WALL, launch_wall_rho(D, P, m, v, g, B.h, B.gradh, B.frec, B.flag, s));
     if (face_flux || track) TIMED(KK_FLUX, launch_face_flux(D, P, m, c->fmesh, v, g, B, s));
-    if (track) TIMED(KK_RESID, launch_bflux(D, m, B.frec, B.F, 1, B.bflux, B.flag, s));
     TIMED(KK_SWEEP, launch_step_wide(D, P, m, c->fmesh, v, g, c->sched, B, s));
+    if (track) TIMED(KK_RESID, launch_bflux(D, m, B.frec, B.F, 1, B.bflux, B.flag, s));
     if (residual) TIMED(KK_RESID, launch_residual(m, B.cellred, B.resid, B.flag, s));
     swap_buffers(B);
     return;
   }
   TIMED(KK_WALL, launch_wall_rho_inline(D, P, m, v, c->fmesh, g, B.h, B.b, B.frec, B.flag, s, track, joint));
-  if (track) TIMED(KK_RESID, launch_bflux(D, m, B.frec, B.F, 0, B.bflux, B.flag, s));
   if (c->sched.whole) {
     // 5, 6.7-6.8, 8-11: the velocity sweep and the rest of every cell's step
     TIMED(KK_SWEEP, launch_step_cell(D, P, m, c->fmesh, v, g, c->sched, B, s));
@@ -919,6 +918,7 @@ void enqueue_step_fused(ugks_ctx* c, bool residual, bool face_flux) {
     // second stage and the heat flux of h^{n+1}
     TIMED(KK_STAGE2, launch_finish(D, P, m, c->fmesh, v, g, c->sched, B, s));
   }
+  if (track) TIMED(KK_RESID, launch_bflux(D, m, B.frec, B.F, 0, B.bflux, B.flag, s));
   if (residual) TIMED(KK_RESID, launch_residual(m, B.cellred, B.resid, B.flag, s));
   swap_buffers(B);
 }
@@ -949,13 +949,13 @@ void enqueue_step(ugks_ctx* c, bool residual, bool face_flux) {
   // 6.7-6.8 microscopic fluxes and their moments
   TIMED(KK_FLUX, launch_flux(D, P, m, v, g, B.frec, B.h, B.b, B.gradh, B.gradb, B.fluxh, B.fluxb,
                               B.F, B.flag, s));
-  if (c->flags & 64) TIMED(KK_RESID, launch_bflux(D, m, B.frec, B.F, 1, B.bflux, B.flag, s));
   // 9 first stage
   TIMED(KK_STAGE1, launch_stage1(D, P, m, v, g, B.prim, B.q, B.h, B.b, B.fluxh, B.fluxb, B.ht,
                                 B.bt, B.flag, s));
   // 8 conservative update, 10 new equilibrium
   TIMED(KK_MACRO, launch_macro_update(D, m, g, B.W, B.F, B.Wn, B.cellred, B.flag, s));
   TIMED(KK_PRIMS, launch_prims(D, m, g, B.Wn, B.primn, B.flag, 1, s));
+  if (c->flags & 64) TIMED(KK_RESID, launch_bflux(D, m, B.frec, B.F, 1, B.bflux, B.flag, s));
   // 11 second stage
   TIMED(KK_STAGE2, launch_stage2(D, P, m, v, g, B.primn, B.q, B.ht, B.bt, B.h, B.b, B.flag, s));
   // 12 residual, commit W^{n+1}

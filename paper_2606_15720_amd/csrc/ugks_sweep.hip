@@ -1825,13 +1825,14 @@ hipError_t launch_wall_rho_inline(int D, int prec, const DevMesh& m, const DevVe
 // The step's boundary flux, added to the running sum acc[0..D+1]: the sum
 // over boundary faces of S_f F_f, from the wall records' fluxes (fused path,
 // FR_BF) or from the face fluxes (staged path, every boundary face).  One
-// work-group; each lane adds its faces in order, then a fixed reduction.
+// work-group; each lane adds its faces in order, then a fixed reduction.  Run
+// after the rest of the step, so that a failed step's flux is left out.
 template <int D>
 __global__ __launch_bounds__(256) void k_bflux(DevMesh m, const double* __restrict__ frec,
                                                const double* __restrict__ F, int staged,
                                                double* __restrict__ acc, const int32_t* flag) {
   __shared__ double red[5 * 16];
-  if (*flag) return;
+  if (flag[0] | flag[2]) return;
   double s[D + 2];
   for (int x = 0; x < D + 2; ++x) s[x] = 0.0;
   if (staged) {

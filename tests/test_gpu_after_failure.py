@@ -11,7 +11,7 @@ from paper_2606_15720_amd.ugks import UGKS_ENUMERIC, Solver, UGKSError, ugks_sna
 
 pytestmark = pytest.mark.gpu
 
-STAGED = 2
+STAGED, TRACK = 2, 64
 
 
 def _quads(cfl):
@@ -77,3 +77,18 @@ def test_a_readout_leaves_the_next_step_as_it_is(make):
         np.testing.assert_array_equal(x, y)
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("make,flags", [(_quads, 0), (_quads, STAGED), (_hexes, 0)])
+@pytest.mark.parametrize("cfl", [3.5, 5.0])
+def test_the_boundary_flux_leaves_the_failed_step_out(make, flags, cfl):
+    a = Solver(make(cfl), flags=flags | TRACK)
+    seen, after = _until_it_fails(a, lambda s: s.boundary_flux()[0])
+    np.testing.assert_array_equal(after, seen[-1])
+    for more in (1, 2, 3):
+        b = Solver(make(cfl), flags=flags | TRACK)
+        with pytest.raises(UGKSError):
+            b.step(len(seen) - 1 + more)
+        np.testing.assert_array_equal(b.boundary_flux()[0], seen[-1])
+        b.close()
+    a.close()
