@@ -923,6 +923,28 @@ void enqueue_step_fused(ugks_ctx* c, bool residual, bool face_flux) {
   swap_buffers(B);
 }
 
+// The face fluxes of wide cells after a call that failed in the middle: such a
+// call had not come to its last step, the one that computes them.  They are the
+// failed step's, as the staged sweep leaves them: that step's records again, from
+// the kept state.
+void face_flux_after_failure(ugks_ctx* c) {
+  StepBuffers B = c->buf;
+  const int D = c->D, P = c->prec;
+  hipStream_t s = c->stream;
+  int32_t* const flags = B.flag;
+  int32_t* const flag = B.flag = flags + 3;  // one of its own, which nothing raises
+  hipError_t e = launch_gradW(D, c->mesh, c->bcs, c->gas, B.W, B.gW, flags, 0, s);
+  if (e == hipSuccess)
+    e = launch_face_eq(D, c->mesh, c->bcs, c->gas, B.W, B.gW, B.q, B.frec, UGKS_FP64, c->nr, B.srec, flag, s);
+  if (e == hipSuccess) e = launch_ghost_rows(D, P, c->fmesh, c->vel, B.frec, B.h, B.b, flag, s);
+  if (e == hipSuccess)
+    e = launch_grad_micro(D, P, c->mesh, c->vel, B.frec, B.h, B.b, B.gradh, B.gradb, flag, s);
+  if (e == hipSuccess) e = launch_wall_rho(D, P, c->mesh, c->vel, c->gas, B.h, B.gradh, B.frec, flag, s);
+  if (e == hipSuccess) e = launch_face_flux(D, P, c->mesh, c->fmesh, c->vel, c->gas, B, s);
+  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  if (e != hipSuccess) throw HipFail{e, "face fluxes after a failure"};
+}
+
 // One time step, enqueued (the one-step algorithm).
 void enqueue_step(ugks_ctx* c, bool residual, bool face_flux) {
   if (c->slots()) {
@@ -1502,6 +1524,7 @@ int ugks_step(ugks_ctx* c, int32_t n_steps, double* residual_out) {
       // the failure.
       const int32_t done = std::max(0, begun - 1);
       if (c->slots() && ((n_steps - done) & 1)) swap_buffers(c->buf);
+      if (c->wide && begun > 0 && !(flag[0] & 2)) face_flux_after_failure(c);
       return set_err(c, UGKS_ENUMERIC, "non-positive density or temperature (flag " +
                                            std::to_string(flag[0] | flag[2]) + ")");
     }
