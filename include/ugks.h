@@ -293,7 +293,8 @@ int ugks_set_state(ugks_ctx* ctx, const double* W, const double* h, const double
 
 /*
  * ugks_face_data - diagnostics of the last step, caller face order:
- *   F[n_faces*(dim+2)] macroscopic time-integrated face fluxes (Eq. macro_flux)
+ *   F[n_faces*(dim+2)] macroscopic time-integrated face fluxes (Eq. macro_flux);
+ *                      0 on the fused sweep, which forms no sums per face
  *   rho_w[n_faces]     wall densities (Eq. wall_density_condition), 0 off walls
  * Either pointer may be NULL.  Host buffers.
  */

@@ -785,6 +785,7 @@ void build(ugks_ctx* c, const ugks_mesh* mesh, const ugks_velocity* vel, const u
   B.flag = (int32_t*)(B.resid + 8);
   B.bflux = dalloc<double>(c, 5);
   HIP_TRY(hipMemsetAsync(B.frec, 0, nf * FREC * sizeof(double), c->stream));
+  HIP_TRY(hipMemsetAsync(B.F, 0, nf * 5 * sizeof(double), c->stream));
   HIP_TRY(hipMemsetAsync(B.resid, 0, kStatus * sizeof(double), c->stream));
   HIP_TRY(hipMemsetAsync(B.bflux, 0, 5 * sizeof(double), c->stream));
   // Results go to the caller through pinned memory: to pageable memory each copy

@@ -116,3 +116,14 @@ def test_face_fluxes_of_wide_cells_after_a_failure(cfl):
         b.close()
     a.close()
     c.close()
+
+
+def test_face_fluxes_are_never_what_memory_held():
+    case = uc.cavity2d(n=6, nv=8)
+    s = Solver(case)
+    s.step(2)
+    assert not s.faces()[0].any()
+    s.close()
+    s = Solver(_hexes(0.5))
+    assert not s.faces()[0].any()
+    s.close()
