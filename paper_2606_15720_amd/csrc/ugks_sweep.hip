@@ -597,7 +597,11 @@ __device__ __forceinline__ void sweep_pass(const SweepIn<C>& in, const T* __rest
       };
       const C G1 = R[0][0], G2 = R[0][1];
       const C eqm = fd(18);  // 0 on a wall: no equilibrium term going out
-      const C sas = fd(19) * fabs(sp[p]);  // S/V |u.n|
+      // S/V |u.n|, in FP32 as two factors of every flux: their product rounded
+      // beforehand is an error that each step repeats (state after 10 steps against
+      // the FP64 form's: tets 0.7 % further off so, limited cylinder flow 4 %)
+      const C as = fabs(sp[p]), sv = sizeof(C) == 4 ? fd(19) : C(1);
+      const C sas = sizeof(C) == 4 ? as : fd(19) * as;
       // g0 (or the scaled wall Maxwellian) at u and -u from the axis tables
       C e0, e1;
       tab_pair(L.tab[p][0], at[0], e0, e1);
@@ -652,7 +656,7 @@ __device__ __forceinline__ void sweep_pass(const SweepIn<C>& in, const T* __rest
           C ff = fo;
 #pragma unroll
           for (int d = 0; d < D; ++d) ff += fd(d) * go[d];
-          acco += sas * (G1 * ff + G2 * ugo + eqm * eqo);
+          acco += sv * (sas * (G1 * ff + G2 * ugo + eqm * eqo));
         };
         auto into = [&](C fj, C fi, C su, C eqi, C& acci) {
           C gj[D];
@@ -668,7 +672,7 @@ __device__ __forceinline__ void sweep_pass(const SweepIn<C>& in, const T* __rest
             ffj += fd(3 + d) * gj[d];
             ugj += vv[d] * gj[d];
           }
-          acci -= sas * (G1 * ffj + G2 * (su * ugj) + eqi);
+          acci -= sv * (sas * (G1 * ffj + G2 * (su * ugj) + eqi));
         };
         if (sp[p] > C(0)) {
           out(f0[r], g0[r], ug0[r], q0, acc0[r]);
