@@ -753,7 +753,8 @@ void build(ugks_ctx* c, const ugks_mesh* mesh, const ugks_velocity* vel, const u
   // row nc of h and b stays zero: the fused sweep's wall faces read it;
   // rows nc+1 ... are the fused sweep's far-field ghost rows.  On the fused
   // path h and ht (b and bt) trade places every step, so both have them.
-  const int64_t rows = nc + 1 + (c->slots() ? c->fmesh.nff : 0), trows = c->slots() ? rows : nc;
+  // (The wide form's ghost rows are FP64 arrays of their own.)
+  const int64_t rows = nc + 1 + (c->fused ? c->fmesh.nff : 0), trows = c->slots() ? rows : nc;
   B.h = dalloc<char>(c, (size_t)rows * nvp * esz);
   B.ht = dalloc<char>(c, (size_t)trows * nvp * esz);
   B.b = c->nr == 2 ? (void*)dalloc<char>(c, (size_t)rows * nvp * esz) : nullptr;
@@ -775,6 +776,10 @@ void build(ugks_ctx* c, const ugks_mesh* mesh, const ugks_velocity* vel, const u
     // wide cells' step the gradients
     B.gradh = dalloc<double>(c, (size_t)nc * 3 * nvp);
     B.gradb = c->nr == 2 ? dalloc<double>(c, (size_t)nc * 3 * nvp) : nullptr;
+  }
+  if (c->wide && c->fmesh.nff) {
+    B.ghosth = dalloc<double>(c, (size_t)c->fmesh.nff * nvp);
+    B.ghostb = c->nr == 2 ? dalloc<double>(c, (size_t)c->fmesh.nff * nvp) : nullptr;
   }
   if (!c->slots()) {
     B.fluxh = dalloc<double>(c, (size_t)nf * nvp);
@@ -894,8 +899,10 @@ void enqueue_step_fused(ugks_ctx* c, bool residual, bool face_flux) {
   // the wall densities
   // (in one launch where neither reads what the other writes)
   const bool joint = c->fmesh.nff && c->fmesh.apart && m.nwall && !c->wide;
-  if (c->fmesh.nff && !joint)
-    TIMED(KK_WALL, launch_ghost_rows(D, P, c->fmesh, v, B.frec, B.h, B.b, B.flag, s));
+  if (c->fmesh.nff && c->wide)
+    TIMED(KK_WALL, launch_ghost_rows(D, UGKS_FP64, c->fmesh, v, B.frec, 0, B.ghosth, B.ghostb, B.flag, s));
+  else if (c->fmesh.nff && !joint)
+    TIMED(KK_WALL, launch_ghost_rows(D, P, c->fmesh, v, B.frec, m.nc + 1, B.h, B.b, B.flag, s));
   // (with boundary-flux tracking the wall pass also keeps each wall face's flux)
   const bool track = (c->flags & 64) != 0;
   if (c->wide) {
@@ -937,7 +944,8 @@ void face_flux_after_failure(ugks_ctx* c) {
   hipError_t e = launch_gradW(D, c->mesh, c->bcs, c->gas, B.W, B.gW, flags, 0, s);
   if (e == hipSuccess)
     e = launch_face_eq(D, c->mesh, c->bcs, c->gas, B.W, B.gW, B.q, B.frec, UGKS_FP64, c->nr, B.srec, flag, s);
-  if (e == hipSuccess) e = launch_ghost_rows(D, P, c->fmesh, c->vel, B.frec, B.h, B.b, flag, s);
+  if (e == hipSuccess)
+    e = launch_ghost_rows(D, UGKS_FP64, c->fmesh, c->vel, B.frec, 0, B.ghosth, B.ghostb, flag, s);
   if (e == hipSuccess)
     e = launch_grad_micro(D, P, c->mesh, c->vel, B.frec, B.h, B.b, B.gradh, B.gradb, flag, s);
   if (e == hipSuccess) e = launch_wall_rho(D, P, c->mesh, c->vel, c->gas, B.h, B.gradh, B.frec, flag, s);

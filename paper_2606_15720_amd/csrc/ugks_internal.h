@@ -88,8 +88,8 @@ constexpr int CRD = 112, CD_N = 0, CD_G = 16, CD_F0 = 32, CD_FS = 20;
 constexpr int CRL = 88, CRL_F0 = 8, CRL_FS = 20;
 // Records of cells with more than four faces (the wide form of the fused
 // step, up to MAXF faces, FP64), in the same arrays with strides CRI and CRD:
-//   [WI_ROW + p] the row across face p (a neighbour, its ghost row, or the zero
-//   row at a wall); [WI_FACE + p]; [WI_KIND + p]; [WI_NF] the cell's faces;
+//   [WI_ROW + p] the row across face p (a neighbour, the zero row nc at a wall, or
+//   nc + 1 + m for row m of the ghost rows, which are FP64 arrays of their own); [WI_FACE + p]; [WI_KIND + p]; [WI_NF] the cell's faces;
 //   face p at WD_FS p: [0..2] outward unit normal, [3..5] x_f - x_cell,
 //   [6..8] x_f - x_neighbour, [9] as [18] above, [10] S/V.
 constexpr int WI_ROW = 0, WI_FACE = 8, WI_KIND = 16, WI_NF = 24;
@@ -194,6 +194,8 @@ struct StepBuffers {
   void* bt;
   double* gradh;   // [nc*3*nvp] microscopic gradients (staged sweep)
   double* gradb;
+  double* ghosth;  // [nff*nvp] ghost rows of wide cells
+  double* ghostb;
   double* fluxh;   // [nf*nvp] time-integrated microscopic fluxes (staged sweep)
   double* fluxb;
   double* resid;   // [8] residual accumulators and state, then flag: one block, read back in one copy
@@ -298,8 +300,8 @@ hipError_t launch_wall_rho_inline(int D, int prec, const DevMesh& m, const DevVe
 hipError_t launch_bflux(int D, const DevMesh& m, const double* frec, const double* F, int staged,
                         double* acc, const int32_t* flag, hipStream_t s);
 hipError_t launch_ghost_rows(int D, int prec, const FusedMesh& fm, const DevVel& v,
-                             const double* frec, void* h, void* b, const int32_t* flag,
-                             hipStream_t s);
+                             const double* frec, int64_t first, void* h, void* b,
+                             const int32_t* flag, hipStream_t s);
 
 // batched forms (one launch per phase over every case of a batch)
 hipError_t launch_cell_prep_b(int D, int prec, const BatchDev& bd, int64_t ncell, hipStream_t s);

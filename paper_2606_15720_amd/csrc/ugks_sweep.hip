@@ -1071,7 +1071,8 @@ constexpr int WGF = 3;
 
 template <int D, typename T, bool HB, int X>
 __device__ __forceinline__ void wide_pass(const SweepIn<double>& in, const T* __restrict__ f,
-                                          const double* __restrict__ gr, T* __restrict__ ft, int64_t ic,
+                                          const double* __restrict__ gr, const double* __restrict__ gg,
+                                          T* __restrict__ ft, int64_t ic, int32_t ghost0,
                                           const SweepTabs<D, double, MAXF>& L, T* stage,
                                           double (&mw)[D + 2]) {
   typedef double C;
@@ -1126,7 +1127,9 @@ __device__ __forceinline__ void wide_pass(const SweepIn<double>& in, const T* __
           for (int d = 0; d < D; ++d) s += vv[d] * cd[WD_FS * p + d];
           sp[p] = s;
           const int32_t row = ci[WI_ROW + p];
-          fj[p] = ldo<T, C>(row_of(row), s > 0.0 ? o1 : o0);  // u.n > 0: the incoming member is -u
+          // u.n > 0: the incoming member is -u
+          if (row < ghost0) fj[p] = ldo<T, C>(row_of(row), s > 0.0 ? o1 : o0);
+          else fj[p] = ldo<double, C>(srow((const char*)gg + (uint64_t)(uint32_t)(row - ghost0) * growb), s > 0.0 ? q1 : q0);
           if (ci[WI_KIND + p] == UGKS_BC_INTERIOR) {
 #pragma unroll
             for (int d = 0; d < D; ++d) gj[p][d] = ldo<double, C>(grad_of(row, d), s > 0.0 ? q1 : q0);
@@ -1202,7 +1205,9 @@ template <int D, typename T, bool HB>
 __global__ __launch_bounds__(CELLT, 4) void k_step_wide(SweepIn<double> in, SweepSched sc, int64_t nc, GasP g,
                                                         const T* __restrict__ h, const T* __restrict__ b,
                                                         const double* __restrict__ gh,
-                                                        const double* __restrict__ gb, T* ht, T* bt,
+                                                        const double* __restrict__ gb,
+                                                        const double* __restrict__ hg,
+                                                        const double* __restrict__ bg, T* ht, T* bt,
                                                         CellOut o) {
   __shared__ SweepLds<D, double, MAXF> L;
   extern __shared__ __attribute__((aligned(16))) char stage_lds[];
@@ -1215,8 +1220,9 @@ __global__ __launch_bounds__(CELLT, 4) void k_step_wide(SweepIn<double> in, Swee
   double mw[D + 2];
 #pragma unroll
   for (int x = 0; x < D + 2; ++x) mw[x] = 0.0;
-  wide_pass<D, T, HB, 0>(in, h, gh, ht, ic, L.s, stage, mw);
-  if constexpr (HB) wide_pass<D, T, HB, 1>(in, b, gb, bt, ic, L.s, stage, mw);
+  const int32_t ghost0 = (int32_t)nc + 1;
+  wide_pass<D, T, HB, 0>(in, h, gh, hg, ht, ic, ghost0, L.s, stage, mw);
+  if constexpr (HB) wide_pass<D, T, HB, 1>(in, b, gb, bg, bt, ic, ghost0, L.s, stage, mw);
   block_total<D + 2>(mw, L.red);
   finish_cell<D, T, double, HB>(g, in.vidx, in.w, o, ht, bt, ic, in.nvp, in.half, in.na, in.axis, stage,
                                 in.keep, mw, L.c, L.red);
@@ -1231,7 +1237,9 @@ __global__ __launch_bounds__(SWT) void k_face_flux(DevMesh m, SweepIn<double> in
                                                    const int32_t* __restrict__ frow,
                                                    const T* __restrict__ h, const T* __restrict__ b,
                                                    const double* __restrict__ gh,
-                                                   const double* __restrict__ gb, double* __restrict__ F,
+                                                   const double* __restrict__ gb,
+                                                   const double* __restrict__ hg,
+                                                   const double* __restrict__ bg, double* __restrict__ F,
                                                    const int32_t* flag) {
   __shared__ double tab[D][NAX], red[5 * 16];
   if (*flag) return;
@@ -1247,7 +1255,7 @@ __global__ __launch_bounds__(SWT) void k_face_flux(DevMesh m, SweepIn<double> in
     tab[d][n] = sc * exp(-R[FR_LAM] * c * c);
   }
   __syncthreads();
-  const int64_t Lc = m.fL[f], Rr = frow[f], nvp = in.nvp;
+  const int64_t Lc = m.fL[f], Rr = frow[f], nvp = in.nvp, gm = Rr - m.nc - 1;  // gm: ghost row
   const bool inner = m.fbc[f] == UGKS_BC_INTERIOR;
   double n[3], dL[3], dR[3];
   for (int d = 0; d < 3; ++d) {
@@ -1276,7 +1284,8 @@ __global__ __launch_bounds__(SWT) void k_face_flux(DevMesh m, SweepIn<double> in
       const T* fv = r ? b : h;
       const double* gr = r ? gb : gh;
       const double* S = in.srec + (f * (HB ? 2 : 1) + r) * SREC;
-      double fl = ld(fv, Lc * nvp + kl), fr = ld(fv, Rr * nvp + kr), ul = 0.0, ur = 0.0;
+      double fl = ld(fv, Lc * nvp + kl), ul = 0.0, ur = 0.0;
+      double fr = gm >= 0 ? (r ? bg : hg)[gm * nvp + kr] : ld(fv, Rr * nvp + kr);
 #pragma unroll
       for (int d = 0; d < D; ++d) {
         const double a = gr[(Lc * 3 + d) * nvp + kl];
@@ -1510,11 +1519,11 @@ __device__ __forceinline__ void wall_rho_at(int64_t wi, const DevMesh& m, const 
   }
 }
 
-// Ghost rows of the far-field / outflow faces: the Maxwellian of the face's
+// Ghost rows of the far-field / outflow faces, from row `first` of h and b on: the Maxwellian of the face's
 // ghost state W_g (written by the interface-equilibrium pass), h and, where
 // b is stored, b = K_xi/(2 lambda_g) h, so the sweep reads them as neighbour rows.
 template <int D, typename T>
-__device__ __forceinline__ void ghost_row_at(int64_t m, int64_t nc, const int32_t* __restrict__ ffaces,
+__device__ __forceinline__ void ghost_row_at(int64_t m, int64_t first, const int32_t* __restrict__ ffaces,
                                              const DevVel& v, const double* __restrict__ frec,
                                              T* __restrict__ h, T* __restrict__ b,
                                              const int32_t* flag) {
@@ -1522,7 +1531,7 @@ __device__ __forceinline__ void ghost_row_at(int64_t m, int64_t nc, const int32_
   const double* R = &frec[(int64_t)ffaces[m] * FREC];
   const double C = R[FR_GC], lam = R[FR_GLAM];
   const double U[3] = {R[FR_GU], R[FR_GU + 1], R[FR_GU + 2]};
-  const int64_t row = (nc + 1 + m) * v.nvp;
+  const int64_t row = (first + m) * v.nvp;
   for (int64_t k = threadIdx.x; k < v.nvp; k += blockDim.x) {
     double c2 = 0.0;
     for (int d = 0; d < D; ++d) {
@@ -1548,16 +1557,16 @@ __global__ __launch_bounds__(WALLT) void k_wall_rho_inline(DevMesh m, DevVel v, 
                                                          T* h, T* b, double* frec, const int32_t* flag) {
   __shared__ WallLds S;
   const int64_t ghost = (int64_t)blockIdx.x - m.nwall;
-  if (ghost >= 0) ghost_row_at<D, T>(ghost, m.nc, fm.ffaces, v, frec, h, b, flag);
+  if (ghost >= 0) ghost_row_at<D, T>(ghost, m.nc + 1, fm.ffaces, v, frec, h, b, flag);
   else wall_rho_at<D, T, LIM, BF>(blockIdx.x, m, v, fm, g, h, frec, flag, S, b);
 }
 
 template <int D, typename T>
-__global__ __launch_bounds__(SWT) void k_ghost_rows(int64_t nc, const int32_t* __restrict__ ffaces,
+__global__ __launch_bounds__(SWT) void k_ghost_rows(int64_t first, const int32_t* __restrict__ ffaces,
                                                     DevVel v, const double* __restrict__ frec,
                                                     T* __restrict__ h, T* __restrict__ b,
                                                     const int32_t* flag) {
-  ghost_row_at<D, T>(blockIdx.x, nc, ffaces, v, frec, h, b, flag);
+  ghost_row_at<D, T>(blockIdx.x, first, ffaces, v, frec, h, b, flag);
 }
 
 // ---- batched forms: one launch covers every case of a batch ---------------
@@ -1588,7 +1597,7 @@ __global__ __launch_bounds__(SWT) void k_ghost_rows_b(BatchDev bd) {
   const int64_t t = blockIdx.x;
   const int c = case_of(bd.ff_off, bd.n, t);
   const CaseDev& C = bd.cases[c];
-  ghost_row_at<D, T>(t - bd.ff_off[c], C.m.nc, C.fm.ffaces, C.v, C.B.frec, (T*)C.B.h, (T*)C.B.b,
+  ghost_row_at<D, T>(t - bd.ff_off[c], C.m.nc + 1, C.fm.ffaces, C.v, C.B.frec, (T*)C.B.h, (T*)C.B.b,
                      C.B.flag);
 }
 
@@ -1783,7 +1792,8 @@ void launch_wide_as(const DevMesh& m, const FusedMesh& fm, const DevVel& v, cons
   const int64_t pair = (HB ? 4 : 2) * (int64_t)sizeof(T);
   in.keep = kept_pairs(16, sc, sizeof(SweepLds<D, double, MAXF>), pair, in.half);
   k_step_wide<D, T, HB><<<grid, sc.lanes, (size_t)in.keep * pair, s>>>(
-      in, sc, fm.nc, g, (const T*)B.h, (const T*)B.b, B.gradh, B.gradb, (T*)B.ht, (T*)B.bt, cell_out(m, B));
+      in, sc, fm.nc, g, (const T*)B.h, (const T*)B.b, B.gradh, B.gradb, B.ghosth, B.ghostb, (T*)B.ht, (T*)B.bt,
+      cell_out(m, B));
 }
 }  // namespace
 
@@ -1802,7 +1812,8 @@ hipError_t launch_face_flux(int D, int prec, const DevMesh& m, const FusedMesh& 
   const unsigned nf = face_grid(m);
 #define UGKS_FACE_FLUX(DD, HB)                                                                       \
   UGKS_DISPATCH_T(prec, (k_face_flux<DD, TT, HB><<<nf, SWT, 0, s>>>(                                 \
-                            m, in, fm.frow, (const TT*)B.h, (const TT*)B.b, B.gradh, B.gradb, B.F, B.flag)))
+                            m, in, fm.frow, (const TT*)B.h, (const TT*)B.b, B.gradh, B.gradb, B.ghosth, \
+                            B.ghostb, B.F, B.flag)))
   if (D == 2) UGKS_FACE_FLUX(2, true);
   else if (B.b) UGKS_FACE_FLUX(3, true);
   else UGKS_FACE_FLUX(3, false);
@@ -1875,11 +1886,11 @@ hipError_t launch_wall_rho_b(int D, int prec, const BatchDev& bd, int64_t nwall,
 }
 
 hipError_t launch_ghost_rows(int D, int prec, const FusedMesh& fm, const DevVel& v,
-                             const double* frec, void* h, void* b, const int32_t* flag,
+                             const double* frec, int64_t first, void* h, void* b, const int32_t* flag,
                              hipStream_t s) {
   if (fm.nff == 0) return hipSuccess;
   UGKS_DISPATCH_DT(D, prec, k_ghost_rows<DD, TT><<<(unsigned)fm.nff, SWT, 0, s>>>(
-      fm.nc, fm.ffaces, v, frec, (TT*)h, (TT*)b, flag));
+      first, fm.ffaces, v, frec, (TT*)h, (TT*)b, flag));
   return hipGetLastError();
 }
 

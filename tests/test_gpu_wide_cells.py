@@ -109,3 +109,21 @@ def test_wide_cells_fp32_tracking_and_graphs_against_the_staged_sweep():
     assert np.all(_normwise(a.W(), b.W()) <= 1e-12)
     a.close()
     b.close()
+
+
+@pytest.mark.parametrize("which", ["far_field", "merged_quads"])
+def test_wide_cells_fp32_form_takes_ghost_states_in_fp64(which):
+    """The first step of the FP32 form starts from f that both sweeps hold alike and
+    computes in FP64, so the states part by FP64 roundings; ghost values rounded to
+    FP32 (6e-8 each) showed at some 1e-10 of W."""
+    case = _case(which)[0]
+    a, b = Solver(case, precision=UGKS_FP32), Solver(case, precision=UGKS_FP32, flags=STAGED)
+    a.step(1)
+    b.step(1)
+    err = _normwise(a.W(), b.W())
+    fa, fb = a.faces()[0], b.faces()[0]
+    print(which, err, _normwise_F(fa, fb), flush=True)
+    assert np.all(err <= 1e-14)
+    assert np.all(_normwise_F(fa, fb) <= 1e-13)
+    a.close()
+    b.close()
