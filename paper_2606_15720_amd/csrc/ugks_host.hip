@@ -940,7 +940,7 @@ void face_flux_after_failure(ugks_ctx* c) {
   const int D = c->D, P = c->prec;
   hipStream_t s = c->stream;
   int32_t* const flags = B.flag;
-  int32_t* const flag = B.flag = flags + 3;  // one of its own, which nothing raises
+  int32_t* const flag = B.flag = flags + 3;
   hipError_t e = launch_gradW(D, c->mesh, c->bcs, c->gas, B.W, B.gW, flags, 0, s);
   if (e == hipSuccess)
     e = launch_face_eq(D, c->mesh, c->bcs, c->gas, B.W, B.gW, B.q, B.frec, UGKS_FP64, c->nr, B.srec, flag, s);
@@ -1566,7 +1566,7 @@ int ugks_moments(ugks_ctx* c, int32_t which, double* out, int32_t on_device) {
       // (of the state that is kept, after a failed call too)
       HIP_TRY(launch_prims(D, c->mesh, c->gas, c->buf.W, c->buf.primn, nullptr, 0, c->stream));
       HIP_TRY(launch_heatflux(D, c->prec, c->mesh, c->vel, c->buf.h, c->buf.b, c->buf.primn, c->buf.qn,
-                              nullptr, c->stream));
+                              c->buf.flag + 3, c->stream));
       HIP_TRY(hipMemcpyAsync(lib, c->buf.qn, c->nc * 3 * sizeof(double), hipMemcpyDeviceToHost, c->stream));
     } else {
       return set_err(c, UGKS_EINVAL, "which must be 0, 1 or 2");

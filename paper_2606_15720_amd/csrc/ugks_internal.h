@@ -203,7 +203,8 @@ struct StepBuffers {
   double* cellred; // [nc*3] per-cell residual contributions
   // [0] numeric error; [1] steps begun without one; [2] numeric error of the
   // whole-cell step now running (taken over into [0] by the next step, so that
-  // every wave of that launch sees one value of [0])
+  // every wave of that launch sees one value of [0]); [3] always 0: the flag of
+  // readouts, which heed no error
   int32_t* flag;
 };
 

@@ -16,6 +16,7 @@ using namespace dev;
 namespace {
 
 // ---------------------------------------------------------------------------
+// (a null flag: a readout, which raises no error)
 template <int D>
 __global__ void k_prims(int64_t nc, GasP g, const double* __restrict__ W, double* __restrict__ prim,
                         int32_t* flag, int check) {
@@ -26,15 +27,14 @@ __global__ void k_prims(int64_t nc, GasP g, const double* __restrict__ W, double
   if (!ok && flag) atomicOr(flag, 1);
 }
 
-// Heat flux q_i = 1/2 sum_k w_k c_k (|c_k|^2 h_ik + b_ik), c = u - U_i.  (A null
-// flag, here and above: a readout, which neither heeds nor raises an error.)
+// Heat flux q_i = 1/2 sum_k w_k c_k (|c_k|^2 h_ik + b_ik), c = u - U_i.
 template <int D, typename T>
 __global__ __launch_bounds__(TPB) void k_heatflux(DevVel v, const T* __restrict__ h,
                                                   const T* __restrict__ b,
                                                   const double* __restrict__ prim,
                                                   double* __restrict__ q, const int32_t* flag) {
   __shared__ double lds[3 * 16];
-  if (flag && *flag) return;
+  if (*flag) return;
   const int64_t i = blockIdx.x;
   const double* P = &prim[i * NPRIM];
   double acc[3] = {0.0, 0.0, 0.0};
