@@ -68,18 +68,26 @@ __device__ __forceinline__ void cons_of(double rho, const double* U, double T, d
   W[D + 1] = 0.5 * rho * u2 + 0.5 * (K + 3.0) * rho * R * T;
 }
 
-// Face of a work-group (one per face, grid a multiple of 8 * FACE_TILE): each XCD
-// takes tiles of faces that follow each other in cell order, so the rows of a
-// cell are read by its faces through one L2 (13,056 faces of hexahedra x 20^3: face
-// fluxes 0.61 ms in face order, 0.45 so; the staged sweep's 1.29 and 1.15).  -1: none.
+// Rows that neighbours share are read through one L2 where the work-groups of an
+// XCD (block index mod 8) take them one after the other: runs of `most` elements
+// that follow each other in cell order, shorter where there are too few of them
+// to give each XCD one (27 hexahedra x 40^3 on the staged sweep, 108 faces: 0.91 ms
+// per step with runs of 32 cells and 64 faces, 0.71 so).
+__host__ __device__ __forceinline__ int64_t xcd_run(int64_t n, int64_t most) {
+  return n >= 8 * most ? most : (n + 7) / 8;
+}
+
+// Face of a work-group (one per face, grid a multiple of 8 runs; 13,056 faces of
+// hexahedra x 20^3: face fluxes 0.61 ms in face order, 0.45 so; the staged sweep's
+// 1.29 and 1.15).  -1: none.
 constexpr int64_t FACE_TILE = 64;
 __device__ __forceinline__ int64_t face_of_block(const DevMesh& m) {
-  const int64_t xcd = blockIdx.x % 8, local = blockIdx.x / 8;
-  const int64_t t = ((local / FACE_TILE) * 8 + xcd) * FACE_TILE + local % FACE_TILE;
+  const int64_t xcd = blockIdx.x % 8, local = blockIdx.x / 8, run = xcd_run(m.nf, FACE_TILE);
+  const int64_t t = ((local / run) * 8 + xcd) * run + local % run;
   return t < m.nf ? m.ford[t] : -1;
 }
 inline unsigned face_grid(const DevMesh& m) {
-  const int64_t per = 8 * FACE_TILE;
+  const int64_t per = 8 * xcd_run(m.nf, FACE_TILE);
   return (unsigned)((m.nf + per - 1) / per * per);
 }
 

@@ -7,6 +7,7 @@
 // where it is symmetric; zero-weight pads to whole waves), fixes the time step
 // from the CFL bound and allocates every device buffer once.  ugks_step only
 // enqueues kernels and reads their status back.
+#include "ugks_device.h"
 #include "ugks_host_util.h"
 
 #include <algorithm>
@@ -579,7 +580,7 @@ void build(ugks_ctx* c, const ugks_mesh* mesh, const ugks_velocity* vel, const u
     c->fmesh.crec_d = upload(c, cdr);
     c->fmesh.frow = upload(c, frow);
     c->sched.lanes = cell_lanes(nc, c->fmesh.half, UGKS_FP64);
-    c->sched.tile = 32;
+    c->sched.tile = dev::xcd_run(nc, 32);  // (as the gradients' runs)
   }
   if (c->fused) {
     // Static records of the fused sweep: the cell's faces, its least-squares

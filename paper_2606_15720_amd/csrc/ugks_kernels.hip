@@ -372,25 +372,28 @@ __global__ __launch_bounds__(64) void k_face_eq(DevMesh m, const DevBC* __restri
 // A lane takes two adjacent velocities (16-byte accesses) and issues all of its
 // neighbour rows before any arithmetic; the work-groups of one XCD take
 // GRAD_TILE cells through one block of velocities, then the next, so that the
-// rows the cells share are read from HBM once.  The gradients bypass the caches,
-// which are left to the rows.  4,096 hexahedra x 20^3, FP64: 0.50 ms with one
-// velocity per lane in cell order, 0.35 (3.0 TB/s) so; plain stores 0.355 and the
-// wall pass that follows 0.084 instead of 0.065.
+// rows the cells share are read from HBM once.  Gradients that the last-level cache
+// cannot hold bypass the caches, which are left to the rows.  4,096 hexahedra x
+// 20^3, FP64: 0.50 ms with one velocity per lane in cell order, 0.35 (3.0 TB/s) so;
+// plain stores 0.355 and the wall pass that follows 0.084 instead of 0.065.  Smaller
+// ones stay: 27 x 48^3 (72 MB) 0.41 for the wall pass bypassing, 0.33 plain.
 constexpr int64_t GRAD_TILE = 32;
+constexpr int64_t kLastLevel = 256 << 20;  // bytes
 
 template <int D, typename T>
 __global__ __launch_bounds__(TPB) void k_grad_micro(DevMesh m, DevVel v,
                                                     const double* __restrict__ frec,
                                                     const T* __restrict__ h, const T* __restrict__ b,
                                                     double* __restrict__ gh, double* __restrict__ gb,
-                                                    const int32_t* flag) {
+                                                    const int32_t* flag, int bypass) {
   typedef T pair_t __attribute__((ext_vector_type(2)));
   typedef double dpair_t __attribute__((ext_vector_type(2)));
   const int64_t nvp = v.nvp, nch = (nvp + 2 * TPB - 1) / (2 * TPB);
-  const int64_t xcd = blockIdx.x % 8, local = blockIdx.x / 8, per_tile = nch * GRAD_TILE;
-  const int64_t rem = local % per_tile;
-  const int64_t i = ((local / per_tile) * 8 + xcd) * GRAD_TILE + rem % GRAD_TILE;
-  const int64_t k = 2 * ((rem / GRAD_TILE) * TPB + threadIdx.x);  // nvp is even
+  const int64_t run = xcd_run(m.nc, GRAD_TILE);
+  const int64_t xcd = blockIdx.x % 8, local = blockIdx.x / 8, per_run = nch * run;
+  const int64_t rem = local % per_run;
+  const int64_t i = ((local / per_run) * 8 + xcd) * run + rem % run;
+  const int64_t k = 2 * ((rem / run) * TPB + threadIdx.x);  // nvp is even
   if (i >= m.nc || k >= nvp || *flag) return;
   const int nfc = m.nfc[i];
   for (int r = 0; r < (v.has_b ? 2 : 1); ++r) {
@@ -441,7 +444,8 @@ __global__ __launch_bounds__(TPB) void k_grad_micro(DevMesh m, DevVel v,
     double* __restrict__ g = r ? gb : gh;
     for (int d = 0; d < D; ++d) {
       const dpair_t o = {a[0][d], a[1][d]};
-      __builtin_nontemporal_store(o, (dpair_t*)&g[(i * 3 + d) * nvp + k]);
+      if (bypass) __builtin_nontemporal_store(o, (dpair_t*)&g[(i * 3 + d) * nvp + k]);
+      else *(dpair_t*)&g[(i * 3 + d) * nvp + k] = o;
     }
   }
 }
@@ -917,10 +921,11 @@ hipError_t launch_face_eq(int D, const DevMesh& m, const DevBC* bcs, const GasP&
 hipError_t launch_grad_micro(int D, int prec, const DevMesh& m, const DevVel& v,
                              const double* frec, const void* h, const void* b, double* gh,
                              double* gb, const int32_t* flag, hipStream_t s) {
-  const int64_t ntile = (m.nc + GRAD_TILE - 1) / GRAD_TILE;
-  const unsigned grid = (unsigned)((ntile + 7) / 8 * 8 * GRAD_TILE) * blocks_for(v.nvp, 2 * TPB);
+  const int64_t per = 8 * xcd_run(m.nc, GRAD_TILE);
+  const int bypass = m.nc * v.nvp * D * (v.has_b ? 2 : 1) * (int64_t)sizeof(double) > kLastLevel;
+  const unsigned grid = (unsigned)((m.nc + per - 1) / per * per) * blocks_for(v.nvp, 2 * TPB);
   UGKS_DISPATCH_DT(D, prec, k_grad_micro<DD, TT><<<grid, TPB, 0, s>>>(
-      m, v, frec, (const TT*)h, (const TT*)b, gh, gb, flag));
+      m, v, frec, (const TT*)h, (const TT*)b, gh, gb, flag, bypass));
   return hipGetLastError();
 }
 

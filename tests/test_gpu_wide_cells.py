@@ -9,7 +9,7 @@ import pytest
 
 import ugks_cases as uc
 from oracle import Oracle
-from paper_2606_15720_amd.ugks import UGKS_FP32, Solver
+from paper_2606_15720_amd.ugks import UGKS_FP32, Solver, ugks_profile_enable, ugks_profile_read
 from test_gpu_parity import LOCAL_DT, STAGED, TRACK, _compare_step, _normwise, _normwise_F
 
 pytestmark = pytest.mark.gpu
@@ -127,3 +127,23 @@ def test_wide_cells_fp32_form_takes_ghost_states_in_fp64(which):
     assert np.all(_normwise_F(fa, fb) <= 1e-13)
     a.close()
     b.close()
+
+
+def test_few_cells_take_every_xcd():
+    """27 cells x 40^3 and 216 x 20^3 have the same gradients to compute and write.  On
+    one XCD of eight the few cells' took over three times as long; both fill the
+    GPU, so they should differ by no more than a half."""
+    def gradients(n, nv):
+        s = Solver(_hexes(nv, n=(n, n, n)), flags=STAGED)
+        s.step(3)
+        best = np.inf
+        for _ in range(5):
+            ugks_profile_enable(s.h, True)
+            s.step(4)
+            n_launch, ms = ugks_profile_read(s.h)["micro_gradient"]
+            best = min(best, ms / n_launch)
+        s.close()
+        return best
+    few, many = gradients(3, 40), gradients(6, 20)
+    print("gradients of 27 x 40^3 and 216 x 20^3, ms:", few, many, flush=True)
+    assert few <= 1.5 * many
