@@ -183,7 +183,7 @@ int cell_lanes(int64_t nc, int64_t pairs, int prec) {
 }
 
 void build(ugks_ctx* c, const ugks_mesh* mesh, const ugks_velocity* vel, const ugks_gas* gas,
-           const ugks_bc* bcs, int32_t n_bc, const double* W0, const ugks_options* opt) {
+           const ugks_bc* bcs, int32_t n_bc, const double* W0, const ugks_options* opt, bool host) {
   check_case_args(mesh, vel, gas, W0);
   const int D = mesh->dim;
   const int64_t nc = mesh->n_cells, nf = mesh->n_faces, nv = vel->nv;
@@ -798,8 +798,9 @@ void build(ugks_ctx* c, const ugks_mesh* mesh, const ugks_velocity* vel, const u
   // is a wait of its own (a one-step call of 1,024 cells x 28^2 and its W: 108 us
   // with three such copies, 86 with two pinned ones).  Larger states are copied
   // at full rate either way.
+  // (The cases of a batch share one piece of it.)
   c->host_room = nc * NW * 8 <= kPinnedCells ? nc * std::max(NW, 3) : 0;
-  HIP_TRY(hipHostMalloc((void**)&c->host, (kStatus + c->host_room) * sizeof(double), hipHostMallocDefault));
+  if (host) HIP_TRY(hipHostMalloc((void**)&c->host, (kStatus + c->host_room) * sizeof(double), hipHostMallocDefault));
   HIP_TRY(hipMemsetAsync(B.q, 0, nc * 3 * sizeof(double), c->stream));
   std::vector<double> W0p(nc * NW);
   for (int64_t i = 0; i < nc; ++i)
@@ -1037,7 +1038,7 @@ struct ugks_batch {
   int32_t* flags_dev = nullptr;  // [4*n], after resid_dev in one block
   std::vector<int> odd;          // per case: its state is in the second set of buffers
   double* resid_dev = nullptr;   // [8*n]
-  double* host = nullptr;        // pinned, [kStatus*n]: a copy of both
+  double* host = nullptr;        // pinned, [kStatus*n]: a copy of both; then what the cases share
   int parity = 0;
   hipGraph_t graph[2] = {nullptr, nullptr};
   hipGraphExec_t exec[2] = {nullptr, nullptr};
@@ -1313,7 +1314,6 @@ void batch_build(ugks_batch* b, const ugks_case* cases, int32_t n, const ugks_op
   }
   b->resid_dev = balloc<double>(b, kStatus * (size_t)n);
   b->flags_dev = (int32_t*)(b->resid_dev + 8 * (size_t)n);
-  HIP_TRY(hipHostMalloc((void**)&b->host, kStatus * (size_t)n * sizeof(double), hipHostMallocDefault));
   HIP_TRY(hipMemset(b->flags_dev, 0, 4 * (size_t)n * sizeof(int32_t)));
   HIP_TRY(hipMemset(b->resid_dev, 0, 8 * (size_t)n * sizeof(double)));
   for (int32_t i = 0; i < n; ++i) {
@@ -1326,7 +1326,7 @@ void batch_build(ugks_batch* b, const ugks_case* cases, int32_t n, const ugks_op
     o.stream = b->stream;
     std::unique_ptr<ugks_ctx> c(new ugks_ctx());
     try {
-      build(c.get(), k.mesh, k.vel, k.gas, k.bcs, k.n_bc, k.W0, &o);
+      build(c.get(), k.mesh, k.vel, k.gas, k.bcs, k.n_bc, k.W0, &o, false);
     } catch (InvalidArg& e) {
       ugks_destroy(c.release());
       throw InvalidArg{"case " + std::to_string(i) + ": " + e.msg};
@@ -1359,6 +1359,10 @@ void batch_build(ugks_batch* b, const ugks_case* cases, int32_t n, const ugks_op
     cc->q_valid = true;
     apply_sched(cc, 32);
   }
+  int64_t room = 0;
+  for (ugks_ctx* c : b->cases) room = std::max(room, c->host_room);
+  HIP_TRY(hipHostMalloc((void**)&b->host, (kStatus * (n + 1) + room) * sizeof(double), hipHostMallocDefault));
+  for (ugks_ctx* c : b->cases) c->host = b->host + kStatus * (int64_t)n;
   b->odd.assign(n, 0);
   // case-offset tables
   const int64_t n1 = n + 1;
@@ -1448,7 +1452,7 @@ int ugks_create(const ugks_mesh* mesh, const ugks_velocity* vel, const ugks_gas*
   Range range("ugks_create");
   std::unique_ptr<ugks_ctx> c(new ugks_ctx());
   try {
-    build(c.get(), mesh, vel, gas, bcs, n_bc, W0, opt);
+    build(c.get(), mesh, vel, gas, bcs, n_bc, W0, opt, true);
   } catch (const InvalidArg& e) {
     ugks_destroy(c.release());
     return set_err(nullptr, UGKS_EINVAL, e.msg);
@@ -1926,7 +1930,10 @@ void ugks_batch_destroy(ugks_batch* b) {
     if (b->exec[par]) (void)hipGraphExecDestroy(b->exec[par]);
     if (b->graph[par]) (void)hipGraphDestroy(b->graph[par]);
   }
-  for (ugks_ctx* c : b->cases) ugks_destroy(c);
+  for (ugks_ctx* c : b->cases) {
+    c->host = nullptr;  // the batch's
+    ugks_destroy(c);
+  }
   for (void* p : b->allocations) (void)hipFree(p);
   if (b->host) (void)hipHostFree(b->host);
   if (b->own_stream && b->stream) (void)hipStreamDestroy(b->stream);

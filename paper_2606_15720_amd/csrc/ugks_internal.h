@@ -348,7 +348,8 @@ struct ugks_ctx {
   std::vector<void*> allocations;
   int64_t bytes = 0;
   // Pinned host memory that results are copied through: the status block
-  // (kStatus doubles), then room for host_room doubles of cell data.
+  // (kStatus doubles), then room for host_room doubles of cell data (in a batch
+  // a piece that its cases share).
   double* host = nullptr;
   int64_t host_room = 0;
   hipStream_t stream = nullptr;
