@@ -1172,9 +1172,10 @@ void enqueue_batch_step(ugks_batch* b, int par) {
   if (!(b->flags & 1)) HIP_TRY(launch_residual_b(bd, s));
 }
 
-// Average duration of `reps` launches of the batched step over `items`.  They
-// leave the state alone, but not the cell records and the error flags.
-double time_sweep(ugks_batch* b, const std::vector<int32_t>& items, int32_t** buf, int64_t* cap,
+// Average duration of `reps` launches of the batched step over `items`, after
+// `warm` that are not counted.  They leave the state alone, but not the cell
+// records and the error flags.
+double time_sweep(ugks_batch* b, const std::vector<int32_t>& items, int32_t** buf, int64_t* cap, int warm,
                   int reps) {
   upload_cases(b);  // the kernels read each case's schedule from the case table
   set_items(b, items, buf, cap);
@@ -1185,7 +1186,7 @@ double time_sweep(ugks_batch* b, const std::vector<int32_t>& items, int32_t** bu
   hipEvent_t e0, e1;
   HIP_TRY(hipEventCreate(&e0));
   HIP_TRY(hipEventCreate(&e1));
-  HIP_TRY(launch_step_b(b->D, b->prec, bd, g, b->threads, b->stream));  // warm-up
+  for (int r = 0; r < warm; ++r) HIP_TRY(launch_step_b(b->D, b->prec, bd, g, b->threads, b->stream));
   HIP_TRY(hipEventRecord(e0, b->stream));
   for (int r = 0; r < reps; ++r) HIP_TRY(launch_step_b(b->D, b->prec, bd, g, b->threads, b->stream));
   HIP_TRY(hipEventRecord(e1, b->stream));
@@ -1194,7 +1195,7 @@ double time_sweep(ugks_batch* b, const std::vector<int32_t>& items, int32_t** bu
   HIP_TRY(hipEventElapsedTime(&ms, e0, e1));
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
-  b->tune_timings += reps + 1;
+  b->tune_timings += reps + warm;
   return 1e3 * ms / reps;
 }
 
@@ -1206,9 +1207,9 @@ void apply_sched(ugks_ctx* c, int64_t tile) {
   c->Bv = (int)(2 * c->fmesh.half);
 }
 
-// Autotuner: for each lane count, each case's tile by timing that case's step
-// alone, then the lane count by timing the whole batch's step; shapes found
-// in the cache are not timed again.
+// Autotuner: the lanes per work-group by timing the whole batch's step, then each
+// case's tile by timing that case's step alone; shapes found in the cache are not
+// timed again.
 void autotune(ugks_batch* b) {
   const int64_t n = (int64_t)b->cases.size();
   int32_t* buf = nullptr;
@@ -1221,53 +1222,41 @@ void autotune(ugks_batch* b) {
     auto it = g_tune_batch.find(bkey);
     if (it != g_tune_batch.end()) best_threads = it->second;
   }
-  const int cand_threads[3] = {64, 128, 256};
-  double best_t = INFINITY;
-  for (int th : cand_threads) {
-    if (best_threads && th != best_threads) continue;
-    b->threads = th;
-    for (int64_t i = 0; i < n; ++i) {
-      ugks_ctx* c = b->cases[i];
-      const std::string key = case_key(b->D, b->prec, th, c->nc, c->nv);
-      TuneCase tc;
-      bool hit = false;
-      {
-        std::lock_guard<std::mutex> lk(g_tune_mu);
-        auto it = g_tune_case.find(key);
-        if (it != g_tune_case.end()) {
-          tc = it->second;
-          hit = true;
-        }
+  if (!best_threads) {
+    double best_t = INFINITY;
+    for (int th : {64, 128, 256}) {
+      b->threads = th;
+      for (ugks_ctx* c : b->cases) apply_sched(c, 32);
+      // (more lanes have to be faster by more than timings differ)
+      const double t = time_sweep(b, work_list(b, {}), &buf, &cap, th == 64 ? 1 : 0, best_t > 300.0 ? 1 : 2);
+      if (t < 0.95 * best_t) {
+        best_t = t;
+        best_threads = th;
       }
-      if (!hit) {
-        tc.us = INFINITY;
-        for (int64_t tile : {16, 64, 256}) {
-          if (tile > 16 && tile / 4 >= c->nc) continue;
-          apply_sched(c, tile);
-          const double us = time_sweep(b, work_list(b, {i}), &buf, &cap, 3);
-          if (us < tc.us) tc = {c->sched.chunk_pairs, c->sched.tile, us};
-        }
-        std::lock_guard<std::mutex> lk(g_tune_mu);
-        g_tune_case[key] = tc;
-      }
-      apply_sched(c, tc.tile);
-    }
-    if (best_threads) break;  // cached lane count: schedules applied above
-    const double t = time_sweep(b, work_list(b, {}), &buf, &cap, 3);
-    if (t < best_t) {
-      best_t = t;
-      best_threads = th;
     }
   }
-  if (b->threads != best_threads) {
-    // re-apply the winning lane count's schedules (all cached by now)
-    b->threads = best_threads;
-    for (int64_t i = 0; i < n; ++i) {
-      ugks_ctx* c = b->cases[i];
+  b->threads = best_threads;
+  for (int64_t i = 0; i < n; ++i) {
+    ugks_ctx* c = b->cases[i];
+    const std::string key = case_key(b->D, b->prec, b->threads, c->nc, c->nv);
+    TuneCase tc;
+    {
       std::lock_guard<std::mutex> lk(g_tune_mu);
-      const TuneCase& tc = g_tune_case[case_key(b->D, b->prec, best_threads, c->nc, c->nv)];
-      apply_sched(c, tc.tile);
+      auto it = g_tune_case.find(key);
+      if (it != g_tune_case.end()) tc = it->second;
     }
+    if (!tc.tile) {
+      tc.us = INFINITY;
+      for (int64_t tile : {16, 64, 256}) {
+        if (tile > 16 && tile / 4 >= c->nc) continue;
+        apply_sched(c, tile);
+        const double us = time_sweep(b, work_list(b, {i}), &buf, &cap, 1, 3);
+        if (us < tc.us) tc = {c->sched.chunk_pairs, c->sched.tile, us};
+      }
+      std::lock_guard<std::mutex> lk(g_tune_mu);
+      g_tune_case[key] = tc;
+    }
+    apply_sched(c, tc.tile);
   }
   std::lock_guard<std::mutex> lk(g_tune_mu);
   g_tune_batch[bkey] = best_threads;
