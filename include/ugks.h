@@ -330,18 +330,20 @@ void ugks_destroy(ugks_ctx* ctx);
  * follows the paper's velocity-block work decomposition (Eq.
  * velocity_block_partition, Sec. 3) with a cell's whole velocity set as the
  * block: sweep and rest of the step are one persistent launch walking a list
- * of (case, cell) work items, the
+ * of (case, cell) work items; in the blocked form the sweep walks (case, cell,
+ * velocity block) items and the rest of the step is a launch of its own; the
  * other phases flatten the cells, faces or wall faces of every case behind
  * case-offset tables, and the whole step is captured once into a HIP graph
  * and replayed.  Every case must qualify for the fused sweep (a tensor
  * product of one symmetric 1-D node set; any face kinds;
  * at most four faces per cell).
  *
- * The cell-tile size of each case and the lanes per work-group of the sweep
- * are chosen by an autotuner that times the sweep on the device at create
- * (options.block_v = 0 and tile_cells = 0) unless the process-wide tuning
- * cache already holds the case's shape; a nonzero tile_cells fixes the tile
- * for every case instead, a nonzero block_v only leaves the tuning out.
+ * The lanes per work-group, the cell-tile size of each case and, for a batch of
+ * few cells, the blocked form and its velocity block are chosen by an autotuner
+ * that times the step on the device at create (options.block_v = 0 and
+ * tile_cells = 0) unless the process-wide tuning cache already holds the batch's
+ * shapes; a nonzero block_v / tile_cells fixes them for every case instead (a
+ * block_v that covers every case's set is the whole-cell form).
  * options.flags bit 3 runs the step eagerly (no graph); the other bits act
  * as for ugks_create.  options.stream as for ugks_create.
  */
@@ -361,7 +363,7 @@ typedef struct {
   int32_t dim;
   int32_t precision;
   int32_t threads;           /* lanes per work-group of the batched sweep */
-  int64_t work_items;        /* (case, cell) items of one sweep, with padding */
+  int64_t work_items;        /* (case, cell[, velocity block]) items of one sweep, with padding */
   int64_t grid;              /* persistent work-groups of the sweep */
   int32_t graph;             /* 1: steps replay a captured HIP graph */
   int32_t tuned;             /* 1: schedule from the autotuner (timed or cached) */

@@ -1005,15 +1005,20 @@ struct ugks_batch_impl;
 
 namespace {
 
-// Autotuner cache: case shape -> (pairs per work item, tile cells, time),
-// batch shape list -> lanes per work-group.
+// Autotuner cache: case shape -> (pairs per work item, tile cells, time) of the
+// whole-cell form, batch shape list -> lanes per work-group and, where the
+// blocked form is the faster one, its pairs per work item (else 0).
 struct TuneCase {
   int64_t chunk_pairs = 0, tile = 0;
   double us = 0.0;
 };
+struct TuneBatch {
+  int threads = 0;
+  int64_t chunk_pairs = 0;
+};
 std::mutex g_tune_mu;
 std::map<std::string, TuneCase> g_tune_case;
-std::map<std::string, int> g_tune_batch;
+std::map<std::string, TuneBatch> g_tune_batch;
 
 std::string case_key(int D, int prec, int threads, int64_t nc, int64_t nv) {
   char buf[128];
@@ -1027,6 +1032,7 @@ struct ugks_batch {
   std::vector<ugks_ctx*> cases;
   int D = 0, prec = 64, flags = 0, nr = 1;
   int threads = 256;
+  bool blocks = false;  // blocked form: sweep by velocity blocks, rest of the step in a launch of its own
   hipStream_t stream = nullptr;
   bool own_stream = false;
   std::vector<void*> allocations;
@@ -1037,6 +1043,7 @@ struct ugks_batch {
   int64_t ncell = 0, nface = 0, nwall = 0, nff = 0;
   int32_t* flags_dev = nullptr;  // [4*n], after resid_dev in one block
   std::vector<int> odd;          // per case: its state is in the second set of buffers
+  std::vector<int64_t> dW_chunks;  // per case: velocity blocks that its dW has room for
   double* resid_dev = nullptr;   // [8*n]
   double* host = nullptr;        // pinned, [kStatus*n]: a copy of both; then what the cases share
   int parity = 0;
@@ -1097,8 +1104,8 @@ void upload_cases(ugks_batch* b) {
   }
 }
 
-// Work list of the batched step.  Tiles of each case go to the XCD queue with
-// the least work so far; queue x holds the cells of its tiles; queues are
+// Work list of the batched step.  The cells of a tile, with one velocity block
+// of theirs, go to the XCD queue with the least work so far; queues are
 // padded to one length and interleaved so that item w lands on a work-group
 // with index = w (mod 8), i.e. on XCD w mod 8.
 std::vector<int32_t> work_list(const ugks_batch* b, const std::vector<int64_t>& only) {
@@ -1108,27 +1115,28 @@ std::vector<int32_t> work_list(const ugks_batch* b, const std::vector<int64_t>& 
     const ugks_ctx* c = b->cases[ci];
     const SweepSched& sc = c->sched;
     const int64_t ntile = (c->nc + sc.tile - 1) / sc.tile;
-    for (int64_t t = 0; t < ntile; ++t) {
-      const int x = (int)(std::min_element(load.begin(), load.end()) - load.begin());
-      const int64_t c0 = t * sc.tile, c1 = std::min(c->nc, c0 + sc.tile);
-      for (int64_t ic = c0; ic < c1; ++ic) {
-        q[x].push_back((int32_t)ci);
-        q[x].push_back((int32_t)ic);
+    for (int64_t t = 0; t < ntile; ++t)
+      for (int64_t ch = 0; ch < sc.nchunk; ++ch) {
+        const int x = (int)(std::min_element(load.begin(), load.end()) - load.begin());
+        const int64_t c0 = t * sc.tile, c1 = std::min(c->nc, c0 + sc.tile);
+        for (int64_t ic = c0; ic < c1; ++ic) {
+          const int32_t item[4] = {(int32_t)ci, (int32_t)ic, (int32_t)ch, 0};
+          q[x].insert(q[x].end(), item, item + 4);
+        }
+        load[x] += (double)(c1 - c0) * (double)std::min(sc.chunk_pairs, c->fmesh.half - ch * sc.chunk_pairs);
       }
-      load[x] += (double)(c1 - c0) * (double)((c->nv + 1) / 2);
-    }
   };
   if (only.empty())
     for (int64_t ci = 0; ci < (int64_t)b->cases.size(); ++ci) add_case(ci);
   else
     for (int64_t ci : only) add_case(ci);
   size_t len = 0;
-  for (auto& v : q) len = std::max(len, v.size() / 2);
-  std::vector<int32_t> out(8 * len * 2, 0);
+  for (auto& v : q) len = std::max(len, v.size() / 4);
+  std::vector<int32_t> out(8 * len * 4, 0);
   for (size_t j = 0; j < len; ++j)
     for (int x = 0; x < 8; ++x) {
-      int32_t* o = &out[(8 * j + x) * 2];
-      if (j < q[x].size() / 2) std::memcpy(o, &q[x][2 * j], 2 * sizeof(int32_t));
+      int32_t* o = &out[(8 * j + x) * 4];
+      if (j < q[x].size() / 4) std::memcpy(o, &q[x][4 * j], 4 * sizeof(int32_t));
       else o[0] = -1;
     }
   return out;
@@ -1138,7 +1146,7 @@ int64_t sweep_grid(const ugks_batch* b, int64_t nitems) {
   int dev = 0, ncu = 0;
   HIP_TRY(hipGetDevice(&dev));
   HIP_TRY(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
-  const int per = std::max(1, step_b_blocks_per_cu(b->D, b->prec, b->threads));
+  const int per = std::max(1, batch_blocks_per_cu(b->D, b->prec, b->threads, b->blocks));
   int64_t g = (int64_t)ncu * per;
   g = std::min<int64_t>(g, nitems);
   g = std::max<int64_t>(8, g / 8 * 8);
@@ -1146,12 +1154,18 @@ int64_t sweep_grid(const ugks_batch* b, int64_t nitems) {
 }
 
 void set_items(ugks_batch* b, const std::vector<int32_t>& items, int32_t** dst, int64_t* cap) {
-  const int64_t n = (int64_t)items.size() / 2;
+  const int64_t n = (int64_t)items.size() / 4;
   if (n > *cap) {
     *dst = balloc<int32_t>(b, items.size());
     *cap = n;
   }
   HIP_TRY(hipMemcpy(*dst, items.data(), items.size() * sizeof(int32_t), hipMemcpyHostToDevice));
+}
+
+// 5, 6.7-6.8, 8-11: the velocity sweep and the rest of every cell's step
+hipError_t launch_cells(const ugks_batch* b, const BatchDev& bd, int64_t grid) {
+  if (b->blocks) return launch_sweep_b(b->D, b->prec, bd, b->ncell, grid, b->threads, b->stream);
+  return launch_step_b(b->D, b->prec, bd, grid, b->threads, b->stream);
 }
 
 // The phases of one step for every case of the batch.
@@ -1165,9 +1179,7 @@ void enqueue_batch_step(ugks_batch* b, int par) {
   // 7 wall densities; far-field ghost rows
   HIP_TRY(launch_ghost_rows_b(D, P, bd, b->nff, s));
   HIP_TRY(launch_wall_rho_b(D, P, bd, b->nwall, s));
-  // 5, 6.7-6.8, 8-11: the velocity sweep and the rest of every cell's step,
-  // one persistent launch
-  HIP_TRY(launch_step_b(D, P, bd, b->grid, b->threads, s));
+  HIP_TRY(launch_cells(b, bd, b->grid));
   // 12 residuals
   if (!(b->flags & 1)) HIP_TRY(launch_residual_b(bd, s));
 }
@@ -1181,14 +1193,14 @@ double time_sweep(ugks_batch* b, const std::vector<int32_t>& items, int32_t** bu
   set_items(b, items, buf, cap);
   BatchDev bd = batch_dev(b, 0);
   bd.items = *buf;
-  bd.nitems = (int64_t)items.size() / 2;
+  bd.nitems = (int64_t)items.size() / 4;
   const int64_t g = sweep_grid(b, bd.nitems);
   hipEvent_t e0, e1;
   HIP_TRY(hipEventCreate(&e0));
   HIP_TRY(hipEventCreate(&e1));
-  for (int r = 0; r < warm; ++r) HIP_TRY(launch_step_b(b->D, b->prec, bd, g, b->threads, b->stream));
+  for (int r = 0; r < warm; ++r) HIP_TRY(launch_cells(b, bd, g));
   HIP_TRY(hipEventRecord(e0, b->stream));
-  for (int r = 0; r < reps; ++r) HIP_TRY(launch_step_b(b->D, b->prec, bd, g, b->threads, b->stream));
+  for (int r = 0; r < reps; ++r) HIP_TRY(launch_cells(b, bd, g));
   HIP_TRY(hipEventRecord(e1, b->stream));
   HIP_TRY(hipEventSynchronize(e1));
   float ms = 0.0f;
@@ -1199,67 +1211,124 @@ double time_sweep(ugks_batch* b, const std::vector<int32_t>& items, int32_t** bu
   return 1e3 * ms / reps;
 }
 
-void apply_sched(ugks_ctx* c, int64_t tile) {
-  c->sched.whole = 1;
-  c->sched.chunk_pairs = c->fmesh.half;
-  c->sched.nchunk = 1;
+// Pairs per work item (at least 32, or all) and cells per tile of one case.
+void apply_sched(ugks_ctx* c, int64_t chunk_pairs, int64_t tile) {
+  const int64_t half = c->fmesh.half;
+  chunk_pairs = std::max(std::min<int64_t>(32, half), std::min(chunk_pairs, half));
+  c->sched.whole = chunk_pairs == half;
+  c->sched.chunk_pairs = chunk_pairs;
+  c->sched.nchunk = (half + chunk_pairs - 1) / chunk_pairs;
   c->sched.tile = std::max<int64_t>(1, std::min(tile, c->nc));
-  c->Bv = (int)(2 * c->fmesh.half);
+  c->Bv = (int)(2 * chunk_pairs);
 }
+void apply_whole(ugks_ctx* c, int64_t tile) { apply_sched(c, c->fmesh.half, tile); }
+
+// Blocked schedule of every case: the moment sums of its blocks get their room.
+constexpr int64_t kBlockTile = 16;
+void apply_blocks(ugks_batch* b, int64_t chunk_pairs, int64_t tile) {
+  b->blocks = true;
+  for (size_t i = 0; i < b->cases.size(); ++i) {
+    ugks_ctx* c = b->cases[i];
+    apply_sched(c, chunk_pairs, tile);
+    if (c->sched.nchunk > b->dW_chunks[i]) {
+      c->buf.dW = balloc<double>(b, (size_t)(c->nc * c->sched.nchunk * 5));
+      b->dW_chunks[i] = c->sched.nchunk;
+    }
+  }
+}
+
+// Fewest cells of a batch that take the whole-cell form without a look at the
+// blocked one.
+constexpr int64_t kBatchCells = 8192;
+constexpr int kMostBlocks = 32;
 
 // Autotuner: the lanes per work-group by timing the whole batch's step, then each
 // case's tile by timing that case's step alone; shapes found in the cache are not
-// timed again.
+// timed again.  A batch of few cells is timed in the blocked form too, by 2 to 32
+// blocks of its largest velocity set.
 void autotune(ugks_batch* b) {
   const int64_t n = (int64_t)b->cases.size();
   int32_t* buf = nullptr;
-  int64_t cap = 0;
+  int64_t cap = 0, half = 0;
   std::string bkey = "batch";
-  for (ugks_ctx* c : b->cases) bkey += " " + case_key(b->D, b->prec, 0, c->nc, c->nv);
-  int best_threads = 0;
+  for (ugks_ctx* c : b->cases) {
+    bkey += " " + case_key(b->D, b->prec, 0, c->nc, c->nv);
+    half = std::max(half, c->fmesh.half);
+  }
+  TuneBatch best;
   {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     auto it = g_tune_batch.find(bkey);
-    if (it != g_tune_batch.end()) best_threads = it->second;
+    if (it != g_tune_batch.end()) best = it->second;
   }
-  if (!best_threads) {
+  if (!best.threads) {
     double best_t = INFINITY;
-    for (int th : {64, 128, 256}) {
-      b->threads = th;
-      for (ugks_ctx* c : b->cases) apply_sched(c, 32);
-      // (more lanes have to be faster by more than timings differ)
-      const double t = time_sweep(b, work_list(b, {}), &buf, &cap, th == 64 ? 1 : 0, best_t > 300.0 ? 1 : 2);
+    // (another choice has to be faster by more than timings differ)
+    auto take = [&](int64_t pairs, bool first) {
+      const double t = time_sweep(b, work_list(b, {}), &buf, &cap, first ? 1 : 0, best_t > 300.0 ? 1 : 2);
       if (t < 0.95 * best_t) {
         best_t = t;
-        best_threads = th;
+        best = {b->threads, pairs};
+      }
+      return t;
+    };
+    if (b->ncell < kBatchCells) {  // room for every list that is timed below
+      cap = 4 * kBatchCells + 512;
+      buf = balloc<int32_t>(b, 4 * (size_t)cap);
+    }
+    bool blocks_met = false;
+    for (int th : {64, 128, 256}) {
+      b->threads = th;
+      b->blocks = false;
+      for (ugks_ctx* c : b->cases) apply_whole(c, 32);
+      take(0, th == 64);
+      if (b->ncell >= kBatchCells || th == 64) continue;
+      // (fewer pairs per block than lanes leave lanes idle, and more items than
+      // fill the GPU a few times over gain nothing)
+      double before = INFINITY;
+      int64_t last = half;
+      for (int nb = 2; nb <= kMostBlocks && b->ncell * nb <= 4 * kBatchCells; nb *= 2) {
+        const int64_t pairs = ((half + nb - 1) / nb + WAVE - 1) / WAVE * WAVE;
+        if (pairs == last || 2 * pairs < th) break;
+        last = pairs;
+        apply_blocks(b, pairs, kBlockTile);
+        const double t = take(pairs, !blocks_met);
+        blocks_met = true;
+        if (t > 1.1 * before) break;
+        before = t;
       }
     }
   }
-  b->threads = best_threads;
-  for (int64_t i = 0; i < n; ++i) {
-    ugks_ctx* c = b->cases[i];
-    const std::string key = case_key(b->D, b->prec, b->threads, c->nc, c->nv);
-    TuneCase tc;
-    {
-      std::lock_guard<std::mutex> lk(g_tune_mu);
-      auto it = g_tune_case.find(key);
-      if (it != g_tune_case.end()) tc = it->second;
-    }
-    if (!tc.tile) {
-      tc.us = INFINITY;
-      for (int64_t tile : {16, 64, 256}) {
-        if (tile > 16 && tile / 4 >= c->nc) continue;
-        apply_sched(c, tile);
-        const double us = time_sweep(b, work_list(b, {i}), &buf, &cap, 1, 3);
-        if (us < tc.us) tc = {c->sched.chunk_pairs, c->sched.tile, us};
+  b->threads = best.threads;
+  if (best.chunk_pairs) {
+    apply_blocks(b, best.chunk_pairs, kBlockTile);
+  } else {
+    b->blocks = false;
+    for (int64_t i = 0; i < n; ++i) {
+      ugks_ctx* c = b->cases[i];
+      const std::string key = case_key(b->D, b->prec, b->threads, c->nc, c->nv);
+      TuneCase tc;
+      {
+        std::lock_guard<std::mutex> lk(g_tune_mu);
+        auto it = g_tune_case.find(key);
+        if (it != g_tune_case.end()) tc = it->second;
       }
-      std::lock_guard<std::mutex> lk(g_tune_mu);
-      g_tune_case[key] = tc;
+      if (!tc.tile) {
+        tc.us = INFINITY;
+        for (int64_t tile : {16, 64, 256}) {
+          if (tile > 16 && tile / 4 >= c->nc) continue;
+          apply_whole(c, tile);
+          const double us = time_sweep(b, work_list(b, {i}), &buf, &cap, 1, 3);
+          if (us < tc.us) tc = {c->sched.chunk_pairs, c->sched.tile, us};
+        }
+        std::lock_guard<std::mutex> lk(g_tune_mu);
+        g_tune_case[key] = tc;
+      }
+      apply_whole(c, tc.tile);
     }
-    apply_sched(c, tc.tile);
   }
   std::lock_guard<std::mutex> lk(g_tune_mu);
-  g_tune_batch[bkey] = best_threads;
+  g_tune_batch[bkey] = best;
 }
 
 void batch_build(ugks_batch* b, const ugks_case* cases, int32_t n, const ugks_options* opt) {
@@ -1346,13 +1415,14 @@ void batch_build(ugks_batch* b, const ugks_case* cases, int32_t n, const ugks_op
     HIP_TRY(launch_heatflux(cc->D, cc->prec, cc->mesh, cc->vel, cc->buf.h, cc->buf.b, cc->buf.prim,
                             cc->buf.q, cc->buf.flag, b->stream));
     cc->q_valid = true;
-    apply_sched(cc, 32);
+    apply_whole(cc, 32);
   }
   int64_t room = 0;
   for (ugks_ctx* c : b->cases) room = std::max(room, c->host_room);
   HIP_TRY(hipHostMalloc((void**)&b->host, (kStatus * (n + 1) + room) * sizeof(double), hipHostMallocDefault));
   for (ugks_ctx* c : b->cases) c->host = b->host + kStatus * (int64_t)n;
   b->odd.assign(n, 0);
+  b->dW_chunks.assign(n, 0);
   // case-offset tables
   const int64_t n1 = n + 1;
   std::vector<int64_t> off(4 * n1, 0);
@@ -1390,7 +1460,12 @@ void batch_build(ugks_batch* b, const ugks_case* cases, int32_t n, const ugks_op
   }
   if (fixed_bv || fixed_tile) {
     b->threads = 256;
-    for (ugks_ctx* c : b->cases) apply_sched(c, fixed_tile ? fixed_tile : 256);
+    const int64_t tile = fixed_tile ? fixed_tile : 256;
+    bool blocks = false;
+    for (const ugks_ctx* c : b->cases) blocks = blocks || (fixed_bv && fixed_bv / 2 < c->fmesh.half);
+    if (blocks) apply_blocks(b, fixed_bv / 2, tile);
+    else
+      for (ugks_ctx* c : b->cases) apply_whole(c, tile);
   } else {
     autotune(b);
     b->tuned = true;
@@ -1403,7 +1478,7 @@ void batch_build(ugks_batch* b, const ugks_case* cases, int32_t n, const ugks_op
   const std::vector<int32_t> items = work_list(b, {});
   int64_t cap = 0;
   set_items(b, items, &b->items, &cap);
-  b->nitems = (int64_t)items.size() / 2;
+  b->nitems = (int64_t)items.size() / 4;
   b->grid = sweep_grid(b, b->nitems);
   HIP_TRY(hipStreamSynchronize(b->stream));
   if (b->use_graph) {
@@ -1943,7 +2018,11 @@ int ugks_autotune_save(const char* path) {
     for (auto& e : g_tune_case)
       f << "case " << e.first << " : " << e.second.chunk_pairs << " " << e.second.tile << " "
         << e.second.us << "\n";
-    for (auto& e : g_tune_batch) f << e.first << " : " << e.second << "\n";
+    for (auto& e : g_tune_batch) {
+      f << e.first << " : " << e.second.threads;
+      if (e.second.chunk_pairs) f << " " << e.second.chunk_pairs;
+      f << "\n";
+    }
     return f.good() ? UGKS_OK : UGKS_EINVAL;
   } catch (...) {
     return UGKS_EHIP;  // no exception crosses the ABI
@@ -1958,7 +2037,7 @@ int ugks_autotune_load(const char* path) {
     std::string line;
     if (!std::getline(f, line) || line != "ugks-autotune 1") return UGKS_EINVAL;
     std::map<std::string, TuneCase> cs;
-    std::map<std::string, int> bs;
+    std::map<std::string, TuneBatch> bs;
     while (std::getline(f, line)) {
       if (line.empty()) continue;
       const size_t sep = line.find(" : ");
@@ -1971,9 +2050,11 @@ int ugks_autotune_load(const char* path) {
           return UGKS_EINVAL;
         cs[key.substr(5)] = t;
       } else if (key.rfind("batch", 0) == 0) {
-        int th = 0;
-        if (!(val >> th) || (th != 64 && th != 128 && th != 256)) return UGKS_EINVAL;
-        bs[key] = th;
+        TuneBatch t;
+        if (!(val >> t.threads) || (t.threads != 64 && t.threads != 128 && t.threads != 256)) return UGKS_EINVAL;
+        if (!(val >> t.chunk_pairs)) t.chunk_pairs = 0;
+        if (t.chunk_pairs < 0) return UGKS_EINVAL;
+        bs[key] = t;
       } else {
         return UGKS_EINVAL;
       }

@@ -238,7 +238,7 @@ struct BatchDev {
   const int64_t* face_off;  // [n+1] faces
   const int64_t* wall_off;  // [n+1] wall faces
   const int64_t* ff_off;    // [n+1] far-field / outflow faces (ghost rows)
-  const int32_t* items;     // [2*nitems] work items: case (-1 = padding), cell
+  const int32_t* items;     // [4*nitems] work items: case (-1 = padding), cell, velocity block, unused
   int64_t nitems;
 };
 
@@ -312,8 +312,11 @@ hipError_t launch_wall_rho_b(int D, int prec, const BatchDev& bd, int64_t nwall,
 hipError_t launch_ghost_rows_b(int D, int prec, const BatchDev& bd, int64_t nff, hipStream_t s);
 hipError_t launch_step_b(int D, int prec, const BatchDev& bd, int64_t grid, int threads,
                          hipStream_t s);
-// resident work-groups of the batched step per CU at `threads` lanes
-int step_b_blocks_per_cu(int D, int prec, int threads);
+// blocked form: the sweep of (case, cell, block) items, then the rest of the step
+hipError_t launch_sweep_b(int D, int prec, const BatchDev& bd, int64_t ncell, int64_t grid, int threads,
+                          hipStream_t s);
+// resident work-groups of either form's sweep per CU at `threads` lanes
+int batch_blocks_per_cu(int D, int prec, int threads, bool blocks);
 hipError_t launch_residual_b(const BatchDev& bd, hipStream_t s);
 
 }  // namespace ugks

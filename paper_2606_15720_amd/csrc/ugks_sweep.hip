@@ -989,6 +989,52 @@ __global__ __launch_bounds__(SWT, (sizeof(T) == 4 ? 6 : 4)) void k_sweep(
     for (int x = 0; x < 5; ++x) dWp[(ic * sc.nchunk + chunk) * 5 + x] = x < D + 2 ? mw[x] : 0.0;
 }
 
+// One case of a batch as the cells' kernels read it.  The work list and the case
+// table are read-only for the whole launch: read through the constant address
+// space they are scalar loads, so the case's pointers and sizes land in scalar
+// registers as kernel arguments do.  An FP32 batch computes in FP32, as the single
+// case does, from the FP32 copies of its records.
+typedef const __attribute__((address_space(4))) int32_t citem_t;
+typedef const __attribute__((address_space(4))) CaseDev ccase_t;
+
+template <typename T>
+__device__ __forceinline__ void case_in(ccase_t& c, SweepIn<T>& in) {
+  in.crec_i = c.fm.crec_i;
+  in.crec_l = nullptr;
+  in.vidx = c.fm.vidx;
+  in.w = c.v.w;
+  in.frec = c.B.frec;
+  in.cs = (const T*)c.B.cs;
+  in.srec = (const T*)c.B.srec;
+  in.prim = c.B.prim;
+  in.dt = c.g.dt;
+  in.nvp = c.v.nvp;
+  in.half = (unsigned)c.fm.half;
+  in.keep = 0;
+  in.na = c.fm.na;
+  in.axis = c.fm.axis;
+  if constexpr (sizeof(T) == 4) in.crec_d = c.fm.crec_d32;
+  else in.crec_d = c.fm.crec_d;
+}
+
+__device__ __forceinline__ void case_out(ccase_t& c, GasP& g, CellOut& o) {
+  g.Pr = c.g.Pr;
+  g.R = c.g.R;
+  g.Tref = c.g.Tref;
+  g.muref = c.g.muref;
+  g.omega = c.g.omega;
+  g.dt = c.g.dt;
+  o.vol = c.m.vol;
+  o.W = c.B.W;
+  o.q = c.B.q;
+  o.Wn = c.B.Wn;
+  o.qn = c.B.qn;
+  o.prim = c.B.prim;
+  o.cs = c.B.cs;
+  o.cellred = c.B.cellred;
+  o.flag = c.B.flag;
+}
+
 // The whole-cell step over a batch of cases: a persistent grid walks a list of
 // (case, cell) work items; item w runs on block w mod the grid size, and the
 // host orders the list so that the blocks of one XCD (block index mod 8) take
@@ -996,57 +1042,18 @@ __global__ __launch_bounds__(SWT, (sizeof(T) == 4 ? 6 : 4)) void k_sweep(
 // against two: 9.6 against 12.4 ms FP64, 5.5 against 6.2 FP32.
 template <int D, typename T>
 __global__ __launch_bounds__(SWT, (D == 3 ? 4 : 3)) void k_step_b(BatchDev bd) {
-  // computes in the storage type, as the single case does: an FP32 batch
-  // reads the FP32 copies of its records
   __shared__ SweepLds<D, T> L;
-  // The work list and the case table are read-only for the whole launch:
-  // read through the constant address space they are scalar loads, so the
-  // case's pointers and sizes land in scalar registers as kernel arguments do.
-  typedef const __attribute__((address_space(4))) int32_t citem_t;
-  typedef const __attribute__((address_space(4))) CaseDev ccase_t;
   citem_t* items = (citem_t*)bd.items;
   ccase_t* cases = (ccase_t*)bd.cases;
   for (int64_t it = blockIdx.x; it < bd.nitems; it += gridDim.x) {
-    const int c = items[2 * it];
+    const int c = items[4 * it];
     if (c < 0) continue;  // padding
-    const int64_t ic = items[2 * it + 1];
+    const int64_t ic = items[4 * it + 1];
     GasP g;
-    g.Pr = cases[c].g.Pr;
-    g.R = cases[c].g.R;
-    g.Tref = cases[c].g.Tref;
-    g.muref = cases[c].g.muref;
-    g.omega = cases[c].g.omega;
-    g.dt = cases[c].g.dt;
     CellOut o;
-    o.vol = cases[c].m.vol;
-    o.W = cases[c].B.W;
-    o.q = cases[c].B.q;
-    o.Wn = cases[c].B.Wn;
-    o.qn = cases[c].B.qn;
-    o.prim = cases[c].B.prim;
-    o.cs = cases[c].B.cs;
-    o.cellred = cases[c].B.cellred;
-    o.flag = cases[c].B.flag;
     SweepIn<T> in;
-    in.crec_i = cases[c].fm.crec_i;
-    in.crec_l = nullptr;
-    in.vidx = cases[c].fm.vidx;
-    in.w = cases[c].v.w;
-    in.frec = cases[c].B.frec;
-    in.cs = (const T*)cases[c].B.cs;
-    in.srec = (const T*)cases[c].B.srec;
-    in.prim = o.prim;
-    in.dt = g.dt;
-    in.nvp = cases[c].v.nvp;
-    in.half = (unsigned)cases[c].fm.half;
-    in.keep = 0;
-    in.na = cases[c].fm.na;
-    in.axis = cases[c].fm.axis;
-    if constexpr (sizeof(T) == 4) {
-      in.crec_d = cases[c].fm.crec_d32;
-    } else {
-      in.crec_d = cases[c].fm.crec_d;
-    }
+    case_out(cases[c], g, o);
+    case_in<T>(cases[c], in);
     const T* h = (const T*)cases[c].B.h;
     const T* b = (const T*)cases[c].B.b;
     T* ht = (T*)cases[c].B.ht;
@@ -1058,6 +1065,37 @@ __global__ __launch_bounds__(SWT, (D == 3 ? 4 : 3)) void k_step_b(BatchDev bd) {
     block_total<D + 2>(mw, L.red);
     finish_cell<D, T, T, D == 2>(g, in.vidx, in.w, o, ht, bt, ic, in.nvp, in.half, in.na, in.axis, nullptr, 0u,
                               mw, L.c, L.red);
+  }
+}
+
+// Blocked form of the batch, for one of few cells (or a caller's block_v): items
+// (case, cell, block of the case's mirror pairs), then the rest of the step.  One
+// work-group per cell leaves compute units idle: 6 tets x 28^3 0.403 ms per step
+// whole, 0.080 in 8 blocks; 4 x 750 x 40^3 4.6 (64 lanes; 3.1 with 256) and 3.1;
+// 16 x 162 x 32^3 2.22 and 1.34.
+template <int D, typename T>
+__global__ __launch_bounds__(SWT, (D == 3 ? 4 : 3)) void k_sweep_b(BatchDev bd) {
+  __shared__ SweepLds<D, T> L;
+  citem_t* items = (citem_t*)bd.items;
+  ccase_t* cases = (ccase_t*)bd.cases;
+  for (int64_t it = blockIdx.x; it < bd.nitems; it += gridDim.x) {
+    const int c = items[4 * it];
+    if (c < 0) continue;  // padding
+    const int64_t ic = items[4 * it + 1], chunk = items[4 * it + 2];
+    if (*cases[c].B.flag) continue;
+    SweepIn<T> in;
+    case_in<T>(cases[c], in);
+    const int64_t nchunk = cases[c].sc.nchunk, pairs = cases[c].sc.chunk_pairs;
+    double* dW = cases[c].B.dW + (ic * nchunk + chunk) * 5;
+    __syncthreads();  // the previous item's readers of LDS are done
+    double mw[D + 2];
+    sweep_item<D, T, T, true, false, D == 2>(in, (const T*)cases[c].B.h, (const T*)cases[c].B.b,
+                                             (T*)cases[c].B.ht, (T*)cases[c].B.bt, ic, (unsigned)(chunk * pairs),
+                                             (unsigned)min((int64_t)in.half, (chunk + 1) * pairs), L.s, nullptr,
+                                             mw);
+    block_total<D + 2>(mw, L.red);
+    if (threadIdx.x == 0)
+      for (int x = 0; x < D + 2; ++x) dW[x] = mw[x];
   }
 }
 
@@ -1333,6 +1371,31 @@ __global__ __launch_bounds__(SWT) void k_finish(SweepIn<T> in, GasP g, int64_t n
   }
   finish_cell<D, T, T, HB>(g, in.vidx, in.w, o, ht, bt, ic, in.nvp, in.half, in.na, in.axis, nullptr, 0u, tot,
                         L.c, L.red);
+}
+
+// The same over a batch, one work-group per cell.
+__device__ __forceinline__ int case_of(const int64_t* __restrict__ off, int n, int64_t t);
+
+template <int D, typename T>
+__global__ __launch_bounds__(SWT) void k_finish_b(BatchDev bd) {
+  __shared__ SweepLds<D, T> L;
+  const int c = case_of(bd.cell_off, bd.n, blockIdx.x);
+  const int64_t ic = (int64_t)blockIdx.x - bd.cell_off[c];
+  ccase_t& C = ((ccase_t*)bd.cases)[c];
+  GasP g;
+  CellOut o;
+  case_out(C, g, o);
+  if (*o.flag) return;
+  const int64_t nchunk = C.sc.nchunk;
+  const double* dW = C.B.dW + ic * nchunk * 5;
+  double tot[D + 2];
+#pragma unroll
+  for (int x = 0; x < D + 2; ++x) {
+    tot[x] = 0.0;
+    for (int64_t k = 0; k < nchunk; ++k) tot[x] += dW[k * 5 + x];
+  }
+  finish_cell<D, T, T, D == 2>(g, C.fm.vidx, C.v.w, o, (T*)C.B.ht, (T*)C.B.bt, ic, C.v.nvp, (unsigned)C.fm.half,
+                               C.fm.na, C.fm.axis, nullptr, 0u, tot, L.c, L.red);
 }
 
 // Wall density with the wall cell's gradient evaluated in place.
@@ -1908,11 +1971,21 @@ hipError_t launch_step_b(int D, int prec, const BatchDev& bd, int64_t grid, int 
   return hipGetLastError();
 }
 
-int step_b_blocks_per_cu(int D, int prec, int threads) {
+hipError_t launch_sweep_b(int D, int prec, const BatchDev& bd, int64_t ncell, int64_t grid, int threads,
+                          hipStream_t s) {
+  if (bd.nitems == 0) return hipSuccess;
+  if (threads % 64 != 0 || threads < 64 || threads > SWT) return hipErrorInvalidValue;
+  UGKS_DISPATCH_DT(D, prec, k_sweep_b<DD, TT><<<(unsigned)grid, threads, 0, s>>>(bd));
+  UGKS_DISPATCH_DT(D, prec, k_finish_b<DD, TT><<<(unsigned)ncell, SWT, 0, s>>>(bd));
+  return hipGetLastError();
+}
+
+int batch_blocks_per_cu(int D, int prec, int threads, bool blocks) {
   int n = 0;
   hipError_t e = hipSuccess;
   UGKS_DISPATCH_DT(D, prec, e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-                                &n, reinterpret_cast<const void*>(&k_step_b<DD, TT>), threads, 0));
+                                &n, blocks ? reinterpret_cast<const void*>(&k_sweep_b<DD, TT>)
+                                           : reinterpret_cast<const void*>(&k_step_b<DD, TT>), threads, 0));
   return e == hipSuccess ? n : 0;
 }
 

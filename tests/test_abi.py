@@ -127,3 +127,20 @@ def test_batch_create_rejects_empty_batch():
     with pytest.raises(U.UGKSError) as e:
         U.ugks_batch_create([])
     assert e.value.code == U.UGKS_EINVAL
+
+
+def test_autotune_cache_file_keeps_the_blocked_form(tmp_path):
+    """A batch's lanes may be followed by the pairs per block of its blocked form."""
+    lib = ugks.load_library()
+    lib.ugks_autotune_clear()
+    lines = ["batch 3 64 0 6 21952 : 256 704", "batch 3 64 0 48 21952 : 128"]
+    good = tmp_path / "good.txt"
+    good.write_text("ugks-autotune 1\n" + "\n".join(lines) + "\n")
+    assert lib.ugks_autotune_load(str(good).encode()) == 0
+    out = tmp_path / "out.txt"
+    assert lib.ugks_autotune_save(str(out).encode()) == 0
+    assert sorted(out.read_text().splitlines()[1:]) == sorted(lines)
+    bad = tmp_path / "bad.txt"
+    bad.write_text("ugks-autotune 1\nbatch x : 128 -704\n")
+    assert lib.ugks_autotune_load(str(bad).encode()) == -1
+    lib.ugks_autotune_clear()
