@@ -279,6 +279,9 @@ hipError_t launch_init_maxwellian(int D, int prec, const DevMesh& m, const DevVe
                                   const double* prim, void* h, void* b, hipStream_t s);
 hipError_t launch_moments(int D, int prec, const DevMesh& m, const DevVel& v, const void* h,
                           const void* b, double* out, hipStream_t s);
+// rows between slots and the caller's order (in: to the slots)
+hipError_t launch_reorder(int prec, int64_t nc, int64_t nv, int64_t nvp, const int32_t* cell, const int32_t* vel,
+                          void* own, void* user, bool in, hipStream_t s);
 hipError_t launch_dt_cells(int D, const DevMesh& m, const DevVel& v, double* cellval,
                            hipStream_t s);
 // fused sweep (ugks_sweep.hip)
@@ -343,6 +346,7 @@ struct ugks_ctx {
   std::vector<int64_t> cell_perm;   // library cell c -> caller cell
   std::vector<int64_t> face_perm;   // library face f -> caller face
   std::vector<int64_t> vel_perm;    // velocity slot k < nvp -> caller velocity (-1: pad)
+  const int32_t *cell_dev = nullptr, *vel_dev = nullptr;  // both on the device
   ugks::DevMesh mesh{};
   const double* lsG_exact = nullptr;  // least-squares coefficients even under first-order reconstruction
   ugks::DevVel vel{};

@@ -783,6 +783,22 @@ __global__ __launch_bounds__(TPB) void k_init_maxwellian(DevVel v, const double*
   if (v.has_b) st(b, i * v.nvp + k, v.kxi / (2.0 * P[4]) * H);
 }
 
+// Rows of h or b in slots (own) and in the caller's order of cells and velocities
+// (user): vel[k] is the velocity of slot k, -1 for a pad, which reads as 0.
+template <typename T>
+__global__ __launch_bounds__(TPB) void k_reorder(int64_t nv, int64_t nvp, const int32_t* __restrict__ cell,
+                                                 const int32_t* __restrict__ vel, T* __restrict__ own,
+                                                 T* __restrict__ user, int in) {
+  const int64_t nch = (nvp + TPB - 1) / TPB;
+  const int64_t i = blockIdx.x / nch;
+  const int64_t k = (blockIdx.x % nch) * TPB + threadIdx.x;
+  if (k >= nvp) return;
+  const int32_t kk = vel[k];
+  const int64_t at = (int64_t)cell[i] * nv + kk;
+  if (in) own[i * nvp + k] = kk >= 0 ? user[at] : T(0);
+  else if (kk >= 0) user[at] = own[i * nvp + k];
+}
+
 // Discrete moments sum_k w_k psi_k (h, b) per cell.
 template <int D, typename T>
 __global__ __launch_bounds__(TPB) void k_moments(DevVel v, const T* __restrict__ h,
@@ -985,6 +1001,16 @@ hipError_t launch_init_maxwellian(int D, int prec, const DevMesh& m, const DevVe
 hipError_t launch_moments(int D, int prec, const DevMesh& m, const DevVel& v, const void* h,
                           const void* b, double* out, hipStream_t s) {
   UGKS_DISPATCH_DT(D, prec, k_moments<DD, TT><<<(unsigned)m.nc, TPB, 0, s>>>(v, (const TT*)h, (const TT*)b, out));
+  return hipGetLastError();
+}
+
+hipError_t launch_reorder(int prec, int64_t nc, int64_t nv, int64_t nvp, const int32_t* cell, const int32_t* vel,
+                          void* own, void* user, bool in, hipStream_t s) {
+  const unsigned grid = blocks_for(nvp, TPB) * (unsigned)nc;
+  if (prec == UGKS_FP32)
+    k_reorder<float><<<grid, TPB, 0, s>>>(nv, nvp, cell, vel, (float*)own, (float*)user, in);
+  else
+    k_reorder<double><<<grid, TPB, 0, s>>>(nv, nvp, cell, vel, (double*)own, (double*)user, in);
   return hipGetLastError();
 }
 
