@@ -168,8 +168,8 @@ typedef struct {
  *                     and vice versa.  Excludes bit 6 (UGKS_EINVAL); the
  *                     batched form refuses it (UGKS_EUNSUPPORTED).  ugks_info's
  *                     dt stays the global dt.
- *              bit 5: replay each step from a HIP graph of its kernels
- *                     (captured at the first step that can use it; not on the
+ *              bit 5: replay the steps from HIP graphs of their kernels
+ *                     (captured when first needed; not on the
  *                     null stream, nor while profiling).  Same results as
  *                     kernel-by-kernel launches.
  *   The fused sweep (one pass for reconstruction, interface flux, moment

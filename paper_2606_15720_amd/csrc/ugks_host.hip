@@ -1612,40 +1612,63 @@ int ugks_create(const ugks_mesh* mesh, const ugks_velocity* vel, const ugks_gas*
 
 namespace {
 
-// Capture one step per order of the buffers it swaps as HIP graphs.  The
-// step records kernels only (no memset or copy), and two captures swap the
-// buffers twice, so the context ends as it started.
-void capture_step_graphs(ugks_ctx* c) {
-  c->graph_q0 = c->buf.q;
-  for (int par = 0; par < 2; ++par) {
-    HIP_TRY(hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
-    try {
-      enqueue_step(c, !(c->flags & 1), true);
-    } catch (...) {
-      hipGraph_t g = nullptr;
-      (void)hipStreamEndCapture(c->stream, &g);
-      if (g) (void)hipGraphDestroy(g);
-      throw;
-    }
-    HIP_TRY(hipStreamEndCapture(c->stream, &c->graph[par]));
-    HIP_TRY(hipGraphInstantiate(&c->graph_exec[par], c->graph[par], nullptr, nullptr, 0));
+// The graph of the last step of a call (full: with the residual and wide cells'
+// face fluxes), or of two steps that leave those out, from the buffers as they
+// are; captured when it is first needed.  Kernels only (no memset or copy).
+// A launch of a graph costs the GPU some 5 us: in graphs of one step, each with
+// the last one's work, 1,024 cells x 24^2 took 53 us per step and 1,728 hexahedra
+// x 16^3 358, where the kernels one by one take 42 and 248; 45 and 251 so.
+hipGraphExec_t step_graph(ugks_ctx* c, bool full) {
+  if (!c->graph_q0) c->graph_q0 = c->buf.q;
+  const int par = c->buf.q == c->graph_q0 ? 0 : 1;
+  hipGraphExec_t& exec = c->graph_exec[full][par];
+  if (exec) return exec;
+  const StepBuffers kept = c->buf;
+  hipGraph_t g = nullptr;
+  HIP_TRY(hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal));
+  try {
+    enqueue_step(c, full && !(c->flags & 1), full);
+    if (!full) enqueue_step(c, false, false);
+  } catch (...) {
+    c->buf = kept;
+    (void)hipStreamEndCapture(c->stream, &g);
+    if (g) (void)hipGraphDestroy(g);
+    throw;
   }
+  c->buf = kept;
+  HIP_TRY(hipStreamEndCapture(c->stream, &g));
+  const hipError_t e = hipGraphInstantiate(&exec, g, nullptr, nullptr, 0);
+  (void)hipGraphDestroy(g);
+  if (e != hipSuccess) {
+    exec = nullptr;
+    throw HipFail{e, "hipGraphInstantiate"};
+  }
+  return exec;
 }
 
-// One step: a graph replay where asked for (flags bit 5) and where one
-// applies (not profiling, the heat flux of the current f known, a stream
-// that can be captured), else the kernels one by one.  Both run the same
-// kernels with the same arguments.
-void run_step(ugks_ctx* c, bool residual, bool face_flux) {
-  const bool graphs = (c->flags & 32) && !c->profiling && c->stream != nullptr;
-  if (!graphs || !c->q_valid || (c->slots() && !c->cs_valid)) {
-    enqueue_step(c, residual, face_flux);
-    return;
+// n steps: replayed from graphs where asked for (flags bit 5) and where that
+// applies (not profiling, the heat flux of the current f known, a stream that can
+// be captured), else the kernels one by one.  Both run the same kernels with the
+// same arguments.
+void run_steps(ugks_ctx* c, int32_t n) {
+  const bool graphs = (c->flags & 32) && !c->profiling && c->stream != nullptr, nores = c->flags & 1;
+  for (int32_t s = 0; s < n;) {
+    // the residual is the last step's, in units of the first non-zero change:
+    // the steps before the last need it only until that unit is known
+    const bool last = s + 1 == n, residual = !nores && (last || !c->resid_set), full = last || residual;
+    const bool replay = graphs && c->q_valid && (!c->slots() || c->cs_valid);
+    if (replay && full) {
+      HIP_TRY(hipGraphLaunch(step_graph(c, true), c->stream));
+      if (c->slots()) swap_buffers(c->buf);  // as the fused step does on the host
+      s += 1;
+    } else if (replay && s + 2 < n) {
+      HIP_TRY(hipGraphLaunch(step_graph(c, false), c->stream));
+      s += 2;
+    } else {
+      enqueue_step(c, residual, last);
+      s += 1;
+    }
   }
-  if (!c->graph_exec[0]) capture_step_graphs(c);
-  const int par = c->buf.q == c->graph_q0 ? 0 : 1;
-  HIP_TRY(hipGraphLaunch(c->graph_exec[par], c->stream));
-  if (c->slots()) swap_buffers(c->buf);  // as the fused step does on the host
 }
 
 }  // namespace
@@ -1655,10 +1678,7 @@ int ugks_step(ugks_ctx* c, int32_t n_steps, double* residual_out) {
   if (n_steps < 0) return set_err(c, UGKS_EINVAL, "n_steps < 0");
   Range range("ugks_step");
   try {
-    // the residual is the last step's, in units of the first non-zero change:
-    // the steps before the last need it only until that unit is known
-    for (int32_t s = 0; s < n_steps; ++s)
-      run_step(c, !(c->flags & 1) && (s + 1 == n_steps || !c->resid_set), s + 1 == n_steps);
+    run_steps(c, n_steps);
     HIP_TRY(hipMemcpyAsync(c->host, c->buf.resid, kStatus * sizeof(double), hipMemcpyDeviceToHost, c->stream));
     HIP_TRY(hipStreamSynchronize(c->stream));
     const double* res = c->host;
@@ -1889,10 +1909,9 @@ int ugks_profile_read(ugks_ctx* c, ugks_kernel_time* out, int32_t max, int32_t* 
 void ugks_destroy(ugks_ctx* c) {
   if (!c) return;
   if (c->stream) (void)hipStreamSynchronize(c->stream);
-  for (int par = 0; par < 2; ++par) {
-    if (c->graph_exec[par]) (void)hipGraphExecDestroy(c->graph_exec[par]);
-    if (c->graph[par]) (void)hipGraphDestroy(c->graph[par]);
-  }
+  for (auto& of : c->graph_exec)
+    for (hipGraphExec_t exec : of)
+      if (exec) (void)hipGraphExecDestroy(exec);
   for (auto& e : c->prof_events) {
     (void)hipEventDestroy(e.second.first);
     (void)hipEventDestroy(e.second.second);

@@ -333,10 +333,10 @@ struct ugks_ctx {
   bool cs_valid = false;    // buf.prim, buf.cs hold the records of the current W and q
   bool resid_set = false;   // the residual's unit (its first non-zero change) is known
   int32_t begun = 0;        // buf.flag[1] when last read
-  // HIP graphs of one step, one per order of the q / q^{n+1} buffers (the
-  // step swaps them); graph_q0 is buf.q when graph 0 was captured
-  hipGraph_t graph[2] = {nullptr, nullptr};
-  hipGraphExec_t graph_exec[2] = {nullptr, nullptr};
+  // HIP graphs of two steps, and (1) of one with what only the last step of a call
+  // computes, each per order of the buffers that a step swaps; graph_q0 is buf.q
+  // in the first order
+  hipGraphExec_t graph_exec[2][2] = {};
   const double* graph_q0 = nullptr;
   ugks::FusedMesh fmesh{};  // static records of the fused sweep
   ugks::SweepSched sched{};

@@ -11,7 +11,7 @@ from paper_2606_15720_amd.ugks import UGKS_ENUMERIC, Solver, UGKSError, ugks_sna
 
 pytestmark = pytest.mark.gpu
 
-STAGED, TRACK = 2, 64
+STAGED, GRAPH, TRACK = 2, 32, 64
 
 
 def _quads(cfl):
@@ -47,7 +47,7 @@ def _moments(s):
     return [s.W(), s.moments(1), s.moments(2), *ugks_snapshot(s.h, s.nc)]
 
 
-@pytest.mark.parametrize("make,flags", [(_quads, 0), (_quads, STAGED), (_hexes, 0)])
+@pytest.mark.parametrize("make,flags", [(_quads, 0), (_quads, STAGED), (_hexes, 0), (_quads, GRAPH), (_hexes, GRAPH)])
 @pytest.mark.parametrize("cfl", [3.5, 5.0])
 def test_readouts_after_a_failure_are_those_of_the_kept_state(make, flags, cfl):
     a = Solver(make(cfl), flags=flags)
