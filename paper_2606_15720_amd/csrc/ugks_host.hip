@@ -1022,9 +1022,12 @@ std::mutex g_tune_mu;
 std::map<std::string, TuneCase> g_tune_case;
 std::map<std::string, TuneBatch> g_tune_batch;
 
+// (the w: timed on the whole-cell step.  Files written before there was one have
+// keys without it; their entries are loaded and kept, but were measured on other
+// kernels and match no case)
 std::string case_key(int D, int prec, int threads, int64_t nc, int64_t nv) {
   char buf[128];
-  std::snprintf(buf, sizeof buf, "%d %d %d %lld %lld", D, prec, threads, (long long)nc, (long long)nv);
+  std::snprintf(buf, sizeof buf, "%d %d %d %lld %lld w", D, prec, threads, (long long)nc, (long long)nv);
   return buf;
 }
 

@@ -109,3 +109,21 @@ def test_a_case_that_fails_in_a_blocked_batch_keeps_its_step():
     assert np.all(_normwise(c.W(1), kept) <= 1e-8)  # (rounding grows with the unstable mode)
     c.close()
     d.close()
+
+
+def test_a_tuning_file_of_the_earlier_kernels_is_loaded_but_not_used(tmp_path):
+    """Files from before the whole-cell step name their shapes without a mark; what
+    they hold was timed on other kernels."""
+    U.ugks_autotune_clear()
+    case = uc.cavity2d(n=6, nv=8)
+    lines = [f"case 2 64 {t} 36 64 : 32 16 {t}.5" for t in (64, 128, 256)] + ["batch 2 64 0 36 64 : 256"]
+    path = tmp_path / "tune.txt"
+    path.write_text("ugks-autotune 1\n" + "\n".join(lines) + "\n")
+    U.ugks_autotune_load(str(path))
+    b = U.Batch([case])
+    assert b.info["tune_timings"] > 0
+    b.close()
+    out = tmp_path / "out.txt"
+    U.ugks_autotune_save(str(out))
+    assert set(lines) < set(out.read_text().splitlines())
+    U.ugks_autotune_clear()
