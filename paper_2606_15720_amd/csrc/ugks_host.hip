@@ -174,9 +174,18 @@ constexpr int64_t kPinnedCells = 4 << 20;  // bytes of cell data read back throu
 //   FP32   7: 0.141 0.147 0.163 0.260;  8: 0.326 0.306 0.349 0.505;
 //         13: 0.236 0.218 0.237 0.331;  32 (48,000 tets): 1.834 1.572 1.524 1.768;
 //         83: - - 1.839 1.846;  172: - - 3.647 3.592
-int cell_lanes(int64_t nc, int64_t pairs, int prec) {
-  static const int64_t from[2][3] = {{3, 13, 58}, {8, 20, 128}};  // waves of pairs for 2, 4, 8 waves
-  const int64_t waves = pairs / WAVE, *line = from[prec == UGKS_FP32 ? 1 : 0];
+// Wide cells' tables take the LDS of two to four narrow ones', so that small groups
+// leave compute units short of waves.  Their kernel alone (4,096 hexahedra, and
+// 13,824 at 54 and 63 waves):
+//   FP64   1: 0.075 0.067 0.067 0.122;  2: 0.093 0.070 0.069 0.124;
+//          3: 0.109 0.087 0.073 0.124;  8: 0.192 0.132 0.104 0.139;
+//         32: 0.655 0.430 0.318 0.331;  54: - - 1.744 1.651;  63: - - 1.998 1.859
+//   FP32   1: 0.078 0.070 0.070 0.130;  3: 0.123 0.094 0.075 0.136;
+//         32: 0.840 0.505 0.343 0.361;  54: - - 1.878 1.889;  63: - - 2.112 2.096
+int cell_lanes(int64_t nc, int64_t pairs, int prec, bool wide) {
+  // waves of pairs from which 2, 4, 8 waves take a cell
+  static const int64_t from[3][3] = {{3, 13, 58}, {8, 20, 128}, {1, 3, 54}};
+  const int64_t waves = pairs / WAVE, *line = from[wide ? 2 : prec == UGKS_FP32 ? 1 : 0];
   int64_t w = 1;
   for (int i = 0; i < 3 && (waves >= line[i] || (nc * w < 4096 && 2 * w <= waves)); ++i) w *= 2;
   return (int)(w * WAVE);
@@ -579,7 +588,7 @@ void build(ugks_ctx* c, const ugks_mesh* mesh, const ugks_velocity* vel, const u
     c->fmesh.crec_i = upload(c, ci);
     c->fmesh.crec_d = upload(c, cdr);
     c->fmesh.frow = upload(c, frow);
-    c->sched.lanes = cell_lanes(nc, c->fmesh.half, UGKS_FP64);
+    c->sched.lanes = cell_lanes(nc, c->fmesh.half, prec, true);
     c->sched.tile = dev::xcd_run(nc, 32);  // (as the gradients' runs)
   }
   if (c->fused) {
@@ -739,7 +748,7 @@ void build(ugks_ctx* c, const ugks_mesh* mesh, const ugks_velocity* vel, const u
     cp = std::max<int64_t>(std::min<int64_t>(32, npairs), std::min<int64_t>(cp, npairs));
     c->sched.whole = cp >= npairs || (!Bv && nc >= kWholeCells) ? 1 : 0;
     if (c->sched.whole) cp = npairs;
-    c->sched.lanes = cell_lanes(nc, npairs, prec);
+    c->sched.lanes = cell_lanes(nc, npairs, prec, false);
     c->sched.chunk_pairs = cp;
     c->sched.nchunk = (npairs + cp - 1) / cp;
     c->sched.tile = tile ? tile : 32;

@@ -147,3 +147,9 @@ def test_few_cells_take_every_xcd():
     few, many = gradients(3, 40), gradients(6, 20)
     print("gradients of 27 x 40^3 and 216 x 20^3, ms:", few, many, flush=True)
     assert few <= 1.5 * many
+
+
+@pytest.mark.parametrize("nv,lim", [(4, {}), (7, dict(limiter=1, limiter_k=0.5))])  # 1 and 3 waves of pairs
+def test_many_wide_cells_with_few_velocities(nv, lim):
+    # enough cells that lanes come from the pairs alone: more of them than pairs
+    _compare_step(_hexes(nv, far=(2,), n=(17, 16, 16)), 2, **lim)
