@@ -82,8 +82,10 @@ __host__ __device__ __forceinline__ int64_t xcd_run(int64_t n, int64_t most) {
 // 1.29 and 1.15).  -1: none.
 constexpr int64_t FACE_TILE = 64;
 __device__ __forceinline__ int64_t face_of_block(const DevMesh& m) {
-  const int64_t xcd = blockIdx.x % 8, local = blockIdx.x / 8, run = xcd_run(m.nf, FACE_TILE);
-  const int64_t t = ((local / run) * 8 + xcd) * run + local % run;
+  const uint32_t xcd = blockIdx.x % 8, local = blockIdx.x / 8;
+  const int64_t t = m.nf >= 8 * FACE_TILE
+                        ? (int64_t)(local / FACE_TILE * 8 + xcd) * FACE_TILE + local % FACE_TILE
+                        : xcd * xcd_run(m.nf, FACE_TILE) + local;
   return t < m.nf ? m.ford[t] : -1;
 }
 inline unsigned face_grid(const DevMesh& m) {

@@ -380,20 +380,27 @@ __global__ __launch_bounds__(64) void k_face_eq(DevMesh m, const DevBC* __restri
 constexpr int64_t GRAD_TILE = 32;
 constexpr int64_t kLastLevel = 256 << 20;  // bytes
 
-template <int D, typename T>
+// (NT: a template argument, as a branch over the two kinds of store becomes one plain one)
+template <int D, typename T, bool NT>
 __global__ __launch_bounds__(TPB) void k_grad_micro(DevMesh m, DevVel v,
                                                     const double* __restrict__ frec,
                                                     const T* __restrict__ h, const T* __restrict__ b,
                                                     double* __restrict__ gh, double* __restrict__ gb,
-                                                    const int32_t* flag, int bypass) {
+                                                    const int32_t* flag) {
   typedef T pair_t __attribute__((ext_vector_type(2)));
   typedef double dpair_t __attribute__((ext_vector_type(2)));
   const int64_t nvp = v.nvp, nch = (nvp + 2 * TPB - 1) / (2 * TPB);
-  const int64_t run = xcd_run(m.nc, GRAD_TILE);
-  const int64_t xcd = blockIdx.x % 8, local = blockIdx.x / 8, per_run = nch * run;
-  const int64_t rem = local % per_run;
-  const int64_t i = ((local / per_run) * 8 + xcd) * run + rem % run;
-  const int64_t k = 2 * ((rem / run) * TPB + threadIdx.x);  // nvp is even
+  const uint32_t xcd = blockIdx.x % 8, local = blockIdx.x / 8;
+  uint32_t tile = 0, rem = local, run = GRAD_TILE;
+  if (m.nc >= 8 * GRAD_TILE) {
+    const uint32_t per_tile = (uint32_t)nch * GRAD_TILE;
+    tile = local / per_tile;
+    rem = local - tile * per_tile;
+  } else {
+    run = (uint32_t)xcd_run(m.nc, GRAD_TILE);
+  }
+  const int64_t i = (int64_t)(tile * 8 + xcd) * run + rem % run;
+  const int64_t k = 2 * ((int64_t)(rem / run) * TPB + threadIdx.x);  // nvp is even
   if (i >= m.nc || k >= nvp || *flag) return;
   const int nfc = m.nfc[i];
   for (int r = 0; r < (v.has_b ? 2 : 1); ++r) {
@@ -444,7 +451,7 @@ __global__ __launch_bounds__(TPB) void k_grad_micro(DevMesh m, DevVel v,
     double* __restrict__ g = r ? gb : gh;
     for (int d = 0; d < D; ++d) {
       const dpair_t o = {a[0][d], a[1][d]};
-      if (bypass) __builtin_nontemporal_store(o, (dpair_t*)&g[(i * 3 + d) * nvp + k]);
+      if constexpr (NT) __builtin_nontemporal_store(o, (dpair_t*)&g[(i * 3 + d) * nvp + k]);
       else *(dpair_t*)&g[(i * 3 + d) * nvp + k] = o;
     }
   }
@@ -938,10 +945,13 @@ hipError_t launch_grad_micro(int D, int prec, const DevMesh& m, const DevVel& v,
                              const double* frec, const void* h, const void* b, double* gh,
                              double* gb, const int32_t* flag, hipStream_t s) {
   const int64_t per = 8 * xcd_run(m.nc, GRAD_TILE);
-  const int bypass = m.nc * v.nvp * D * (v.has_b ? 2 : 1) * (int64_t)sizeof(double) > kLastLevel;
   const unsigned grid = (unsigned)((m.nc + per - 1) / per * per) * blocks_for(v.nvp, 2 * TPB);
-  UGKS_DISPATCH_DT(D, prec, k_grad_micro<DD, TT><<<grid, TPB, 0, s>>>(
-      m, v, frec, (const TT*)h, (const TT*)b, gh, gb, flag, bypass));
+  if (m.nc * v.nvp * D * (v.has_b ? 2 : 1) * (int64_t)sizeof(double) > kLastLevel)
+    UGKS_DISPATCH_DT(D, prec, k_grad_micro<DD, TT, true><<<grid, TPB, 0, s>>>(
+        m, v, frec, (const TT*)h, (const TT*)b, gh, gb, flag));
+  else
+    UGKS_DISPATCH_DT(D, prec, k_grad_micro<DD, TT, false><<<grid, TPB, 0, s>>>(
+        m, v, frec, (const TT*)h, (const TT*)b, gh, gb, flag));
   return hipGetLastError();
 }
 
