@@ -575,6 +575,7 @@ void build(ugks_ctx* c, const ugks_mesh* mesh, const ugks_velocity* vel, const u
         I[WI_ROW + p] = j >= 0 ? j : ghost_row[f] >= 0 ? ghost_row[f] : (int32_t)nc;
         I[WI_FACE + p] = f;
         I[WI_KIND + p] = fbc[f];
+        if (p < nfc[i] && ghost_row[f] >= 0) I[WI_FAR] = 1;
         for (int d = 0; d < 3; ++d) {
           fd[d] = sg * fnorm[f * 3 + d];
           fd[3 + d] = sg > 0.0 ? fdxL[f * 3 + d] : fdxR[f * 3 + d];
@@ -765,8 +766,9 @@ void build(ugks_ctx* c, const ugks_mesh* mesh, const ugks_velocity* vel, const u
   // row nc of h and b stays zero: the fused sweep's wall faces read it;
   // rows nc+1 ... are the fused sweep's far-field ghost rows.  On the fused
   // path h and ht (b and bt) trade places every step, so both have them.
-  // (The wide form's ghost rows are FP64 arrays of their own.)
-  const int64_t rows = nc + 1 + (c->fused ? c->fmesh.nff : 0), trows = c->slots() ? rows : nc;
+  // (Wide cells' ghost rows in the FP32 form are FP64 arrays of their own.)
+  const bool apart = c->wide && prec == UGKS_FP32;
+  const int64_t rows = nc + 1 + (c->slots() && !apart ? c->fmesh.nff : 0), trows = c->slots() ? rows : nc;
   B.h = dalloc<char>(c, (size_t)rows * nvp * esz);
   B.ht = dalloc<char>(c, (size_t)trows * nvp * esz);
   B.b = c->nr == 2 ? (void*)dalloc<char>(c, (size_t)rows * nvp * esz) : nullptr;
@@ -789,7 +791,7 @@ void build(ugks_ctx* c, const ugks_mesh* mesh, const ugks_velocity* vel, const u
     B.gradh = dalloc<double>(c, (size_t)nc * 3 * nvp);
     B.gradb = c->nr == 2 ? dalloc<double>(c, (size_t)nc * 3 * nvp) : nullptr;
   }
-  if (c->wide && c->fmesh.nff) {
+  if (apart && c->fmesh.nff) {
     B.ghosth = dalloc<double>(c, (size_t)c->fmesh.nff * nvp);
     B.ghostb = c->nr == 2 ? dalloc<double>(c, (size_t)c->fmesh.nff * nvp) : nullptr;
   }
@@ -912,7 +914,7 @@ void enqueue_step_fused(ugks_ctx* c, bool residual, bool face_flux) {
   // the wall densities
   // (in one launch where neither reads what the other writes)
   const bool joint = c->fmesh.nff && c->fmesh.apart && m.nwall && !c->wide;
-  if (c->fmesh.nff && c->wide)
+  if (c->fmesh.nff && B.ghosth)
     TIMED(KK_WALL, launch_ghost_rows(D, UGKS_FP64, c->fmesh, v, B.frec, 0, B.ghosth, B.ghostb, B.flag, s));
   else if (c->fmesh.nff && !joint)
     TIMED(KK_WALL, launch_ghost_rows(D, P, c->fmesh, v, B.frec, m.nc + 1, B.h, B.b, B.flag, s));
@@ -958,7 +960,8 @@ void face_flux_after_failure(ugks_ctx* c) {
   if (e == hipSuccess)
     e = launch_face_eq(D, c->mesh, c->bcs, c->gas, B.W, B.gW, B.q, B.frec, UGKS_FP64, c->nr, B.srec, flag, s);
   if (e == hipSuccess)
-    e = launch_ghost_rows(D, UGKS_FP64, c->fmesh, c->vel, B.frec, 0, B.ghosth, B.ghostb, flag, s);
+    e = B.ghosth ? launch_ghost_rows(D, UGKS_FP64, c->fmesh, c->vel, B.frec, 0, B.ghosth, B.ghostb, flag, s)
+                 : launch_ghost_rows(D, P, c->fmesh, c->vel, B.frec, c->nc + 1, B.h, B.b, flag, s);
   if (e == hipSuccess)
     e = launch_grad_micro(D, P, c->mesh, c->vel, B.frec, B.h, B.b, B.gradh, B.gradb, flag, s);
   if (e == hipSuccess) e = launch_wall_rho(D, P, c->mesh, c->vel, c->gas, B.h, B.gradh, B.frec, flag, s);

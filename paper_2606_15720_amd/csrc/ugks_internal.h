@@ -89,12 +89,12 @@ constexpr int CRL = 88, CRL_F0 = 8, CRL_FS = 20;
 // Records of cells with more than four faces (the wide form of the fused
 // step, up to MAXF faces, FP64), in the same arrays with strides CRI and CRD:
 //   [WI_ROW + p] the row across face p (a neighbour, the zero row nc at a wall, or
-//   nc + 1 + m for row m of the ghost rows, which are FP64 arrays of their own); [WI_FACE + p]; [WI_KIND + p]; [WI_NF] the cell's faces;
+//   nc + 1 + m for ghost row m, in the FP32 form a row of FP64 arrays of their own); [WI_FACE + p]; [WI_KIND + p]; [WI_NF] the cell's faces; [WI_FAR] 1 if one has a ghost row;
 //   face p at WD_FS p: [0..2] outward unit normal, [3..5] x_f - x_cell,
 //   [6..8] x_f - x_neighbour, [9] as [18] above, [10] S/V.
-constexpr int WI_ROW = 0, WI_FACE = 8, WI_KIND = 16, WI_NF = 24;
+constexpr int WI_ROW = 0, WI_FACE = 8, WI_KIND = 16, WI_NF = 24, WI_FAR = 25;
 constexpr int WD_FS = 12;
-static_assert(WD_FS * MAXF <= CRD && WI_NF < CRI, "records of wide cells");
+static_assert(WD_FS * MAXF <= CRD && WI_FAR < CRI, "records of wide cells");
 // Per-step records of the fused path in its compute type, SREC values per
 // face or cell and distribution (h, then b where it is carried):
 //   face: [0..1] Gamma_1, Gamma_2; cell: [0] dt/(2 tau), [1] K_xi/(2 lambda);
@@ -194,7 +194,7 @@ struct StepBuffers {
   void* bt;
   double* gradh;   // [nc*3*nvp] microscopic gradients (staged sweep)
   double* gradb;
-  double* ghosth;  // [nff*nvp] ghost rows of wide cells
+  double* ghosth;  // [nff*nvp] ghost rows of wide cells in the FP32 form
   double* ghostb;
   double* fluxh;   // [nf*nvp] time-integrated microscopic fluxes (staged sweep)
   double* fluxb;

@@ -1107,7 +1107,7 @@ __global__ __launch_bounds__(SWT, (D == 3 ? 4 : 3)) void k_sweep_b(BatchDev bd) 
 // 2, 3, 4 and 6: 0.562, 0.552, 0.552 and 0.554 ms on 4,096 hexahedra x 20^3).
 constexpr int WGF = 3;
 
-template <int D, typename T, bool HB, int X>
+template <int D, typename T, bool HB, bool GH, int X>
 __device__ __forceinline__ void wide_pass(const SweepIn<double>& in, const T* __restrict__ f,
                                           const double* __restrict__ gr, const double* __restrict__ gg,
                                           T* __restrict__ ft, int64_t ic, int32_t ghost0,
@@ -1166,7 +1166,7 @@ __device__ __forceinline__ void wide_pass(const SweepIn<double>& in, const T* __
           sp[p] = s;
           const int32_t row = ci[WI_ROW + p];
           // u.n > 0: the incoming member is -u
-          if (row < ghost0) fj[p] = ldo<T, C>(row_of(row), s > 0.0 ? o1 : o0);
+          if (!GH || row < ghost0) fj[p] = ldo<T, C>(row_of(row), s > 0.0 ? o1 : o0);
           else fj[p] = ldo<double, C>(srow((const char*)gg + (uint64_t)(uint32_t)(row - ghost0) * growb), s > 0.0 ? q1 : q0);
           if (ci[WI_KIND + p] == UGKS_BC_INTERIOR) {
 #pragma unroll
@@ -1239,7 +1239,7 @@ __device__ __forceinline__ void wide_pass(const SweepIn<double>& in, const T* __
 // 4,096 hexahedra x 20^3, FP64: 0.55 ms (2.4 TB/s of rows and gradients read once
 // and states written), where face fluxes, two stages and heat flux as passes of
 // their own take 2.0.
-template <int D, typename T, bool HB>
+template <int D, typename T, bool HB, bool GH>
 __global__ __launch_bounds__(CELLT, 4) void k_step_wide(SweepIn<double> in, SweepSched sc, int64_t nc, GasP g,
                                                         const T* __restrict__ h, const T* __restrict__ b,
                                                         const double* __restrict__ gh,
@@ -1259,8 +1259,17 @@ __global__ __launch_bounds__(CELLT, 4) void k_step_wide(SweepIn<double> in, Swee
 #pragma unroll
   for (int x = 0; x < D + 2; ++x) mw[x] = 0.0;
   const int32_t ghost0 = (int32_t)nc + 1;
-  wide_pass<D, T, HB, 0>(in, h, gh, hg, ht, ic, ghost0, L.s, stage, mw);
-  if constexpr (HB) wide_pass<D, T, HB, 1>(in, b, gb, bg, bt, ic, ghost0, L.s, stage, mw);
+  auto passes = [&](auto far) {
+    constexpr bool FAR = decltype(far)::value;
+    wide_pass<D, T, HB, FAR, 0>(in, h, gh, hg, ht, ic, ghost0, L.s, stage, mw);
+    if constexpr (HB) wide_pass<D, T, HB, FAR, 1>(in, b, gb, bg, bt, ic, ghost0, L.s, stage, mw);
+  };
+  if constexpr (GH) {
+    if (((crec_i_t*)(in.crec_i + ic * CRI))[WI_FAR]) passes(std::true_type{});
+    else passes(std::false_type{});
+  } else {
+    passes(std::false_type{});
+  }
   block_total<D + 2>(mw, L.red);
   finish_cell<D, T, double, HB>(g, in.vidx, in.w, o, ht, bt, ic, in.nvp, in.half, in.na, in.axis, stage,
                                 in.keep, mw, L.c, L.red);
@@ -1270,7 +1279,7 @@ __global__ __launch_bounds__(CELLT, 4) void k_step_wide(SweepIn<double> in, Swee
 // stored gradients, one work-group per face.  The step itself does not need
 // it: it runs for the last step of a call, whose face fluxes can be asked for,
 // and with boundary-flux tracking.
-template <int D, typename T, bool HB>
+template <int D, typename T, bool HB, bool GH>
 __global__ __launch_bounds__(SWT) void k_face_flux(DevMesh m, SweepIn<double> in,
                                                    const int32_t* __restrict__ frow,
                                                    const T* __restrict__ h, const T* __restrict__ b,
@@ -1323,7 +1332,7 @@ __global__ __launch_bounds__(SWT) void k_face_flux(DevMesh m, SweepIn<double> in
       const double* gr = r ? gb : gh;
       const double* S = in.srec + (f * (HB ? 2 : 1) + r) * SREC;
       double fl = ld(fv, Lc * nvp + kl), ul = 0.0, ur = 0.0;
-      double fr = gm >= 0 ? (r ? bg : hg)[gm * nvp + kr] : ld(fv, Rr * nvp + kr);
+      double fr = GH && gm >= 0 ? (r ? bg : hg)[gm * nvp + kr] : ld(fv, Rr * nvp + kr);
 #pragma unroll
       for (int d = 0; d < D; ++d) {
         const double a = gr[(Lc * 3 + d) * nvp + kl];
@@ -1854,9 +1863,15 @@ void launch_wide_as(const DevMesh& m, const FusedMesh& fm, const DevVel& v, cons
   SweepIn<double> in = sweep_in<double>(fm, v, g, B);
   const int64_t pair = (HB ? 4 : 2) * (int64_t)sizeof(T);
   in.keep = kept_pairs(16, sc, sizeof(SweepLds<D, double, MAXF>), pair, in.half);
-  k_step_wide<D, T, HB><<<grid, sc.lanes, (size_t)in.keep * pair, s>>>(
-      in, sc, fm.nc, g, (const T*)B.h, (const T*)B.b, B.gradh, B.gradb, B.ghosth, B.ghostb, (T*)B.ht, (T*)B.bt,
-      cell_out(m, B));
+  auto run = [&](auto gh) {
+    k_step_wide<D, T, HB, decltype(gh)::value><<<grid, sc.lanes, (size_t)in.keep * pair, s>>>(
+        in, sc, fm.nc, g, (const T*)B.h, (const T*)B.b, B.gradh, B.gradb, B.ghosth, B.ghostb, (T*)B.ht,
+        (T*)B.bt, cell_out(m, B));
+  };
+  if constexpr (sizeof(T) == 4) {
+    if (B.ghosth) return run(std::true_type{});
+  }
+  run(std::false_type{});
 }
 }  // namespace
 
@@ -1869,18 +1884,27 @@ hipError_t launch_step_wide(int D, int prec, const DevMesh& m, const FusedMesh& 
   return hipGetLastError();
 }
 
+namespace {
+template <int D, typename T, bool HB>
+void launch_face_flux_as(const DevMesh& m, const FusedMesh& fm, const DevVel& v, const GasP& g,
+                         const StepBuffers& B, hipStream_t s) {
+  auto run = [&](auto gh) {
+    k_face_flux<D, T, HB, decltype(gh)::value><<<face_grid(m), SWT, 0, s>>>(
+        m, sweep_in<double>(fm, v, g, B), fm.frow, (const T*)B.h, (const T*)B.b, B.gradh, B.gradb, B.ghosth,
+        B.ghostb, B.F, B.flag);
+  };
+  if constexpr (sizeof(T) == 4) {
+    if (B.ghosth) return run(std::true_type{});
+  }
+  run(std::false_type{});
+}
+}  // namespace
+
 hipError_t launch_face_flux(int D, int prec, const DevMesh& m, const FusedMesh& fm, const DevVel& v,
                             const GasP& g, const StepBuffers& B, hipStream_t s) {
-  const SweepIn<double> in = sweep_in<double>(fm, v, g, B);
-  const unsigned nf = face_grid(m);
-#define UGKS_FACE_FLUX(DD, HB)                                                                       \
-  UGKS_DISPATCH_T(prec, (k_face_flux<DD, TT, HB><<<nf, SWT, 0, s>>>(                                 \
-                            m, in, fm.frow, (const TT*)B.h, (const TT*)B.b, B.gradh, B.gradb, B.ghosth, \
-                            B.ghostb, B.F, B.flag)))
-  if (D == 2) UGKS_FACE_FLUX(2, true);
-  else if (B.b) UGKS_FACE_FLUX(3, true);
-  else UGKS_FACE_FLUX(3, false);
-#undef UGKS_FACE_FLUX
+  if (D == 2) UGKS_DISPATCH_T(prec, (launch_face_flux_as<2, TT, true>(m, fm, v, g, B, s)));
+  else if (B.b) UGKS_DISPATCH_T(prec, (launch_face_flux_as<3, TT, true>(m, fm, v, g, B, s)));
+  else UGKS_DISPATCH_T(prec, (launch_face_flux_as<3, TT, false>(m, fm, v, g, B, s)));
   return hipGetLastError();
 }
 
