@@ -1019,8 +1019,8 @@ struct ugks_batch_impl;
 
 namespace {
 
-// Autotuner cache: case shape -> (pairs per work item, tile cells, time) of the
-// whole-cell form, batch shape list -> lanes per work-group and, where the
+// Autotuner cache: case shape -> (pairs per work item: the whole set, a column of
+// the file; tile cells; time) of the whole-cell form, batch shape list -> lanes per work-group and, where the
 // blocked form is the faster one, its pairs per work item (else 0).
 struct TuneCase {
   int64_t chunk_pairs = 0, tile = 0;

@@ -1,11 +1,12 @@
 // Fused velocity sweep for tensor-product, mirror-symmetric velocity sets.
 //
 // A work item is one cell with all of its velocities (or, where cells are
-// too few, with one block of them).  Each lane owns a mirror pair of velocities (u, -u): for every face of the cell
-// exactly one of the two leaves the cell, so the lane evaluates one
-// time-integrated flux from the cell's own reconstruction (outgoing) and one
-// from the neighbour's reconstruction (incoming), with no divergence between
-// lanes.  The face and cell data are wave-uniform:
+// too few, with one block of them).  Each lane owns a mirror pair of velocities
+// (u, -u): for every face of the cell exactly one of the two leaves the cell, so
+// the lane evaluates one time-integrated flux from the cell's own reconstruction
+// (outgoing) and one from the neighbour's reconstruction (incoming); a wave
+// diverges only where its pairs differ in which member leaves.  The face and cell
+// data are wave-uniform:
 //   * the Maxwellians g0, g_cell and the wall Maxwellian factor over the
 //     velocity axes and are staged in LDS once per work item, so
 //     exp(-lambda |u - U|^2) is a product of three table entries;
@@ -25,8 +26,9 @@
 // u and -u, each neighbour's stencil at the incoming member) are issued
 // before any arithmetic so their latency overlaps.  In 2-D the b equation
 // (same transport and relaxation, its own equilibrium polynomials) runs as a
-// second pass over the cell's velocities after h, except in the batched form,
-// whose short work items carry h and b in one pass.  The work-group that has
+// second pass over the cell's velocities after h, or in one pass with it: in the
+// batched forms, and for a single case where the registers hold both
+// (kBothPasses).  The work-group that has
 // swept a whole cell goes on with the rest of the cell's step (conservative
 // update, second stage of Eq. f_final, heat flux, the next step's cell
 // record); the new state goes to the second of two buffers, which the host
@@ -717,9 +719,9 @@ __device__ __forceinline__ void sweep_pass(const SweepIn<C>& in, const T* __rest
 // One work item of the fused sweep: the mirror pairs [kbeg, kend) of cell ic.
 // Leaves the first stage in ht, bt and each lane's moment sums in mw.  h and b
 // run as two passes (each pass's records and row addresses then fit the scalar
-// registers, where h and b together spill them), or with BOTH in one (the
-// batched form's small cases run only a few iterations, whose dependent-load
-// latency two passes would pay twice).  HB: b is carried.
+// registers, where h and b together spill them), or with BOTH in one (kBothPasses,
+// and the batched forms, whose small cases run only a few iterations, whose
+// dependent-load latency two passes would pay twice).  HB: b is carried.
 // SPARSE: the pairs from in.full on have a pad for their second member.
 template <int D, typename T, typename C, bool BOTH, bool LIM, bool HB, bool SPARSE = false>
 __device__ __forceinline__ void sweep_item(const SweepIn<C>& in, const T* __restrict__ h,
@@ -749,8 +751,11 @@ __device__ __forceinline__ void sweep_item(const SweepIn<C>& in, const T* __rest
 // in the first wave), the second stage (Eq. f_final) with the equilibrium of
 // W^{n+1} and q^n (reading R17) in place on the first stage's row, the heat
 // flux of the result, and the next step's cell record.  Where the work-group
-// has swept the cell, each lane takes the pairs it swept and reads back what
-// it wrote itself.  What is done once per cell is done by the first wave: by
+// has swept the cell, the first stage comes from LDS and from the row it wrote: a
+// lane takes the pairs it swept, but for the single points of a sparse set, which
+// are swept from `full` on and finished from 0 on, so by other lanes and waves.
+// The barriers of block_total and of this function, between the sweep's stores and
+// the loads here, make that right.  What is done once per cell is done by the first wave: by
 // all eight it was a tenth of the kernel's VALU instructions.
 template <int D, typename T, typename C, bool HB, bool SPARSE = false>
 __device__ __forceinline__ void finish_cell(const GasP& g, const int32_t* __restrict__ vidx,
@@ -921,9 +926,9 @@ __device__ __forceinline__ void finish_cell(const GasP& g, const int32_t* __rest
 
 // Single case: the sweep computes in the storage type T (FP32 storage uses
 // FP32 copies of the records; moment sums stay FP64).  The FP32
-// body fits in half the registers; its bound asks for the occupancy that
-// hides the gathers' latency (measured: 7 waves per SIMD, no spills).  NB:
-// a 3-D gas with internal degrees of freedom, whose b runs a second pass.
+// body fits in half the registers; its bound (kCellWaves) asks for the occupancy
+// that hides the gathers' latency.  Every variant spills scalar registers (48 to
+// 176), the limited 3-D FP64 ones 7 to 9 vector registers too.
 //
 // Whole-cell form: one work-group takes a cell through all of its velocities
 // and then through the rest of the step, so the first stage's rows are read
@@ -1039,7 +1044,8 @@ __device__ __forceinline__ void case_out(ccase_t& c, GasP& g, CellOut& o) {
 // (case, cell) work items; item w runs on block w mod the grid size, and the
 // host orders the list so that the blocks of one XCD (block index mod 8) take
 // whole tiles of one case.  Measured on the 64-case batch, one pass for h and b
-// against two: 9.6 against 12.4 ms FP64, 5.5 against 6.2 FP32.
+// against two: 9.2 against 10.4 ms FP64 (9.5 with the registers of 4 waves per
+// SIMD), 4.7 against 5.4 FP32 (5.5).
 template <int D, typename T>
 __global__ __launch_bounds__(SWT, (D == 3 ? 4 : 3)) void k_step_b(BatchDev bd) {
   __shared__ SweepLds<D, T> L;
@@ -1792,10 +1798,10 @@ void launch_step_as(const DevMesh& m, const FusedMesh& fm, const DevVel& v, cons
   const int64_t ntile = (fm.nc + sc.tile - 1) / sc.tile;
   const unsigned grid = (unsigned)(((ntile + 7) / 8) * 8 * sc.tile);
   SweepIn<T> in = sweep_in<T>(fm, v, g, B);
-  // The first stage stays in what LDS the resident work-groups leave free (16
-  // waves per compute unit in FP64, 24 in FP32, the registers' bound), so that
+  // The first stage stays in what LDS the resident work-groups leave free (4
+  // kCellWaves waves per compute unit, the registers' bound), so that
   // much of it does not go to memory and back: 48,000 x 24^3 FP64 9.18 ->
-  // 8.36 ms per step (56 % of the row kept), x 28^3 FP32 8.07 -> 7.90 (51 %),
+  // 8.36 ms per step (58 % of the row kept), x 28^3 FP32 8.07 -> 7.90 (51 %),
   // 16,384 cells x 32^2 FP32 0.317 -> 0.283 (all).  One grain too many costs a
   // resident work-group: 8.48 on the second.
   const int64_t pair = (HB ? 4 : 2) * (int64_t)sizeof(T);
