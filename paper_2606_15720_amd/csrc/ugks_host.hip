@@ -1020,8 +1020,9 @@ struct ugks_batch_impl;
 namespace {
 
 // Autotuner cache: case shape -> (pairs per work item: the whole set, a column of
-// the file; tile cells; time) of the whole-cell form, batch shape list -> lanes per work-group and, where the
-// blocked form is the faster one, its pairs per work item (else 0).
+// the file; tile cells; time) of the whole-cell form, batch shape list -> lanes
+// per work-group and, where the blocked form is the faster one, its pairs per work
+// item (else 0).
 struct TuneCase {
   int64_t chunk_pairs = 0, tile = 0;
   double us = 0.0;
